@@ -101,6 +101,15 @@ __device__ __forceinline__ float trimmed_guess(float s1, float s2, int n, float 
     return mu + z * sqrtf(fmaxf(s2 * inv - mu * mu, 0.0f));
 }
 
+// Step of the threshold search away from a count outside the window, from a
+// tenth of |tau| doubling from round to round.  A tile that keeps a few values
+// too many is usually inside the window one such step on, still well below
+// the token's k-th value; a step of |tau| / 4 + 1 went past its maximum, and
+// a tile that keeps none of its ten best sends the token to the repair.
+__device__ __forceinline__ float refine_step(float tau, int it) {
+    return ldexpf(0.1f * (fabsf(tau) + 0.1f), it);
+}
+
 __device__ __forceinline__ bf16x8_t as_bf16x8(const uint4& v) {
     return __builtin_bit_cast(bf16x8_t, v);
 }
@@ -332,8 +341,7 @@ __device__ __forceinline__ void select_slices(const float* const (&vrow)[NT], in
             } else if (isfinite(lo[t]) && isfinite(hi[t])) {
                 tau[t] = 0.5f * (lo[t] + hi[t]);
             } else {
-                // step away from the bad side by a growing fraction of |tau| + 1
-                const float step = ldexpf(0.25f * (fabsf(tau[t]) + 1.0f), it);
+                const float step = refine_step(tau[t], it);
                 tau[t] = isfinite(hi[t]) ? tau[t] - step : tau[t] + step;
             }
         }
@@ -1233,7 +1241,7 @@ sae_gemm_kernel(const uint16_t* __restrict__ xs_g, int32_t d, int32_t n_pad,
                 if (isfinite(lo_b[nb]) && isfinite(hi_b[nb])) {
                     tau[nb] = 0.5f * (lo_b[nb] + hi_b[nb]);
                 } else {
-                    const float step = ldexpf(0.25f * (fabsf(tau[nb]) + 1.0f), it);
+                    const float step = refine_step(tau[nb], it);
                     tau[nb] = isfinite(hi_b[nb]) ? tau[nb] - step : tau[nb] + step;
                 }
             }
@@ -2145,33 +2153,69 @@ static int enc_grid(int32_t n_mt, int32_t n_nt) {
 }
 
 // Candidate emission parameters for a dictionary of m latents and top-k:
-// target emitted per tile (so that m/256 tiles together hold about twice
-// the k needed, plus slack), the per-tile capacity, the lower count bound
-// (non-zero only when few tiles must supply all k), and the standard normal
-// quantile that aims the first threshold guess at the target.
+// the per-tile capacity, the lower count bound, and the standard normal
+// quantile of the first threshold guess.
 struct EmitPlan {
-    int target, cap, lo;
+    int cap, lo;
     float z;
 };
 
+// Pairs one tile may emit: four times a target of twice the tile's share of
+// the k winners, plus one.
+static int emit_cap(int32_t m, int32_t k) {
+    const int t = (2 * k * kBM + m - 1) / m + 1;
+    const int cap = 4 * (t < 2 ? 2 : t);
+    return cap < kMaxCap ? cap : kMaxCap;
+}
+
+// 0.5 * erfc(z / sqrt 2): the share of a standard normal above z
+static double upper_tail(double z) { return 0.5 * erfc(z / sqrt(2.0)); }
+
+// z with f(z) = want for an f that falls with z, by bisection
+template <typename F>
+static double falling_root(F f, double want) {
+    double a = -8.0, b = 8.0;
+    for (int i = 0; i < 40; ++i) {
+        const double mid = 0.5 * (a + b);
+        if (f(mid) > want) a = mid;
+        else b = mid;
+    }
+    return 0.5 * (a + b);
+}
+
+// The guess mean + z * stdev comes from the tile's own 256 values, so it is
+// off by about sqrt(1/256 + z^2/512) stdev.  A tile whose guess ends up
+// above the token's k-th value hides a winner and sends the token to the
+// repair (50 us of one workgroup), so the guess is aimed five such errors
+// below the k-th value's quantile, and at two values a tile or more.  A
+// lower bound on the count is set only where the tiles together might not
+// supply k values (their total within six Poisson deviations of k): every
+// tile would search for it.  Measured: 391 tokens, m = 32768, k = 64
+// (repairs in most launches with the former aim of 2 a tile) merge 62 -> 9
+// us; 1777 tokens of width 2304, m = 16384, k = 64 (where the former rule
+// asked every tile for exactly 12 values) prefill GEMM 240 -> 146 us.
 static EmitPlan emit_plan(int32_t m, int32_t k) {
     const int n_mt = m / kBM;
     EmitPlan e;
-    e.target = (2 * k * kBM + m - 1) / m + 1;
-    e.target = e.target < 2 ? 2 : (e.target > 64 ? 64 : e.target);
-    e.cap = 4 * e.target;
-    e.cap = e.cap < 8 ? 8 : (e.cap > kMaxCap ? kMaxCap : e.cap);
-    e.lo = (n_mt * e.target >= 4 * k) ? 0 : (k < e.cap ? k : e.cap);
-    const double want = e.lo ? 0.5 * (e.lo + e.cap) : e.target;
-    // upper-tail quantile: 0.5 * erfc(z / sqrt 2) = want / 256, by bisection
-    const double f = want / kBM;
-    double a = -8.0, b = 8.0;
-    for (int i = 0; i < 100; ++i) {
-        const double mid = 0.5 * (a + b);
-        if (0.5 * erfc(mid / sqrt(2.0)) > f) a = mid;
-        else b = mid;
+    e.cap = emit_cap(m, k);
+    const double share = static_cast<double>(k) / n_mt;  // of the winners, per tile
+    double target = 2.0;
+    if (share < 0.45 * kBM) {
+        const double zk = falling_root(upper_tail, share / kBM);
+        const double z = falling_root(
+            [](double q) { return -(q + 5.0 * sqrt((1.0 + 0.5 * q * q) / kBM)); }, -zk);
+        target = kBM * upper_tail(z);
+        // room for the counts' own spread below the capacity
+        const double most = e.cap < kMaxCap ? e.cap - 1.8 * sqrt(e.cap) : 45.0;
+        target = target < most ? target : most;
+        target = target < 2.0 ? 2.0 : target;
+    } else {
+        target = 45.0;
     }
-    e.z = static_cast<float>(0.5 * (a + b));
+    const double total = n_mt * target;
+    e.lo = total - k >= 6.0 * sqrt(total) ? 0 : (k < e.cap ? k : e.cap);
+    const double want = e.lo ? 0.5 * (e.lo + e.cap) : target;
+    e.z = static_cast<float>(falling_root(upper_tail, want / kBM));
     return e;
 }
 
@@ -2195,9 +2239,8 @@ static int32_t stage_tokens(int32_t T_max) {
 }
 
 static size_t candidate_bytes(int32_t T_max, int32_t m, int32_t k) {
-    const EmitPlan e = emit_plan(m, k);
     const size_t slots = static_cast<size_t>(T_max) * (m / kBM);
-    return slots * (static_cast<size_t>(e.cap) * 8u + 8u);
+    return slots * (static_cast<size_t>(emit_cap(m, k)) * 8u + 8u);
 }
 
 size_t sae_candidate_bytes(int32_t T_max, int32_t d, int32_t m, int32_t k) {
@@ -2274,8 +2317,8 @@ hipError_t launch_sae_merge(const uint16_t* h, int32_t d, int32_t T_max,
                             int32_t* idx_out, uint16_t* val_out, void* cand,
                             const MergeRing* ring, hipStream_t stream) {
     const int32_t n_mt = m / kBM;
-    const EmitPlan e = emit_plan(m, k);
-    const CandArea a = cand_area(cand, T_max, n_mt, e.cap);
+    const int cap = emit_cap(m, k);
+    const CandArea a = cand_area(cand, T_max, n_mt, cap);
     RingOut r{};
     if (ring) {
         r.slots = ring->slots;
@@ -2287,7 +2330,7 @@ hipError_t launch_sae_merge(const uint16_t* h, int32_t d, int32_t T_max,
         r.app_id = ring->app_id;
     }
     hipLaunchKernelGGL(sae_merge_kernel, dim3(T_max), dim3(kMergeThreads), 0, stream, a.cand,
-                       a.cnt, a.tau, n_mt, e.cap, app_count, tok_list, k, h, d, W_enc,
+                       a.cnt, a.tau, n_mt, cap, app_count, tok_list, k, h, d, W_enc,
                        c_fold, idx_out, val_out, r);
     return hipGetLastError();
 }
