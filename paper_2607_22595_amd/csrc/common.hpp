@@ -35,15 +35,38 @@ __device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
 // rounding: first round to fp32 with round-to-odd (truncate, then set the
 // last bit if anything was dropped), which keeps the information a later
 // round-to-nearest needs because fp32 carries 16 more bits than bf16; then
-// round that fp32 value to bf16.
+// round that fp32 value to bf16.  Any value, subnormal results included.
 __device__ __forceinline__ uint16_t f64_to_bf16_rne(double x) {
     float f = __double2float_rz(x);
     if (static_cast<double>(f) != x && x == x) f = __uint_as_float(__float_as_uint(f) | 1u);
     return f32_to_bf16_rne(f);
 }
+// The same rounding of a value whose bf16 image is a normal number, on the
+// high word of the double alone: the low word only matters as "not zero",
+// half an ulp of bf16 is bit 12 of the high word, and a carry runs into the
+// exponent field as it should.  Seven 32-bit operations instead of the
+// conversions above, which run at a fraction of the rate.
+__device__ __forceinline__ uint32_t f64_to_bf16_normal(uint32_t hi, uint32_t lo) {
+    const uint32_t s = hi | (lo != 0u ? 1u : 0u);
+    const uint32_t r = s + 0x0FFFu + ((hi >> 13) & 1u);
+    return ((r - (896u << 20)) >> 13 & 0x7FFFu) | (hi >> 16 & 0x8000u);
+}
+// Two values rounded and packed (a in the low half).  Magnitudes in
+// [2^-126, 2^127) take the short form; zeros, subnormal results, values at the
+// top of the range, infinities and NaN the general one.
 __device__ __forceinline__ uint32_t pack_bf16_from_f64(double a, double b) {
-    return static_cast<uint32_t>(f64_to_bf16_rne(a)) |
-           (static_cast<uint32_t>(f64_to_bf16_rne(b)) << 16);
+    const uint32_t ah = static_cast<uint32_t>(__double2hiint(a));
+    const uint32_t bh = static_cast<uint32_t>(__double2hiint(b));
+    uint32_t ra = f64_to_bf16_normal(ah, static_cast<uint32_t>(__double2loint(a)));
+    uint32_t rb = f64_to_bf16_normal(bh, static_cast<uint32_t>(__double2loint(b)));
+    // exponent fields 897 .. 1149: the images' exponents 1 .. 253
+    const bool plain = ((ah & 0x7FFFFFFFu) - (897u << 20)) < (253u << 20) &&
+                       ((bh & 0x7FFFFFFFu) - (897u << 20)) < (253u << 20);
+    if (!plain) {
+        ra = f64_to_bf16_rne(a);
+        rb = f64_to_bf16_rne(b);
+    }
+    return ra | (rb << 16);
 }
 
 // Order-preserving map of fp32 onto uint32: a < b  <=>  key(a) < key(b).

@@ -3,87 +3,163 @@
 // (bf16/fp32) are exact in fp64 and the few-term sum carries ~1e-16
 // relative error, so the single rounding to the storage type is correct even
 // when h and the steering terms nearly cancel (fp32 accumulation can be off
-// by an ulp of the small result there).  The kernel is bound by HBM, so the
-// fp64 arithmetic costs nothing measurable.  One workgroup per token slot; each
-// thread owns 16-byte slices of the row, so every global access is a
-// coalesced 16-byte load or store.  Rows without a steering bit return
-// before touching memory beyond their mask word.
+// by an ulp of the small result there).
+//
+// A thread owns one 16-byte column slice of TT token rows: every access is a
+// coalesced 16-byte load or store, the rows of the group are in flight
+// together, and a steering vector is fetched and widened once for the group.
+// HBM bounds a chunk of many tokens, but only just: the fp64 adds run at the
+// fp32 rate, while each widening and the rounding back cost several times as
+// much (pack_bf16_from_f64 rounds on 32-bit words for that reason).  Rows
+// without a steering bit are not read; a group without one returns after
+// reading its mask words.
 #include "common.hpp"
 #include "kernels.hpp"
 #include "launch.hpp"
-#include "steer_add.hpp"
 
 namespace xmix {
 
 constexpr int kSteerThreads = 256;
+constexpr int kSteerGroup = 4;  // token rows per workgroup in a large launch
 
-template <bool BF16>
+template <bool BF16, int TT>
 __global__ void __launch_bounds__(kSteerThreads)
-steer_kernel(void* __restrict__ h, int32_t d, const uint32_t* __restrict__ tok_mask,
-             const int32_t* __restrict__ req, const void* __restrict__ vecs, BitList bits,
-             const float* __restrict__ alpha, int32_t n_steer) {
-    const int32_t t = blockIdx.x;
-    const uint32_t mask = tok_mask[t];
-    uint32_t sel = 0;
-    for (int s = 0; s < n_steer; ++s) sel |= ((mask >> bits.bit[s]) & 1u) << s;
-    if (sel == 0) return;
-    const float* a_row = alpha + static_cast<int64_t>(req[t]) * n_steer;
-
+steer_kernel(void* __restrict__ h, int32_t d, int32_t T_max,
+             const uint32_t* __restrict__ tok_mask, const int32_t* __restrict__ req,
+             const void* __restrict__ vecs, BitList bits, const float* __restrict__ alpha,
+             int32_t n_steer) {
     constexpr int EPV = BF16 ? 8 : 4;  // elements per 16-byte vector
+    const int32_t t0 = static_cast<int32_t>(blockIdx.x) * TT;
     const int32_t nvec = d / EPV;
-    uint4* row = reinterpret_cast<uint4*>(h) + static_cast<int64_t>(t) * nvec;
-    const uint4* V = reinterpret_cast<const uint4*>(vecs);
-    for (int32_t i = threadIdx.x; i < nvec; i += kSteerThreads) {
-        // the row and the first four vectors with their alphas, loaded
-        // together (one memory round trip before the first add)
-        const uint4 hv = row[i];
-        uint32_t rest = sel;
-        SteerGroup g0;
-        steer_fetch(g0, rest, a_row, V, nvec, i);
-        const uint32_t hw[4] = {hv.x, hv.y, hv.z, hv.w};
-        double acc[EPV];
+    const int32_t i = static_cast<int32_t>(blockIdx.y * blockDim.x + threadIdx.x);
+    uint32_t sel[TT], any = 0;
+    const float* a_row[TT];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            if constexpr (BF16) {
-                acc[2 * e] = lo_bf16(hw[e]);
-                acc[2 * e + 1] = hi_bf16(hw[e]);
-            } else {
-                acc[e] = __uint_as_float(hw[e]);
+    for (int j = 0; j < TT; ++j) {
+        const int32_t t = min(t0 + j, T_max - 1);
+        const uint32_t mask = t0 + j < T_max ? tok_mask[t] : 0u;
+        uint32_t m = 0;
+        for (int s = 0; s < n_steer; ++s) m |= ((mask >> bits.bit[s]) & 1u) << s;
+        sel[j] = m;
+        any |= m;
+        a_row[j] = m ? alpha + static_cast<int64_t>(req[t]) * n_steer : alpha;
+    }
+    if (any == 0 || i >= nvec) return;
+
+    uint4* row = reinterpret_cast<uint4*>(h) + static_cast<int64_t>(t0) * nvec + i;
+    const uint4* V = reinterpret_cast<const uint4*>(vecs) + i;
+    uint4 hv[TT];
+#pragma unroll
+    for (int j = 0; j < TT; ++j)
+        hv[j] = sel[j] ? row[static_cast<int64_t>(j) * nvec] : make_uint4(0u, 0u, 0u, 0u);
+    double acc[TT][EPV];
+    bool widened = false;
+    for (uint32_t rest = any; rest != 0;) {
+        // up to four vectors (ascending bits), fetched together
+        uint4 v[4];
+        int sv[4], n = 0;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            v[q] = make_uint4(0u, 0u, 0u, 0u);
+            sv[q] = 0;
+            if (rest != 0) {
+                sv[q] = __builtin_ctz(rest);
+                rest &= rest - 1;
+                v[q] = V[static_cast<int64_t>(sv[q]) * nvec];
+                n = q + 1;
             }
         }
-        steer_add_group<BF16>(acc, g0);
-        if (rest) steer_accumulate<BF16>(acc, rest, a_row, V, nvec, i);
+        if (!widened) {  // the rows, once the first vectors are on their way
+            widened = true;
+#pragma unroll
+            for (int j = 0; j < TT; ++j) {
+                const uint32_t hw[4] = {hv[j].x, hv[j].y, hv[j].z, hv[j].w};
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    if constexpr (BF16) {
+                        acc[j][2 * e] = lo_bf16(hw[e]);
+                        acc[j][2 * e + 1] = hi_bf16(hw[e]);
+                    } else {
+                        acc[j][e] = __uint_as_float(hw[e]);
+                    }
+                }
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            if (q >= n) break;  // uniform
+            const uint32_t vw[4] = {v[q].x, v[q].y, v[q].z, v[q].w};
+            double x[EPV];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                if constexpr (BF16) {
+                    x[2 * e] = lo_bf16(vw[e]);
+                    x[2 * e + 1] = hi_bf16(vw[e]);
+                } else {
+                    x[e] = __uint_as_float(vw[e]);
+                }
+            }
+#pragma unroll
+            for (int j = 0; j < TT; ++j) {
+                if (!((sel[j] >> sv[q]) & 1u)) continue;  // uniform
+                const double a = a_row[j][sv[q]];
+#pragma unroll
+                for (int e = 0; e < EPV; ++e) acc[j][e] = fma(a, x[e], acc[j][e]);
+            }
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < TT; ++j) {
+        if (!sel[j]) continue;  // uniform
         uint4 out;
         if constexpr (BF16) {
-            out.x = pack_bf16_from_f64(acc[0], acc[1]);
-            out.y = pack_bf16_from_f64(acc[2], acc[3]);
-            out.z = pack_bf16_from_f64(acc[4], acc[5]);
-            out.w = pack_bf16_from_f64(acc[6], acc[7]);
+            out.x = pack_bf16_from_f64(acc[j][0], acc[j][1]);
+            out.y = pack_bf16_from_f64(acc[j][2], acc[j][3]);
+            out.z = pack_bf16_from_f64(acc[j][4], acc[j][5]);
+            out.w = pack_bf16_from_f64(acc[j][6], acc[j][7]);
         } else {
-            out.x = __float_as_uint(static_cast<float>(acc[0]));
-            out.y = __float_as_uint(static_cast<float>(acc[1]));
-            out.z = __float_as_uint(static_cast<float>(acc[2]));
-            out.w = __float_as_uint(static_cast<float>(acc[3]));
+            out.x = __float_as_uint(static_cast<float>(acc[j][0]));
+            out.y = __float_as_uint(static_cast<float>(acc[j][1]));
+            out.z = __float_as_uint(static_cast<float>(acc[j][2]));
+            out.w = __float_as_uint(static_cast<float>(acc[j][3]));
         }
-        row[i] = out;
+        row[static_cast<int64_t>(j) * nvec] = out;
     }
+}
+
+template <bool BF16>
+static hipError_t launch_steer_t(void* h, int32_t d, int32_t T_max, const uint32_t* tok_mask,
+                                 const int32_t* req, const void* vecs, const BitList& bits,
+                                 const float* alpha, int32_t n_steer, hipStream_t stream) {
+    const int32_t nvec = d / (BF16 ? 8 : 4);
+    const int32_t threads = nvec < kSteerThreads ? (nvec + kWave - 1) / kWave * kWave : kSteerThreads;
+    const int32_t cols = (nvec + threads - 1) / threads;
+    // a group of rows per workgroup once that still fills the chip with
+    // several workgroups a CU; below, one row each for the shortest chain
+    if (static_cast<int64_t>(T_max) * cols >= 4096)
+        hipLaunchKernelGGL((steer_kernel<BF16, kSteerGroup>),
+                           dim3((T_max + kSteerGroup - 1) / kSteerGroup, cols), dim3(threads), 0,
+                           stream, h, d, T_max, tok_mask, req, vecs, bits, alpha, n_steer);
+    else
+        hipLaunchKernelGGL((steer_kernel<BF16, 1>), dim3(T_max, cols), dim3(threads), 0, stream, h,
+                           d, T_max, tok_mask, req, vecs, bits, alpha, n_steer);
+    return hipGetLastError();
 }
 
 hipError_t launch_steer(void* h, bool bf16, int32_t d, int32_t T_max, const uint32_t* tok_mask,
                         const int32_t* req, const void* vecs, const BitList& bits,
                         const float* alpha, int32_t n_steer, hipStream_t stream) {
-    if (bf16)
-        hipLaunchKernelGGL(steer_kernel<true>, dim3(T_max), dim3(kSteerThreads), 0, stream, h, d,
-                           tok_mask, req, vecs, bits, alpha, n_steer);
-    else
-        hipLaunchKernelGGL(steer_kernel<false>, dim3(T_max), dim3(kSteerThreads), 0, stream, h,
-                           d, tok_mask, req, vecs, bits, alpha, n_steer);
-    return hipGetLastError();
+    return bf16 ? launch_steer_t<true>(h, d, T_max, tok_mask, req, vecs, bits, alpha, n_steer,
+                                       stream)
+                : launch_steer_t<false>(h, d, T_max, tok_mask, req, vecs, bits, alpha, n_steer,
+                                        stream);
 }
 
 void add_steer_kernels(std::vector<KernelInfo>& t) {
-    t.push_back(kernel_info(steer_kernel<true>));
-    t.push_back(kernel_info(steer_kernel<false>));
+    t.push_back(kernel_info(steer_kernel<true, 1>));
+    t.push_back(kernel_info(steer_kernel<true, kSteerGroup>));
+    t.push_back(kernel_info(steer_kernel<false, 1>));
+    t.push_back(kernel_info(steer_kernel<false, kSteerGroup>));
 }
 
 }  // namespace xmix

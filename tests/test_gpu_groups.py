@@ -1,0 +1,73 @@
+
+
+
+@pytest.fixture(scope="module")
+def px():
+    import paper_2607_22595_amd as px
+    return px
+
+
+def dev(a):
+    a = np.ascontiguousarray(a)
+    if a.dtype == np.uint16:
+        return torch.from_numpy(a.view(np.int16)).cuda().view(torch.bfloat16)
+    return torch.from_numpy(a.view(np.int32) if a.dtype == np.uint32 else a).cuda()
+
+
+def build(px, req, T_valid, sub, n_apps):
+    rt = px.Route(len(req), n_apps)
+    err = torch.zeros(1, dtype=torch.int32, device="cuda")
+    px.xmix_route_build(dev(req), torch.tensor([T_valid], dtype=torch.int32, device="cuda"),
+                        dev(sub), rt, err)
+    return rt, err
+
+
+def batch(T, n_apps, p=0.5, seed=0, R=None):
+    rng = np.random.default_rng(seed)
+    R = T if R is None else R
+    req = np.sort(rng.integers(0, R, T)).astype(np.int32)
+    sub = np.zeros(R, np.uint32)
+    for a in range(n_apps):
+        sub |= (rng.random(R) < p).astype(np.uint32) << np.uint32(a)
+    return rng, req, sub
+
+
+@pytest.mark.parametrize("T,d,n_steer,dtype", [
+    (5, 8, 1, "bf16"), (4095, 264, 5, "bf16"), (4096, 264, 5, "bf16"), (4098, 1000, 9, "bf16"),
+    (2049, 2056, 32, "bf16"), (7, 4, 3, "f32"), (4097, 260, 5, "f32"), (2047, 1028, 4, "f32")])
+def test_steer_token_groups(px, T, d, n_steer, dtype):
+    rng, req, sub = batch(T, n_steer, p=0.3, seed=T)
+    bf = dtype == "bf16"
+    draw = synth.normal_bf16 if bf else synth.normal_f32
+    h, v = draw("g/h", (T, d), 1.0), draw("g/v", (n_steer, d), 0.2)
+    alpha = rng.uniform(-8, 8, (T, n_steer)).astype(np.float32)
+    rt, _ = build(px, req, T, sub, n_steer)
+    hd = dev(h)
+    px.xmix_steer_apply(hd, rt, dev(req), dev(v), range(n_steer), dev(alpha))
+    tm = oracle.route(req, T, sub, n_steer)[0]
+    ref = oracle.steer(h, tm, req, v, list(range(n_steer)), alpha)
+    got = torch_bits(hd) if bf else hd.cpu().numpy()
+    # fp64 sums of a few exact products, rounded once: the oracle's own value
+    assert np.array_equal(got, ref)
+
+
+@pytest.mark.parametrize("T", [64, 4096])
+def test_steer_rounding_over_the_whole_range(px, T):
+    """Zeros, subnormal results, halfway ties, the top of the range, infinities
+    and NaN: one rounding from fp64, as the oracle's."""
+    d = 64
+    rng = np.random.default_rng(T)
+    h = rng.integers(0, 1 << 16, (T, d)).astype(np.uint16)   # every kind of bf16
+    v = rng.integers(0, 1 << 16, (1, d)).astype(np.uint16)
+    v[0, :16] = 0
+    v[0, 16:24] = 0x0080                                      # 2^-126
+    alpha = np.exp2(rng.integers(-20, 3, (T, 1))).astype(np.float32)
+    alpha[::5] = 0.0
+    req = np.arange(T, dtype=np.int32)
+    rt, _ = build(px, req, T, np.ones(T, np.uint32), 1)
+    hd = dev(h)
+    px.xmix_steer_apply(hd, rt, dev(req), dev(v), [0], dev(alpha))
+    ref = oracle.steer(h, np.ones(T, np.uint32), req, v, [0], alpha)
+    got, nan = torch_bits(hd), np.isnan(bf16_f64(ref))
+    assert np.array_equal(np.isnan(bf16_f64(got)), nan)
+    assert np.array_equal(got[~nan], ref[~nan])
