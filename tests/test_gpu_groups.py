@@ -71,3 +71,52 @@ def test_steer_rounding_over_the_whole_range(px, T):
     got, nan = torch_bits(hd), np.isnan(bf16_f64(ref))
     assert np.array_equal(np.isnan(bf16_f64(got)), nan)
     assert np.array_equal(got[~nan], ref[~nan])
+
+
+@pytest.mark.parametrize("T,d,k,n_clamp,n_apps", [(1, 8, 1, 1, 1), (5, 264, 64, 16, 3),
+                                                  (4097, 264, 32, 5, 9), (130, 4104, 8, 4, 2)])
+def test_clamp_token_groups(px, T, d, k, n_clamp, n_apps):
+    """Clamps of single calls and of a batched call (more apps than one launch
+    takes) over whole and partial groups; clamp ids outside the dictionary,
+    ids that the encode selected, and an unused slot (-1) in its output."""
+    m = 512
+    rng, req, sub = batch(T, n_apps, p=0.6, seed=T + k)
+    h = synth.normal_bf16("c/h", (T, d), 1.0)
+    rt, _ = build(px, req, T, sub, n_apps)
+    tm = oracle.route(req, T, sub, n_apps)[0]
+    apps, ref = [], h.copy()
+    one = dev(h)
+    for a in range(n_apps):
+        W = synth.normal_bf16(f"c/W{a}", (m, d), d ** -0.5)
+        idx = np.argsort(rng.random((T, m)), axis=1)[:, :k].astype(np.int32)
+        val = synth.normal_bf16(f"c/val{a}", (T, k), 2.0) & np.uint16(0x7FFF)
+        ids = rng.choice(m, n_clamp, replace=False).astype(np.int32)
+        idx[T // 2, 0] = ids[0]
+        idx[T // 2, k - 1] = -1 if k > 1 else ids[0]
+        vals = rng.normal(5, 2, n_clamp).astype(np.float32)
+        ids_ref, vals_ref = ids, vals
+        if n_clamp > 1:      # an id outside the dictionary clamps nothing
+            ids_ref, vals_ref = ids[:-1].copy(), vals[:-1]
+            ids[-1] = m + 3 if a % 2 else -1
+        da = [dev(x) for x in (idx, val, W, ids, vals)]
+        delta = torch.zeros((T, d), dtype=torch.float32, device="cuda")
+        px.xmix_sae_clamp_decode(one, rt, a, *da, delta)
+        prev = ref
+        ref, dref = oracle.clamp_decode(prev, tm, a, idx, val, W, ids_ref, vals_ref,
+                                        want_delta=True)
+        got, dg = torch_bits(one), delta.cpu().numpy()
+        rows = (tm >> np.uint32(a)) & 1 == 1
+        assert np.array_equal(got[~rows], prev[~rows])
+        # n_clamp fp32 multiply-adds: each within 2^-24 of the sum of magnitudes
+        worst = np.abs(vals).sum() + 64 * n_clamp
+        assert np.all(np.abs(dg[rows] - dref[rows]) <= n_clamp * 2.0 ** -23 * worst)
+        for t in np.nonzero(rows)[0][:: max(1, T // 50)]:
+            check_residual(got[t], ref[t], dref[t])
+        ref = got.copy()          # the next app starts from the same rows
+        apps.append((a, *da, delta.clone()))
+    many = dev(h)
+    again = [(*a[:6], torch.zeros_like(a[6])) for a in apps]
+    px.xmix_sae_clamp_decode_multi(many, rt, again)
+    assert torch.equal(many.view(torch.int16), one.view(torch.int16))
+    for a, b in zip(apps, again):
+        assert torch.equal(a[6], b[6])
