@@ -1,9 +1,15 @@
 // Linear probes: per-token logit/sigmoid, and mean-pooled per request.
 //
-// Token pass: one workgroup per token slot reads the row once in 16-byte
-// slices and accumulates one partial dot product per subscribed probe in
-// registers; partials are reduced with fixed DPP moves inside each wave
-// and a fixed-order sum over the waves (bit-reproducible, no atomics).
+// Token pass: a workgroup of 512 threads takes TT token slots (one in a small
+// launch, for the shortest chain; four in a large one).  Each thread reads
+// 16-byte slices of the rows, the group's rows in flight together, and
+// accumulates one partial dot product per (token, probe) in registers, the
+// probe weights fetched and widened once for the group; partials are reduced
+// with fixed DPP moves inside each wave and a fixed-order sum over the waves
+// (bit-reproducible, no atomics, and the same for either TT).  HBM bounds a
+// large launch; with one token per workgroup 8192 tokens of width 4096 and
+// four probes took 28 us, most of it the chain mask -> row -> reduction of
+// eight rounds of workgroups.
 //
 // Mean pooling is a segmented reduction in two launches: the token pass
 // writes each token's dot products (without bias) to the workspace, then one
@@ -25,119 +31,147 @@ namespace xmix {
 constexpr int kProbeThreads = 512;  // the fused probe + steering pass slices rows the same way
 constexpr int kProbeWaves = kProbeThreads / kWave;
 
-// The request whose span [cu[r], cu[r+1]) holds token t, or -1: with cu
-// non-decreasing, r + 1 is the number of entries cu[0..R] that are <= t.
-// Called by every thread of the workgroup (the count is a barrier).
-__device__ __forceinline__ int32_t span_of_token(const int32_t* __restrict__ cu, int32_t R,
-                                                 int32_t t) {
-    int c = 0;
-    for (int32_t i0 = 0; i0 <= R; i0 += kProbeThreads) {
-        const int32_t i = i0 + static_cast<int32_t>(threadIdx.x);
-        c += __syncthreads_count(i <= R && cu[i] <= t);
+// The requests whose spans [cu[r], cu[r+1]) hold tokens t0 .. t0 + TT - 1, or
+// -1: with cu non-decreasing, r + 1 is the number of entries cu[0..R] that
+// are <= t.  Each wave counts for itself (no barrier); the results are uniform.
+template <int TT>
+__device__ __forceinline__ void span_of_tokens(const int32_t* __restrict__ cu, int32_t R,
+                                               int32_t t0, int32_t (&r)[TT]) {
+#pragma unroll
+    for (int j = 0; j < TT; ++j) r[j] = -1;
+    for (int32_t i0 = 0; i0 <= R; i0 += kWave) {
+        const int32_t i = i0 + lane_id();
+        const int32_t c = i <= R ? cu[i] : 0x7FFFFFFF;
+#pragma unroll
+        for (int j = 0; j < TT; ++j) r[j] += __popcll(wave_ballot(c <= t0 + j));
     }
-    const int32_t r = c - 1;
-    if (r < 0 || r >= R) return -1;
-    return t < cu[r + 1] ? r : -1;
 }
 
-template <bool BF16, int MAXP>
+template <bool BF16, int MAXP, int TT>
 __global__ void __launch_bounds__(kProbeThreads)
 probe_token_kernel(const void* __restrict__ h, int32_t d, int32_t T_max,
                    const uint32_t* __restrict__ tok_mask, const void* __restrict__ w,
                    const float* __restrict__ b, BitList bits, int32_t n_probe,
-                   const int32_t* __restrict__ cu, int32_t R, int32_t mode,
+                   const int32_t* __restrict__ cu, int32_t R, int32_t mode, int32_t slots,
                    float* __restrict__ logit, float* __restrict__ score,
                    float* __restrict__ dots) {
-    __shared__ float red[kProbeWaves][MAXP];
+    __shared__ float red[kProbeWaves][TT * MAXP];
     // token mode: slot = token; last-token mode: slot = request, reading the
     // last token of its span (subscription of its first token); mean mode:
     // slot = token, subscription of the first token of its span
-    int32_t t = blockIdx.x;
-    int32_t out_len = T_max;
-    uint32_t mask;
-    if (mode == 2) {
-        const int32_t lo = cu[blockIdx.x], hi = cu[blockIdx.x + 1];
-        if (hi <= lo || lo < 0 || hi > T_max) return;
-        t = hi - 1;
-        mask = tok_mask[lo];
-        out_len = static_cast<int32_t>(gridDim.x);
-    } else if (mode == 1) {
-        const int32_t r = span_of_token(cu, R, t);
-        if (r < 0) return;
-        const int32_t lo = cu[r], hi = cu[r + 1];
-        if (lo < 0 || hi > T_max) return;  // the pooling skips such a span too
-        mask = tok_mask[lo];
-    } else {
-        mask = tok_mask[t];
+    const int32_t s0 = static_cast<int32_t>(blockIdx.x) * TT;
+    int32_t tok[TT];
+    uint32_t sel[TT], any = 0;  // probes of each slot, of the group
+    int32_t span[TT];
+    if (mode == 1) span_of_tokens<TT>(cu, R, s0, span);
+#pragma unroll
+    for (int j = 0; j < TT; ++j) {
+        tok[j] = s0 + j;
+        sel[j] = 0;
+        if (s0 + j >= slots) continue;  // uniform
+        int32_t at = s0 + j;            // the token whose mask decides (< 0: none)
+        if (mode == 2) {
+            const int32_t lo = cu[s0 + j], hi = cu[s0 + j + 1];
+            at = hi <= lo || lo < 0 || hi > T_max ? -1 : lo;
+            tok[j] = hi - 1;
+        } else if (mode == 1) {
+            const int32_t r = span[j];
+            at = -1;
+            if (r >= 0 && r < R) {
+                const int32_t lo = cu[r], hi = cu[r + 1];
+                // a token past its span's end lies in none; the pooling skips
+                // a span outside the slots too
+                if (s0 + j < hi && lo >= 0 && hi <= T_max) at = lo;
+            }
+        }
+        if (at < 0) continue;
+        const uint32_t mask = tok_mask[at];
+        uint32_t m = 0;
+        for (int p = 0; p < n_probe; ++p) m |= ((mask >> bits.bit[p]) & 1u) << p;
+        sel[j] = m;
+        any |= m;
     }
-    uint32_t sel = 0;
-    for (int p = 0; p < n_probe; ++p) sel |= ((mask >> bits.bit[p]) & 1u) << p;
-    if (sel == 0) return;
+    if (any == 0) return;  // uniform
 
     constexpr int EPV = BF16 ? 8 : 4;
     const int32_t nvec = d / EPV;
-    const uint4* row = reinterpret_cast<const uint4*>(h) + static_cast<int64_t>(t) * nvec;
+    const uint4* H = reinterpret_cast<const uint4*>(h);
     const uint4* W = reinterpret_cast<const uint4*>(w);
-    float part[MAXP];
+    float part[TT][MAXP];
 #pragma unroll
-    for (int p = 0; p < MAXP; ++p) part[p] = 0.0f;
+    for (int j = 0; j < TT; ++j)
+#pragma unroll
+        for (int p = 0; p < MAXP; ++p) part[j][p] = 0.0f;
 
-    // weights fetched together with the row (the rest, for more than eight
+    // weights fetched together with the rows (the rest, for more than eight
     // probes, when used)
     constexpr int AP = MAXP < 8 ? MAXP : 8;
     for (int32_t i = threadIdx.x; i < nvec; i += kProbeThreads) {
-        // the row and the weights of the token's probes, all loaded before the
+        // the rows and the weights of the group's probes, all loaded before the
         // first use, so that the slice waits for one memory round trip
-        const uint4 hv = row[i];
-        uint4 wv[AP];
+        uint4 hv[TT], wv[AP];
+#pragma unroll
+        for (int j = 0; j < TT; ++j)
+            hv[j] = sel[j] ? H[static_cast<int64_t>(tok[j]) * nvec + i]
+                           : make_uint4(0u, 0u, 0u, 0u);
 #pragma unroll
         for (int p = 0; p < AP; ++p)
-            wv[p] = ((sel >> p) & 1u) ? W[static_cast<int64_t>(p) * nvec + i]
+            wv[p] = ((any >> p) & 1u) ? W[static_cast<int64_t>(p) * nvec + i]
                                       : make_uint4(0u, 0u, 0u, 0u);
-        const uint32_t hw[4] = {hv.x, hv.y, hv.z, hv.w};
-        float x[EPV];
+        float x[TT][EPV];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            if constexpr (BF16) {
-                x[2 * e] = lo_bf16(hw[e]);
-                x[2 * e + 1] = hi_bf16(hw[e]);
-            } else {
-                x[e] = __uint_as_float(hw[e]);
+        for (int j = 0; j < TT; ++j) {
+            const uint32_t hw[4] = {hv[j].x, hv[j].y, hv[j].z, hv[j].w};
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                if constexpr (BF16) {
+                    x[j][2 * e] = lo_bf16(hw[e]);
+                    x[j][2 * e + 1] = hi_bf16(hw[e]);
+                } else {
+                    x[j][e] = __uint_as_float(hw[e]);
+                }
             }
         }
 #pragma unroll
         for (int p = 0; p < MAXP; ++p) {
-            if (!((sel >> p) & 1u)) continue;
+            if (!((any >> p) & 1u)) continue;  // uniform
             const uint4 w4 = p < AP ? wv[p < AP ? p : 0] : W[static_cast<int64_t>(p) * nvec + i];
             const uint32_t ww[4] = {w4.x, w4.y, w4.z, w4.w};
-            float acc = part[p];
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                if constexpr (BF16) {
-                    acc = fmaf(lo_bf16(ww[e]), x[2 * e], acc);
-                    acc = fmaf(hi_bf16(ww[e]), x[2 * e + 1], acc);
-                } else {
-                    acc = fmaf(__uint_as_float(ww[e]), x[e], acc);
+#pragma unroll
+                for (int j = 0; j < TT; ++j) {
+                    if constexpr (BF16) {
+                        part[j][p] = fmaf(lo_bf16(ww[e]), x[j][2 * e], part[j][p]);
+                        part[j][p] = fmaf(hi_bf16(ww[e]), x[j][2 * e + 1], part[j][p]);
+                    } else {
+                        part[j][p] = fmaf(__uint_as_float(ww[e]), x[j][e], part[j][p]);
+                    }
                 }
             }
-            part[p] = acc;
         }
     }
 
     const int wave = threadIdx.x / kWave;
 #pragma unroll
     for (int p = 0; p < MAXP; ++p) {
-        if (!((sel >> p) & 1u)) continue;
-        const float s = wave_sum(part[p]);
-        if (lane_id() == 0) red[wave][p] = s;
+        if (!((any >> p) & 1u)) continue;
+#pragma unroll
+        for (int j = 0; j < TT; ++j) {
+            const float s = wave_sum(part[j][p]);
+            if (lane_id() == 0) red[wave][p * TT + j] = s;
+        }
     }
     __syncthreads();
-    const int p = threadIdx.x;
-    if (p < n_probe && ((sel >> p) & 1u)) {
+    const int p = threadIdx.x / TT, j = threadIdx.x % TT;
+    uint32_t sj = sel[0];
+#pragma unroll
+    for (int u = 1; u < TT; ++u) sj = j == u ? sel[u] : sj;
+    if (p < n_probe && ((sj >> p) & 1u)) {
         float dot = 0.0f;
 #pragma unroll
-        for (int wv = 0; wv < kProbeWaves; ++wv) dot += red[wv][p];
-        const int64_t o = static_cast<int64_t>(p) * out_len + blockIdx.x;
+        for (int wv = 0; wv < kProbeWaves; ++wv) dot += red[wv][p * TT + j];
+        const int64_t o = static_cast<int64_t>(p) * slots + s0 + j;
         if (dots) {
             dots[o] = dot;
         } else {
@@ -148,39 +182,57 @@ probe_token_kernel(const void* __restrict__ h, int32_t d, int32_t T_max,
     }
 }
 
-// One workgroup per request: pooled logit of every probe whose bit the
-// request carries.  Threads sum strided tokens of the span in order, then a
-// fixed DPP pattern and a fixed-order sum over the waves combine them.
+// One workgroup per (request, probe): the pooled logit where the request
+// carries the probe's bit.  Threads sum strided tokens of the span in order,
+// then a fixed DPP pattern and a fixed-order sum over the waves combine them.
 __global__ void __launch_bounds__(kProbeThreads)
 probe_pool_kernel(const float* __restrict__ dots, int32_t T_max,
                   const uint32_t* __restrict__ tok_mask, const int32_t* __restrict__ cu,
                   const float* __restrict__ b, BitList bits, int32_t n_probe, int32_t R_max,
                   float* __restrict__ logit, float* __restrict__ score) {
     __shared__ float red[kProbeWaves];
-    const int32_t r = blockIdx.x;
+    const int32_t r = blockIdx.x, p = blockIdx.y;
     const int32_t lo = cu[r], hi = cu[r + 1];
     if (hi <= lo || lo < 0 || hi > T_max) return;
     const uint32_t mask = tok_mask[lo];
-    const int wave = threadIdx.x / kWave;
-    for (int p = 0; p < n_probe; ++p) {
-        if (!((mask >> bits.bit[p]) & 1u)) continue;  // uniform over the block
-        const float* dp = dots + static_cast<int64_t>(p) * T_max;
-        float s = 0.0f;
-        for (int32_t t = lo + threadIdx.x; t < hi; t += kProbeThreads) s += dp[t];
-        s = wave_sum(s);
-        if (lane_id() == 0) red[wave] = s;
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            float tot = 0.0f;
+    if (!((mask >> bits.bit[p]) & 1u)) return;  // uniform over the block
+    const float* dp = dots + static_cast<int64_t>(p) * T_max;
+    float s = 0.0f;
+    for (int32_t t = lo + threadIdx.x; t < hi; t += kProbeThreads) s += dp[t];
+    s = wave_sum(s);
+    if (lane_id() == 0) red[threadIdx.x / kWave] = s;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        float tot = 0.0f;
 #pragma unroll
-            for (int wv = 0; wv < kProbeWaves; ++wv) tot += red[wv];
-            const float l = b[p] + tot / static_cast<float>(hi - lo);
-            const int64_t o = static_cast<int64_t>(p) * R_max + r;
-            logit[o] = l;
-            score[o] = logistic(l);
-        }
-        __syncthreads();
+        for (int wv = 0; wv < kProbeWaves; ++wv) tot += red[wv];
+        const float l = b[p] + tot / static_cast<float>(hi - lo);
+        const int64_t o = static_cast<int64_t>(p) * R_max + r;
+        logit[o] = l;
+        score[o] = logistic(l);
     }
+}
+
+// Slots from which a workgroup takes four: the groups still fill the chip
+// twice over.
+constexpr int kProbeGroupMin = 2048;
+
+template <bool BF16, int MAXP>
+static void launch_probe_p(const void* h, int32_t d, int32_t T_max, const uint32_t* tok_mask,
+                           const void* w, const float* b, const BitList& bits, int32_t n_probe,
+                           const int32_t* cu, int32_t R, int32_t mode, int32_t slots,
+                           float* logit, float* score, float* dots, hipStream_t stream) {
+    if constexpr (MAXP <= 8) {
+        if (slots >= kProbeGroupMin) {
+            hipLaunchKernelGGL((probe_token_kernel<BF16, MAXP, 4>), dim3((slots + 3) / 4),
+                               dim3(kProbeThreads), 0, stream, h, d, T_max, tok_mask, w, b, bits,
+                               n_probe, cu, R, mode, slots, logit, score, dots);
+            return;
+        }
+    }
+    hipLaunchKernelGGL((probe_token_kernel<BF16, MAXP, 1>), dim3(slots), dim3(kProbeThreads), 0,
+                       stream, h, d, T_max, tok_mask, w, b, bits, n_probe, cu, R, mode, slots,
+                       logit, score, dots);
 }
 
 template <bool BF16>
@@ -189,19 +241,12 @@ static hipError_t launch_probe_t(const void* h, int32_t d, int32_t T_max,
                                  const BitList& bits, int32_t n_probe, const int32_t* cu,
                                  int32_t R, int32_t mode, int32_t slots, float* logit,
                                  float* score, float* dots, hipStream_t stream) {
-    dim3 g(slots), blk(kProbeThreads);
-    if (n_probe <= 4)
-        hipLaunchKernelGGL((probe_token_kernel<BF16, 4>), g, blk, 0, stream, h, d, T_max,
-                           tok_mask, w, b, bits, n_probe, cu, R, mode, logit, score, dots);
-    else if (n_probe <= 8)
-        hipLaunchKernelGGL((probe_token_kernel<BF16, 8>), g, blk, 0, stream, h, d, T_max,
-                           tok_mask, w, b, bits, n_probe, cu, R, mode, logit, score, dots);
-    else if (n_probe <= 16)
-        hipLaunchKernelGGL((probe_token_kernel<BF16, 16>), g, blk, 0, stream, h, d, T_max,
-                           tok_mask, w, b, bits, n_probe, cu, R, mode, logit, score, dots);
-    else
-        hipLaunchKernelGGL((probe_token_kernel<BF16, 32>), g, blk, 0, stream, h, d, T_max,
-                           tok_mask, w, b, bits, n_probe, cu, R, mode, logit, score, dots);
+    const auto launch = n_probe <= 4    ? launch_probe_p<BF16, 4>
+                        : n_probe <= 8  ? launch_probe_p<BF16, 8>
+                        : n_probe <= 16 ? launch_probe_p<BF16, 16>
+                                        : launch_probe_p<BF16, 32>;
+    launch(h, d, T_max, tok_mask, w, b, bits, n_probe, cu, R, mode, slots, logit, score, dots,
+           stream);
     return hipGetLastError();
 }
 
@@ -218,20 +263,24 @@ hipError_t launch_probe(const void* h, bool bf16, int32_t d, int32_t T_max,
                         : launch_probe_t<false>(h, d, T_max, tok_mask, w, b, bits, n_probe, cu,
                                                 R_max, mode, slots, logit, score, dots, stream);
     if (e != hipSuccess || mode != 1) return e;
-    hipLaunchKernelGGL(probe_pool_kernel, dim3(R_max), dim3(kProbeThreads), 0, stream, ws, T_max,
-                       tok_mask, cu_seqlens, b, bits, n_probe, R_max, logit, score);
+    hipLaunchKernelGGL(probe_pool_kernel, dim3(R_max, n_probe), dim3(kProbeThreads), 0, stream,
+                       ws, T_max, tok_mask, cu_seqlens, b, bits, n_probe, R_max, logit, score);
     return hipGetLastError();
 }
 
 void add_probe_kernels(std::vector<KernelInfo>& t) {
-    t.push_back(kernel_info(probe_token_kernel<true, 4>));
-    t.push_back(kernel_info(probe_token_kernel<true, 8>));
-    t.push_back(kernel_info(probe_token_kernel<true, 16>));
-    t.push_back(kernel_info(probe_token_kernel<true, 32>));
-    t.push_back(kernel_info(probe_token_kernel<false, 4>));
-    t.push_back(kernel_info(probe_token_kernel<false, 8>));
-    t.push_back(kernel_info(probe_token_kernel<false, 16>));
-    t.push_back(kernel_info(probe_token_kernel<false, 32>));
+    t.push_back(kernel_info(probe_token_kernel<true, 4, 1>));
+    t.push_back(kernel_info(probe_token_kernel<true, 4, 4>));
+    t.push_back(kernel_info(probe_token_kernel<true, 8, 1>));
+    t.push_back(kernel_info(probe_token_kernel<true, 8, 4>));
+    t.push_back(kernel_info(probe_token_kernel<true, 16, 1>));
+    t.push_back(kernel_info(probe_token_kernel<true, 32, 1>));
+    t.push_back(kernel_info(probe_token_kernel<false, 4, 1>));
+    t.push_back(kernel_info(probe_token_kernel<false, 4, 4>));
+    t.push_back(kernel_info(probe_token_kernel<false, 8, 1>));
+    t.push_back(kernel_info(probe_token_kernel<false, 8, 4>));
+    t.push_back(kernel_info(probe_token_kernel<false, 16, 1>));
+    t.push_back(kernel_info(probe_token_kernel<false, 32, 1>));
     t.push_back(kernel_info(probe_pool_kernel));
 }
 

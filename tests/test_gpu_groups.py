@@ -73,6 +73,57 @@ def test_steer_rounding_over_the_whole_range(px, T):
     assert np.array_equal(got[~nan], ref[~nan])
 
 
+@pytest.mark.parametrize("T,d,n_probe,R", [(2047, 264, 4, 5), (2048, 264, 1, 70), (2050, 4104, 5, 64),
+                                           (2049, 264, 8, 63), (2300, 520, 9, 129)])
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_probe_token_groups(px, T, d, n_probe, R, dtype):
+    """Per-token and mean-pooled probes on either side of the group rule; spans
+    that end inside a group, empty ones and one past the slots."""
+    rng = np.random.default_rng(T + n_probe)
+    cu = np.sort(rng.integers(0, T, R + 1)).astype(np.int32)
+    cu[0], cu[R - 1:] = 0, T
+    cu[R // 2] = cu[R // 2 - 1]                                # an empty span
+    req = np.full(T, -1, np.int32)
+    for r in range(R):
+        req[cu[r]:cu[r + 1]] = r
+    sub = (rng.random((R, n_probe)) < 0.6) @ (1 << np.arange(n_probe, dtype=np.uint64))
+    sub = sub.astype(np.uint32)
+    bf = dtype == "bf16"
+    draw = synth.normal_bf16 if bf else synth.normal_f32
+    h, w = draw("p/h", (T, d), 1.0), draw("p/w", (n_probe, d), d ** -0.5)
+    b = rng.normal(0, 0.3, n_probe).astype(np.float32)
+    bits = list(range(n_probe))
+    rt, _ = build(px, req, T, sub, n_probe)
+    tm = oracle.route(req, T, sub, n_probe)[0]
+    hd, wd, bd = dev(h), dev(w), dev(b)
+
+    def call(mode, n_out, hh, route, cu_d=None):
+        out = [torch.full((n_probe, n_out), float("nan"), device="cuda") for _ in range(2)]
+        nb = px.probe_workspace(route.T_max, n_probe, mode)
+        ws = torch.full((max(nb, 1),), 0xFF, dtype=torch.uint8, device="cuda")
+        px.xmix_probe_score(hh, route, wd, bd, bits, mode, *out, cu_seqlens=cu_d, ws=ws)
+        return [o.cpu().numpy() for o in out]
+
+    hf, wf = (bf16_f64(h), bf16_f64(w)) if bf else (h.astype(np.float64), w.astype(np.float64))
+    absdot = np.abs(wf) @ np.abs(hf).T
+    lg, sg = call(px.XMIX_PROBE_TOKEN, T, hd, rt)
+    lr, sr = oracle.probe_token(h, tm, w, b, bits)
+    assert np.array_equal(np.isnan(lg), np.isnan(lr))
+    check_probe(lg, sg, lr, sr, ~np.isnan(lr), absdot)
+    # the same bits from launches of fewer slots than the group rule asks for
+    for t0 in (0, 1001):
+        n = min(700, T - t0)
+        part, _ = build(px, req[t0:t0 + n], n, sub, n_probe)
+        lp, _ = call(px.XMIX_PROBE_TOKEN, n, dev(h[t0:t0 + n]), part)
+        assert np.array_equal(lp, lg[:, t0:t0 + n], equal_nan=True)
+    lg, sg = call(px.XMIX_PROBE_MEAN, R, hd, rt, dev(cu))
+    lr, sr = oracle.probe_mean(h, tm, w, b, bits, cu)
+    assert np.array_equal(np.isnan(lg), np.isnan(lr))
+    floor = np.stack([[absdot[q, cu[r]:cu[r + 1]].mean() if cu[r + 1] > cu[r] else 0.0
+                       for r in range(R)] for q in range(n_probe)])
+    check_probe(lg, sg, lr, sr, ~np.isnan(lr), floor)
+
+
 @pytest.mark.parametrize("T,d,k,n_clamp,n_apps", [(1, 8, 1, 1, 1), (5, 264, 64, 16, 3),
                                                   (4097, 264, 32, 5, 9), (130, 4104, 8, 4, 2)])
 def test_clamp_token_groups(px, T, d, k, n_clamp, n_apps):
