@@ -15,9 +15,16 @@ namespace xmix {
 constexpr int kCompactThreads = 256;
 constexpr int kRowsPerBlock = kCompactThreads / kWave;
 
+// Four words at any 4-byte boundary: one 16-byte access (global memory takes
+// them at word alignment), the unit of long rows.
+typedef uint32_t words4_t __attribute__((ext_vector_type(4), aligned(4)));
+
 // Row copies move U-sized units (uint32_t when every row and segment size
 // is a multiple of 4 bytes, else uint16_t, so that rows of any even size are
-// written with aligned stores).
+// written with aligned stores).  HBM bounds long rows; words alone, one
+// outstanding per lane and turn, did not keep it busy (2500 rows of 8 KB: 21.6
+// us), so with U = uint32_t a wave moves 16 bytes per lane, four of them in
+// flight, and single words only at a segment's end.
 template <typename U>
 __global__ void __launch_bounds__(kCompactThreads)
 compact_kernel(Segments segs, const int32_t* __restrict__ app_count,
@@ -55,7 +62,22 @@ compact_kernel(Segments segs, const int32_t* __restrict__ app_count,
         for (int s = 0; s < segs.n; ++s) {
             const int32_t nu = segs.bytes[s] / kU;
             const U* src = reinterpret_cast<const U*>(segs.ptr[s]) + static_cast<int64_t>(t) * nu;
-            for (int32_t w = lane; w < nu; w += kWave) dst[off + w] = src[w];
+            int32_t w0 = 0;
+            if constexpr (kU == 4) {
+                const int32_t n4 = nu / 4;
+                const words4_t* s4 = reinterpret_cast<const words4_t*>(src);
+                words4_t* d4 = reinterpret_cast<words4_t*>(dst + off);
+                for (int32_t q0 = lane; q0 < n4; q0 += 4 * kWave) {
+                    words4_t v[4];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) v[u] = s4[min(q0 + u * kWave, n4 - 1)];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u)
+                        if (q0 + u * kWave < n4) d4[q0 + u * kWave] = v[u];
+                }
+                w0 = 4 * n4;
+            }
+            for (int32_t w = w0 + lane; w < nu; w += kWave) dst[off + w] = src[w];
             off += nu;
         }
     }

@@ -171,3 +171,27 @@ def test_clamp_token_groups(px, T, d, k, n_clamp, n_apps):
     assert torch.equal(many.view(torch.int16), one.view(torch.int16))
     for a, b in zip(apps, again):
         assert torch.equal(a[6], b[6])
+
+
+@pytest.mark.parametrize("widths", [(4,), (12, 16), (1024, 4), (1036, 20), (4096, 1028), (2, 6),
+                                    (2048, 10)])
+@pytest.mark.parametrize("off", [0, 4])
+def test_readback_row_sizes(px, widths, off):
+    """Segments around the 16-byte unit and the wave's 4 KB turn, on sources at
+    a 4-byte offset, into a ring that wraps."""
+    T, cap = 301, 200
+    rng, req, sub = batch(T, 1, p=0.7, seed=sum(widths))
+    rt, _ = build(px, req, T, sub, 1)
+    tm = oracle.route(req, T, sub, 1)[0]
+    segs, host = [], []
+    for n in widths:
+        raw = rng.integers(0, 256, T * n + 16).astype(np.uint8)
+        segs.append(torch.from_numpy(raw).cuda()[off:off + T * n].view(T, n))
+        host.append(raw[off:off + T * n].reshape(T, n))
+    ring = px.Ring(cap, 16 + sum(widths))
+    slots, head = np.zeros((cap, 16 + sum(widths)), np.uint8), 0
+    for _ in range(3):
+        px.xmix_readback_compact(segs, rt, 0, dev(req), 3, 5, ring)
+        slots, head = oracle.compact(host, tm, 0, req, 3, 5, slots, head)
+        assert int(ring.head[0].item()) == head and int(ring.head[1].item()) == 0
+        assert np.array_equal(ring.slots.cpu().numpy(), slots)
