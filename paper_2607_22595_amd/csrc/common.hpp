@@ -118,6 +118,25 @@ __device__ __forceinline__ float wave_sum(float v) {
     return (readlane_f(v, 0) + readlane_f(v, 16)) + (readlane_f(v, 32) + readlane_f(v, 48));
 }
 
+// Inclusive prefix sum over the lanes of a wave (every lane active), on the
+// DPP row shifts and broadcasts described below.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ int dpp_rows(int v) {
+    return __builtin_amdgcn_update_dpp(0, v, CTRL, ROWS, 0xF, false);
+}
+// row_shr 1, 2, 4, 8 inside each row
+// (a lane with no source adds 0), then row_bcast:15 adds row 0's total to
+// row 1 and row 2's to row 3, and row_bcast:31 the total of rows 0-1 to
+// rows 2 and 3
+__device__ __forceinline__ int wave_incl_sum(int v) {
+    v += dpp_rows<0x111, 0xF>(v);
+    v += dpp_rows<0x112, 0xF>(v);
+    v += dpp_rows<0x114, 0xF>(v);
+    v += dpp_rows<0x118, 0xF>(v);
+    v += dpp_rows<0x142, 0xA>(v);
+    v += dpp_rows<0x143, 0xC>(v);
+    return v;
+}
 __device__ __forceinline__ float logistic(float x) { return 1.0f / (1.0f + expf(-x)); }
 
 }  // namespace xmix

@@ -1447,23 +1447,6 @@ constexpr int kFloorRounds = 3;                    // pool refills above a raise
 // Wave-wide scans and reductions on DPP lane moves (every lane active):
 // within each row of 16 lanes, then across the four rows (row_bcast for the
 // scan, lane reads for the reductions, whose results are uniform).
-template <int CTRL, int ROWS>
-__device__ __forceinline__ int dpp_rows(int v) {
-    return __builtin_amdgcn_update_dpp(0, v, CTRL, ROWS, 0xF, false);
-}
-// inclusive prefix sum over the lanes: row_shr 1, 2, 4, 8 inside each row
-// (a lane with no source adds 0), then row_bcast:15 adds row 0's total to
-// row 1 and row 2's to row 3, and row_bcast:31 the total of rows 0-1 to
-// rows 2 and 3
-__device__ __forceinline__ int wave_incl_sum(int v) {
-    v += dpp_rows<0x111, 0xF>(v);
-    v += dpp_rows<0x112, 0xF>(v);
-    v += dpp_rows<0x114, 0xF>(v);
-    v += dpp_rows<0x118, 0xF>(v);
-    v += dpp_rows<0x142, 0xA>(v);
-    v += dpp_rows<0x143, 0xC>(v);
-    return v;
-}
 template <int CTRL>
 __device__ __forceinline__ uint64_t dpp_u64(uint64_t v) {
     const uint32_t lo = static_cast<uint32_t>(dpp_i<CTRL>(static_cast<int>(v)));

@@ -1,4 +1,15 @@
+"""Kernels that take several token slots per workgroup, at the edges of their
+groups and of the rules that choose between the kernels: the oracle's results,
+and the same bits from a launch that takes one slot per workgroup."""
+import numpy as np
+import pytest
+import torch
 
+import oracle
+import synth
+from parity import bf16_f64, check_probe, check_residual, torch_bits
+
+pytestmark = pytest.mark.gpu
 
 
 @pytest.fixture(scope="module")
@@ -30,6 +41,22 @@ def batch(T, n_apps, p=0.5, seed=0, R=None):
     for a in range(n_apps):
         sub |= (rng.random(R) < p).astype(np.uint32) << np.uint32(a)
     return rng, req, sub
+
+
+@pytest.mark.parametrize("T,R_max", [(1, 1), (1023, 7), (1025, 9), (8191, 30), (8192, 8192),
+                                     (8193, 5), (20001, 300)])
+def test_route_build_batches(px, T, R_max):
+    """One slot, a chunk and a batch of chunks more or less by one."""
+    rng, req, sub = batch(T, 32, seed=T, R=R_max)
+    req[rng.integers(0, T, 3)] = -1
+    req[rng.integers(0, T, 2)] = R_max + 1
+    for tv in (T, T // 2, T + 1):
+        rt, err = build(px, req, tv, sub, 32)
+        tm, cnt, lists, e = oracle.route(req, tv, sub, 32)
+        assert np.array_equal(rt.tok_mask.cpu().numpy().view(np.uint32), tm)
+        assert np.array_equal(rt.app_count.cpu().numpy(), cnt)
+        assert np.array_equal(rt.app_tokens.cpu().numpy(), lists)
+        assert int(err.item()) == e
 
 
 @pytest.mark.parametrize("T,d,n_steer,dtype", [
