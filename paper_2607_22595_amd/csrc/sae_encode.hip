@@ -54,6 +54,7 @@
 #include <string.h>
 
 #include <atomic>
+#include <type_traits>
 
 #include "common.hpp"
 #include "kernels.hpp"
@@ -78,9 +79,6 @@ constexpr int kMaxCap = 64;  // most candidate pairs one slice may emit
 // guess (one strong latent, or one of a large norm on either side, would
 // otherwise raise the guess for its whole tile).
 constexpr float kTrimZ = 5.0f;
-constexpr int kLatentFastTiles = 4;  // token tiles up to which the latent tile runs fastest
-constexpr int kBlkTok = 8;           // prefill block: token tiles
-constexpr int kBlkLat = 4;           // prefill block: latent tiles
 
 // v[r] for a lane-varying r in [0, 16), by a select tree on the bits of r
 // (registers cannot be indexed per lane)
@@ -170,73 +168,102 @@ sae_fold_kernel(const uint16_t* __restrict__ Wp, const uint16_t* __restrict__ b_
 }
 
 // ------------------------------------------------ wave-local slice selection
-// After a tile's K loop, its values are written to LDS token-major (one row
-// of kSelStride floats per token, 256 latents each) and the 256 values of a
-// token are taken by 8 lanes of one wave, 32 contiguous latents per lane.
-// The threshold search, the counts and the emission prefix then reduce over
-// those 8 lanes with DPP moves: no barrier and no LDS atomic between the
+// After a tile's K loop, its values are written to LDS token-major and the
+// values of a token's slice are taken by a group of LPS lanes of one wave,
+// VPL contiguous latents per lane (VPL * LPS = the slice's latents).  The
+// threshold search, the counts and the emission prefix then reduce over
+// those lanes with DPP moves: no barrier and no LDS atomic between the
 // waves.  Each lane works on NT tokens at once (independent chains that
-// fill each other's latencies).  The row stride is 4 words past a multiple
+// fill each other's latencies).  A row's stride is 4 words past a multiple
 // of the 64 LDS banks, so the 16-byte reads of the 64 lanes at one step
 // spread over every bank.
-constexpr int kSelStride = 260;  // floats per token row
+constexpr int kSelStride = 260;  // floats per token row of 256 latents
 
-// Reductions inside groups of 8 lanes on DPP moves (quad_perm, row_half_mirror)
-__device__ __forceinline__ float sum8(float v) {
+// Reductions inside groups of LPS lanes (8, 4 or 2) on DPP moves (quad_perm,
+// row_half_mirror)
+template <int LPS>
+__device__ __forceinline__ float sum_g(float v) {
     v += dpp_f<kDppXor1>(v);
-    v += dpp_f<kDppXor2>(v);
-    return v + dpp_f<kDppHalfMirror>(v);
+    if constexpr (LPS >= 4) v += dpp_f<kDppXor2>(v);
+    if constexpr (LPS >= 8) v += dpp_f<kDppHalfMirror>(v);
+    return v;
 }
-__device__ __forceinline__ int isum8(int v) {
+template <int LPS>
+__device__ __forceinline__ int isum_g(int v) {
     v += dpp_i<kDppXor1>(v);
-    v += dpp_i<kDppXor2>(v);
-    return v + dpp_i<kDppHalfMirror>(v);
+    if constexpr (LPS >= 4) v += dpp_i<kDppXor2>(v);
+    if constexpr (LPS >= 8) v += dpp_i<kDppHalfMirror>(v);
+    return v;
 }
-__device__ __forceinline__ float max8(float v) {
+template <int LPS>
+__device__ __forceinline__ float max_g(float v) {
     v = fmaxf(v, dpp_f<kDppXor1>(v));
-    v = fmaxf(v, dpp_f<kDppXor2>(v));
-    return fmaxf(v, dpp_f<kDppHalfMirror>(v));
+    if constexpr (LPS >= 4) v = fmaxf(v, dpp_f<kDppXor2>(v));
+    if constexpr (LPS >= 8) v = fmaxf(v, dpp_f<kDppHalfMirror>(v));
+    return v;
 }
-// sum over the lanes q' < q of the group of 8 (q = lane & 7)
-__device__ __forceinline__ int excl_scan8(int v, int q) {
+// sum over the lanes q' < q of the group (q = lane % LPS)
+template <int LPS>
+__device__ __forceinline__ int excl_scan_g(int v, int q) {
     int incl = v;
     int y = dpp_i<0x111>(incl);  // row_shr:1
     incl += q >= 1 ? y : 0;
-    y = dpp_i<0x112>(incl);      // row_shr:2
-    incl += q >= 2 ? y : 0;
-    y = dpp_i<0x114>(incl);      // row_shr:4
-    incl += q >= 4 ? y : 0;
+    if constexpr (LPS >= 4) {
+        y = dpp_i<0x112>(incl);  // row_shr:2
+        incl += q >= 2 ? y : 0;
+    }
+    if constexpr (LPS >= 8) {
+        y = dpp_i<0x114>(incl);  // row_shr:4
+        incl += q >= 4 ? y : 0;
+    }
     return incl - v;
 }
 
-// The selection of NT tokens over one 256-latent slice each: per token a
-// threshold tau with lo_cnt <= count(pre >= tau) <= cap (first guess
-// mean + z * stdev of the 256 values, then bisection on the value), and
-// every latent with pre >= tau written to dst[t][0 .. count) as (fp32 bits,
-// latent), with the count and the slice's bound beside it.  vrow[t]: token
-// t's LDS row; q = lane & 7 takes latents [32q, 32q + 32); lat0: the slice's first
-// latent.  Every lane of the wave calls it (the cross-lane steps are
-// wave-wide); the lanes of a token with valid[t] == false take part in them
-// and write nothing.  With TRIM, the values beyond mean +- 5 stdev are left
-// out of the statistics behind the first guess (a few outlying latents would
-// otherwise lift it for the whole slice).
-template <bool TRIM, int NT>
-__device__ __forceinline__ void select_slices(const float* const (&vrow)[NT], int q,
+// The value at v of a tile kept as NP partial sums `pstride` floats apart (the
+// K shares of a narrow slice's waves), added in a fixed order.
+template <int NP>
+__device__ __forceinline__ float tile_value(const float* v, int pstride) {
+    if constexpr (NP == 1) return v[0];
+    else if constexpr (NP == 2) return v[0] + v[pstride];
+    else return (v[0] + v[pstride]) + (v[2 * pstride] + v[3 * pstride]);
+}
+
+// The selection of NT tokens over one slice each: per token a threshold tau
+// with lo_cnt <= count(pre >= tau) <= cap (first guess mean + z * stdev of
+// the slice's values, then bisection on the value), and every latent with
+// pre >= tau written to dst[t][0 .. count) as (fp32 bits, latent), with the
+// count and the slice's bound beside it.  vrow[t]: this lane's VPL values of
+// token t in LDS (NP partial sums each); q: the lane's place in its group;
+// lat0: its first latent.  Every lane of the wave calls it (the cross-lane
+// steps are wave-wide); the lanes of a token with valid[t] == false take part
+// in them and write nothing.  With TRIM, the values beyond mean +- 5 stdev
+// are left out of the statistics behind the first guess (a few outlying
+// latents would otherwise lift it for the whole slice).
+template <bool TRIM, int NT, int VPL, int LPS, int NP>
+__device__ __forceinline__ void select_slices(const float* const (&vrow)[NT], int pstride, int q,
                                               const bool (&valid)[NT], float z, int lo_cnt,
                                               int cap, int32_t lat0, uint2* const (&dst)[NT],
                                               int32_t* const (&cnt_out)[NT],
                                               float* const (&tau_out)[NT]) {
-    float x[NT][32];
+    constexpr int kW = VPL * LPS;  // latents of a slice
+    float x[NT][VPL];
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
-        const float4* src = reinterpret_cast<const float4*>(vrow[t]);
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const float4 v = src[8 * q + i];
-            x[t][4 * i] = v.x;
-            x[t][4 * i + 1] = v.y;
-            x[t][4 * i + 2] = v.z;
-            x[t][4 * i + 3] = v.w;
+        for (int i = 0; i < VPL / 4; ++i) {
+            float4 v[NP];
+#pragma unroll
+            for (int p = 0; p < NP; ++p)
+                v[p] = reinterpret_cast<const float4*>(vrow[t] + p * pstride)[i];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                auto part = [&](int p) __attribute__((always_inline)) {
+                    return e == 0 ? v[p].x : e == 1 ? v[p].y : e == 2 ? v[p].z : v[p].w;
+                };
+                if constexpr (NP == 1) x[t][4 * i + e] = part(0);
+                else if constexpr (NP == 2) x[t][4 * i + e] = part(0) + part(1);
+                else x[t][4 * i + e] = (part(0) + part(1)) + (part(2) + part(3));
+            }
         }
     }
     // ax[t]: the largest magnitude among the token's values
@@ -245,7 +272,7 @@ __device__ __forceinline__ void select_slices(const float* const (&vrow)[NT], in
     for (int t = 0; t < NT; ++t) {
         float a = 0.0f, b = 0.0f, c = 0.0f;
 #pragma unroll
-        for (int i = 0; i < 32; ++i) {
+        for (int i = 0; i < VPL; ++i) {
             a += x[t][i];
             b = fmaf(x[t][i], x[t][i], b);
             if (TRIM) c = fmaxf(c, fabsf(x[t][i]));
@@ -256,11 +283,11 @@ __device__ __forceinline__ void select_slices(const float* const (&vrow)[NT], in
     }
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
-        s1[t] = sum8(s1[t]);
-        s2[t] = sum8(s2[t]);
-        if (TRIM) ax[t] = max8(ax[t]);
-        mu[t] = s1[t] * (1.0f / kBM);
-        sd[t] = sqrtf(fmaxf(s2[t] * (1.0f / kBM) - mu[t] * mu[t], 0.0f));
+        s1[t] = sum_g<LPS>(s1[t]);
+        s2[t] = sum_g<LPS>(s2[t]);
+        if (TRIM) ax[t] = max_g<LPS>(ax[t]);
+        mu[t] = s1[t] * (1.0f / kW);
+        sd[t] = sqrtf(fmaxf(s2[t] * (1.0f / kW) - mu[t] * mu[t], 0.0f));
         tau[t] = mu[t] + z * sd[t];
     }
     if (TRIM) {
@@ -283,16 +310,16 @@ __device__ __forceinline__ void select_slices(const float* const (&vrow)[NT], in
                 float e1 = 0.0f, e2 = 0.0f;
                 int ne = 0;
 #pragma unroll
-                for (int i = 0; i < 32; ++i) {
+                for (int i = 0; i < VPL; ++i) {
                     const bool o = x[t][i] > cut || x[t][i] < cut_lo;
                     ne += o ? 1 : 0;
                     e1 += o ? x[t][i] : 0.0f;
                     e2 = fmaf(o ? x[t][i] : 0.0f, x[t][i], e2);
                 }
-                e1 = sum8(e1);
-                e2 = sum8(e2);
-                ne = isum8(ne);
-                if (trim[t]) tau[t] = trimmed_guess(s1[t] - e1, s2[t] - e2, kBM - ne, z);
+                e1 = sum_g<LPS>(e1);
+                e2 = sum_g<LPS>(e2);
+                ne = isum_g<LPS>(ne);
+                if (trim[t]) tau[t] = trimmed_guess(s1[t] - e1, s2[t] - e2, kW - ne, z);
             }
         }
     }
@@ -310,7 +337,7 @@ __device__ __forceinline__ void select_slices(const float* const (&vrow)[NT], in
         for (int t = 0; t < NT; ++t) {
             uint32_t b = 0;
 #pragma unroll
-            for (int i = 0; i < 32; ++i) b |= (x[t][i] >= tau[t] ? 1u : 0u) << i;
+            for (int i = 0; i < VPL; ++i) b |= (x[t][i] >= tau[t] ? 1u : 0u) << i;
             m[t] = b;
         }
     };
@@ -321,7 +348,7 @@ __device__ __forceinline__ void select_slices(const float* const (&vrow)[NT], in
         bool bad[NT], any = false;
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
-            c[t] = isum8(__popc(m[t]));
+            c[t] = isum_g<LPS>(__popc(m[t]));
             bad[t] = valid[t] && (c[t] > cap || c[t] < lo_cnt);
             any = any || bad[t];
         }
@@ -357,12 +384,12 @@ __device__ __forceinline__ void select_slices(const float* const (&vrow)[NT], in
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
         const int cl = __popc(m[t]);
-        base[t] = excl_scan8(cl, q);
-        total[t] = isum8(cl);
+        base[t] = excl_scan_g<LPS>(cl, q);
+        total[t] = isum_g<LPS>(cl);
         float l = -INFINITY;
 #pragma unroll
-        for (int i = 0; i < 32; ++i) l = fmaxf(l, x[t][i] >= tau[t] ? -INFINITY : x[t][i]);
-        nk[t] = max8(l);
+        for (int i = 0; i < VPL; ++i) l = fmaxf(l, x[t][i] >= tau[t] ? -INFINITY : x[t][i]);
+        nk[t] = max_g<LPS>(l);
     }
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
@@ -373,8 +400,8 @@ __device__ __forceinline__ void select_slices(const float* const (&vrow)[NT], in
             const int i = __builtin_ctz(b);
             b &= b - 1;
             if (slot < cap)
-                dst[t][slot] = make_uint2(__float_as_uint(vrow[t][32 * q + i]),
-                                          static_cast<uint32_t>(lat0 + 32 * q + i));
+                dst[t][slot] = make_uint2(__float_as_uint(tile_value<NP>(vrow[t] + i, pstride)),
+                                          static_cast<uint32_t>(lat0 + i));
             ++slot;
         }
         if (q == 0) {
@@ -419,34 +446,56 @@ __device__ __forceinline__ void load_bias(float (&cfv)[16], const float* c_fold,
     for (int r = 0; r < 16; ++r) cfv[r] = cf[8 * (r / 4) + (r % 4)];
 }
 
-// Where one app's slices put their candidates, and how they select them.
+// Where one app's slices put their candidates, and how they select them:
+// per token slot a row of n_sl slices.
 struct SliceSink {
     uint2* cand;
     int32_t* tile_cnt;
     float* tile_tau;
-    int32_t n_mt, lo_cnt, cap;
+    int32_t n_sl, lo_cnt, cap;
     float z;
 };
 
-// The GEMM and candidate emission of latent slice mt over the token tiles
-// nt, nt + 1, ... of the app's list tl[0, cnt) (only tile nt unless
-// in_turn); the caller has checked nt * kBN < cnt.  On entry wa0..wa2 hold
+// Word 3 of a raw buffer resource (32-bit element format, no swizzle).
+constexpr int kBufferDword3 = 0x00020000;
+// A buffer offset past every resource (none is larger than 2^31 - 1 bytes), and
+// far enough from 2^32 that no scalar offset wraps it.
+constexpr uint32_t kOutOfRange = 0x80000000u;
+
+// A 16-byte buffer load; offsets past the resource's end read zero and touch no
+// memory, so a load past the K loop's last chunk needs no branch: its resource
+// is empty (and its scalar offset zero: the range check subtracts it).
+template <int AUX>
+__device__ __forceinline__ uint4 buffer_load16(__amdgpu_buffer_rsrc_t r, uint32_t voff,
+                                               uint32_t soff) {
+    const u32x4_t v = __builtin_bit_cast(
+        u32x4_t, __builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, AUX));
+    return make_uint4(v.x, v.y, v.z, v.w);
+}
+constexpr int kNontemporal = 2;  // cache policy bit of the buffer loads
+
+// The GEMM and candidate emission of latent slice mt over the token tiles of
+// the app's list tl[0, cnt) in turn, cnt > 0.  On entry wa0..wa2 hold
 // the slice's K chunks 0-2 and cfv its folded bias when `issued`.  The K
 // loop fetches three chunks ahead; past the slice's last chunk it fetches
 // the first chunks of what runs next: the same slice again for the next
 // token tile, else slice `nxt` when has_nxt (then also its bias from
-// nxt_cf, after this tile's selection), else nothing new (the last chunk
+// nxt_bias_of(), after this tile's selection), else nothing new (the last chunk
 // again, unused).  Returns has_nxt: whether wa0..wa2 and cfv now hold nxt's
 // first chunks and bias.  lds_main is the workgroup's token-chunk and
-// selection space.
+// selection space; sink_of() is asked for after the K loop, whose scalar
+// registers are few.  ONE: cnt <= kBN, a single tile (its bias then need not
+// outlive the accumulators' start, which leaves the K loop its registers).
+template <bool ONE, typename SinkOf, typename BiasOf>
 __device__ __forceinline__ bool slice_tiles(
     uint4* lds_main, const uint16_t* __restrict__ h, int32_t d, const int32_t* tl, int cnt,
-    int nt, bool in_turn, int mt, const SliceSrc cur, const SliceSink sink, bool issued,
-    const SliceSrc nxt, bool has_nxt, int nxt_mt, const float* __restrict__ nxt_cf,
+    int mt, const SliceSrc cur, SinkOf sink_of, bool issued,
+    const SliceSrc nxt, bool has_nxt, int nxt_mt, BiasOf nxt_bias_of,
     const float* __restrict__ c_fold, uint4 (&wa0)[4], uint4 (&wa1)[4], uint4 (&wa2)[4],
     uint4 (&wa3)[4], float (&cfv)[16]) {
     uint4 (*xs)[kBN * 8] = reinterpret_cast<uint4 (*)[kBN * 8]>(lds_main);
-    const int tid = threadIdx.x;
+    int tid = threadIdx.x;  // opaque (see big_tile)
+    if (ONE) asm volatile("" : "+v"(tid));
     const int lane = tid & 63, wave = tid >> 6;
     const int g = lane >> 5, j32 = lane & 31;
     const int nK = d / kBK;  // a multiple of 4 (d % 256 == 0)
@@ -506,10 +555,9 @@ __device__ __forceinline__ bool slice_tiles(
     };
 
     if (!issued) load_bias(cfv, c_fold, mt);  // the slice's bias serves every token tile
-    for (;; ++nt) {
-        const int n0 = nt * kBN;
+    for (int n0 = 0;; n0 += kBN) {
         const int ntok = min(kBN, cnt - n0);
-        const bool last = !in_turn || n0 + kBN >= cnt;
+        const bool last = ONE || n0 + kBN >= cnt;
         // the stream past this slice's last chunk: the next token tile's
         // first chunks, nxt's, or the last chunk again (unused)
         const uint4* after = !last ? cur.base : has_nxt ? nxt.base : cur.base + (nK - 1) * cur.stride;
@@ -580,87 +628,505 @@ __device__ __forceinline__ bool slice_tiles(
                                 acc[nb][4 * j + 3]);
         }
         __syncthreads();
+        const SliceSink sink = sink_of();
         const int q = lane & 7;
         const int r0 = 16 * wave + (lane >> 3), r1 = r0 + 8;
-        const int64_t row0 = static_cast<int64_t>(n0 + r0) * sink.n_mt + mt;
-        const int64_t row1 = static_cast<int64_t>(n0 + r1) * sink.n_mt + mt;
-        const float* const vr[2] = {V + r0 * kSelStride, V + r1 * kSelStride};
+        const int64_t row0 = static_cast<int64_t>(n0 + r0) * sink.n_sl + mt;
+        const int64_t row1 = static_cast<int64_t>(n0 + r1) * sink.n_sl + mt;
+        const float* const vr[2] = {V + r0 * kSelStride + 32 * q, V + r1 * kSelStride + 32 * q};
         const bool ok[2] = {r0 < ntok, r1 < ntok};
         uint2* const dst[2] = {sink.cand + row0 * sink.cap, sink.cand + row1 * sink.cap};
         int32_t* const co[2] = {sink.tile_cnt + row0, sink.tile_cnt + row1};
         float* const to[2] = {sink.tile_tau + row0, sink.tile_tau + row1};
-        select_slices<true, 2>(vr, q, ok, sink.z, sink.lo_cnt, sink.cap, mt * kBM, dst, co, to);
+        select_slices<true, 2, 32, 8, 1>(vr, 0, q, ok, sink.z, sink.lo_cnt, sink.cap,
+                                         mt * kBM + 32 * q, dst, co, to);
         if (last) {
-            if (has_nxt && nxt_cf) load_bias(cfv, nxt_cf, nxt_mt);
+            if (has_nxt) load_bias(cfv, nxt_bias_of(), nxt_mt);
             return has_nxt;
         }
         __syncthreads();  // the tile rows are read before the next tile's token chunks land
     }
 }
 
-// One workgroup's tile: L is the tile's launch slot within its app's grid,
-// own the workgroup's index in the launch (its route-publishing duty).
-__device__ __forceinline__ void stream_tile(
-    int L, int own, const uint16_t* __restrict__ h, int32_t d,
-    const int32_t* __restrict__ app_count, const int32_t* __restrict__ tok_list,
-    const uint16_t* __restrict__ W, const float* __restrict__ c_fold, int32_t n_mt, int32_t n_nt,
-    float z_guess, int32_t lo_cnt, int32_t cap, uint2* __restrict__ cand,
-    int32_t* __restrict__ tile_cnt, float* __restrict__ tile_tau,
-    const int32_t* __restrict__ r_req, const int32_t* __restrict__ r_tvalid,
-    const uint32_t* __restrict__ r_sub, int32_t r_Rmax, int32_t r_Tmax, int32_t r_napps,
-    int32_t r_bit, uint32_t* __restrict__ r_mask, int32_t* __restrict__ r_count,
-    int32_t* __restrict__ r_lists, uint32_t* __restrict__ r_err) {
-    // K loop: two 16 KiB token chunks; epilogue: the tile's 128 token rows
-    __shared__ uint4 lds_main[kBN * kSelStride / 4];
-    static_assert(kBN * kSelStride / 4 >= 2 * kBN * 8, "token chunks fit");
+// ------------------------------------------------------------ narrow slices
+// A dictionary of few 256-latent slices leaves CUs idle when every slice is
+// one workgroup, so it is cut finer: a workgroup owns 256 / WK latents and
+// its waves share the K loop WK ways (wave = WL * share + latent group, WL =
+// 8 / WK), every wave still streaming whole 4 KB dictionary chunks straight
+// into registers, three in flight.  A window of WK K chunks of the token rows
+// is shared through LDS (double buffered, staged in registers two windows
+// ahead, so that the in-order wait for a window leaves the dictionary chunks
+// issued after it in flight).  The tile's token rows are 32 * NB: 32, 64 or 128
+// by the tokens left, since a batch of a few requests is the usual one here.
+// The WK partial sums of a value are added when the selection reads them.
+// Measured against one workgroup per 256 latents: 9 tokens of width 2304, m =
+// 16384 (64 workgroups then, 256 now) 33.8 -> 16.7 us.
+template <int WK>
+struct Narrow {
+    static constexpr int kSW = kBM / WK;           // latents of a slice
+    static constexpr int kWL = kEncWaves / WK;     // latent groups of 32
+    static constexpr int kStride = kSW + 4;        // floats per selection row
+    static constexpr int kPart = kBN * kStride;    // floats per partial-sum plane (128 rows)
+    static constexpr int kPieces = WK * kBN * 8;   // 16-byte pieces of a token window (128 rows)
+};
+
+// Window w (a K chunk per share) of slice sl's dictionary stream.
+template <int WK>
+__device__ __forceinline__ void narrow_load(uint4 (&a)[4], const uint16_t* W, int n_mt, int sl,
+                                            int w, int nW) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int wl = wave % Narrow<WK>::kWL, wk = wave / Narrow<WK>::kWL;
+    const int64_t chunk = static_cast<int64_t>(n_mt) * 32768;  // bytes of one K chunk
+    const char* base = reinterpret_cast<const char*>(W) + static_cast<int64_t>(sl / WK) * 32768 +
+                       chunk * WK * min(w, nW - 1);
+    const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<char*>(base), 0, w < nW ? static_cast<int>(chunk * (WK - 1) + 32768) : 0,
+        kBufferDword3);
+    const uint32_t off = static_cast<uint32_t>(wk) * static_cast<uint32_t>(chunk) +
+                         (((sl % WK) * Narrow<WK>::kWL + wl) * 256 + lane) * 16u;
+#pragma unroll
+    for (int s = 0; s < 4; ++s) a[s] = buffer_load16<kNontemporal>(r, off + s * 1024u, 0);
+}
+
+// One tile: slice sl over tokens [n0, n0 + 32 * NB) of the app's list.  On
+// entry wa0..wa2 hold the slice's first three windows when `issued`; on exit
+// those of slice `nxt` when nxt >= 0.
+template <int WK, int NB>
+__device__ __forceinline__ void narrow_tile(uint4* lds_main, const uint16_t* __restrict__ h,
+                                            uint32_t h_bytes, int32_t d, const int32_t* tl,
+                                            int cnt, int n0, int sl,
+                                            const uint16_t* __restrict__ W, int n_mt,
+                                            const SliceSink sink,
+                                            const float* __restrict__ c_fold, bool issued,
+                                            int nxt, uint4 (&wa0)[4], uint4 (&wa1)[4],
+                                            uint4 (&wa2)[4], uint4 (&wa3)[4]) {
+    using N = Narrow<WK>;
+    constexpr int kRows = 32 * NB;
+    constexpr int kPlane = kRows * 8;       // pieces of one share's token chunk
+    constexpr int kXP = WK * kPlane / kEncThreads;  // pieces per thread and window
+    static_assert(kXP >= 1, "a window has a piece for every thread");
+    int tid = threadIdx.x;  // opaque (see big_tile)
+    asm volatile("" : "+v"(tid));
+    const int lane = tid & 63, wave = tid >> 6;
+    const int wl = wave % N::kWL, wk = wave / N::kWL;
+    const int g = lane >> 5, j32 = lane & 31;
+    const int nW = d / (kBK * WK);
+    const int ntok = min(kRows, cnt - n0);
+    // piece q of a window: share q / kPlane, row (q % kPlane) / 8, 16-byte chunk
+    // q % 8; thread tid holds q = tid + 512 p
+    uint32_t xoff[kXP];
+#pragma unroll
+    for (int p = 0; p < kXP; ++p) {
+        const int q = tid + kEncThreads * p;
+        const int n = (q % kPlane) / 8;
+        xoff[p] = n < ntok ? static_cast<uint32_t>(tl[n0 + n]) * static_cast<uint32_t>(d) * 2u +
+                                 static_cast<uint32_t>(q / kPlane) * 128u + (q & 7) * 16u
+                           : kOutOfRange;
+    }
+    f32x16_t acc[NB];
+    {
+        const float* cf = c_fold + sl * N::kSW + 32 * wl + 4 * g;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const float c = wk == 0 ? cf[8 * (r / 4) + (r % 4)] : 0.0f;
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb) acc[nb][r] = c;
+        }
+    }
+    uint4 xv0[kXP], xv1[kXP];
+    auto load_x = [&](uint4 (&xv)[kXP], int w) __attribute__((always_inline)) {
+        const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<uint16_t*>(h), 0, w < nW ? static_cast<int>(h_bytes) : 0, kBufferDword3);
+        const uint32_t soff = w < nW ? static_cast<uint32_t>(w * WK) * 128u : 0u;
+#pragma unroll
+        for (int p = 0; p < kXP; ++p) xv[p] = buffer_load16<0>(r, xoff[p], soff);
+    };
+    // row n's chunk c sits at n*8 + (c ^ ((n >> 1) & 7)) of its share's plane;
+    // 512 pieces on are whole rows on, a multiple of 16 of them
+    static_assert(kEncThreads / 8 % 16 == 0, "the swizzle repeats every 16 rows");
+    const int xdst = (tid & ~7) + ((tid & 7) ^ ((tid >> 4) & 7));
+    auto store_x = [&](const uint4 (&xv)[kXP], int buf) __attribute__((always_inline)) {
+#pragma unroll
+        for (int p = 0; p < kXP; ++p)
+            lds_main[buf * (WK * kPlane) + xdst + kEncThreads * p] = xv[p];
+    };
+    const int xsrc = wk * kPlane + j32 * 8, sw = (j32 >> 1) & 7;
+    auto compute = [&](const uint4 (&a)[4], int buf) __attribute__((always_inline)) {
+        const uint4* xs = lds_main + buf * (WK * kPlane) + xsrc;
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            uint4 bop[NB];
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb) bop[nb] = xs[((2 * s + g) ^ sw) + 256 * nb];
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb)
+                acc[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(a[s]),
+                                                                  as_bf16x8(bop[nb]), acc[nb], 0,
+                                                                  0, 0);
+        }
+    };
+    auto step = [&](int w, const uint4 (&cur)[4], uint4 (&wnext)[4], uint4 (&xload)[kXP],
+                    const uint4 (&xstore)[kXP]) __attribute__((always_inline)) {
+        load_x(xload, w + 2);
+        __builtin_amdgcn_sched_barrier(0);  // keep the token loads ahead of the W loads
+        narrow_load<WK>(wnext, W, n_mt, sl, w + 3, nW);
+        __syncthreads();
+        compute(cur, w & 1);
+        store_x(xstore, (w + 1) & 1);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    load_x(xv0, 0);
+    load_x(xv1, 1);
+    if (!issued) {
+        narrow_load<WK>(wa0, W, n_mt, sl, 0, nW);
+        narrow_load<WK>(wa1, W, n_mt, sl, 1, nW);
+        narrow_load<WK>(wa2, W, n_mt, sl, 2, nW);
+    }
+    store_x(xv0, 0);
+    for (int w = 0;;) {  // the W registers rotate; any number of windows
+        step(w, wa0, wa3, xv0, xv1);
+        if (++w == nW) break;
+        step(w, wa1, wa0, xv1, xv0);
+        if (++w == nW) break;
+        step(w, wa2, wa1, xv0, xv1);
+        if (++w == nW) break;
+        step(w, wa3, wa2, xv1, xv0);
+        if (++w == nW) break;
+    }
+    if (nxt >= 0) {  // uniform: the next slice's stream starts under the selection
+        narrow_load<WK>(wa0, W, n_mt, nxt, 0, nW);
+        narrow_load<WK>(wa1, W, n_mt, nxt, 1, nW);
+        narrow_load<WK>(wa2, W, n_mt, nxt, 2, nW);
+    }
+    __syncthreads();  // every wave is done with the token windows
+    constexpr int kPlaneF = kRows * N::kStride;  // floats of a partial-sum plane
+    float* V = reinterpret_cast<float*>(lds_main);
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) {
+        float* rowp = V + wk * kPlaneF + (32 * nb + j32) * N::kStride + 32 * wl + 4 * g;
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            *reinterpret_cast<float4*>(rowp + 8 * j) = make_float4(
+                acc[nb][4 * j], acc[nb][4 * j + 1], acc[nb][4 * j + 2], acc[nb][4 * j + 3]);
+    }
+    __syncthreads();
+    // NT rows per lane group: 16 rows a wave in the widest tile, 8 below (every
+    // wave then has rows, or only the first ones)
+    constexpr int NT = NB == 4 ? 2 : 1;
+    if (8 * NT * wave < ntok) {  // uniform over the wave
+        constexpr int VPL = N::kSW / 8;
+        const int q = lane & 7;
+        const float* vr[NT];
+        bool ok[NT];
+        uint2* dst[NT];
+        int32_t* co[NT];
+        float* to[NT];
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+            const int r = 8 * NT * wave + (lane >> 3) + 8 * t;
+            const int64_t row = static_cast<int64_t>(n0 + r) * sink.n_sl + sl;
+            ok[t] = r < ntok;
+            vr[t] = V + (ok[t] ? r : 0) * N::kStride + VPL * q;
+            dst[t] = sink.cand + row * sink.cap;
+            co[t] = sink.tile_cnt + row;
+            to[t] = sink.tile_tau + row;
+        }
+        select_slices<true, NT, VPL, 8, WK>(vr, kPlaneF, q, ok, sink.z, sink.lo_cnt, sink.cap,
+                                            sl * N::kSW + VPL * q, dst, co, to);
+    }
+    __syncthreads();  // the rows are read before the next tile's tokens land
+}
+
+// Candidates of narrow slices sl, sl + step, ... (< n_end), each over the live
+// token tiles in turn.  On entry wa0..wa2 hold the first one's first three
+// windows when `issued`.
+template <int WK>
+__device__ __forceinline__ void narrow_slices(uint4* lds_main, const uint16_t* __restrict__ h,
+                                              uint32_t h_bytes, int32_t d, const int32_t* tl,
+                                              int cnt, int sl, int step, int n_end,
+                                              const uint16_t* __restrict__ W, int n_mt,
+                                              const SliceSink sink,
+                                              const float* __restrict__ c_fold, bool issued,
+                                              uint4 (&wa0)[4], uint4 (&wa1)[4], uint4 (&wa2)[4],
+                                              uint4 (&wa3)[4]) {
+    for (;;) {
+        for (int n0 = 0; n0 < cnt; n0 += kBN) {
+            const int left = cnt - n0;
+            // what streams next: the slice again for its next tile, or the next slice
+            const int nxt = left > kBN ? sl : sl + step < n_end ? sl + step : -1;
+            if (left <= 32)
+                narrow_tile<WK, 1>(lds_main, h, h_bytes, d, tl, cnt, n0, sl, W, n_mt, sink, c_fold,
+                                   issued, nxt, wa0, wa1, wa2, wa3);
+            else if (left <= 64)
+                narrow_tile<WK, 2>(lds_main, h, h_bytes, d, tl, cnt, n0, sl, W, n_mt, sink, c_fold,
+                                   issued, nxt, wa0, wa1, wa2, wa3);
+            else
+                narrow_tile<WK, 4>(lds_main, h, h_bytes, d, tl, cnt, n0, sl, W, n_mt, sink, c_fold,
+                                   issued, nxt, wa0, wa1, wa2, wa3);
+            issued = nxt >= 0;
+        }
+        sl += step;
+        if (sl >= n_end) return;
+    }
+}
+
+// ------------------------------------------------------------- big token tiles
+// From 129 live tokens a 128-token tile streams the dictionary more than once
+// (or, with few slices, leaves the reuse to chance), and from about 200 the
+// matrix cores bound it, not HBM.  Here a workgroup multiplies 256 latents by
+// 256 tokens, each of its eight waves 64 x 128 (128 accumulator registers).
+// The token rows of a K stage of 32 are shared through LDS (double buffered,
+// one barrier a stage, staged in registers); the dictionary goes straight into
+// the registers of the two waves that share a latent quarter: both operands
+// through LDS are 128 KB of traffic a stage, as long as the stage's MFMAs.
+// Measured at 391 tokens, m = 32768, d = 4096, per launch: 258 us as four
+// 128-token tiles in turn, 156 with both operands through LDS, 143 so.
+constexpr int kBigTok = 256;
+constexpr int kBigPieces = 1024;  // 16-byte pieces of a stage's token rows
+
+// Stage swizzle: the 16-byte piece c of token n sits at n*4 + (c ^ gsw(n));
+// with it the MFMA-layout reads of 16 tokens x 4 pieces hit distinct banks.
+__device__ __forceinline__ int gsw(int n) { return ((n >> 3) ^ (n >> 4)) & 3; }
+
+// Whether an app with cnt live tokens takes big tiles: always from 129 tokens
+// on whole slices, where the alternative streams the dictionary once per 128
+// tokens; on slices cut in two where they are the cheaper way to deal the work
+// to 256 CUs (a 128-token tile of half a slice costs about 12 units, a big
+// tile 20); never on slices cut in four, whose dictionaries have too few whole
+// ones to fill the CUs.  The rule holds the routing's count against sizes
+// alone, so that every call that can encode an app decides alike.
+__device__ __forceinline__ bool big_tiles(int cnt, int n_mt, int n_sl) {
+    if (cnt <= kBN) return false;
+    if (n_sl == n_mt) return true;
+    const int cut = n_sl / n_mt;
+    if (cut > 2) return false;
+    const int small = ((n_sl + 255) / 256) * ((cnt + kBN - 1) / kBN) * (4 + 16 / cut);
+    const int big = ((n_mt * ((cnt + kBigTok - 1) / kBigTok) + 255) / 256) * 20;
+    return big < small;
+}
+
+template <int WK>
+__device__ __forceinline__ void big_tile(uint4* lds_main, const uint16_t* __restrict__ h,
+                                         uint32_t h_bytes, int32_t d, const int32_t* tl, int cnt,
+                                         int nt, int mt, const uint16_t* __restrict__ W, int n_mt,
+                                         const SliceSink sink, const float* __restrict__ c_fold) {
+    // opaque, so that nothing computed from it here is merged with the other
+    // paths' address arithmetic and held in registers across both
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
+    const int lane = tid & 63, wave = tid >> 6;
+    const int wm = wave & 3, wn = wave >> 2;  // 64 latents, 128 tokens
+    const int g = lane >> 5, j32 = lane & 31;
+    const int n0 = nt * kBigTok;
+    const int ntok = min(kBigTok, cnt - n0);
+    const int nS = d / 32;  // a multiple of 8
+    uint4* xsb = lds_main;
+    // a stage of 32 is half a K chunk: steps 2 hh, 2 hh + 1 of its four; this
+    // wave's A operands of step s, latent group a: piece (2 wm + a) * 256 +
+    // (2 hh + s) * 64 + lane of the slice's chunk
+    const char* Wb = reinterpret_cast<const char*>(W) + static_cast<int64_t>(mt) * 32768;
+    const int64_t chunk = static_cast<int64_t>(n_mt) * 32768;
+    const uint32_t woff = static_cast<uint32_t>(2 * wm * 256 + lane) * 16u;
+    uint32_t xoff[2];
+    int xdst[2];
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+        const int P = tid + kEncThreads * p;
+        const int n = P >> 2, c = P & 3;
+        xoff[p] = n < ntok ? static_cast<uint32_t>(tl[n0 + n]) * static_cast<uint32_t>(d) * 2u +
+                                 c * 16u
+                           : kOutOfRange;
+        xdst[p] = n * 4 + (c ^ gsw(n));
+    }
+    auto load_w = [&](uint4 (&w)[4], int j) __attribute__((always_inline)) {
+        const int jc = min(j, nS - 1);
+        const __amdgpu_buffer_rsrc_t wr = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<char*>(Wb + (jc >> 1) * chunk + (jc & 1) * 2048), 0,
+            j < nS ? 32768 - 2048 : 0, kBufferDword3);
+#pragma unroll
+        for (int q = 0; q < 4; ++q)  // q = 2 s + a
+            w[q] = buffer_load16<0>(wr, woff + (q & 1) * 4096u + (q >> 1) * 1024u, 0);
+    };
+    auto load_x = [&](uint4 (&x)[2], int j) __attribute__((always_inline)) {
+        const __amdgpu_buffer_rsrc_t xr = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<uint16_t*>(h), 0, j < nS ? static_cast<int>(h_bytes) : 0, kBufferDword3);
+#pragma unroll
+        for (int p = 0; p < 2; ++p)
+            x[p] = buffer_load16<0>(xr, xoff[p], j < nS ? static_cast<uint32_t>(j) * 64u : 0u);
+    };
+    auto store_x = [&](const uint4 (&x)[2], int j) __attribute__((always_inline)) {
+#pragma unroll
+        for (int p = 0; p < 2; ++p) xsb[(j & 1) * kBigPieces + xdst[p]] = x[p];
+    };
+    f32x16_t acc[2][4];
+    {
+        const float* cf = c_fold + mt * kBM + 64 * wm + 4 * g;
+#pragma unroll
+        for (int a = 0; a < 2; ++a)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const float4 c4 = *reinterpret_cast<const float4*>(cf + 32 * a + 8 * q);
+#pragma unroll
+                for (int nb = 0; nb < 4; ++nb) {
+                    acc[a][nb][4 * q + 0] = c4.x;
+                    acc[a][nb][4 * q + 1] = c4.y;
+                    acc[a][nb][4 * q + 2] = c4.z;
+                    acc[a][nb][4 * q + 3] = c4.w;
+                }
+            }
+    }
+    auto compute = [&](const uint4 (&w)[4], int j) __attribute__((always_inline)) {
+        const uint4* xb = xsb + (j & 1) * kBigPieces;
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            uint4 B[4];
+#pragma unroll
+            for (int nb = 0; nb < 4; ++nb) {
+                const int n = 128 * wn + 32 * nb + j32;
+                B[nb] = xb[n * 4 + ((2 * s + g) ^ gsw(n))];
+            }
+#pragma unroll
+            for (int a = 0; a < 2; ++a)
+#pragma unroll
+                for (int nb = 0; nb < 4; ++nb)
+                    acc[a][nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                        as_bf16x8(w[2 * s + a]), as_bf16x8(B[nb]), acc[a][nb], 0, 0, 0);
+        }
+    };
+    // stage j is multiplied, stage j + 1's token rows move to the other buffer
+    // (which every wave left before this step's barrier), and later stages are
+    // fetched: the rows two ahead, the dictionary three ahead into the
+    // registers just used
+    auto step = [&](int j, uint4 (&w)[4], uint4 (&xload)[2], const uint4 (&xnext)[2])
+        __attribute__((always_inline)) {
+        load_x(xload, j + 2);
+        __syncthreads();
+        compute(w, j);
+        store_x(xnext, j + 1);
+        load_w(w, j + 3);
+    };
+    uint4 w0[4], w1[4], w2[4], x0[2], x1[2];
+    load_x(x0, 0);
+    load_w(w0, 0);
+    load_x(x1, 1);
+    load_w(w1, 1);
+    load_w(w2, 2);
+    store_x(x0, 0);
+    for (int j = 0;; j += 6) {  // an even number of stages
+        step(j, w0, x0, x1);
+        step(j + 1, w1, x1, x0);
+        if (j + 2 == nS) break;
+        step(j + 2, w2, x0, x1);
+        step(j + 3, w0, x1, x0);
+        if (j + 4 == nS) break;
+        step(j + 4, w1, x0, x1);
+        step(j + 5, w2, x1, x0);
+        if (j + 6 == nS) break;
+    }
+
+    // acc[a][nb][r] holds latent 64*wm + 32*a + 8*(r/4) + 4*g + r%4 of token
+    // 128*wn + 32*nb + j32; the tile's tokens are selected 128 at a time
+    float* V = reinterpret_cast<float*>(lds_main);
+    for (int half = 0; half < 2; ++half) {
+        if (128 * half >= ntok) break;  // uniform
+        __syncthreads();  // the stages, or the first half's rows, are read
+        if (wn == half) {
+#pragma unroll
+            for (int nb = 0; nb < 4; ++nb)
+#pragma unroll
+                for (int a = 0; a < 2; ++a) {
+                    float* rowp = V + (32 * nb + j32) * kSelStride + 64 * wm + 32 * a + 4 * g;
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+                        *reinterpret_cast<float4*>(rowp + 8 * j) =
+                            make_float4(acc[a][nb][4 * j], acc[a][nb][4 * j + 1],
+                                        acc[a][nb][4 * j + 2], acc[a][nb][4 * j + 3]);
+                }
+        }
+        __syncthreads();
+        if (128 * half + 16 * wave < ntok) {  // uniform over the wave
+            constexpr int LPS = 8 / WK;
+            const int q8 = lane & 7;
+            const int sl = mt * WK + q8 / LPS;
+            // one token per lane group at a time: the second half's
+            // accumulators are still held
+#pragma unroll 1
+            for (int r = 16 * wave + (lane >> 3), i = 0; i < 2; r += 8, ++i) {
+                const int64_t row = static_cast<int64_t>(n0 + 128 * half + r) * sink.n_sl + sl;
+                const float* const vr[1] = {V + r * kSelStride + 32 * q8};
+                const bool ok[1] = {128 * half + r < ntok};
+                uint2* const dst[1] = {sink.cand + row * sink.cap};
+                int32_t* const co[1] = {sink.tile_cnt + row};
+                float* const to[1] = {sink.tile_tau + row};
+                select_slices<true, 1, 32, LPS, 1>(vr, 0, q8 % LPS, ok, sink.z, sink.lo_cnt,
+                                                   sink.cap, mt * kBM + 32 * q8, dst, co, to);
+            }
+        }
+    }
+    __syncthreads();  // the rows are read before what runs next
+}
+
+// A value that is the same in every lane, in a scalar register.
+__device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
+
+// K loop: token chunks and stages; epilogue: the selection rows (of a narrow
+// slice, its partial-sum planes)
+constexpr int kLdsMain = Narrow<4>::kPart * 4 / 4;  // 16-byte pieces
+static_assert(kLdsMain >= kBN * kSelStride / 4 && kLdsMain >= Narrow<2>::kPart * 2 / 4 &&
+                  kLdsMain >= 2 * Narrow<4>::kPieces && kLdsMain >= 2 * kBigPieces,
+              "every path's LDS fits");
+
+// Candidates of one app.  WK: the cut of its slices (1: whole ones of 256
+// latents); BIG: the batch may hold more than 128 live tokens of the app, so
+// that big tiles are compiled in.  Workgroup u owns slice u and takes its live
+// token tiles in turn; with big tiles the pairs (slice, 256 tokens) are dealt
+// to the workgroups.
+//
+// With r_req given, the kernel also builds the step's routing (in place
+// of a route-build launch): every workgroup builds its app's token list
+// in LDS from the routing inputs staged there (in the space of the K
+// loop's token chunks); workgroup a < n_apps publishes app a's list and
+// count, and workgroup 0 the token masks and the error word.  A
+// workgroup with a slice starts its first dictionary chunks as soon as the
+// staged table shows a request subscribed to the app, so that the stream
+// runs while the list is built (without a subscriber it reads nothing).
+template <int WK, bool BIG>
+__global__ void __launch_bounds__(kEncThreads, 1)
+sae_stream_kernel(const uint16_t* __restrict__ h, int32_t d,
+                  const int32_t* __restrict__ app_count, const int32_t* __restrict__ tok_list,
+                  const uint16_t* __restrict__ W, const float* __restrict__ c_fold,
+                  int32_t n_mt, int32_t T_max, float z_guess, int32_t lo_cnt, int32_t cap,
+                  uint2* __restrict__ cand, int32_t* __restrict__ tile_cnt,
+                  float* __restrict__ tile_tau, const int32_t* __restrict__ r_req,
+                  const int32_t* __restrict__ r_tvalid, const uint32_t* __restrict__ r_sub,
+                  int32_t r_Rmax, int32_t r_napps, int32_t r_bit,
+                  uint32_t* __restrict__ r_mask, int32_t* __restrict__ r_count,
+                  int32_t* __restrict__ r_lists, uint32_t* __restrict__ r_err) {
+    __shared__ uint4 lds_main[WK == 1 ? kBN * kSelStride / 4 : kLdsMain];
     __shared__ int32_t list_s[kRouteMaxT];    // the app's token list (in-kernel route build)
     __shared__ int32_t rtot_s[kEncWaves];
     __shared__ int32_t seen_s[kEncWaves];
-
-    // Tile order.  Few token tiles (decode): one workgroup per latent tile,
-    // which takes the live token tiles of its slice in turn (no workgroup
-    // is launched for a tile past the live count; the first tile, the one
-    // every live token count reaches, spreads over every CU).
-    // Many token tiles (prefill): launch slot L runs on XCD L % 8; XCD x
-    // owns the latent tiles [x*M8, (x+1)*M8) and walks them in blocks of 8
-    // token tiles x 4 latent tiles, 32 consecutive slots per block, token
-    // blocks fastest.  The 32 workgroups of a block run together on the
-    // XCD's 32 CUs, so each K chunk of 8 token tiles and 4 dictionary
-    // slices is fetched into the XCD's L2 once and read by 4 and 8
-    // workgroups; consecutive blocks reuse the same 4 slices.
-    int nt, mt;
-    bool live;  // the tile exists (its tokens are counted below)
-    if (n_nt <= kLatentFastTiles) {
-        nt = L / n_mt;
-        mt = L % n_mt;
-        live = nt < n_nt;
-    } else {
-        const int xcd = L % 8, slot = L / 8;
-        const int m8 = (n_mt + 7) / 8;              // latent tiles per XCD
-        const int nbt = (n_nt + kBlkTok - 1) / kBlkTok;
-        const int b = slot / (kBlkTok * kBlkLat), p = slot % (kBlkTok * kBlkLat);
-        const int bt = b % nbt, bl = b / nbt;
-        const int lt = kBlkLat * bl + p / kBlkTok;
-        nt = kBlkTok * bt + p % kBlkTok;
-        mt = xcd * m8 + lt;
-        live = nt < n_nt && lt < m8;
-    }
-    live = live && mt < n_mt;
-
+    const int own = blockIdx.x;
+    const int n_sl = n_mt * WK;
+    const bool live = own < n_sl;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const SliceSrc src = slice_src(W, n_mt, mt);
+    const int nW = d / (kBK * WK);
+    const SliceSrc src = slice_src(W, n_mt, min(own, n_mt - 1));
     uint4 wa0[4], wa1[4], wa2[4], wa3[4];   // W ring: 4 chunks, 3 in flight
     float cfv[16];
+    auto first_chunks = [&]() __attribute__((always_inline)) {
+        if constexpr (WK == 1) {
+            load_chunk(wa0, src.base);
+            load_chunk(wa1, src.base + src.stride);
+            load_chunk(wa2, src.base + 2 * src.stride);
+            load_bias(cfv, c_fold, own);
+        } else {
+            narrow_load<WK>(wa0, W, n_mt, own, 0, nW);
+            narrow_load<WK>(wa1, W, n_mt, own, 1, nW);
+            narrow_load<WK>(wa2, W, n_mt, own, 2, nW);
+        }
+    };
 
-    // With r_req given, the kernel also builds the step's routing (in place
-    // of a route-build launch): every workgroup builds its app's token list
-    // in LDS from the routing inputs staged there (in the space of the K
-    // loop's token chunks); workgroup a < n_apps publishes app a's list and
-    // count, and workgroup 0 the token masks and the error word.  A
-    // workgroup of the first token tile starts its first dictionary chunks
-    // as soon as the staged table shows a request subscribed to the app, so
-    // that the stream runs while the list is built (without a subscriber it
-    // reads nothing).
     const int32_t* tl = tok_list;
     int cnt = 0;
     bool w_issued = false;
@@ -668,12 +1134,12 @@ __device__ __forceinline__ void stream_tile(
         static_assert(sizeof(lds_main) >= (kRouteMaxT + kStageSubMax) * 4, "staging fits");
         int32_t* req_s = reinterpret_cast<int32_t*>(lds_main);
         uint32_t* sub_s = reinterpret_cast<uint32_t*>(lds_main) + kRouteMaxT;
-        const bool seen = stage_route<kEncThreads>(r_req, r_Tmax, r_sub, r_Rmax, req_s, sub_s,
+        const bool seen = stage_route<kEncThreads>(r_req, T_max, r_sub, r_Rmax, req_s, sub_s,
                                                    1u << r_bit);
         const uint64_t seen_b = wave_ballot(seen);
         if (lane == 0) seen_s[wave] = seen_b != 0;
         uint32_t err = 0;
-        const int32_t tv = clamp_t_valid(*r_tvalid, r_Tmax, err);
+        const int32_t tv = clamp_t_valid(*r_tvalid, T_max, err);
         const uint32_t keep = r_napps >= 32 ? 0xFFFFFFFFu : ((1u << r_napps) - 1u);
         uint32_t* masks = own == 0 ? r_mask : nullptr;
         __syncthreads();  // the staged inputs
@@ -683,60 +1149,62 @@ __device__ __forceinline__ void stream_tile(
         // no request subscribes to the app: no token is listed, and a
         // workgroup with nothing to publish is done
         if (!any && own >= r_napps) return;  // uniform
-        if (live && nt == 0 && any) {  // uniform
-            load_chunk(wa0, src.base);
-            load_chunk(wa1, src.base + src.stride);
-            load_chunk(wa2, src.base + 2 * src.stride);
-            load_bias(cfv, c_fold, mt);
+        // (of a narrow slice that may yet be part of a big tile they would
+        // only hold registers)
+        if (live && any && (WK == 1 || !BIG)) {  // uniform
+            first_chunks();
             w_issued = true;
         }
         if (own < r_napps && own != r_bit) {
             const int32_t n = build_token_list<kEncThreads>(req_s, tv, sub_s, r_sub, r_Rmax, keep,
-                                                            own, r_Tmax, list_s, rtot_s, masks,
+                                                            own, T_max, list_s, rtot_s, masks,
                                                             err);
             masks = nullptr;
-            publish_token_list<kEncThreads>(list_s, n, r_Tmax,
-                                            r_lists + static_cast<int64_t>(own) * r_Tmax,
+            publish_token_list<kEncThreads>(list_s, n, T_max,
+                                            r_lists + static_cast<int64_t>(own) * T_max,
                                             r_count + own);
             __syncthreads();  // list_s is rebuilt below
         }
-        cnt = build_token_list<kEncThreads>(req_s, tv, sub_s, r_sub, r_Rmax, keep, r_bit, r_Tmax,
+        cnt = build_token_list<kEncThreads>(req_s, tv, sub_s, r_sub, r_Rmax, keep, r_bit, T_max,
                                             list_s, rtot_s, masks, err);
         if (own == r_bit)
-            publish_token_list<kEncThreads>(list_s, cnt, r_Tmax,
-                                            r_lists + static_cast<int64_t>(r_bit) * r_Tmax,
+            publish_token_list<kEncThreads>(list_s, cnt, T_max,
+                                            r_lists + static_cast<int64_t>(r_bit) * T_max,
                                             r_count + r_bit);
         if (own == 0) publish_error(err, r_err);
         tl = list_s;
     } else {
         cnt = *app_count;
     }
-    if (!live || nt * kBN >= cnt) return;
-    const SliceSink sink{cand, tile_cnt, tile_tau, n_mt, lo_cnt, cap, z_guess};
-    slice_tiles(lds_main, h, d, tl, cnt, nt, n_nt <= kLatentFastTiles, mt, src, sink, w_issued,
-                src, false, 0, nullptr, c_fold, wa0, wa1, wa2, wa3, cfv);
+    const SliceSink sink{cand, tile_cnt, tile_tau, n_sl, lo_cnt, cap, z_guess};
+    if constexpr (BIG) {
+        if (big_tiles(cnt, n_mt, n_sl)) {  // uniform
+            const int units = n_mt * ((cnt + kBigTok - 1) / kBigTok);
+            const uint32_t h_bytes = static_cast<uint32_t>(T_max) * static_cast<uint32_t>(d) * 2u;
+            for (int u = own; u < units; u += static_cast<int>(gridDim.x))
+                big_tile<WK>(lds_main, h, h_bytes, d, tl, cnt, u / n_mt, u % n_mt, W, n_mt, sink,
+                             c_fold);
+            return;
+        }
+    }
+    if (!live || cnt <= 0) return;
+    if constexpr (WK == 1)
+        slice_tiles<BIG>(lds_main, h, d, tl, cnt, own, src, [&]() { return sink; }, w_issued, src,
+                         false, 0, [&]() { return c_fold; }, c_fold, wa0, wa1, wa2, wa3, cfv);
+    else
+        narrow_slices<WK>(lds_main, h,
+                          static_cast<uint32_t>(T_max) * static_cast<uint32_t>(d) * 2u, d, tl, cnt,
+                          own, n_sl, n_sl, W, n_mt, sink, c_fold, w_issued, wa0, wa1, wa2, wa3);
 }
 
-__global__ void __launch_bounds__(kEncThreads, 1)
-sae_stream_kernel(const uint16_t* __restrict__ h, int32_t d,
-                  const int32_t* __restrict__ app_count, const int32_t* __restrict__ tok_list,
-                  const uint16_t* __restrict__ W, const float* __restrict__ c_fold,
-                  int32_t n_mt, int32_t n_nt, float z_guess, int32_t lo_cnt, int32_t cap,
-                  uint2* __restrict__ cand, int32_t* __restrict__ tile_cnt,
-                  float* __restrict__ tile_tau, const int32_t* __restrict__ r_req,
-                  const int32_t* __restrict__ r_tvalid, const uint32_t* __restrict__ r_sub,
-                  int32_t r_Rmax, int32_t r_Tmax, int32_t r_napps, int32_t r_bit,
-                  uint32_t* __restrict__ r_mask, int32_t* __restrict__ r_count,
-                  int32_t* __restrict__ r_lists, uint32_t* __restrict__ r_err) {
-    stream_tile(blockIdx.x, blockIdx.x, h, d, app_count, tok_list, W, c_fold, n_mt, n_nt,
-                z_guess, lo_cnt, cap, cand, tile_cnt, tile_tau, r_req, r_tvalid, r_sub, r_Rmax,
-                r_Tmax, r_napps, r_bit, r_mask, r_count, r_lists, r_err);
-}
-
-// Several SAE apps of one hook in one launch: the apps' grids follow each
-// other (app i owns launch slots [grid0[i], grid0[i + 1])), so a CU that
-// finishes its slice of one app takes a slice of the next, and the step
-// pays one launch for every app's candidates.
+// Several SAE apps of one hook in one launch, on a persistent grid: an app's
+// units are its slices, each over the live token tiles in turn, or its (slice,
+// 256 tokens) pairs with big tiles; an app without a token has none.
+// Workgroup w runs units w, w + G, w + 2G, ... of the apps' units laid end to
+// end (G the grid, at most one workgroup per CU).  The routing inputs are
+// staged once per workgroup, in LDS of their own; the dictionary stream runs on
+// from one whole slice into the next, so the next slice's first chunks load
+// while this one's candidates are selected.
 struct EncApp {
     const int32_t* app_count;
     const int32_t* tok_list;
@@ -745,110 +1213,104 @@ struct EncApp {
     uint2* cand;
     int32_t* tile_cnt;
     float* tile_tau;
-    int32_t n_mt, lo_cnt, cap, bit, grid0;
+    int32_t n_mt, n_sl, lo_cnt, cap, bit;
     float z;
 };
 struct EncApps {
     EncApp a[kMultiMax];
-    int32_t n, grid_end;
+    int32_t n;
 };
 
-__global__ void __launch_bounds__(kEncThreads, 1)
-sae_stream_multi_kernel(const uint16_t* __restrict__ h, int32_t d, int32_t n_nt, EncApps apps,
-                        const int32_t* __restrict__ r_req, const int32_t* __restrict__ r_tvalid,
-                        const uint32_t* __restrict__ r_sub, int32_t r_Rmax, int32_t r_Tmax,
-                        int32_t r_napps, uint32_t* __restrict__ r_mask,
-                        int32_t* __restrict__ r_count, int32_t* __restrict__ r_lists,
-                        uint32_t* __restrict__ r_err) {
-    const int g = blockIdx.x;
-    int i = 0;
-    for (int j = 1; j < apps.n; ++j) i = g >= apps.a[j].grid0 ? j : i;  // uniform
-    const EncApp& a = apps.a[i];
-    stream_tile(g - a.grid0, g, h, d, a.app_count, a.tok_list, a.W, a.c_fold, a.n_mt, n_nt, a.z,
-                a.lo_cnt, a.cap, a.cand, a.tile_cnt, a.tile_tau, r_req, r_tvalid, r_sub, r_Rmax,
-                r_Tmax, r_napps, a.bit, r_mask, r_count, r_lists, r_err);
-}
-
-// The same batch with few token tiles, on a persistent grid: workgroup w
-// runs slices w, w + G, w + 2G, ... of the apps' slices laid end to end (G
-// the grid, at most one workgroup per CU), each over its app's live token
-// tiles in turn, and skips the slices of an app without a token.  The
-// routing inputs are staged once per workgroup, in LDS of their own; the
-// dictionary stream runs on from one slice into the next, so the next
-// slice's first chunks load while this one's candidates are selected.
+// NARROW: every app's slices are cut, else none's; BIG: as in sae_stream_kernel.
+template <bool NARROW, bool BIG>
 __global__ void __launch_bounds__(kEncThreads, 1)
 sae_stream_apps_kernel(const uint16_t* __restrict__ h, int32_t d, EncApps apps,
                        const int32_t* __restrict__ r_req, const int32_t* __restrict__ r_tvalid,
-                       const uint32_t* __restrict__ r_sub, int32_t r_Rmax, int32_t r_Tmax,
+                       const uint32_t* __restrict__ r_sub, int32_t r_Rmax, int32_t T_max,
                        int32_t r_napps, uint32_t* __restrict__ r_mask,
                        int32_t* __restrict__ r_count, int32_t* __restrict__ r_lists,
                        uint32_t* __restrict__ r_err) {
-    __shared__ uint4 lds_main[kBN * kSelStride / 4];
+    __shared__ uint4 lds_main[NARROW ? kLdsMain : kBN * kSelStride / 4];
     __shared__ int32_t list_s[kRouteMaxT];
     __shared__ int32_t rtot_s[kEncWaves];
     __shared__ int32_t stage_s[kRouteMaxT + kStageSubMax];
-    __shared__ uint32_t bits_s;
+    __shared__ int32_t cnt_s[kMultiMax];
     const int tid = threadIdx.x, lane = tid & 63;
-    const int own = blockIdx.x, G = gridDim.x, U = apps.grid_end;
+    const int own = blockIdx.x, G = gridDim.x;
 
-    // the batch's apps with at least one token (bit i for apps.a[i])
-    uint32_t live = 0;
     int32_t* req_s = stage_s;
     uint32_t* sub_s = reinterpret_cast<uint32_t*>(stage_s + kRouteMaxT);
     int32_t tv = 0;
     uint32_t keep = 0;
     if (r_req) {  // uniform
-        if (tid == 0) bits_s = 0u;
-        stage_route<kEncThreads>(r_req, r_Tmax, r_sub, r_Rmax, req_s, sub_s);
+        if (tid < kMultiMax) cnt_s[tid] = 0;
+        stage_route<kEncThreads>(r_req, T_max, r_sub, r_Rmax, req_s, sub_s);
         uint32_t err = 0;
-        tv = clamp_t_valid(*r_tvalid, r_Tmax, err);
+        tv = clamp_t_valid(*r_tvalid, T_max, err);
         keep = r_napps >= 32 ? 0xFFFFFFFFu : ((1u << r_napps) - 1u);
         __syncthreads();  // the staged inputs
-        // every app bit some token slot carries
-        uint32_t any = 0u;
-        for (int32_t t = tid; t < r_Tmax; t += kEncThreads)
-            any |= slot_mask_staged(req_s, t, tv, sub_s, r_sub, r_Rmax, keep, err);
-#pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) any |= __shfl_xor(any, off, kWave);
-        if (lane == 0 && any != 0u) atomicOr(&bits_s, any);
+        // every app's count
+        for (int32_t t0 = 0; t0 < T_max; t0 += kEncThreads) {
+            const int32_t t = t0 + tid;
+            const uint32_t m =
+                t < T_max ? slot_mask_staged(req_s, t, tv, sub_s, r_sub, r_Rmax, keep, err) : 0u;
+            for (int i = 0; i < apps.n; ++i) {
+                const int c = __popcll(wave_ballot((m >> apps.a[i].bit) & 1u));
+                if (lane == 0 && c > 0) atomicAdd(&cnt_s[i], c);
+            }
+        }
         if (own < r_napps) {
             const int32_t n = build_token_list<kEncThreads>(
-                req_s, tv, sub_s, r_sub, r_Rmax, keep, own, r_Tmax, list_s, rtot_s,
+                req_s, tv, sub_s, r_sub, r_Rmax, keep, own, T_max, list_s, rtot_s,
                 own == 0 ? r_mask : nullptr, err);
-            publish_token_list<kEncThreads>(list_s, n, r_Tmax,
-                                            r_lists + static_cast<int64_t>(own) * r_Tmax,
+            publish_token_list<kEncThreads>(list_s, n, T_max,
+                                            r_lists + static_cast<int64_t>(own) * T_max,
                                             r_count + own);
         }
         if (own == 0) publish_error(err, r_err);
-        __syncthreads();  // bits_s complete; list_s free
-        const uint32_t bits = bits_s;
-        for (int i = 0; i < apps.n; ++i) live |= ((bits >> apps.a[i].bit) & 1u) << i;
-    } else {
-        for (int i = 0; i < apps.n; ++i) live |= (*apps.a[i].app_count > 0 ? 1u : 0u) << i;
+    } else if (tid < apps.n) {
+        cnt_s[tid] = *apps.a[tid].app_count;
     }
+    __syncthreads();  // the counts; list_s free
 
-    auto app_of = [&](int u) {
-        int i = 0;
-        for (int j = 1; j < apps.n; ++j) i = u >= apps.a[j].grid0 ? j : i;
-        return i;
+    // the app's units: 0 without a token
+    auto units_of = [&](int i) {
+        const EncApp& a = apps.a[i];
+        const int c = uniform(cnt_s[i]);
+        if (c <= 0) return 0;
+        if (BIG && big_tiles(c, a.n_mt, a.n_sl)) return a.n_mt * ((c + kBigTok - 1) / kBigTok);
+        return a.n_sl;
     };
-    // the first of u, u + G, ... whose app has a token (U if none)
-    auto live_from = [&](int u) {
-        for (; u < U; u += G)
-            if ((live >> app_of(u)) & 1u) break;
-        return u;
+    // moves (i, base), an app and its first unit, to the app of unit u; false
+    // past the last unit
+    auto seek = [&](int u, int& i, int& base) {
+        for (; i < apps.n; ++i) {
+            const int n = units_of(i);
+            if (u < base + n) return true;
+            base += n;
+        }
+        return false;
     };
-    int u = live_from(own);
-    if (u >= U) return;  // uniform
-    int i = app_of(u);
-    int mt = u - apps.a[i].grid0;
-    SliceSrc src = slice_src(apps.a[i].W, apps.a[i].n_mt, mt);
+    // whether a unit of app i is a whole slice whose stream can start early
+    auto whole = [&](int i) {
+        const EncApp& a = apps.a[i];
+        return !NARROW && !(BIG && big_tiles(uniform(cnt_s[i]), a.n_mt, a.n_sl));
+    };
+    const uint32_t h_bytes = static_cast<uint32_t>(T_max) * static_cast<uint32_t>(d) * 2u;
+    int u = own, i = 0, base = 0;
+    if (!seek(u, i, base)) return;  // uniform
     uint4 wa0[4], wa1[4], wa2[4], wa3[4];
     float cfv[16];
-    load_chunk(wa0, src.base);
-    load_chunk(wa1, src.base + src.stride);
-    load_chunk(wa2, src.base + 2 * src.stride);
-    load_bias(cfv, apps.a[i].c_fold, mt);
+    SliceSrc src = slice_src(apps.a[i].W, apps.a[i].n_mt, 0);
+    bool issued = false;
+    if (whole(i)) {
+        src = slice_src(apps.a[i].W, apps.a[i].n_mt, u - base);
+        load_chunk(wa0, src.base);
+        load_chunk(wa1, src.base + src.stride);
+        load_chunk(wa2, src.base + 2 * src.stride);
+        load_bias(cfv, apps.a[i].c_fold, u - base);
+        issued = true;
+    }
     int list_app = -1, cnt = 0;
     const int32_t* tl = nullptr;
     for (;;) {
@@ -857,28 +1319,68 @@ sae_stream_apps_kernel(const uint16_t* __restrict__ h, int32_t d, EncApps apps,
             if (r_req) {
                 uint32_t e = 0;
                 cnt = build_token_list<kEncThreads>(req_s, tv, sub_s, r_sub, r_Rmax, keep, a.bit,
-                                                    r_Tmax, list_s, rtot_s, nullptr, e);
+                                                    T_max, list_s, rtot_s, nullptr, e);
                 tl = list_s;
             } else {
-                cnt = *a.app_count;
+                cnt = uniform(cnt_s[i]);
                 tl = a.tok_list;
             }
             list_app = i;
         }
-        const int un = live_from(u + G);
-        const bool has_nxt = un < U;
-        const int in = has_nxt ? app_of(un) : i;
-        const int mtn = has_nxt ? un - apps.a[in].grid0 : mt;
-        const SliceSrc nsrc = has_nxt ? slice_src(apps.a[in].W, apps.a[in].n_mt, mtn) : src;
-        const SliceSink sink{a.cand, a.tile_cnt, a.tile_tau, a.n_mt, a.lo_cnt, a.cap, a.z};
-        slice_tiles(lds_main, h, d, tl, cnt, 0, true, mt, src, sink, true, nsrc, has_nxt, mtn,
-                    apps.a[in].c_fold, a.c_fold, wa0, wa1, wa2, wa3, cfv);
-        if (!has_nxt) return;
+        const int unit = u - base;
+        const SliceSink sink{a.cand, a.tile_cnt, a.tile_tau, a.n_sl, a.lo_cnt, a.cap, a.z};
+        const bool bt = BIG && big_tiles(cnt, a.n_mt, a.n_sl);
+        int un = u + G;  // what runs next, if anything
+        // every narrow slice of this app that is this workgroup's, in one go
+        if (NARROW && !bt) un = u + (a.n_sl - unit + G - 1) / G * G;
+        int in = i, bn = base;
+        const bool more = seek(un, in, bn);
+        if (NARROW || bt) {
+            const int nt = unit / a.n_mt, mt = unit % a.n_mt;
+            if (bt)
+                big_tile<NARROW ? 2 : 1>(lds_main, h, h_bytes, d, tl, cnt, nt, mt, a.W, a.n_mt,
+                                         sink, a.c_fold);
+            else if (a.n_sl == 4 * a.n_mt)
+                narrow_slices<4>(lds_main, h, h_bytes, d, tl, cnt, unit, G, a.n_sl, a.W, a.n_mt,
+                                 sink, a.c_fold, false, wa0, wa1, wa2, wa3);
+            else
+                narrow_slices<2>(lds_main, h, h_bytes, d, tl, cnt, unit, G, a.n_sl, a.W, a.n_mt,
+                                 sink, a.c_fold, false, wa0, wa1, wa2, wa3);
+            // nothing is in flight (and the registers need not outlive the tile)
+            issued = false;
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                wa0[r] = wa1[r] = wa2[r] = wa3[r] = make_uint4(0u, 0u, 0u, 0u);
+#pragma unroll
+            for (int r = 0; r < 16; ++r) cfv[r] = 0.0f;
+        } else {
+            if (!issued) src = slice_src(a.W, a.n_mt, unit);
+            const bool run_on = more && whole(in);
+            const int mtn = run_on ? un - bn : unit;
+            const SliceSrc nsrc = run_on ? slice_src(apps.a[in].W, apps.a[in].n_mt, mtn) : src;
+            // the descriptors are read again where they are used (an opaque index
+            // keeps their fields out of registers until then)
+            auto sink_of = [&]() __attribute__((always_inline)) {
+                int k = i;
+                asm volatile("" : "+s"(k));
+                const EncApp& b = apps.a[k];
+                return SliceSink{b.cand, b.tile_cnt, b.tile_tau, b.n_sl, b.lo_cnt, b.cap, b.z};
+            };
+            auto bias_of = [&]() __attribute__((always_inline)) {
+                int k = in;
+                asm volatile("" : "+s"(k));
+                return apps.a[k].c_fold;
+            };
+            slice_tiles<BIG>(lds_main, h, d, tl, cnt, unit, src, sink_of, issued, nsrc, run_on,
+                             mtn, bias_of, a.c_fold, wa0, wa1, wa2, wa3, cfv);
+            src = nsrc;
+            issued = run_on;
+        }
+        if (!more) return;  // uniform
         __syncthreads();  // the tile rows and list_s are read before they are rewritten
         u = un;
         i = in;
-        mt = mtn;
-        src = nsrc;
+        base = bn;
     }
 }
 
@@ -904,14 +1406,6 @@ constexpr int kStagePieces = 1024;  // 16-byte pieces per operand per stage
 constexpr int kPrefillMinT = 1025;  // token slots from which the prefill GEMM runs
 constexpr int kGBlkTok = 8;         // XCD block: token tiles
 constexpr int kGBlkLat = 4;         // XCD block: latent tiles
-
-// Stage-plane LDS swizzle: the 16-byte piece c of token n sits at
-// n*4 + (c ^ gsw(n)); with it the MFMA-layout reads of 16 tokens x 4
-// pieces hit distinct banks.
-__device__ __forceinline__ int gsw(int n) { return ((n >> 3) ^ (n >> 4)) & 3; }
-
-// Word 3 of a raw buffer resource (32-bit element format, no swizzle).
-constexpr int kBufferDword3 = 0x00020000;
 
 // s_waitcnt: at most n vector-memory operations of this wave outstanding
 // and no LDS operation.
@@ -1545,7 +2039,7 @@ __device__ __forceinline__ float slice_dot(const uint16_t* __restrict__ Wp,
 // kFloorRounds times.  n: the workgroup's slot of the app's token list.
 __device__ __forceinline__ void merge_token(
     int n, const uint2* __restrict__ cand, const int32_t* __restrict__ tile_cnt,
-    const float* __restrict__ tile_tau, int32_t n_mt, int32_t cap,
+    const float* __restrict__ tile_tau, int32_t n_sl, int32_t n_mt, int32_t cap,
     const int32_t* __restrict__ app_count, const int32_t* __restrict__ tok_list, int32_t k,
     const uint16_t* __restrict__ h, int32_t d, const uint16_t* __restrict__ Wp,
     const float* __restrict__ c_fold, int32_t* __restrict__ idx_out,
@@ -1564,7 +2058,7 @@ __device__ __forceinline__ void merge_token(
     __shared__ uint32_t floor_s;
     __shared__ uint64_t rbest_s[kMergeWaves], kth_s;  // repair: next slice, k-th composite
     const int tid = threadIdx.x, lane = lane_id(), wave = tid / kWave;
-    const int64_t row0 = static_cast<int64_t>(n) * n_mt;
+    const int64_t row0 = static_cast<int64_t>(n) * n_sl;
     // The first round of the gather below does not depend on the token
     // count: its loads go out before the count is read (the slot's area
     // exists for every slot below T_max; a slot past the count leaves
@@ -1574,7 +2068,7 @@ __device__ __forceinline__ void merge_token(
     int c0 = 0;
     float tf0 = 0.0f;
     {
-        const bool own = tid < n_mt;
+        const bool own = tid < n_sl;
         const int64_t row = row0 + (own ? tid : 0);
         const uint4* src = reinterpret_cast<const uint4*>(cand + row * cap);
 #pragma unroll
@@ -1604,9 +2098,9 @@ __device__ __forceinline__ void merge_token(
     auto gather = [&](uint64_t floor) __attribute__((always_inline)) {
         int total = 0;
         uint64_t cmn = ~0ull, cmx = 0ull;
-        for (int t0 = 0; t0 < n_mt; t0 += kMergeThreads) {
+        for (int t0 = 0; t0 < n_sl; t0 += kMergeThreads) {
             const int tl = t0 + tid;
-            const bool own = tl < n_mt;
+            const bool own = tl < n_sl;
             const int64_t row = row0 + (own ? tl : 0);
             // count, threshold and the first 8 pairs of the slice, in one round
             // (a slice holds about 2-3 candidates; more are fetched below)
@@ -1905,11 +2399,16 @@ __device__ __forceinline__ void merge_token(
             uint64_t prev = ~0ull;  // the slices with bounds below it are left
             for (;;) {
                 uint64_t best = 0ull;
+                const int wk = n_sl / n_mt;
                 for (int q = tid; q < n_mt; q += kMergeThreads) {
-                    const uint32_t tk = f32_key(tile_tau[row0 + q]);
-                    const uint64_t bq = tk == 0u ? 0ull
-                                                 : (static_cast<uint64_t>(tk - 1u) << 32) |
-                                                       static_cast<uint32_t>(~(q * kBM));
+                    // of a cut slice's parts, the highest bound
+                    uint64_t bq = 0ull;
+                    for (int j = q * wk; j < (q + 1) * wk; ++j) {
+                        const uint32_t tk = f32_key(tile_tau[row0 + j]);
+                        if (tk != 0u)
+                            bq = max(bq, (static_cast<uint64_t>(tk - 1u) << 32) |
+                                             static_cast<uint32_t>(~(j * (kBM / wk))));
+                    }
                     if (bq < prev) best = max(best, bq);
                 }
                 best = wave_minmax_u64<true>(best);
@@ -2071,13 +2570,13 @@ __device__ __forceinline__ void merge_token(
 
 __global__ void __launch_bounds__(kMergeThreads) __attribute__((amdgpu_waves_per_eu(4)))
 sae_merge_kernel(const uint2* __restrict__ cand, const int32_t* __restrict__ tile_cnt,
-                 const float* __restrict__ tile_tau, int32_t n_mt, int32_t cap,
+                 const float* __restrict__ tile_tau, int32_t n_sl, int32_t n_mt, int32_t cap,
                  const int32_t* __restrict__ app_count, const int32_t* __restrict__ tok_list,
                  int32_t k, const uint16_t* __restrict__ h, int32_t d,
                  const uint16_t* __restrict__ Wp, const float* __restrict__ c_fold,
                  int32_t* __restrict__ idx_out, uint16_t* __restrict__ val_out,
                  RingOut ring) {
-    merge_token(blockIdx.x, cand, tile_cnt, tile_tau, n_mt, cap, app_count, tok_list, k, h, d,
+    merge_token(blockIdx.x, cand, tile_cnt, tile_tau, n_sl, n_mt, cap, app_count, tok_list, k, h, d,
                 Wp, c_fold, idx_out, val_out, ring);
 }
 
@@ -2093,7 +2592,7 @@ struct MergeApp {
     int32_t* idx_out;
     uint16_t* val_out;
     RingOut ring;
-    int32_t n_mt, cap, k;
+    int32_t n_sl, n_mt, cap, k;
 };
 struct MergeApps {
     MergeApp a[kMultiMax];
@@ -2120,23 +2619,55 @@ sae_merge_apps_kernel(const uint16_t* __restrict__ h, int32_t d, int32_t T_max, 
 #pragma unroll
         for (int j = 1; j < kMultiMax; ++j) i = j < n_apps && p >= start[j] ? j : i;
         const MergeApp& a = apps.a[i];
-        merge_token(p - start[i], a.cand, a.tile_cnt, a.tile_tau, a.n_mt, a.cap, a.app_count,
+        merge_token(p - start[i], a.cand, a.tile_cnt, a.tile_tau, a.n_sl, a.n_mt, a.cap, a.app_count,
                     a.tok_list, a.k, h, d, a.Wp, a.c_fold, a.idx_out, a.val_out, a.ring);
         __syncthreads();  // the token's LDS is read before the next token's gather
     }
 }
 
 // ------------------------------------------------------------------ launch
-static int enc_grid(int32_t n_mt, int32_t n_nt) {
-    if (n_nt <= kLatentFastTiles) return n_mt;  // one workgroup per slice, tiles in turn
-    const int m8 = (n_mt + 7) / 8;
-    const int nbt = (n_nt + kBlkTok - 1) / kBlkTok;
-    const int nbl = (m8 + kBlkLat - 1) / kBlkLat;
-    return 8 * nbt * nbl * kBlkTok * kBlkLat;
+// CUs of the current device (256 if the query fails), looked up once per device.
+static int32_t cu_count() {
+    constexpr int kDevs = 64;
+    static std::atomic<int32_t> cache[kDevs];
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kDevs) return 256;
+    int32_t n = cache[dev].load(std::memory_order_relaxed);
+    if (n <= 0) {
+        int v = 0;
+        n = hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&
+                    v > 0
+                ? v
+                : 256;
+        cache[dev].store(n, std::memory_order_relaxed);
+    }
+    return n;
 }
 
-// Candidate emission parameters for a dictionary of m latents and top-k:
-// the per-tile capacity, the lower count bound, and the standard normal
+// Slices that one 256-latent tile is cut into (see narrow_tile): as many as
+// keep the workgroups at 256 or fewer.  A CU alone draws about 45 GB/s, so 160
+// whole slices saturate HBM and more than 128 are left whole; batches of more
+// than 512 slots keep whole slices too, which keeps the candidate area of
+// every call that fitted the static workspace within it.
+static int32_t slice_cut(int32_t T_max, int32_t d, int32_t m) {
+    const int32_t n_mt = m / kBM;
+    if (T_max > 512 || static_cast<int64_t>(T_max) * d * 2 > 0x7FFFFFFF) return 1;
+    return n_mt <= 64 ? 4 : n_mt <= 128 ? 2 : 1;
+}
+
+// Whether big token tiles are compiled in (their buffer offsets are 32 bits).
+static bool big_possible(int32_t T_max, int32_t d) {
+    return T_max > kBN && static_cast<int64_t>(T_max) * d * 2 <= 0x7FFFFFFF;
+}
+
+// Most workgroups an app's candidates can use.
+static int32_t enc_units(int32_t T_max, int32_t d, int32_t n_mt, int32_t n_sl) {
+    const int32_t big = big_possible(T_max, d) && n_sl <= 2 * n_mt ? n_mt * ((T_max + kBigTok - 1) / kBigTok) : 0;
+    return n_sl > big ? n_sl : big;
+}
+
+// Candidate emission parameters for a dictionary of m latents in tiles of
+// `width`, and top-k: the per-tile capacity, the lower count bound, and the standard normal
 // quantile of the first threshold guess.
 struct EmitPlan {
     int cap, lo;
@@ -2145,8 +2676,8 @@ struct EmitPlan {
 
 // Pairs one tile may emit: four times a target of twice the tile's share of
 // the k winners, plus one.
-static int emit_cap(int32_t m, int32_t k) {
-    const int t = (2 * k * kBM + m - 1) / m + 1;
+static int emit_cap(int32_t m, int32_t k, int32_t width) {
+    const int t = (2 * k * width + m - 1) / m + 1;
     const int cap = 4 * (t < 2 ? 2 : t);
     return cap < kMaxCap ? cap : kMaxCap;
 }
@@ -2166,8 +2697,8 @@ static double falling_root(F f, double want) {
     return 0.5 * (a + b);
 }
 
-// The guess mean + z * stdev comes from the tile's own 256 values, so it is
-// off by about sqrt(1/256 + z^2/512) stdev.  A tile whose guess ends up
+// The guess mean + z * stdev comes from the tile's own values, so of 256 of
+// them it is off by about sqrt(1/256 + z^2/512) stdev.  A tile whose guess ends up
 // above the token's k-th value hides a winner and sends the token to the
 // repair (50 us of one workgroup), so the guess is aimed five such errors
 // below the k-th value's quantile, and at two values a tile or more.  A
@@ -2177,17 +2708,17 @@ static double falling_root(F f, double want) {
 // (repairs in most launches with the former aim of 2 a tile) merge 62 -> 9
 // us; 1777 tokens of width 2304, m = 16384, k = 64 (where the former rule
 // asked every tile for exactly 12 values) prefill GEMM 240 -> 146 us.
-static EmitPlan emit_plan(int32_t m, int32_t k) {
-    const int n_mt = m / kBM;
+static EmitPlan emit_plan(int32_t m, int32_t k, int32_t width) {
+    const int n = m / width;
     EmitPlan e;
-    e.cap = emit_cap(m, k);
-    const double share = static_cast<double>(k) / n_mt;  // of the winners, per tile
+    e.cap = emit_cap(m, k, width);
+    const double share = static_cast<double>(k) / n;  // of the winners, per tile
     double target = 2.0;
-    if (share < 0.45 * kBM) {
-        const double zk = falling_root(upper_tail, share / kBM);
+    if (share < 0.45 * width) {
+        const double zk = falling_root(upper_tail, share / width);
         const double z = falling_root(
-            [](double q) { return -(q + 5.0 * sqrt((1.0 + 0.5 * q * q) / kBM)); }, -zk);
-        target = kBM * upper_tail(z);
+            [width](double q) { return -(q + 5.0 * sqrt((1.0 + 0.5 * q * q) / width)); }, -zk);
+        target = width * upper_tail(z);
         // room for the counts' own spread below the capacity
         const double most = e.cap < kMaxCap ? e.cap - 1.8 * sqrt(e.cap) : 45.0;
         target = target < most ? target : most;
@@ -2195,21 +2726,21 @@ static EmitPlan emit_plan(int32_t m, int32_t k) {
     } else {
         target = 45.0;
     }
-    const double total = n_mt * target;
+    const double total = n * target;
     e.lo = total - k >= 6.0 * sqrt(total) ? 0 : (k < e.cap ? k : e.cap);
     const double want = e.lo ? 0.5 * (e.lo + e.cap) : target;
-    e.z = static_cast<float>(falling_root(upper_tail, want / kBM));
+    e.z = static_cast<float>(falling_root(upper_tail, want / width));
     return e;
 }
 
 struct CandArea {
-    uint2* cand;   // (fp32 bits, latent) pairs, [T_max][n_mt][cap]
-    int32_t* cnt;  // [T_max][n_mt]
-    float* tau;    // [T_max][n_mt]
+    uint2* cand;   // (fp32 bits, latent) pairs, [T_max][n_sl][cap]
+    int32_t* cnt;  // [T_max][n_sl]
+    float* tau;    // [T_max][n_sl]
 };
 
-static CandArea cand_area(void* base, int32_t T_max, int32_t n_mt, int cap) {
-    const size_t slots = static_cast<size_t>(T_max) * n_mt;
+static CandArea cand_area(void* base, int32_t T_max, int32_t n_sl, int cap) {
+    const size_t slots = static_cast<size_t>(T_max) * n_sl;
     CandArea a;
     a.cand = static_cast<uint2*>(base);
     a.cnt = reinterpret_cast<int32_t*>(a.cand + slots * cap);
@@ -2221,13 +2752,14 @@ static int32_t stage_tokens(int32_t T_max) {
     return (T_max + kGemmTok - 1) / kGemmTok * kGemmTok;
 }
 
-static size_t candidate_bytes(int32_t T_max, int32_t m, int32_t k) {
-    const size_t slots = static_cast<size_t>(T_max) * (m / kBM);
-    return slots * (static_cast<size_t>(emit_cap(m, k)) * 8u + 8u);
+static size_t candidate_bytes(int32_t T_max, int32_t d, int32_t m, int32_t k) {
+    const int32_t cut = slice_cut(T_max, d, m);
+    const size_t slots = static_cast<size_t>(T_max) * (m / kBM * cut);
+    return slots * (static_cast<size_t>(emit_cap(m, k, kBM / cut)) * 8u + 8u);
 }
 
 size_t sae_candidate_bytes(int32_t T_max, int32_t d, int32_t m, int32_t k) {
-    size_t bytes = (candidate_bytes(T_max, m, k) + 255u) / 256u * 256u;
+    size_t bytes = (candidate_bytes(T_max, d, m, k) + 255u) / 256u * 256u;
     if (T_max >= kPrefillMinT)  // staged token rows of the prefill GEMM
         bytes += static_cast<size_t>(stage_tokens(T_max)) * d * sizeof(uint16_t);
     return bytes;
@@ -2253,13 +2785,14 @@ hipError_t launch_sae_candidates(const uint16_t* h, int32_t d, int32_t T_max,
                                  const uint16_t* W_enc, const float* c_fold, int32_t m,
                                  int32_t k, void* cand, hipStream_t stream,
                                  const RouteIn* route) {
-    const int32_t n_mt = m / kBM;
-    const EmitPlan e = emit_plan(m, k);
-    const CandArea a = cand_area(cand, T_max, n_mt, e.cap);
+    const int32_t n_mt = m / kBM, cut = slice_cut(T_max, d, m), n_sl = n_mt * cut;
+    const EmitPlan e = emit_plan(m, k, kBM / cut);
+    const CandArea a = cand_area(cand, T_max, n_sl, e.cap);
+    int32_t grid = enc_units(T_max, d, n_mt, n_sl);
+    if (grid > n_sl) grid = n_sl > cu_count() ? n_sl : grid < cu_count() ? grid : cu_count();
     // the decode kernel routes when the batch fits its LDS list and its grid
     // has a workgroup for every app to publish
-    if (route && (T_max > kRouteMaxT ||
-                  enc_grid(n_mt, (T_max + kBN - 1) / kBN) < route->n_apps)) {
+    if (route && (T_max > kRouteMaxT || grid < route->n_apps)) {
         const hipError_t r = launch_route_build(route->req, route->T_valid, route->sub,
                                                 route->R_max, T_max, route->n_apps,
                                                 route->tok_mask, route->app_count,
@@ -2270,7 +2803,7 @@ hipError_t launch_sae_candidates(const uint16_t* h, int32_t d, int32_t T_max,
     if (T_max >= kPrefillMinT) {
         const int32_t n_pad = stage_tokens(T_max);
         uint16_t* xs = reinterpret_cast<uint16_t*>(
-            static_cast<char*>(cand) + (candidate_bytes(T_max, m, k) + 255u) / 256u * 256u);
+            static_cast<char*>(cand) + (candidate_bytes(T_max, d, m, k) + 255u) / 256u * 256u);
         const int64_t pieces = static_cast<int64_t>(n_pad) * (d / 8);
         hipLaunchKernelGGL(sae_xstage_kernel, dim3(static_cast<uint32_t>((pieces + 255) / 256)),
                            dim3(256), 0, stream, h, d, app_count, tok_list, n_pad, xs);
@@ -2283,14 +2816,16 @@ hipError_t launch_sae_candidates(const uint16_t* h, int32_t d, int32_t T_max,
                            n_mt, n_nt, e.z, e.lo, e.cap, a.cand, a.cnt, a.tau);
         return hipGetLastError();
     }
-    const int32_t n_nt = (T_max + kBN - 1) / kBN;
     const RouteIn none{};
     const RouteIn& ri = route ? *route : none;
-    hipLaunchKernelGGL(sae_stream_kernel, dim3(enc_grid(n_mt, n_nt)), dim3(kEncThreads), 0,
-                       stream, h, d, app_count, tok_list, W_enc, c_fold, n_mt, n_nt, e.z, e.lo,
-                       e.cap, a.cand, a.cnt, a.tau, ri.req, ri.T_valid, ri.sub, ri.R_max, T_max,
-                       ri.n_apps, ri.app_bit, ri.tok_mask, ri.app_count, ri.app_tokens,
-                       ri.err_word);
+    const bool big = big_possible(T_max, d);
+    const auto kernel = cut == 4   ? sae_stream_kernel<4, false>
+                        : cut == 2 ? (big ? sae_stream_kernel<2, true> : sae_stream_kernel<2, false>)
+                                   : (big ? sae_stream_kernel<1, true> : sae_stream_kernel<1, false>);
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(kEncThreads), 0, stream, h, d, app_count, tok_list,
+                       W_enc, c_fold, n_mt, T_max, e.z, e.lo, e.cap, a.cand, a.cnt, a.tau, ri.req,
+                       ri.T_valid, ri.sub, ri.R_max, ri.n_apps, ri.app_bit, ri.tok_mask,
+                       ri.app_count, ri.app_tokens, ri.err_word);
     return hipGetLastError();
 }
 
@@ -2299,9 +2834,9 @@ hipError_t launch_sae_merge(const uint16_t* h, int32_t d, int32_t T_max,
                             const uint16_t* W_enc, const float* c_fold, int32_t m, int32_t k,
                             int32_t* idx_out, uint16_t* val_out, void* cand,
                             const MergeRing* ring, hipStream_t stream) {
-    const int32_t n_mt = m / kBM;
-    const int cap = emit_cap(m, k);
-    const CandArea a = cand_area(cand, T_max, n_mt, cap);
+    const int32_t n_mt = m / kBM, cut = slice_cut(T_max, d, m), n_sl = n_mt * cut;
+    const int cap = emit_cap(m, k, kBM / cut);
+    const CandArea a = cand_area(cand, T_max, n_sl, cap);
     RingOut r{};
     if (ring) {
         r.slots = ring->slots;
@@ -2313,50 +2848,37 @@ hipError_t launch_sae_merge(const uint16_t* h, int32_t d, int32_t T_max,
         r.app_id = ring->app_id;
     }
     hipLaunchKernelGGL(sae_merge_kernel, dim3(T_max), dim3(kMergeThreads), 0, stream, a.cand,
-                       a.cnt, a.tau, n_mt, cap, app_count, tok_list, k, h, d, W_enc,
+                       a.cnt, a.tau, n_sl, n_mt, cap, app_count, tok_list, k, h, d, W_enc,
                        c_fold, idx_out, val_out, r);
     return hipGetLastError();
 }
 
 bool sae_multi_supported(int32_t T_max) { return T_max < kPrefillMinT; }
 
-// CUs of the current device (256 if the query fails), looked up once per device.
-static int32_t cu_count() {
-    constexpr int kDevs = 64;
-    static std::atomic<int32_t> cache[kDevs];
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kDevs) return 256;
-    int32_t n = cache[dev].load(std::memory_order_relaxed);
-    if (n <= 0) {
-        int v = 0;
-        n = hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&
-                    v > 0
-                ? v
-                : 256;
-        cache[dev].store(n, std::memory_order_relaxed);
-    }
-    return n;
-}
-
 hipError_t launch_sae_encode_multi(const uint16_t* h, int32_t d, int32_t T_max, int32_t n,
                                    const SaeAppIn* apps, hipStream_t stream,
                                    const RouteIn* route) {
-    const int32_t n_nt = (T_max + kBN - 1) / kBN;
+    const bool big = big_possible(T_max, d);
     for (int32_t c0 = 0; c0 < n; c0 += kMultiMax) {
         const int32_t nc = n - c0 < kMultiMax ? n - c0 : kMultiMax;
-        EncApps ea;
+        // whole slices and cut ones in a launch each (most batches are of one
+        // kind): together they would not fit the registers
+        EncApps ea[2];
         MergeApps ma;
-        memset(&ea, 0, sizeof(ea));
+        memset(ea, 0, sizeof(ea));
         memset(&ma, 0, sizeof(ma));
-        int32_t grid = 0;
+        int32_t units[2] = {0, 0};
         for (int32_t i = 0; i < nc; ++i) {
             const SaeAppIn& in = apps[c0 + i];
-            const int32_t n_mt = in.m / kBM;
-            const EmitPlan e = emit_plan(in.m, in.k);
-            const CandArea a = cand_area(in.cand, T_max, n_mt, e.cap);
-            ea.a[i] = EncApp{in.app_count, in.tok_list, in.W, in.c_fold, a.cand, a.cnt, a.tau,
-                             n_mt, e.lo, e.cap, in.bit, grid, e.z};
-            grid += enc_grid(n_mt, n_nt);
+            const int32_t n_mt = in.m / kBM, cut = slice_cut(T_max, d, in.m);
+            const int32_t n_sl = n_mt * cut;
+            const EmitPlan e = emit_plan(in.m, in.k, kBM / cut);
+            const CandArea a = cand_area(in.cand, T_max, n_sl, e.cap);
+            const int kind = cut > 1 ? 1 : 0;
+            ea[kind].a[ea[kind].n++] =
+                EncApp{in.app_count, in.tok_list, in.W, in.c_fold, a.cand, a.cnt, a.tau,
+                       n_mt, n_sl, e.lo, e.cap, in.bit, e.z};
+            units[kind] += enc_units(T_max, d, n_mt, n_sl);
             RingOut r{};
             if (in.ring) {
                 r.slots = in.ring->slots;
@@ -2368,14 +2890,12 @@ hipError_t launch_sae_encode_multi(const uint16_t* h, int32_t d, int32_t T_max, 
                 r.app_id = in.ring->app_id;
             }
             ma.a[i] = MergeApp{a.cand, a.cnt, a.tau, in.app_count, in.tok_list, in.W, in.c_fold,
-                               in.idx_out, in.val_out, r, n_mt, e.cap, in.k};
+                               in.idx_out, in.val_out, r, n_sl, n_mt, e.cap, in.k};
         }
-        ea.n = nc;
-        ea.grid_end = grid;
         // the first launch builds the routing when the batch fits its LDS list
         // and its grid has a workgroup for every app to publish
         const RouteIn* ri = c0 == 0 ? route : nullptr;
-        if (ri && (T_max > kRouteMaxT || grid < ri->n_apps)) {
+        if (ri && (T_max > kRouteMaxT || units[0] + units[1] < ri->n_apps)) {
             const hipError_t r = launch_route_build(ri->req, ri->T_valid, ri->sub, ri->R_max,
                                                     T_max, ri->n_apps, ri->tok_mask,
                                                     ri->app_count, ri->app_tokens,
@@ -2383,22 +2903,25 @@ hipError_t launch_sae_encode_multi(const uint16_t* h, int32_t d, int32_t T_max, 
             if (r != hipSuccess) return r;
             ri = nullptr;
         }
-        const RouteIn none{};
-        const RouteIn& rr = ri ? *ri : none;
-        if (n_nt <= kLatentFastTiles) {
+        hipError_t e = hipSuccess;
+        for (int kind = 0; kind < 2; ++kind) {
+            if (ea[kind].n == 0) continue;
+            const RouteIn none{};
+            const RouteIn& rr = ri ? *ri : none;
             // persistent: one workgroup per CU (and one per app to publish)
-            int32_t g = grid < cu_count() ? grid : cu_count();
+            int32_t g = units[kind] < cu_count() ? units[kind] : cu_count();
             if (ri && g < ri->n_apps) g = ri->n_apps;
-            hipLaunchKernelGGL(sae_stream_apps_kernel, dim3(g), dim3(kEncThreads), 0, stream, h,
-                               d, ea, rr.req, rr.T_valid, rr.sub, rr.R_max, T_max, rr.n_apps,
+            const auto kernel =
+                kind ? (big ? sae_stream_apps_kernel<true, true> : sae_stream_apps_kernel<true, false>)
+                     : (big ? sae_stream_apps_kernel<false, true>
+                            : sae_stream_apps_kernel<false, false>);
+            hipLaunchKernelGGL(kernel, dim3(g), dim3(kEncThreads), 0, stream, h, d, ea[kind],
+                               rr.req, rr.T_valid, rr.sub, rr.R_max, T_max, rr.n_apps,
                                rr.tok_mask, rr.app_count, rr.app_tokens, rr.err_word);
-        } else {
-            hipLaunchKernelGGL(sae_stream_multi_kernel, dim3(grid), dim3(kEncThreads), 0, stream,
-                               h, d, n_nt, ea, rr.req, rr.T_valid, rr.sub, rr.R_max, T_max,
-                               rr.n_apps, rr.tok_mask, rr.app_count, rr.app_tokens, rr.err_word);
+            e = hipGetLastError();
+            if (e != hipSuccess) return e;
+            ri = nullptr;  // the routing is built
         }
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
         // persistent merges: up to four workgroups per CU
         const int32_t mg = nc * T_max < 4 * cu_count() ? nc * T_max : 4 * cu_count();
         hipLaunchKernelGGL(sae_merge_apps_kernel, dim3(mg), dim3(kMergeThreads), 0, stream, h, d,
@@ -2452,13 +2975,19 @@ struct ArgPointers<MergeApps> {
 void add_sae_kernels(std::vector<KernelInfo>& t) {
     t.push_back(kernel_info(sae_pack_kernel));
     t.push_back(kernel_info(sae_fold_kernel));
-    t.push_back(kernel_info(sae_stream_kernel));
+    t.push_back(kernel_info(sae_stream_kernel<1, false>));
+    t.push_back(kernel_info(sae_stream_kernel<1, true>));
+    t.push_back(kernel_info(sae_stream_kernel<2, false>));
+    t.push_back(kernel_info(sae_stream_kernel<2, true>));
+    t.push_back(kernel_info(sae_stream_kernel<4, false>));
     t.push_back(kernel_info(sae_xstage_kernel));
     t.push_back(kernel_info(sae_gemm_kernel));
     t.push_back(kernel_info(sae_merge_kernel));
-    t.push_back(kernel_info(sae_stream_multi_kernel));
     t.push_back(kernel_info(sae_merge_apps_kernel));
-    t.push_back(kernel_info(sae_stream_apps_kernel));
+    t.push_back(kernel_info(sae_stream_apps_kernel<false, false>));
+    t.push_back(kernel_info(sae_stream_apps_kernel<false, true>));
+    t.push_back(kernel_info(sae_stream_apps_kernel<true, false>));
+    t.push_back(kernel_info(sae_stream_apps_kernel<true, true>));
 }
 
 }  // namespace xmix
