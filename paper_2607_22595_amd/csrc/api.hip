@@ -27,6 +27,9 @@ bool bits_ok(const int32_t* bits, int32_t n, int32_t n_apps, BitList* out) {
         if (bits[i] < 0 || bits[i] >= n_apps) return false;
         out->bit[i] = bits[i];
     }
+    out->first = bits[0];
+    for (int i = 1; i < n; ++i)
+        if (bits[i] != bits[0] + i) out->first = -1;
     return true;
 }
 

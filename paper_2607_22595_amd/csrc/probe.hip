@@ -85,11 +85,8 @@ probe_token_kernel(const void* __restrict__ h, int32_t d, int32_t T_max,
             }
         }
         if (at < 0) continue;
-        const uint32_t mask = tok_mask[at];
-        uint32_t m = 0;
-        for (int p = 0; p < n_probe; ++p) m |= ((mask >> bits.bit[p]) & 1u) << p;
-        sel[j] = m;
-        any |= m;
+        sel[j] = select_bits(tok_mask[at], bits, n_probe);
+        any |= sel[j];
     }
     if (any == 0) return;  // uniform
 

@@ -23,8 +23,7 @@ router_kernel(void* __restrict__ logits, int32_t n_experts, int32_t n_elem,
     if (i >= n_elem) return;
     const int32_t t = i / n_experts, e = i - t * n_experts;
     const uint32_t mask = tok_mask[t];
-    uint32_t sel = 0;
-    for (int s = 0; s < n_router; ++s) sel |= ((mask >> bits.bit[s]) & 1u) << s;
+    const uint32_t sel = select_bits(mask, bits, n_router);
     if (sel == 0) return;
     double acc = BF16 ? static_cast<double>(bf16_to_f32(static_cast<const uint16_t*>(logits)[i]))
                       : static_cast<double>(static_cast<const float*>(logits)[i]);

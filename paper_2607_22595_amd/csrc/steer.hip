@@ -37,9 +37,7 @@ steer_kernel(void* __restrict__ h, int32_t d, int32_t T_max,
 #pragma unroll
     for (int j = 0; j < TT; ++j) {
         const int32_t t = min(t0 + j, T_max - 1);
-        const uint32_t mask = t0 + j < T_max ? tok_mask[t] : 0u;
-        uint32_t m = 0;
-        for (int s = 0; s < n_steer; ++s) m |= ((mask >> bits.bit[s]) & 1u) << s;
+        const uint32_t m = select_bits(t0 + j < T_max ? tok_mask[t] : 0u, bits, n_steer);
         sel[j] = m;
         any |= m;
         a_row[j] = m ? alpha + static_cast<int64_t>(req[t]) * n_steer : alpha;

@@ -70,9 +70,8 @@ steer_probe_kernel(void* __restrict__ h, int32_t d, int32_t T_max,
     } else {
         mask = tok_mask[t];
     }
-    uint32_t ss = 0, sp = 0;
-    for (int s = 0; s < n_steer; ++s) ss |= ((mask >> sbits.bit[s]) & 1u) << s;
-    for (int p = 0; p < n_probe; ++p) sp |= ((mask >> pbits.bit[p]) & 1u) << p;
+    const uint32_t ss = select_bits(mask, sbits, n_steer);
+    const uint32_t sp = select_bits(mask, pbits, n_probe);
     if ((ss | sp) == 0) return;
     const float* a_row = ss ? alpha + static_cast<int64_t>(rq) * n_steer : alpha;
 

@@ -222,3 +222,33 @@ def test_readback_row_sizes(px, widths, off):
         slots, head = oracle.compact(host, tm, 0, req, 3, 5, slots, head)
         assert int(ring.head[0].item()) == head and int(ring.head[1].item()) == 0
         assert np.array_equal(ring.slots.cpu().numpy(), slots)
+
+
+@pytest.mark.parametrize("sbits,pbits", [([0, 1, 2], [3, 4]), ([5, 6], [0, 1, 2]), ([6, 2, 4], [3, 0]),
+                                         ([1, 3], [6, 5, 4]), ([31, 0], [30, 31]), ([30, 31], [0])])
+def test_app_bits_in_any_order(px, sbits, pbits):
+    """Consecutive bits (one shift) and every other order, in the three kernels."""
+    T, d = 70, 264
+    rng, req, sub = batch(T, 32, p=0.4, seed=len(sbits) + 7 * pbits[0])
+    h = synth.normal_bf16("b/h", (T, d), 1.0)
+    v, w = synth.normal_bf16("b/v", (len(sbits), d), 0.2), synth.normal_bf16("b/w", (len(pbits), d), 0.1)
+    alpha = rng.uniform(-8, 8, (T, len(sbits))).astype(np.float32)
+    b = np.zeros(len(pbits), np.float32)
+    rt, _ = build(px, req, T, sub, 32)
+    tm = oracle.route(req, T, sub, 32)[0]
+    ref = oracle.steer(h, tm, req, v, sbits, alpha)
+    lr, _ = oracle.probe_token(h, tm, w, b, pbits)
+    for fused in (False, True):
+        hd = dev(h)
+        out = [torch.full((len(pbits), T), float("nan"), device="cuda") for _ in range(2)]
+        if fused:
+            px.xmix_steer_probe(hd, rt, dev(req), dev(v), sbits, dev(alpha), dev(w), dev(b), pbits,
+                                *out)
+        else:
+            px.xmix_probe_score(hd, rt, dev(w), dev(b), pbits, px.XMIX_PROBE_TOKEN, *out)
+            px.xmix_steer_apply(hd, rt, dev(req), dev(v), sbits, dev(alpha))
+        assert np.array_equal(torch_bits(hd), ref)
+        got = out[0].cpu().numpy()
+        assert np.array_equal(np.isnan(got), np.isnan(lr))
+        # 264 fp32 multiply-adds of terms of about 0.1
+        assert np.nanmax(np.abs(got - lr)) <= 264 * 2.0 ** -24 * 100
