@@ -3,6 +3,8 @@
 Argument marshalling only: every function below checks shapes and dtypes,
 takes device pointers and the current HIP stream from torch tensors, and
 calls the C entry point of the same name (declared in include/xmix.h).
+The calls of a step that is issued from Python call by call do so through
+the extension module _call (csrc/call.cpp), the others through ctypes.
 All arithmetic runs in the library's HIP kernels.  There is no fallback:
 importing this package fails if the built library is missing.
 
@@ -29,6 +31,7 @@ if not os.path.exists(LIB_PATH):
         "python paper_2607_22595_amd/build.py)")
 
 _lib = ctypes.CDLL(LIB_PATH)
+from . import _call  # noqa: E402  (built beside the library)
 
 XMIX_OK, XMIX_E_INVAL, XMIX_E_UNSUPPORTED, XMIX_E_WORKSPACE, XMIX_E_LAUNCH = range(5)
 XMIX_F32, XMIX_BF16 = 0, 1
@@ -137,6 +140,57 @@ for _name, (_args, _res) in _sigs.items():
 EXPORTED = tuple(_sigs)
 
 
+def _native(name: str, args: str, c_args: str):
+    """The C entry point `name` behind native checks and marshalling: its Python
+    arguments and the C arguments made of them, as csrc/call.cpp describes."""
+    return _call.Function(name, ctypes.cast(getattr(_lib, name), _vp).value, args, c_args)
+
+
+_STEER = "vecs:A[...,d] sbits:bits(n) alpha:f32[R,n]"
+_PROBE = "w:A[p,d] b:f32 pbits:bits(p) logit:*[p,T] score:*[p,T]"
+_ENCODE = ("h:bf16[T,d] route:struct bit:int W:struct b_enc?:* b_dec?:* fold?:* k:dim "
+           "idx:i32[T,k] val:bf16[T,k] ws:*")
+_ENCODE_C = "h d route bit W b_enc b_dec fold k idx val ws %ws"
+
+_route_build = _native(
+    "xmix_route_build", "req:i32{T} T_valid:i32 sub:i32 route:rt err:* stream:stream",
+    "req T_valid sub #sub route err stream")
+_route_gate = _native(
+    "xmix_route_gate", "route:struct bit:int signal:f32 threshold:f32 signal_bit:int req?:* "
+    "stream:stream", "route bit signal req #signal signal_bit threshold stream")
+_route_trigger = _native(
+    "xmix_route_trigger", "route:struct bit:int ids:i32 vocab:* size:int stream:stream",
+    "route bit ids vocab size stream")
+_steer_apply = _native(
+    "xmix_steer_apply", f"h:A[T,d] route:rt req:* {_STEER} stream:stream",
+    "h @A d route req vecs sbits alpha n R stream")
+_steer_probe = _native(
+    "xmix_steer_probe", f"h:A[T,d] route:rt req:* {_STEER} {_PROBE} stream:stream",
+    "h @A d route req vecs sbits alpha n R w b pbits p logit score stream")
+_route_steer_probe = _native(
+    "xmix_route_steer_probe", f"req:i32{{T}} T_valid:* sub:* route:rt err:* h:A[T,d] {_STEER} "
+    f"{_PROBE} stream:stream",
+    "req T_valid sub #sub route err h @A d vecs sbits alpha n w b pbits p logit score stream")
+_router_write = _native(
+    "xmix_router_write", "logits:A[T,E] route:rt bits:bits(n) offsets:f32[n,E] stream:stream",
+    "logits @A E route bits offsets n stream")
+_probe_score_token = _native(
+    "xmix_probe_score", "h:A[T,d] route:struct w:A[n,d] b:f32 bits:bits(n) mode:int cu?:* R:int "
+    "logit:*[n,T] score:* ws?:* stream:stream",
+    "h @A d route w b bits n mode cu R logit score ws %ws stream")
+_probe_score_span = _native(
+    "xmix_probe_score", "h:A[_,d] route:struct w:A[n,d] b:f32 bits:bits(n) mode:int cu?:* R:dim "
+    "logit:*[n,R] score:* ws?:* stream:stream",
+    "h @A d route w b bits n mode cu R logit score ws %ws stream")
+_encode_topk = _native("xmix_sae_encode_topk", f"{_ENCODE} stream:stream",
+                       f"{_ENCODE_C} stream")
+_encode_topk_ring = _native(
+    "xmix_sae_encode_topk_ring",
+    f"{_ENCODE} req:i32{{T}} layer:int app:int ring:struct stream:stream",
+    f"{_ENCODE_C} req layer app ring stream")
+_graph_launch = _native("xmix_graph_launch", "graph:int stream:stream", "graph stream")
+
+
 class XmixError(RuntimeError):
     def __init__(self, fn: str, status: int):
         msg = _lib.xmix_status_string(status).decode()
@@ -194,6 +248,10 @@ class Route:
         self.struct = XmixRoute(self.tok_mask.data_ptr(), self.app_count.data_ptr(),
                                 self.app_tokens.data_ptr(), self.T_max, self.n_apps)
 
+    @property
+    def _addr(self) -> int:
+        return ctypes.addressof(self.struct)
+
 
 class Ring:
     """Device readback ring: slots [capacity, row_bytes] and head [2] (uint64)."""
@@ -205,17 +263,18 @@ class Ring:
         self.struct = XmixRing(self.slots.data_ptr(), self.head.data_ptr(), self.capacity,
                                self.row_bytes)
 
+    @property
+    def _addr(self) -> int:
+        return ctypes.addressof(self.struct)
+
 
 # ------------------------------------------------------------------ entries
 
 def xmix_route_build(req_of_token, T_valid, sub_mask, route: Route, err_word, stream=None):
     """req_of_token int32 [T_max]; T_valid int32 [1]; sub_mask int32 [R_max]
     (uint32 bit patterns); err_word int32 [1] (bits ORed in)."""
-    assert req_of_token.dtype == torch.int32 and req_of_token.numel() == route.T_max
-    assert T_valid.dtype == torch.int32 and sub_mask.dtype == torch.int32
-    _check("xmix_route_build", _lib.xmix_route_build(
-        _ptr(req_of_token), _ptr(T_valid), _ptr(sub_mask), sub_mask.numel(),
-        ctypes.byref(route.struct), _ptr(err_word), _stream(stream)))
+    _check("xmix_route_build", _route_build(req_of_token, T_valid, sub_mask, route, err_word,
+                                            stream))
 
 
 def xmix_route_gate(route: Route, app_bit: int, signal, threshold, signal_bit: int = -1,
@@ -223,52 +282,32 @@ def xmix_route_gate(route: Route, app_bit: int, signal, threshold, signal_bit: i
     """Activation-driven conditional write: keep app `app_bit` only on tokens
     whose signal (fp32 [T_max] per token, or [R] per request with
     req_of_token) is >= the device scalar `threshold`."""
-    assert signal.dtype == torch.float32 and threshold.dtype == torch.float32
-    _check("xmix_route_gate", _lib.xmix_route_gate(
-        ctypes.byref(route.struct), app_bit, _ptr(signal), _ptr(req_of_token), signal.numel(),
-        signal_bit, _ptr(threshold), _stream(stream)))
+    _check("xmix_route_gate", _route_gate(route, app_bit, signal, threshold, signal_bit,
+                                          req_of_token, stream))
 
 
 def xmix_route_trigger(route: Route, app_bit: int, token_ids, vocab_bits, vocab_size: int,
                        stream=None):
     """Token-driven conditional write: keep app `app_bit` only on tokens whose
     id (int32 [T_max]) is set in the trigger bitmap (int32 words)."""
-    assert token_ids.dtype == torch.int32 and vocab_bits.numel() * 32 >= vocab_size
-    _check("xmix_route_trigger", _lib.xmix_route_trigger(
-        ctypes.byref(route.struct), app_bit, _ptr(token_ids), _ptr(vocab_bits), vocab_size,
-        _stream(stream)))
+    assert vocab_bits.numel() * 32 >= vocab_size
+    _check("xmix_route_trigger", _route_trigger(route, app_bit, token_ids, vocab_bits, vocab_size,
+                                                stream))
 
 
 def xmix_steer_apply(h, route: Route, req_of_token, vecs, app_bits: Sequence[int], alpha,
                      stream=None):
     """h [T_max, d] bf16/fp32 in place; vecs [n_steer, d] same dtype;
     alpha fp32 [R_max, n_steer]; app_bits: host list of route bits."""
-    T_max, d = h.shape
-    assert T_max == route.T_max and vecs.dtype == h.dtype and vecs.shape[-1] == d
-    n = len(app_bits)
-    assert alpha.dtype == torch.float32 and alpha.dim() == 2 and alpha.shape[1] == n
-    bits = (ctypes.c_int32 * n)(*app_bits)
-    _check("xmix_steer_apply", _lib.xmix_steer_apply(
-        _ptr(h), _dt(h), d, ctypes.byref(route.struct), _ptr(req_of_token), _ptr(vecs), bits,
-        _ptr(alpha), n, alpha.shape[0], _stream(stream)))
+    _check("xmix_steer_apply", _steer_apply(h, route, req_of_token, vecs, app_bits, alpha, stream))
 
 
 def xmix_steer_probe(h, route: Route, req_of_token, vecs, steer_bits: Sequence[int], alpha,
                      w, b, probe_bits: Sequence[int], logit_out, score_out, stream=None):
     """Token-mode probes and the steering add in one pass: the same results
     as xmix_probe_score(mode TOKEN) followed by xmix_steer_apply."""
-    T_max, d = h.shape
-    assert T_max == route.T_max and vecs.dtype == h.dtype and vecs.shape[-1] == d
-    ns, npb = len(steer_bits), len(probe_bits)
-    assert alpha.dtype == torch.float32 and alpha.dim() == 2 and alpha.shape[1] == ns
-    assert w.dtype == h.dtype and w.shape == (npb, d) and b.dtype == torch.float32
-    assert logit_out.shape == (npb, T_max) and score_out.shape == (npb, T_max)
-    sb = (ctypes.c_int32 * ns)(*steer_bits)
-    pb = (ctypes.c_int32 * npb)(*probe_bits)
-    _check("xmix_steer_probe", _lib.xmix_steer_probe(
-        _ptr(h), _dt(h), d, ctypes.byref(route.struct), _ptr(req_of_token), _ptr(vecs), sb,
-        _ptr(alpha), ns, alpha.shape[0], _ptr(w), _ptr(b), pb, npb, _ptr(logit_out),
-        _ptr(score_out), _stream(stream)))
+    _check("xmix_steer_probe", _steer_probe(h, route, req_of_token, vecs, steer_bits, alpha, w, b,
+                                            probe_bits, logit_out, score_out, stream))
 
 
 def xmix_route_steer_probe(req_of_token, T_valid, sub_mask, route: Route, err_word, h, vecs,
@@ -277,34 +316,16 @@ def xmix_route_steer_probe(req_of_token, T_valid, sub_mask, route: Route, err_wo
     """Route build and the fused probes + steering pass in one launch (up to
     1024 token slots): the same results as xmix_route_build followed by
     xmix_steer_probe."""
-    T_max, d = h.shape
-    assert T_max == route.T_max and vecs.dtype == h.dtype and vecs.shape[-1] == d
-    ns, npb = len(steer_bits), len(probe_bits)
-    assert alpha.dtype == torch.float32 and alpha.dim() == 2 and alpha.shape[1] == ns
-    assert w.dtype == h.dtype and w.shape == (npb, d) and b.dtype == torch.float32
-    assert logit_out.shape == (npb, T_max) and score_out.shape == (npb, T_max)
-    assert req_of_token.dtype == torch.int32 and req_of_token.numel() == T_max
-    sb = (ctypes.c_int32 * ns)(*steer_bits)
-    pb = (ctypes.c_int32 * npb)(*probe_bits)
-    _check("xmix_route_steer_probe", _lib.xmix_route_steer_probe(
-        _ptr(req_of_token), _ptr(T_valid), _ptr(sub_mask), sub_mask.numel(),
-        ctypes.byref(route.struct), _ptr(err_word), _ptr(h), _dt(h), d, _ptr(vecs), sb,
-        _ptr(alpha), ns, _ptr(w), _ptr(b), pb, npb, _ptr(logit_out), _ptr(score_out),
-        _stream(stream)))
+    _check("xmix_route_steer_probe", _route_steer_probe(
+        req_of_token, T_valid, sub_mask, route, err_word, h, vecs, steer_bits, alpha, w, b,
+        probe_bits, logit_out, score_out, stream))
 
 
 def xmix_router_write(logits, route: Route, app_bits: Sequence[int], offsets, stream=None):
     """logits [T_max, n_experts] bf16/fp32 in place; offsets fp32
     [n_router, n_experts] (-inf removes an expert); app_bits: host list of
     route bits, one per router app."""
-    T_max, E = logits.shape
-    assert T_max == route.T_max and logits.is_contiguous()
-    n = len(app_bits)
-    assert offsets.dtype == torch.float32 and tuple(offsets.shape) == (n, E)
-    bits = (ctypes.c_int32 * n)(*app_bits)
-    _check("xmix_router_write", _lib.xmix_router_write(
-        _ptr(logits), _dt(logits), E, ctypes.byref(route.struct), bits, _ptr(offsets), n,
-        _stream(stream)))
+    _check("xmix_router_write", _router_write(logits, route, app_bits, offsets, stream))
 
 
 class Graph:
@@ -350,8 +371,8 @@ class Graph:
         return int(n.value)
 
     def launch(self, stream=None):
-        _check("xmix_graph_launch", _lib.xmix_graph_launch(
-            self._h, _stream(self.stream if stream is None else stream)))
+        _check("xmix_graph_launch", _graph_launch(
+            self._h.value or 0, self.stream if stream is None else stream))
 
     def close(self):
         if self._h:
@@ -373,21 +394,12 @@ def xmix_probe_score(h, route: Route, w, b, app_bits: Sequence[int], mode: int, 
                      score_out, cu_seqlens=None, ws=None, stream=None):
     """Token mode: outputs fp32 [n_probe, T_max].  Mean and last-token modes:
     outputs fp32 [n_probe, R_max] with cu_seqlens int32 [R_max + 1]."""
-    T_max, d = h.shape
-    n = len(app_bits)
-    assert w.dtype == h.dtype and w.shape == (n, d) and b.dtype == torch.float32
-    R_max = 0
     if mode in (XMIX_PROBE_MEAN, XMIX_PROBE_LAST):
-        R_max = cu_seqlens.numel() - 1
-        assert logit_out.shape == (n, R_max)
+        fn, R_max = _probe_score_span, cu_seqlens.numel() - 1
     else:
-        assert logit_out.shape == (n, T_max)
-    bits = (ctypes.c_int32 * n)(*app_bits)
-    ws_bytes = 0 if ws is None else ws.numel() * ws.element_size()
-    _check("xmix_probe_score", _lib.xmix_probe_score(
-        _ptr(h), _dt(h), d, ctypes.byref(route.struct), _ptr(w), _ptr(b), bits, n, mode,
-        _ptr(cu_seqlens), R_max, _ptr(logit_out), _ptr(score_out), _ptr(ws), ws_bytes,
-        _stream(stream)))
+        fn, R_max = _probe_score_token, 0
+    _check("xmix_probe_score", fn(h, route, w, b, app_bits, mode, cu_seqlens, R_max, logit_out,
+                                  score_out, ws, stream))
 
 
 def sae_encode_workspace(T_max: int, d: int, m: int, k: int) -> int:
@@ -415,6 +427,10 @@ class SaeDict:
 
     def ref(self):
         return ctypes.byref(self.struct)
+
+    @property
+    def _addr(self) -> int:
+        return ctypes.addressof(self.struct)
 
 
 def _dict(W) -> SaeDict:
@@ -449,15 +465,8 @@ def xmix_sae_encode_topk(h, route: Route, app_bit: int, W: SaeDict, b_enc, b_dec
                          k: int, idx_out, val_out, ws, stream=None):
     """h bf16 [T_max, d]; W the packed dictionary; c_fold fp32 [m] or None;
     idx_out int32 [T_max, k]; val_out bf16 [T_max, k]; ws uint8 workspace."""
-    T_max, d = h.shape
-    W = _dict(W)
-    assert h.dtype == torch.bfloat16
-    assert idx_out.dtype == torch.int32 and idx_out.shape == (T_max, k)
-    assert val_out.dtype == torch.bfloat16 and val_out.shape == (T_max, k)
-    ws_bytes = ws.numel() * ws.element_size()
-    _check("xmix_sae_encode_topk", _lib.xmix_sae_encode_topk(
-        _ptr(h), d, ctypes.byref(route.struct), app_bit, W.ref(), _ptr(b_enc), _ptr(b_dec),
-        _ptr(c_fold), k, _ptr(idx_out), _ptr(val_out), _ptr(ws), ws_bytes, _stream(stream)))
+    _check("xmix_sae_encode_topk", _encode_topk(
+        h, route, app_bit, _dict(W), b_enc, b_dec, c_fold, k, idx_out, val_out, ws, stream))
 
 
 XMIX_STATIC_SCRATCH_BYTES = 16 << 20
@@ -482,16 +491,9 @@ def xmix_sae_encode_topk_ring(h, route: Route, app_bit: int, W: SaeDict, b_enc, 
                               app_id: int, ring: Ring, stream=None):
     """xmix_sae_encode_topk with the ring readback of (idx, val) rows fused
     into the merge; ring.row_bytes must be 16 + 6 k."""
-    T_max, d = h.shape
-    W = _dict(W)
-    assert h.dtype == torch.bfloat16
-    assert idx_out.dtype == torch.int32 and idx_out.shape == (T_max, k)
-    assert val_out.dtype == torch.bfloat16 and val_out.shape == (T_max, k)
-    assert req_of_token.dtype == torch.int32 and req_of_token.numel() == T_max
-    _check("xmix_sae_encode_topk_ring", _lib.xmix_sae_encode_topk_ring(
-        _ptr(h), d, ctypes.byref(route.struct), app_bit, W.ref(), _ptr(b_enc), _ptr(b_dec),
-        _ptr(c_fold), k, _ptr(idx_out), _ptr(val_out), _ptr(ws), ws.numel() * ws.element_size(),
-        _ptr(req_of_token), layer_id, app_id, ctypes.byref(ring.struct), _stream(stream)))
+    _check("xmix_sae_encode_topk_ring", _encode_topk_ring(
+        h, route, app_bit, _dict(W), b_enc, b_dec, c_fold, k, idx_out, val_out, ws, req_of_token,
+        layer_id, app_id, ring, stream))
 
 
 def xmix_sae_merge_topk_ring(h, route: Route, app_bit: int, W: SaeDict, c_fold, k: int, idx_out,

@@ -4,12 +4,14 @@ Each source under csrc/ is compiled by hipcc into _build/, then linked into
 paper_2607_22595_amd/libxmix.so.  The measured-ceiling kernels under
 ceiling/ (a benchmark aid, no part of the hook step) become
 libxmix_ceiling.so.  Packed-fp32 instruction selection is switched off for
-device code."""
+device code.  The binding's argument marshalling (call.cpp, host code against
+Python's and torch's headers) becomes the extension module _call.so."""
 import concurrent.futures as cf
 import glob
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
@@ -40,6 +42,23 @@ def _link(objs, lib: str) -> None:
     os.replace(tmp, lib)
 
 
+def _compile_binding() -> None:
+    import torch
+    inc = os.path.join(os.path.dirname(torch.__file__), "include")
+    lib = os.path.join(os.path.dirname(torch.__file__), "lib")
+    out = os.path.join(HERE, "_call.so")
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-w",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           "-I", inc, "-I", os.path.join(inc, "torch", "csrc", "api", "include"),
+           "-I", sysconfig.get_path("include"), "-o", out + ".tmp",
+           os.path.join(HERE, "csrc", "call.cpp"),
+           "-L", lib, "-ltorch_python", "-ltorch_cpu", "-lc10"]  # loaded by `import torch`
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"building the binding failed:\n{r.stderr}")
+    os.replace(out + ".tmp", out)
+
+
 def build(extra=(), jobs: int = 8) -> str:
     out_dir = os.path.join(ROOT, "_build")
     os.makedirs(out_dir, exist_ok=True)
@@ -49,7 +68,9 @@ def build(extra=(), jobs: int = 8) -> str:
     ceil_obj = os.path.join(out_dir, "ceiling.hip.o")
     pairs = list(zip(srcs, objs)) + [(ceil_src, ceil_obj)]
     with cf.ThreadPoolExecutor(max_workers=jobs) as ex:
+        binding = ex.submit(_compile_binding)
         list(ex.map(lambda so: _compile(so[0], so[1], list(extra)), pairs))
+        binding.result()
     lib = os.path.join(HERE, "libxmix.so")
     _link(objs, lib)
     _link([ceil_obj], os.path.join(HERE, "libxmix_ceiling.so"))

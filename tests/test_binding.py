@@ -1,0 +1,71 @@
+"""The binding's argument marshalling: what it binds, passes and refuses."""
+import ctypes
+
+import numpy as np
+import pytest
+import torch
+
+
+@pytest.fixture(scope="module")
+def px():
+    import paper_2607_22595_amd as px
+    return px
+
+
+def function(px, args, c_args):
+    abs_ = ctypes.cast(ctypes.CDLL(None).abs, ctypes.c_void_p).value
+    return px._call.Function("abs", abs_, args, c_args)
+
+
+def test_ints_dims_and_bits(px):
+    f = function(px, "x:int b:bits(n)", "x")
+    assert f(-5, [1, 2]) == 5 and f(-7, range(3)) == 7 and f(3, ()) == 3
+    assert function(px, "x:int b:bits(n)", "n")(-5, [4] * 40) == 40  # the C side refuses it
+    g = function(px, "n:dim b:bits(n)", "n")
+    assert g(2, (8, 9)) == 2
+    with pytest.raises(AssertionError):
+        g(3, (8, 9))
+    with pytest.raises(TypeError):
+        f("a", [1])
+    with pytest.raises(TypeError):
+        f(1, ["a"])
+    with pytest.raises(TypeError):
+        f(1)
+
+
+@pytest.mark.parametrize("args,c_args", [("x:zz", "x"), ("x", "x"), ("x:int", "y"), ("x:i32[", "x")])
+def test_bad_specifications_are_refused(px, args, c_args):
+    with pytest.raises(ValueError):
+        function(px, args, c_args)
+
+
+def test_tensors_without_gpu_storage_are_refused(px):
+    f = function(px, "t?:*", "t")
+    assert f(None) == 0
+    with pytest.raises(ValueError):
+        f(torch.zeros(3))
+    with pytest.raises(AssertionError):
+        f(np.zeros(3))
+
+
+@pytest.mark.gpu
+def test_gpu_tensors_are_checked(px):
+    rt = px.Route(8, 2)
+    h = torch.zeros((8, 64), dtype=torch.bfloat16, device="cuda")
+    v, alpha = torch.zeros((2, 64), dtype=torch.bfloat16, device="cuda"), torch.zeros((4, 2)).cuda()
+    req = torch.zeros(8, dtype=torch.int32, device="cuda")
+    px.xmix_steer_apply(h, rt, req, v, [0, 1], alpha)
+    px.xmix_steer_apply(h, rt, req, v[0], [0], alpha[:, :1].contiguous())   # one vector as a row
+    px.xmix_steer_apply(h, rt, req, v, (1, 0), alpha, stream=torch.cuda.Stream())
+    for bad, err in [((h[:7], rt, req, v, [0, 1], alpha), AssertionError),
+                     ((h, rt, req, v.float(), [0, 1], alpha), AssertionError),
+                     ((h, rt, req, v[:, :32].contiguous(), [0, 1], alpha), AssertionError),
+                     ((h, rt, req, v, [0], alpha), AssertionError),
+                     ((h, rt, req, v, [0, 1], alpha.half()), AssertionError),
+                     ((h, rt, req, v, [0, 1], alpha.cpu()), ValueError),
+                     ((h.t(), rt, req, v, [0, 1], alpha), ValueError),
+                     ((h.half(), rt, req, v, [0, 1], alpha), TypeError),
+                     ((h, rt, req, v, [0, 2], alpha), px.XmixError)]:
+        with pytest.raises(err):
+            px.xmix_steer_apply(*bad)
+    torch.cuda.synchronize()
