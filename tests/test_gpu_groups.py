@@ -224,6 +224,23 @@ def test_readback_row_sizes(px, widths, off):
         assert np.array_equal(ring.slots.cpu().numpy(), slots)
 
 
+@pytest.mark.parametrize("T,n,cap", [(4500, 64, 4700), (9000, 36, 5000), (2300, 4100, 2000),
+                                     (1300, 8196, 900)])
+def test_readback_more_rows_than_workgroups(px, T, n, cap):
+    """Rows that the workgroups take in turns, by one, two and four waves a row."""
+    rng, req, sub = batch(T, 1, p=0.95, seed=n)
+    rt, _ = build(px, req, T, sub, 1)
+    tm = oracle.route(req, T, sub, 1)[0]
+    raw = rng.integers(0, 256, (T, n)).astype(np.uint8)
+    ring = px.Ring(cap, 16 + n)
+    slots, head = np.zeros((cap, 16 + n), np.uint8), 0
+    for _ in range(2):
+        px.xmix_readback_compact([dev(raw)], rt, 0, dev(req), 3, 5, ring)
+        slots, head = oracle.compact([raw], tm, 0, req, 3, 5, slots, head)
+        assert int(ring.head[0].item()) == head and int(ring.head[1].item()) == 0
+        assert np.array_equal(ring.slots.cpu().numpy(), slots)
+
+
 @pytest.mark.parametrize("sbits,pbits", [([0, 1, 2], [3, 4]), ([5, 6], [0, 1, 2]), ([6, 2, 4], [3, 0]),
                                          ([1, 3], [6, 5, 4]), ([31, 0], [30, 31]), ([30, 31], [0])])
 def test_app_bits_in_any_order(px, sbits, pbits):
