@@ -1406,6 +1406,7 @@ constexpr int kStagePieces = 1024;  // 16-byte pieces per operand per stage
 constexpr int kPrefillMinT = 1025;  // token slots from which the prefill GEMM runs
 constexpr int kGBlkTok = 8;         // XCD block: token tiles
 constexpr int kGBlkLat = 4;         // XCD block: latent tiles
+constexpr int kSmallTiles = 768;    // most 128-token tiles of a launch
 
 // s_waitcnt: at most n vector-memory operations of this wave outstanding
 // and no LDS operation.
@@ -1423,12 +1424,22 @@ sae_xstage_kernel(const uint16_t* __restrict__ h, int32_t d, const int32_t* __re
     const int64_t jn = q >> 2;
     const int32_t n = static_cast<int32_t>(jn % n_pad);
     const int32_t j = static_cast<int32_t>(jn / n_pad);
+    const int32_t cnt = *app_count;
+    if (n >= (cnt + kGemmTok - 1) / kGemmTok * kGemmTok) return;  // no tile reads it
     uint4 v = make_uint4(0u, 0u, 0u, 0u);
-    if (n < *app_count)
+    if (n < cnt)
         v = *reinterpret_cast<const uint4*>(h + static_cast<int64_t>(tok_list[n]) * d + 32 * j + 8 * c);
     reinterpret_cast<uint4*>(xs)[q] = v;
 }
 
+// The live count decides the tile: 64 * NB tokens.  256-token tiles feed the
+// matrix cores best, but few of them leave CUs idle; a 128-token tile has half the
+// MFMAs and the same dictionary copies, so it is taken where its rounds of 256 CUs,
+// priced at 0.58 of a round of the large ones, are the cheaper ones (up to 768 of
+// them, which the launch has the workgroups for).  A prefill encode of 1318 tokens,
+// 4608 latents: 46.9 -> 37.8 us at d = 768, 103 -> 82 at d = 4096; 250 tokens, 16384
+// latents, d = 2048: 65 -> 48; at three small rounds for two large ones (1030
+// tokens, 16384 latents, d = 4096) the two sides meet, 240 and 237 us.
 __global__ void __launch_bounds__(kGemmThreads, 1)
 sae_gemm_kernel(const uint16_t* __restrict__ xs_g, int32_t d, int32_t n_pad,
                 const int32_t* __restrict__ app_count, const uint16_t* __restrict__ W,
@@ -1442,29 +1453,15 @@ sae_gemm_kernel(const uint16_t* __restrict__ xs_g, int32_t d, int32_t n_pad,
     __shared__ int cnt_s[kGemmTok];
     __shared__ int cnt2_s[2][kGemmTok];
     __shared__ float red3[2][kGemmTok];  // per-token maxima
-
-    // Tile order: launch slot L runs on XCD L % 8, which owns the latent
-    // tiles [x*M8, (x+1)*M8) and walks them in blocks of 8 token tiles x 4
-    // latent tiles (32 consecutive slots, one per CU of the XCD), token
-    // blocks fastest, so each stage of a block's operands is fetched into
-    // the XCD's L2 once and read by 4 and 8 workgroups.
-    const int L = blockIdx.x;
-    const int xcd = L % 8, slot = L / 8;
-    const int m8 = (n_mt + 7) / 8;
-    const int nbt = (n_nt + kGBlkTok - 1) / kGBlkTok;
-    const int b = slot / (kGBlkTok * kGBlkLat), p = slot % (kGBlkTok * kGBlkLat);
-    const int bt = b % nbt, bl = b / nbt;
-    const int lt = kGBlkLat * bl + p / kGBlkTok;
-    const int nt = kGBlkTok * bt + p % kGBlkTok;
-    if (nt >= n_nt || lt >= m8) return;
-    const int mt = xcd * m8 + lt;
-    if (mt >= n_mt) return;
-    const int cnt = *app_count;
-    const int n0 = nt * kGemmTok;
-    if (n0 >= cnt) return;
-    const int ntok = min(kGemmTok, cnt - n0);
-
-    const int tid = threadIdx.x;
+    // One tile: latent slice mt over tokens [n0, n0 + 64 * NB) of the staged
+    // list (ntok of them live), NB = 4 or 2.
+    auto gemm_tile = [&](auto nb_c, const int mt, const int n0, const int ntok)
+        __attribute__((always_inline)) {
+    constexpr int NB = decltype(nb_c)::value;
+    constexpr int kTok = 64 * NB;    // tokens of the tile
+    constexpr int kHalf = 32 * NB;   // tokens of a wave
+    int tid = threadIdx.x;  // opaque (see big_tile)
+    asm volatile("" : "+v"(tid));
     const int lane = tid & 63, wave = tid >> 6;
     const int wm = wave & 1, wn = wave >> 1;  // latent half, token half
     const int g = lane >> 5, j32 = lane & 31;
@@ -1476,13 +1473,13 @@ sae_gemm_kernel(const uint16_t* __restrict__ xs_g, int32_t d, int32_t n_pad,
     const int64_t xplane = static_cast<int64_t>(n_pad) * 4;     // pieces per stage plane
     // copy sources, in pieces from the start of the stage's operand block
     // (lane-contiguous LDS destinations q*256 + wave*64 + lane)
-    int wsrc[4], xsrc[4];
+    int wsrc[4], xsrc[NB];
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
         const int P = q * 256 + wave * 64 + lane;
         wsrc[q] = (P >> 7) * 256 + (P & 127);
         const int n = P >> 2;
-        xsrc[q] = n * 4 + ((P & 3) ^ gsw(n));
+        if (q < NB) xsrc[q] = n * 4 + ((P & 3) ^ gsw(n));
     }
     W4 += static_cast<int64_t>(mt) * 2048;  // this tile's latent slice
     X4 += static_cast<int64_t>(n0) * 4;     // this tile's tokens
@@ -1497,14 +1494,14 @@ sae_gemm_kernel(const uint16_t* __restrict__ xs_g, int32_t d, int32_t n_pad,
         const __amdgpu_buffer_rsrc_t wr = __builtin_amdgcn_make_buffer_rsrc(
             const_cast<uint4*>(W4 + kc * wstride + hh * 128), 0, 2048 * 16, kBufferDword3);
         const __amdgpu_buffer_rsrc_t xr = __builtin_amdgcn_make_buffer_rsrc(
-            const_cast<uint4*>(X4 + j * xplane), 0, kStagePieces * 16, kBufferDword3);
+            const_cast<uint4*>(X4 + j * xplane), 0, kTok * 64, kBufferDword3);
 #pragma unroll
         for (int q = 0; q < 4; ++q)
             __builtin_amdgcn_raw_ptr_buffer_load_lds(
                 wr, (__attribute__((address_space(3))) void*)(wdst + q * 256 + wave * 64),
                 16, static_cast<unsigned>(wsrc[q]) * 16u, 0, 0, 0);
 #pragma unroll
-        for (int q = 0; q < 4; ++q)
+        for (int q = 0; q < NB; ++q)
             __builtin_amdgcn_raw_ptr_buffer_load_lds(
                 xr, (__attribute__((address_space(3))) void*)(xdst + q * 256 + wave * 64),
                 16, static_cast<unsigned>(xsrc[q]) * 16u, 0, 0, 0);
@@ -1512,7 +1509,7 @@ sae_gemm_kernel(const uint16_t* __restrict__ xs_g, int32_t d, int32_t n_pad,
 
     // accumulators start at the folded bias of their latent:
     // acc[a][nb][r] holds latent 128*wm + 32*a + 8*(r/4) + 4*g + r%4
-    f32x16_t acc[4][4];
+    f32x16_t acc[4][NB];
     {
         const float* cf = c_fold + mt * 256 + 128 * wm + 4 * g;
 #pragma unroll
@@ -1521,7 +1518,7 @@ sae_gemm_kernel(const uint16_t* __restrict__ xs_g, int32_t d, int32_t n_pad,
             for (int q = 0; q < 4; ++q) {
                 const float4 c4 = *reinterpret_cast<const float4*>(cf + 32 * a + 8 * q);
 #pragma unroll
-                for (int nb = 0; nb < 4; ++nb) {
+                for (int nb = 0; nb < NB; ++nb) {
                     acc[a][nb][4 * q + 0] = c4.x;
                     acc[a][nb][4 * q + 1] = c4.y;
                     acc[a][nb][4 * q + 2] = c4.z;
@@ -1530,22 +1527,22 @@ sae_gemm_kernel(const uint16_t* __restrict__ xs_g, int32_t d, int32_t n_pad,
             }
     }
 
-    uint4 FA[4], FB[4], PA[4], PB[4];
-    auto read_step = [&](const uint4* wb, const uint4* xb, int s, uint4 (&A)[4], uint4 (&B)[4])
+    uint4 FA[4], FB[NB], PA[4], PB[NB];
+    auto read_step = [&](const uint4* wb, const uint4* xb, int s, uint4 (&A)[4], uint4 (&B)[NB])
         __attribute__((always_inline)) {
 #pragma unroll
         for (int a = 0; a < 4; ++a) A[a] = wb[(4 * wm + a) * 128 + s * 64 + lane];
 #pragma unroll
-        for (int nb = 0; nb < 4; ++nb) {
-            const int n = 128 * wn + 32 * nb + j32;
+        for (int nb = 0; nb < NB; ++nb) {
+            const int n = kHalf * wn + 32 * nb + j32;
             B[nb] = xb[n * 4 + ((2 * s + g) ^ gsw(n))];
         }
     };
-    auto mfma_step = [&](const uint4 (&A)[4], const uint4 (&B)[4]) __attribute__((always_inline)) {
+    auto mfma_step = [&](const uint4 (&A)[4], const uint4 (&B)[NB]) __attribute__((always_inline)) {
 #pragma unroll
         for (int a = 0; a < 4; ++a)
 #pragma unroll
-            for (int nb = 0; nb < 4; ++nb)
+            for (int nb = 0; nb < NB; ++nb)
                 acc[a][nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(A[a]),
                                                                      as_bf16x8(B[nb]), acc[a][nb],
                                                                      0, 0, 0);
@@ -1577,31 +1574,41 @@ sae_gemm_kernel(const uint16_t* __restrict__ xs_g, int32_t d, int32_t n_pad,
         // the first refill between them; step-0 MFMAs with step-1 reads;
         // second stage's step-0 reads and the second refill between the
         // carried MFMAs; step-0 MFMAs with step-1 reads
-        __builtin_amdgcn_sched_group_barrier(0x100, 8, 0);
+        constexpr int kReads = 4 + NB, kMfma = 4 * NB, kCopies = 4 + NB;
+        __builtin_amdgcn_sched_group_barrier(0x100, kReads, 0);
         if (!first) {
 #pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
+            for (int i = 0; i < kCopies; ++i) {
+                __builtin_amdgcn_sched_group_barrier(0x008, kMfma / 8, 0);
                 __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
             }
         } else {
-            __builtin_amdgcn_sched_group_barrier(0x020, 8, 0);
+            __builtin_amdgcn_sched_group_barrier(0x020, kCopies, 0);
         }
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
+        for (int i = 0; i < kReads; ++i) {
+            __builtin_amdgcn_sched_group_barrier(0x008, kMfma / 8, 0);
             __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
         }
+        if constexpr (NB == 4) {
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-            __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+            for (int i = 0; i < 8; ++i) {
+                __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < kReads; ++i) {
+                __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
+            }
         }
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
+        for (int i = 0; i < kReads; ++i) {
+            __builtin_amdgcn_sched_group_barrier(0x008, kMfma / 8, 0);
             __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
         }
     };
@@ -1651,7 +1658,7 @@ sae_gemm_kernel(const uint16_t* __restrict__ xs_g, int32_t d, int32_t n_pad,
     // mean and variance over the tile's 256 latents, per token, and the
     // largest value
 #pragma unroll
-    for (int nb = 0; nb < 4; ++nb) {
+    for (int nb = 0; nb < NB; ++nb) {
         float s1 = 0.0f, s2 = 0.0f, mx = -INFINITY;
 #pragma unroll
         for (int a = 0; a < 4; ++a)
@@ -1665,18 +1672,18 @@ sae_gemm_kernel(const uint16_t* __restrict__ xs_g, int32_t d, int32_t n_pad,
         s2 += __shfl_xor(s2, 32, kWave);
         mx = fmaxf(mx, __shfl_xor(mx, 32, kWave));
         if (g == 0) {
-            red1[wm][128 * wn + 32 * nb + j32] = s1;
-            red2[wm][128 * wn + 32 * nb + j32] = s2;
-            red3[wm][128 * wn + 32 * nb + j32] = mx;
+            red1[wm][kHalf * wn + 32 * nb + j32] = s1;
+            red2[wm][kHalf * wn + 32 * nb + j32] = s2;
+            red3[wm][kHalf * wn + 32 * nb + j32] = mx;
         }
     }
     __syncthreads();
-    float tau[4], lo_b[4], hi_b[4], mxv[4];
-    uint32_t m0[4], m1[4];  // bit i: value i >= tau (m1: value 32 + i)
-    bool bad[4];
+    float tau[NB], lo_b[NB], hi_b[NB], mxv[NB];
+    uint32_t m0[NB], m1[NB];  // bit i: value i >= tau (m1: value 32 + i)
+    bool bad[NB];
 #pragma unroll
-    for (int nb = 0; nb < 4; ++nb) {
-        const int n = 128 * wn + 32 * nb + j32;
+    for (int nb = 0; nb < NB; ++nb) {
+        const int n = kHalf * wn + 32 * nb + j32;
         const float s1 = red1[0][n] + red1[1][n], s2 = red2[0][n] + red2[1][n];
         const float mu = s1 * (1.0f / 256.0f);
         const float sd = sqrtf(fmaxf(s2 * (1.0f / 256.0f) - mu * mu, 0.0f));
@@ -1710,16 +1717,16 @@ sae_gemm_kernel(const uint16_t* __restrict__ xs_g, int32_t d, int32_t n_pad,
     bool gave_up = false;
     for (int it = 0; it < kRefineIters; ++it) {
 #pragma unroll
-        for (int nb = 0; nb < 4; ++nb) {
+        for (int nb = 0; nb < NB; ++nb) {
             const int c_lane = count_at(nb);
             const int c = c_lane + __shfl_xor(c_lane, 32, kWave);
-            if (g == 0) cnt2_s[wm][128 * wn + 32 * nb + j32] = c;
+            if (g == 0) cnt2_s[wm][kHalf * wn + 32 * nb + j32] = c;
         }
         __syncthreads();
         bool any_bad = false;
 #pragma unroll
-        for (int nb = 0; nb < 4; ++nb) {
-            const int n = 128 * wn + 32 * nb + j32;
+        for (int nb = 0; nb < NB; ++nb) {
+            const int n = kHalf * wn + 32 * nb + j32;
             const int cn = cnt2_s[0][n] + cnt2_s[1][n];
             bad[nb] = false;
             if (n < ntok) {
@@ -1745,22 +1752,22 @@ sae_gemm_kernel(const uint16_t* __restrict__ xs_g, int32_t d, int32_t n_pad,
         // out of rounds: a threshold whose count is known to be <= cap
         if (it == kRefineIters - 1) {
 #pragma unroll
-            for (int nb = 0; nb < 4; ++nb)
+            for (int nb = 0; nb < NB; ++nb)
                 if (bad[nb]) tau[nb] = hi_b[nb];
             gave_up = true;
         }
     }
     if (gave_up) {
 #pragma unroll
-        for (int nb = 0; nb < 4; ++nb) count_at(nb);
+        for (int nb = 0; nb < NB; ++nb) count_at(nb);
     }
     // emit every latent with pre >= tau: reserve the lane's slots with one
     // LDS atomic, then write one selected (value, latent) pair per round,
     // the value read back from where it was parked
     const int lat0 = mt * 256 + 128 * wm + 4 * g;
 #pragma unroll
-    for (int nb = 0; nb < 4; ++nb) {
-        const int n = 128 * wn + 32 * nb + j32;
+    for (int nb = 0; nb < NB; ++nb) {
+        const int n = kHalf * wn + 32 * nb + j32;
         const float* pk = park[nb & 1];
         uint32_t b0 = n < ntok ? m0[nb] : 0u, b1 = n < ntok ? m1[nb] : 0u;
         const int c = __popc(b0) + __popc(b1);
@@ -1786,10 +1793,39 @@ sae_gemm_kernel(const uint16_t* __restrict__ xs_g, int32_t d, int32_t n_pad,
         if (n < ntok && wm == 0 && g == 0)
             tile_tau[row] = mxv[nb] < tau[nb] ? key_f32(f32_key(mxv[nb]) + 1u) : tau[nb];
         // the wave's reads of this buffer precede these stores in its LDS queue
-        if (nb < 2) park_group(nb + 2);
+        if (nb + 2 < NB) park_group(nb + 2);
     }
     __syncthreads();
     if (tid < ntok) tile_cnt[static_cast<int64_t>(n0 + tid) * n_mt + mt] = min(cnt_s[tid], cap);
+    };
+    const int cnt = *app_count;
+    const int L = blockIdx.x;
+    const int t256 = n_mt * ((cnt + 255) / 256), t128 = n_mt * ((cnt + 127) / 128);
+    if (t128 <= kSmallTiles && (t128 + 255) / 256 * 58 < (t256 + 255) / 256 * 100) {  // uniform
+        if (L >= t128) return;
+        const int mt = L % n_mt, n0 = L / n_mt * 128;
+        gemm_tile(std::integral_constant<int, 2>{}, mt, n0, min(128, cnt - n0));
+        return;
+    }
+
+    // Tile order: launch slot L runs on XCD L % 8, which owns the latent
+    // tiles [x*M8, (x+1)*M8) and walks them in blocks of 8 token tiles x 4
+    // latent tiles (32 consecutive slots, one per CU of the XCD), token
+    // blocks fastest, so each stage of a block's operands is fetched into
+    // the XCD's L2 once and read by 4 and 8 workgroups.
+    const int xcd = L % 8, slot = L / 8;
+    const int m8 = (n_mt + 7) / 8;
+    const int nbt = (n_nt + kGBlkTok - 1) / kGBlkTok;
+    const int b = slot / (kGBlkTok * kGBlkLat), p = slot % (kGBlkTok * kGBlkLat);
+    const int bt = b % nbt, bl = b / nbt;
+    const int lt = kGBlkLat * bl + p / kGBlkTok;
+    const int nt = kGBlkTok * bt + p % kGBlkTok;
+    if (nt >= n_nt || lt >= m8) return;
+    const int mt = xcd * m8 + lt;
+    if (mt >= n_mt) return;
+    const int n0 = nt * kGemmTok;
+    if (n0 >= cnt) return;
+    gemm_tile(std::integral_constant<int, 4>{}, mt, n0, min(kGemmTok, cnt - n0));
 }
 
 // ------------------------------------------------------------- final merge
@@ -2811,9 +2847,14 @@ hipError_t launch_sae_candidates(const uint16_t* h, int32_t d, int32_t T_max,
         const int m8 = (n_mt + 7) / 8;
         const int nbt = (n_nt + kGBlkTok - 1) / kGBlkTok;
         const int nbl = (m8 + kGBlkLat - 1) / kGBlkLat;
-        hipLaunchKernelGGL(sae_gemm_kernel, dim3(8 * nbt * nbl * kGBlkTok * kGBlkLat),
-                           dim3(kGemmThreads), 0, stream, xs, d, n_pad, app_count, W_enc, c_fold,
-                           n_mt, n_nt, e.z, e.lo, e.cap, a.cand, a.cnt, a.tau);
+        // workgroups for the blocks of 256-token tiles and for the 128-token
+        // tiles that a small live count takes instead
+        const int32_t small = 2 * n_mt * n_nt < kSmallTiles ? 2 * n_mt * n_nt : kSmallTiles;
+        int32_t grid_g = 8 * nbt * nbl * kGBlkTok * kGBlkLat;
+        grid_g = grid_g > small ? grid_g : small;
+        hipLaunchKernelGGL(sae_gemm_kernel, dim3(grid_g), dim3(kGemmThreads), 0, stream, xs, d,
+                           n_pad, app_count, W_enc, c_fold, n_mt, n_nt, e.z, e.lo, e.cap, a.cand,
+                           a.cnt, a.tau);
         return hipGetLastError();
     }
     const RouteIn none{};
