@@ -103,6 +103,11 @@ probe_token_kernel(const void* __restrict__ h, int32_t d, int32_t T_max,
     // weights fetched together with the rows (the rest, for more than eight
     // probes, when used)
     constexpr int AP = MAXP < 8 ? MAXP : 8;
+    // words of a row widened at a time: one where that brings the kernel from 70
+    // registers under 64 (four workgroups per CU, not three: four token and four
+    // pooled probes of 8192 tokens of width 4096, 46.5 -> 43.5 us for the pass of
+    // all reads), else all (eight probes stay above 80 and were 3 % slower)
+    constexpr int EW = BF16 && MAXP == 4 ? 1 : 4;
     for (int32_t i = threadIdx.x; i < nvec; i += kProbeThreads) {
         // the rows and the weights of the group's probes, all loaded before the
         // first use, so that the slice waits for one memory round trip
@@ -115,34 +120,38 @@ probe_token_kernel(const void* __restrict__ h, int32_t d, int32_t T_max,
         for (int p = 0; p < AP; ++p)
             wv[p] = ((any >> p) & 1u) ? W[static_cast<int64_t>(p) * nvec + i]
                                       : make_uint4(0u, 0u, 0u, 0u);
-        float x[TT][EPV];
 #pragma unroll
-        for (int j = 0; j < TT; ++j) {
-            const uint32_t hw[4] = {hv[j].x, hv[j].y, hv[j].z, hv[j].w};
+        for (int e0 = 0; e0 < 4; e0 += EW) {
+            float x[TT][EW * EPV / 4];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                if constexpr (BF16) {
-                    x[j][2 * e] = lo_bf16(hw[e]);
-                    x[j][2 * e + 1] = hi_bf16(hw[e]);
-                } else {
-                    x[j][e] = __uint_as_float(hw[e]);
+            for (int j = 0; j < TT; ++j) {
+                const uint32_t hw[4] = {hv[j].x, hv[j].y, hv[j].z, hv[j].w};
+#pragma unroll
+                for (int e = 0; e < EW; ++e) {
+                    if constexpr (BF16) {
+                        x[j][2 * e] = lo_bf16(hw[e0 + e]);
+                        x[j][2 * e + 1] = hi_bf16(hw[e0 + e]);
+                    } else {
+                        x[j][e] = __uint_as_float(hw[e0 + e]);
+                    }
                 }
             }
-        }
 #pragma unroll
-        for (int p = 0; p < MAXP; ++p) {
-            if (!((any >> p) & 1u)) continue;  // uniform
-            const uint4 w4 = p < AP ? wv[p < AP ? p : 0] : W[static_cast<int64_t>(p) * nvec + i];
-            const uint32_t ww[4] = {w4.x, w4.y, w4.z, w4.w};
+            for (int p = 0; p < MAXP; ++p) {
+                if (!((any >> p) & 1u)) continue;  // uniform
+                const uint4 w4 =
+                    p < AP ? wv[p < AP ? p : 0] : W[static_cast<int64_t>(p) * nvec + i];
+                const uint32_t ww[4] = {w4.x, w4.y, w4.z, w4.w};
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
+                for (int e = 0; e < EW; ++e) {
 #pragma unroll
-                for (int j = 0; j < TT; ++j) {
-                    if constexpr (BF16) {
-                        part[j][p] = fmaf(lo_bf16(ww[e]), x[j][2 * e], part[j][p]);
-                        part[j][p] = fmaf(hi_bf16(ww[e]), x[j][2 * e + 1], part[j][p]);
-                    } else {
-                        part[j][p] = fmaf(__uint_as_float(ww[e]), x[j][e], part[j][p]);
+                    for (int j = 0; j < TT; ++j) {
+                        if constexpr (BF16) {
+                            part[j][p] = fmaf(lo_bf16(ww[e0 + e]), x[j][2 * e], part[j][p]);
+                            part[j][p] = fmaf(hi_bf16(ww[e0 + e]), x[j][2 * e + 1], part[j][p]);
+                        } else {
+                            part[j][p] = fmaf(__uint_as_float(ww[e0 + e]), x[j][e], part[j][p]);
+                        }
                     }
                 }
             }
