@@ -25,7 +25,7 @@ bool bits_ok(const int32_t* bits, int32_t n, int32_t n_apps, BitList* out) {
     memset(out, 0, sizeof(*out));
     for (int i = 0; i < n; ++i) {
         if (bits[i] < 0 || bits[i] >= n_apps) return false;
-        out->bit[i] = bits[i];
+        out->bit4[i >> 2] |= static_cast<uint32_t>(bits[i]) << (8 * (i & 3));
     }
     out->first = bits[0];
     for (int i = 1; i < n; ++i)

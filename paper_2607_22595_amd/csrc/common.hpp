@@ -8,6 +8,40 @@ namespace xmix {
 
 constexpr int kWave = 64;
 
+// Has the kernel arguments named ("s"(x), ...) in scalar registers here.  The
+// compiler reads an argument where it is first used, so a short kernel's chain
+// holds a round trip to the argument block between each of its steps; with this
+// the reads are issued together, and beside the first loads from memory.
+#define XMIX_ARGS_NOW(...) asm volatile("" ::__VA_ARGS__)
+
+// Whether a launch of one workgroup per token row reads its rows before it knows
+// which ones carry a bit: a step of few rows is a chain of round trips (mask, row,
+// result), and reading all of at most 8 MB costs it less than one of them.  The
+// fused probe and steering pass with this, its arguments read together and no
+// load behind a branch: 32 layers of 256 rows of 8 KB 150 -> 128 us, 16 layers of
+// 512 rows of 16 KB 177 -> 143 us (a third of the bits set) and 130 -> 102 (5 %).
+// The steering kernel keeps to the rows it needs: few rows of a gated step carry
+// a bit, and eight such layers took 62 us with this and 56 without.
+__host__ __device__ inline bool early_rows(int32_t rows, int32_t nvec) {
+    return static_cast<int64_t>(rows) * nvec <= (8 << 20) / 16;
+}
+
+// Word 3 of a raw buffer resource (32-bit element format, no swizzle).
+constexpr int kBufferDword3 = 0x00020000;
+typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+
+// This lane's 16-byte slice, `off` bytes on, of the n slices at p (both uniform):
+// lanes past them read zero, and with n = 0 no memory is touched.  Loads that a
+// step may or may not need go out this way without a branch, since a load behind
+// one is easily waited for before the next is issued.
+__device__ __forceinline__ uint4 slice_load(const uint4* p, int32_t n, uint32_t off) {
+    const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<uint4*>(p), 0, n * 16, kBufferDword3);
+    const u32x4_t v =
+        __builtin_bit_cast(u32x4_t, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0));
+    return make_uint4(v.x, v.y, v.z, v.w);
+}
+
 // ---------------------------------------------------------------- bf16 bits
 __device__ __forceinline__ float bf16_to_f32(uint16_t b) {
     return __uint_as_float(static_cast<uint32_t>(b) << 16);

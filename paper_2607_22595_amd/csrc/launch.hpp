@@ -8,8 +8,9 @@
 namespace xmix {
 
 struct BitList {  // static app bits, passed by value into a launch
-    int32_t bit[32];
     int32_t first;  // bit[0] when the bits are consecutive and ascending, else -1
+    uint32_t bit4[8];  // the bits, four to a word (scalar loads take no bytes)
+    __host__ __device__ uint32_t bit(int s) const { return (bit4[s >> 2] >> (8 * (s & 3))) & 31u; }
 };
 
 #ifdef __HIPCC__
@@ -20,7 +21,7 @@ struct BitList {  // static app bits, passed by value into a launch
 __device__ __forceinline__ uint32_t select_bits(uint32_t mask, const BitList& bits, int32_t n) {
     if (bits.first >= 0) return (mask >> bits.first) & (0xFFFFFFFFu >> (32 - n));
     uint32_t sel = 0;
-    for (int s = 0; s < n; ++s) sel |= ((mask >> bits.bit[s]) & 1u) << s;
+    for (int s = 0; s < n; ++s) sel |= ((mask >> bits.bit(s)) & 1u) << s;
     return sel;
 }
 #endif

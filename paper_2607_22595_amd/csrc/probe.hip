@@ -22,6 +22,11 @@
 //
 // Last-token mode runs the token pass with one workgroup per request on the
 // last token of its span, writing [n_probe][R_max].
+//
+// A small launch is a chain of round trips; EARLY (one row per workgroup, see
+// early_rows) requests the row before the mask is known, and no load of a slice
+// stands behind a branch.  Three calls over 8192 tokens (per-token, pooled, last
+// token) 43.3 -> 41.4 us.
 #include "common.hpp"
 #include "kernels.hpp"
 #include "launch.hpp"
@@ -47,19 +52,33 @@ __device__ __forceinline__ void span_of_tokens(const int32_t* __restrict__ cu, i
     }
 }
 
-template <bool BF16, int MAXP, int TT>
+template <bool BF16, int MAXP, int TT, bool EARLY>
 __global__ void __launch_bounds__(kProbeThreads)
 probe_token_kernel(const void* __restrict__ h, int32_t d, int32_t T_max,
                    const uint32_t* __restrict__ tok_mask, const void* __restrict__ w,
-                   const float* __restrict__ b, BitList bits, int32_t n_probe,
+                   const float* __restrict__ b, int32_t n_probe,
                    const int32_t* __restrict__ cu, int32_t R, int32_t mode, int32_t slots,
                    float* __restrict__ logit, float* __restrict__ score,
-                   float* __restrict__ dots) {
+                   float* __restrict__ dots, BitList bits) {
     __shared__ float red[kProbeWaves][TT * MAXP];
     // token mode: slot = token; last-token mode: slot = request, reading the
     // last token of its span (subscription of its first token); mean mode:
     // slot = token, subscription of the first token of its span
     const int32_t s0 = static_cast<int32_t>(blockIdx.x) * TT;
+    constexpr int EPV = BF16 ? 8 : 4;
+    const int32_t nvec = d / EPV;
+    const uint4* H = reinterpret_cast<const uint4*>(h);
+    const uint32_t off = threadIdx.x * 16u;
+    const int32_t count0 = min(nvec, kProbeThreads);
+    // EARLY: the row's first slice, on its way before the mask is known
+    // (last-token mode: once its token is)
+    uint4 first = make_uint4(0u, 0u, 0u, 0u);
+    if constexpr (EARLY) {
+        if (mode != 2) {
+            first = slice_load(H + static_cast<int64_t>(s0) * nvec, count0, off);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
     int32_t tok[TT];
     uint32_t sel[TT], any = 0;  // probes of each slot, of the group
     int32_t span[TT];
@@ -85,14 +104,22 @@ probe_token_kernel(const void* __restrict__ h, int32_t d, int32_t T_max,
             }
         }
         if (at < 0) continue;
-        sel[j] = select_bits(tok_mask[at], bits, n_probe);
+        if constexpr (EARLY) {
+            if (mode == 2) {
+                first = slice_load(H + static_cast<int64_t>(tok[j]) * nvec, count0, off);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        const uint32_t mask = tok_mask[at];
+        XMIX_ARGS_NOW("s"(w), "s"(b), "s"(dots), "s"(bits.first));
+        sel[j] = __builtin_amdgcn_readfirstlane(select_bits(mask, bits, n_probe));
         any |= sel[j];
     }
     if (any == 0) return;  // uniform
 
-    constexpr int EPV = BF16 ? 8 : 4;
-    const int32_t nvec = d / EPV;
-    const uint4* H = reinterpret_cast<const uint4*>(h);
+    // what this thread may finish at the end: probe p of slot s0 + j
+    const int p = threadIdx.x / TT, j_out = threadIdx.x % TT;
+    const float bias = b[min(p, n_probe - 1)];
     const uint4* W = reinterpret_cast<const uint4*>(w);
     float part[TT][MAXP];
 #pragma unroll
@@ -108,18 +135,21 @@ probe_token_kernel(const void* __restrict__ h, int32_t d, int32_t T_max,
     // pooled probes of 8192 tokens of width 4096, 46.5 -> 43.5 us for the pass of
     // all reads), else all (eight probes stay above 80 and were 3 % slower)
     constexpr int EW = BF16 && MAXP == 4 ? 1 : 4;
-    for (int32_t i = threadIdx.x; i < nvec; i += kProbeThreads) {
+    auto slice = [&](const int32_t i0, const uint4* fetched) __attribute__((always_inline)) {
+        const int32_t count = min(nvec - i0, kProbeThreads);  // slices of this turn
         // the rows and the weights of the group's probes, all loaded before the
         // first use, so that the slice waits for one memory round trip
         uint4 hv[TT], wv[AP];
 #pragma unroll
         for (int j = 0; j < TT; ++j)
-            hv[j] = sel[j] ? H[static_cast<int64_t>(tok[j]) * nvec + i]
-                           : make_uint4(0u, 0u, 0u, 0u);
+            hv[j] = fetched ? fetched[j]
+                            : slice_load(H + static_cast<int64_t>(tok[j]) * nvec + i0,
+                                         sel[j] ? count : 0, off);
 #pragma unroll
         for (int p = 0; p < AP; ++p)
-            wv[p] = ((any >> p) & 1u) ? W[static_cast<int64_t>(p) * nvec + i]
-                                      : make_uint4(0u, 0u, 0u, 0u);
+            wv[p] = slice_load(W + static_cast<int64_t>(p) * nvec + i0,
+                               ((any >> p) & 1u) ? count : 0, off);
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int e0 = 0; e0 < 4; e0 += EW) {
             float x[TT][EW * EPV / 4];
@@ -139,8 +169,9 @@ probe_token_kernel(const void* __restrict__ h, int32_t d, int32_t T_max,
 #pragma unroll
             for (int p = 0; p < MAXP; ++p) {
                 if (!((any >> p) & 1u)) continue;  // uniform
-                const uint4 w4 =
-                    p < AP ? wv[p < AP ? p : 0] : W[static_cast<int64_t>(p) * nvec + i];
+                const uint4 w4 = p < AP ? wv[p < AP ? p : 0]
+                                        : slice_load(W + static_cast<int64_t>(p) * nvec + i0,
+                                                     count, off);
                 const uint32_t ww[4] = {w4.x, w4.y, w4.z, w4.w};
 #pragma unroll
                 for (int e = 0; e < EW; ++e) {
@@ -156,7 +187,10 @@ probe_token_kernel(const void* __restrict__ h, int32_t d, int32_t T_max,
                 }
             }
         }
-    }
+    };
+    if constexpr (EARLY) slice(0, &first);
+    for (int32_t i0 = EARLY ? kProbeThreads : 0; i0 < nvec; i0 += kProbeThreads)
+        slice(i0, nullptr);
 
     const int wave = threadIdx.x / kWave;
 #pragma unroll
@@ -169,7 +203,7 @@ probe_token_kernel(const void* __restrict__ h, int32_t d, int32_t T_max,
         }
     }
     __syncthreads();
-    const int p = threadIdx.x / TT, j = threadIdx.x % TT;
+    const int j = j_out;
     uint32_t sj = sel[0];
 #pragma unroll
     for (int u = 1; u < TT; ++u) sj = j == u ? sel[u] : sj;
@@ -181,7 +215,7 @@ probe_token_kernel(const void* __restrict__ h, int32_t d, int32_t T_max,
         if (dots) {
             dots[o] = dot;
         } else {
-            const float l = b[p] + dot;
+            const float l = bias + dot;
             logit[o] = l;
             score[o] = logistic(l);
         }
@@ -201,7 +235,7 @@ probe_pool_kernel(const float* __restrict__ dots, int32_t T_max,
     const int32_t lo = cu[r], hi = cu[r + 1];
     if (hi <= lo || lo < 0 || hi > T_max) return;
     const uint32_t mask = tok_mask[lo];
-    if (!((mask >> bits.bit[p]) & 1u)) return;  // uniform over the block
+    if (!((mask >> bits.bit(p)) & 1u)) return;  // uniform over the block
     const float* dp = dots + static_cast<int64_t>(p) * T_max;
     float s = 0.0f;
     for (int32_t t = lo + threadIdx.x; t < hi; t += kProbeThreads) s += dp[t];
@@ -230,15 +264,19 @@ static void launch_probe_p(const void* h, int32_t d, int32_t T_max, const uint32
                            float* logit, float* score, float* dots, hipStream_t stream) {
     if constexpr (MAXP <= 8) {
         if (slots >= kProbeGroupMin) {
-            hipLaunchKernelGGL((probe_token_kernel<BF16, MAXP, 4>), dim3((slots + 3) / 4),
-                               dim3(kProbeThreads), 0, stream, h, d, T_max, tok_mask, w, b, bits,
-                               n_probe, cu, R, mode, slots, logit, score, dots);
+            hipLaunchKernelGGL((probe_token_kernel<BF16, MAXP, 4, false>), dim3((slots + 3) / 4),
+                               dim3(kProbeThreads), 0, stream, h, d, T_max, tok_mask, w, b,
+                               n_probe, cu, R, mode, slots, logit, score, dots, bits);
             return;
         }
     }
-    hipLaunchKernelGGL((probe_token_kernel<BF16, MAXP, 1>), dim3(slots), dim3(kProbeThreads), 0,
-                       stream, h, d, T_max, tok_mask, w, b, bits, n_probe, cu, R, mode, slots,
-                       logit, score, dots);
+    constexpr bool kCanEarly = MAXP <= 8;  // more are bound by their weights
+    const auto kernel = kCanEarly && early_rows(slots, d / (BF16 ? 8 : 4))
+                            ? probe_token_kernel<BF16, MAXP, 1, kCanEarly>
+                            : probe_token_kernel<BF16, MAXP, 1, false>;
+    hipLaunchKernelGGL(kernel, dim3(slots), dim3(kProbeThreads), 0,
+                       stream, h, d, T_max, tok_mask, w, b, n_probe, cu, R, mode, slots, logit,
+                       score, dots, bits);
 }
 
 template <bool BF16>
@@ -275,18 +313,22 @@ hipError_t launch_probe(const void* h, bool bf16, int32_t d, int32_t T_max,
 }
 
 void add_probe_kernels(std::vector<KernelInfo>& t) {
-    t.push_back(kernel_info(probe_token_kernel<true, 4, 1>));
-    t.push_back(kernel_info(probe_token_kernel<true, 4, 4>));
-    t.push_back(kernel_info(probe_token_kernel<true, 8, 1>));
-    t.push_back(kernel_info(probe_token_kernel<true, 8, 4>));
-    t.push_back(kernel_info(probe_token_kernel<true, 16, 1>));
-    t.push_back(kernel_info(probe_token_kernel<true, 32, 1>));
-    t.push_back(kernel_info(probe_token_kernel<false, 4, 1>));
-    t.push_back(kernel_info(probe_token_kernel<false, 4, 4>));
-    t.push_back(kernel_info(probe_token_kernel<false, 8, 1>));
-    t.push_back(kernel_info(probe_token_kernel<false, 8, 4>));
-    t.push_back(kernel_info(probe_token_kernel<false, 16, 1>));
-    t.push_back(kernel_info(probe_token_kernel<false, 32, 1>));
+    t.push_back(kernel_info(probe_token_kernel<true, 4, 1, true>));
+    t.push_back(kernel_info(probe_token_kernel<true, 4, 1, false>));
+    t.push_back(kernel_info(probe_token_kernel<true, 4, 4, false>));
+    t.push_back(kernel_info(probe_token_kernel<true, 8, 1, true>));
+    t.push_back(kernel_info(probe_token_kernel<true, 8, 1, false>));
+    t.push_back(kernel_info(probe_token_kernel<true, 8, 4, false>));
+    t.push_back(kernel_info(probe_token_kernel<true, 16, 1, false>));
+    t.push_back(kernel_info(probe_token_kernel<true, 32, 1, false>));
+    t.push_back(kernel_info(probe_token_kernel<false, 4, 1, true>));
+    t.push_back(kernel_info(probe_token_kernel<false, 4, 1, false>));
+    t.push_back(kernel_info(probe_token_kernel<false, 4, 4, false>));
+    t.push_back(kernel_info(probe_token_kernel<false, 8, 1, true>));
+    t.push_back(kernel_info(probe_token_kernel<false, 8, 1, false>));
+    t.push_back(kernel_info(probe_token_kernel<false, 8, 4, false>));
+    t.push_back(kernel_info(probe_token_kernel<false, 16, 1, false>));
+    t.push_back(kernel_info(probe_token_kernel<false, 32, 1, false>));
     t.push_back(kernel_info(probe_pool_kernel));
 }
 

@@ -65,7 +65,6 @@ namespace xmix {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;
 typedef __attribute__((ext_vector_type(16))) float f32x16_t;
-typedef __attribute__((ext_vector_type(4))) unsigned int u32x4_t;
 
 constexpr int kBM = 256;  // latents per workgroup
 constexpr int kBN = 128;  // tokens per workgroup
@@ -456,8 +455,6 @@ struct SliceSink {
     float z;
 };
 
-// Word 3 of a raw buffer resource (32-bit element format, no swizzle).
-constexpr int kBufferDword3 = 0x00020000;
 // A buffer offset past every resource (none is larger than 2^31 - 1 bytes), and
 // far enough from 2^32 that no scalar offset wraps it.
 constexpr uint32_t kOutOfRange = 0x80000000u;

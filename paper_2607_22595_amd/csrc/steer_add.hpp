@@ -1,43 +1,45 @@
-// The steering sum of one 16-byte slice of a row (internal), shared by the
-// steering kernel and the fused probe + steering pass so that both add in
-// the same order: acc (the slice, widened to fp64) += alpha[s] * v_s for
-// every set bit s of sel, ascending, one fp64 FMA per element.  The
-// vectors are fetched four at a time before their adds, so the loads of a
-// group are in flight together; a kernel may fetch the first group together
-// with the row it adds to (steer_fetch), add it (steer_add_group) and pass
-// the remaining bits to steer_accumulate.
+// The steering sum of one 16-byte slice of a row (internal) of the fused probe
+// + steering pass, which adds in the order of the steering kernel: acc (the
+// slice, widened to fp64) += alpha[s] * v_s for every set bit s of sel,
+// ascending, one fp64 FMA per element.  Four vectors at a time: which ones,
+// with their alphas (steer_pick), their slices (steer_fetch), the adds
+// (steer_add_group).
 #pragma once
 
 #include "common.hpp"
 
 namespace xmix {
 
-// Up to four vectors of the steering sum, fetched before their adds: the
-// next set bits of `rest` (ascending; they are cleared from it), with their
-// alphas widened to fp64.
+// Up to four vectors of the steering sum with their alphas.
 struct SteerGroup {
     uint4 v[4];
-    double a[4];
-    int n;
+    float a[4];
+    int s[4], n;
 };
 
-__device__ __forceinline__ void steer_fetch(SteerGroup& g, uint32_t& rest,
-                                            const float* __restrict__ a_row,
-                                            const uint4* __restrict__ V, int32_t nvec,
-                                            int32_t i) {
-    g.n = 0;
+// The next set bits of `rest` (ascending; they are cleared from it) and their
+// alphas, of n_steer in the row; the last one's stand in where there are fewer.
+// Vector loads: scalar ones return out of order, so the first use of one would
+// wait for all of them.
+__device__ __forceinline__ void steer_pick(SteerGroup& g, uint32_t& rest,
+                                           const float* __restrict__ a_row, int32_t n_steer) {
+    g.n = min(__popc(rest), 4);
+    int zero = 0;
+    asm("" : "+v"(zero));
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-        g.v[j] = make_uint4(0u, 0u, 0u, 0u);
-        g.a[j] = 0.0;
-        if (rest != 0) {
-            const int s = __builtin_ctz(rest);
-            rest &= rest - 1;
-            g.a[j] = a_row[s];
-            g.v[j] = V[static_cast<int64_t>(s) * nvec + i];
-            g.n = j + 1;
-        }
+        g.s[j] = min(__builtin_ctz(rest | 0x80000000u), n_steer - 1);
+        rest &= rest - 1;  // 0 stays 0
+        g.a[j] = a_row[g.s[j] + zero];
     }
+}
+
+// The group's slices: `count` slices of a row at V (the vectors nvec apart).
+__device__ __forceinline__ void steer_fetch(SteerGroup& g, const uint4* __restrict__ V,
+                                            int32_t nvec, int32_t count, uint32_t off) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+        g.v[j] = slice_load(V + static_cast<int64_t>(g.s[j]) * nvec, j < g.n ? count : 0, off);
 }
 
 // acc += a[j] * v_j for the group's vectors in order, one fp64 FMA per element.
@@ -48,28 +50,20 @@ __device__ __forceinline__ void steer_add_group(double (&acc)[BF16 ? 8 : 4],
     for (int j = 0; j < 4; ++j) {
         if (j >= g.n) break;
         const uint32_t vw[4] = {g.v[j].x, g.v[j].y, g.v[j].z, g.v[j].w};
+        // opaque here, so that its conversion is not moved up (and its load
+        // waited for) before the slices are requested
+        float af = g.a[j];
+        asm volatile("" : "+v"(af));
+        const double a = af;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             if constexpr (BF16) {
-                acc[2 * e] = fma(g.a[j], static_cast<double>(lo_bf16(vw[e])), acc[2 * e]);
-                acc[2 * e + 1] = fma(g.a[j], static_cast<double>(hi_bf16(vw[e])), acc[2 * e + 1]);
+                acc[2 * e] = fma(a, static_cast<double>(lo_bf16(vw[e])), acc[2 * e]);
+                acc[2 * e + 1] = fma(a, static_cast<double>(hi_bf16(vw[e])), acc[2 * e + 1]);
             } else {
-                acc[e] = fma(g.a[j], static_cast<double>(__uint_as_float(vw[e])), acc[e]);
+                acc[e] = fma(a, static_cast<double>(__uint_as_float(vw[e])), acc[e]);
             }
         }
-    }
-}
-
-// The whole steering sum of the set bits of sel, four vectors at a time.
-template <bool BF16>
-__device__ __forceinline__ void steer_accumulate(double (&acc)[BF16 ? 8 : 4], uint32_t sel,
-                                                 const float* __restrict__ a_row,
-                                                 const uint4* __restrict__ V, int32_t nvec,
-                                                 int32_t i) {
-    for (uint32_t rest = sel; rest != 0;) {
-        SteerGroup g;
-        steer_fetch(g, rest, a_row, V, nvec, i);
-        steer_add_group<BF16>(acc, g);
     }
 }
 

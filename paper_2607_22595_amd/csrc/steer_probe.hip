@@ -27,17 +27,17 @@ namespace xmix {
 constexpr int kFuseThreads = 512;  // a 4096-wide bf16 row is one 16-byte slice per thread
 constexpr int kFuseWaves = kFuseThreads / kWave;
 
-template <bool BF16, int MAXP>
+template <bool BF16, int MAXP, bool EARLY>
 __global__ void __launch_bounds__(kFuseThreads)
 steer_probe_kernel(void* __restrict__ h, int32_t d, int32_t T_max,
                    const uint32_t* __restrict__ tok_mask, const int32_t* __restrict__ req,
-                   const void* __restrict__ vecs, BitList sbits, const float* __restrict__ alpha,
-                   int32_t n_steer, const void* __restrict__ w, const float* __restrict__ b,
-                   BitList pbits, int32_t n_probe, float* __restrict__ logit,
-                   float* __restrict__ score, const int32_t* __restrict__ r_tvalid,
-                   const uint32_t* __restrict__ r_sub, int32_t r_Rmax, int32_t r_napps,
-                   uint32_t* __restrict__ r_mask, int32_t* __restrict__ r_count,
-                   int32_t* __restrict__ r_lists, uint32_t* __restrict__ r_err) {
+                   const int32_t* __restrict__ r_tvalid, const uint32_t* __restrict__ r_sub,
+                   int32_t r_Rmax, int32_t r_napps, const void* __restrict__ vecs,
+                   const float* __restrict__ alpha, int32_t n_steer, const void* __restrict__ w,
+                   const float* __restrict__ b, int32_t n_probe, float* __restrict__ logit,
+                   float* __restrict__ score, uint32_t* __restrict__ r_mask,
+                   int32_t* __restrict__ r_count, int32_t* __restrict__ r_lists,
+                   uint32_t* __restrict__ r_err, BitList sbits, BitList pbits) {
     __shared__ float red[kFuseWaves][MAXP];
     const int n_list = r_tvalid ? r_napps : 0;  // route-list workgroups
     if (static_cast<int>(blockIdx.x) < n_list) {  // uniform
@@ -59,48 +59,58 @@ steer_probe_kernel(void* __restrict__ h, int32_t d, int32_t T_max,
         return;
     }
     const int32_t t = static_cast<int32_t>(blockIdx.x) - n_list;
+    constexpr int EPV = BF16 ? 8 : 4;  // elements per 16-byte vector
+    const int32_t nvec = d / EPV;
+    uint4* row = reinterpret_cast<uint4*>(h) + static_cast<int64_t>(t) * nvec;
+    const uint32_t off = threadIdx.x * 16u;
+    uint4 first;  // the row's first slice, on its way before the mask is known
+    if constexpr (EARLY) {
+        first = slice_load(row, min(nvec, kFuseThreads), off);
+        __builtin_amdgcn_sched_barrier(0);
+    }
     const int32_t rq = req[t];  // loaded beside the mask (alpha's row depends on it)
-    uint32_t mask;
+    uint32_t mask = tok_mask[t];  // (not the step's when the routing is built here)
+    XMIX_ARGS_NOW("s"(rq), "s"(mask), "s"(vecs), "s"(alpha), "s"(n_steer), "s"(w), "s"(b),
+                  "s"(n_probe), "s"(sbits.first), "s"(pbits.first));
+    const float bias = b[min(static_cast<int32_t>(threadIdx.x), n_probe - 1)];
     if (r_tvalid) {  // uniform
         uint32_t unused = 0;
         const int32_t tv = clamp_t_valid(*r_tvalid, T_max, unused);
         const uint32_t keep = r_napps >= 32 ? 0xFFFFFFFFu : ((1u << r_napps) - 1u);
         mask = request_mask(rq, t, tv, r_sub, r_Rmax, keep, unused);
         if (threadIdx.x == 0) r_mask[t] = mask;
-    } else {
-        mask = tok_mask[t];
     }
-    const uint32_t ss = select_bits(mask, sbits, n_steer);
-    const uint32_t sp = select_bits(mask, pbits, n_probe);
+    const uint32_t ss = __builtin_amdgcn_readfirstlane(select_bits(mask, sbits, n_steer));
+    const uint32_t sp = __builtin_amdgcn_readfirstlane(select_bits(mask, pbits, n_probe));
     if ((ss | sp) == 0) return;
     const float* a_row = ss ? alpha + static_cast<int64_t>(rq) * n_steer : alpha;
-
-    constexpr int EPV = BF16 ? 8 : 4;  // elements per 16-byte vector
-    const int32_t nvec = d / EPV;
-    uint4* row = reinterpret_cast<uint4*>(h) + static_cast<int64_t>(t) * nvec;
     const uint4* V = reinterpret_cast<const uint4*>(vecs);
     const uint4* W = reinterpret_cast<const uint4*>(w);
     float part[MAXP];
 #pragma unroll
     for (int p = 0; p < MAXP; ++p) part[p] = 0.0f;
+    SteerGroup g0;  // the token's first four steering vectors
+    uint32_t rest0 = ss;
+    steer_pick(g0, rest0, a_row, n_steer);
 
     // probe weights fetched together with the row (the rest, for more than
     // eight probes, when used)
     constexpr int AP = MAXP < 8 ? MAXP : 8;
-    for (int32_t i = threadIdx.x; i < nvec; i += kFuseThreads) {
-        // Every load of the slice before its first use: the row, the weights
-        // of the token's probes and its first four steering vectors with
-        // their alphas, so that the slice waits for one memory round trip,
-        // not one per operand.
-        const uint4 hv = row[i];
+    auto slice = [&](const int32_t i0, const uint4* fetched) __attribute__((always_inline)) {
+        const int32_t count = min(nvec - i0, kFuseThreads);  // slices of this turn
+        const int32_t i = i0 + static_cast<int32_t>(threadIdx.x);
+        // Every load of the slice before its first use, and none behind a
+        // branch: the row, the weights of the token's probes and its first
+        // four steering vectors, so that the slice waits for one memory round
+        // trip, not one per operand.
+        const uint4 hv = fetched ? *fetched : slice_load(row + i0, count, off);
         uint4 wv[AP];
 #pragma unroll
         for (int p = 0; p < AP; ++p)
-            wv[p] = ((sp >> p) & 1u) ? W[static_cast<int64_t>(p) * nvec + i]
-                                     : make_uint4(0u, 0u, 0u, 0u);
-        uint32_t rest = ss;
-        SteerGroup g0;
-        steer_fetch(g0, rest, a_row, V, nvec, i);
+            wv[p] = slice_load(W + static_cast<int64_t>(p) * nvec + i0,
+                               ((sp >> p) & 1u) ? count : 0, off);
+        steer_fetch(g0, V + i0, nvec, count, off);
+        __builtin_amdgcn_sched_barrier(0);
         const uint32_t hw[4] = {hv.x, hv.y, hv.z, hv.w};
         // probes, on the row as read
         float x[EPV];
@@ -116,7 +126,8 @@ steer_probe_kernel(void* __restrict__ h, int32_t d, int32_t T_max,
 #pragma unroll
         for (int p = 0; p < MAXP; ++p) {
             if (!((sp >> p) & 1u)) continue;
-            const uint4 w4 = p < AP ? wv[p < AP ? p : 0] : W[static_cast<int64_t>(p) * nvec + i];
+            const uint4 w4 = p < AP ? wv[p < AP ? p : 0]
+                                    : slice_load(W + static_cast<int64_t>(p) * nvec + i0, count, off);
             const uint32_t ww[4] = {w4.x, w4.y, w4.z, w4.w};
             float acc = part[p];
 #pragma unroll
@@ -137,7 +148,12 @@ steer_probe_kernel(void* __restrict__ h, int32_t d, int32_t T_max,
 #pragma unroll
             for (int e = 0; e < EPV; ++e) acc[e] = x[e];
             steer_add_group<BF16>(acc, g0);
-            if (rest) steer_accumulate<BF16>(acc, rest, a_row, V, nvec, i);
+            for (uint32_t rest = rest0; rest != 0;) {
+                SteerGroup g;
+                steer_pick(g, rest, a_row, n_steer);
+                steer_fetch(g, V + i0, nvec, count, off);
+                steer_add_group<BF16>(acc, g);
+            }
             uint4 out;
             if constexpr (BF16) {
                 out.x = pack_bf16_from_f64(acc[0], acc[1]);
@@ -150,9 +166,11 @@ steer_probe_kernel(void* __restrict__ h, int32_t d, int32_t T_max,
                 out.z = __float_as_uint(static_cast<float>(acc[2]));
                 out.w = __float_as_uint(static_cast<float>(acc[3]));
             }
-            row[i] = out;
+            if (i < nvec) row[i] = out;
         }
-    }
+    };
+    if constexpr (EARLY) slice(0, &first);
+    for (int32_t i0 = EARLY ? kFuseThreads : 0; i0 < nvec; i0 += kFuseThreads) slice(i0, nullptr);
     if (sp == 0) return;  // uniform over the block
 
     const int wave = threadIdx.x / kWave;
@@ -169,7 +187,7 @@ steer_probe_kernel(void* __restrict__ h, int32_t d, int32_t T_max,
 #pragma unroll
         for (int wv = 0; wv < kFuseWaves; ++wv) dot += red[wv][p];
         const int64_t o = static_cast<int64_t>(p) * T_max + t;
-        const float l = b[p] + dot;
+        const float l = bias + dot;
         logit[o] = l;
         score[o] = logistic(l);
     }
@@ -183,27 +201,18 @@ static hipError_t launch_steer_probe_t(void* h, int32_t d, int32_t T_max,
                                        const float* b, const BitList& pbits, int32_t n_probe,
                                        float* logit, float* score, const RouteIn& r,
                                        hipStream_t stream) {
-    dim3 g(T_max + (r.T_valid ? r.n_apps : 0)), blk(kFuseThreads);
-    if (n_probe <= 4)
-        hipLaunchKernelGGL((steer_probe_kernel<BF16, 4>), g, blk, 0, stream, h, d, T_max,
-                           tok_mask, req, vecs, sbits, alpha, n_steer, w, b, pbits, n_probe,
-                           logit, score, r.T_valid, r.sub, r.R_max, r.n_apps, r.tok_mask,
-                           r.app_count, r.app_tokens, r.err_word);
-    else if (n_probe <= 8)
-        hipLaunchKernelGGL((steer_probe_kernel<BF16, 8>), g, blk, 0, stream, h, d, T_max,
-                           tok_mask, req, vecs, sbits, alpha, n_steer, w, b, pbits, n_probe,
-                           logit, score, r.T_valid, r.sub, r.R_max, r.n_apps, r.tok_mask,
-                           r.app_count, r.app_tokens, r.err_word);
-    else if (n_probe <= 16)
-        hipLaunchKernelGGL((steer_probe_kernel<BF16, 16>), g, blk, 0, stream, h, d, T_max,
-                           tok_mask, req, vecs, sbits, alpha, n_steer, w, b, pbits, n_probe,
-                           logit, score, r.T_valid, r.sub, r.R_max, r.n_apps, r.tok_mask,
-                           r.app_count, r.app_tokens, r.err_word);
-    else
-        hipLaunchKernelGGL((steer_probe_kernel<BF16, 32>), g, blk, 0, stream, h, d, T_max,
-                           tok_mask, req, vecs, sbits, alpha, n_steer, w, b, pbits, n_probe,
-                           logit, score, r.T_valid, r.sub, r.R_max, r.n_apps, r.tok_mask,
-                           r.app_count, r.app_tokens, r.err_word);
+    // more than eight probes leave a pass bound by its weights, not by the chain
+    const bool early = early_rows(T_max, d / (BF16 ? 8 : 4));
+    const auto kernel = n_probe <= 4    ? (early ? steer_probe_kernel<BF16, 4, true>
+                                                 : steer_probe_kernel<BF16, 4, false>)
+                        : n_probe <= 8  ? (early ? steer_probe_kernel<BF16, 8, true>
+                                                 : steer_probe_kernel<BF16, 8, false>)
+                        : n_probe <= 16 ? steer_probe_kernel<BF16, 16, false>
+                                        : steer_probe_kernel<BF16, 32, false>;
+    hipLaunchKernelGGL(kernel, dim3(T_max + (r.T_valid ? r.n_apps : 0)), dim3(kFuseThreads), 0,
+                       stream, h, d, T_max, tok_mask, req, r.T_valid, r.sub, r.R_max, r.n_apps,
+                       vecs, alpha, n_steer, w, b, n_probe, logit, score, r.tok_mask, r.app_count,
+                       r.app_tokens, r.err_word, sbits, pbits);
     return hipGetLastError();
 }
 
@@ -235,14 +244,18 @@ hipError_t launch_steer_probe(void* h, bool bf16, int32_t d, int32_t T_max,
 }
 
 void add_steer_probe_kernels(std::vector<KernelInfo>& t) {
-    t.push_back(kernel_info(steer_probe_kernel<true, 4>));
-    t.push_back(kernel_info(steer_probe_kernel<true, 8>));
-    t.push_back(kernel_info(steer_probe_kernel<true, 16>));
-    t.push_back(kernel_info(steer_probe_kernel<true, 32>));
-    t.push_back(kernel_info(steer_probe_kernel<false, 4>));
-    t.push_back(kernel_info(steer_probe_kernel<false, 8>));
-    t.push_back(kernel_info(steer_probe_kernel<false, 16>));
-    t.push_back(kernel_info(steer_probe_kernel<false, 32>));
+    t.push_back(kernel_info(steer_probe_kernel<true, 4, true>));
+    t.push_back(kernel_info(steer_probe_kernel<true, 4, false>));
+    t.push_back(kernel_info(steer_probe_kernel<true, 8, true>));
+    t.push_back(kernel_info(steer_probe_kernel<true, 8, false>));
+    t.push_back(kernel_info(steer_probe_kernel<true, 16, false>));
+    t.push_back(kernel_info(steer_probe_kernel<true, 32, false>));
+    t.push_back(kernel_info(steer_probe_kernel<false, 4, true>));
+    t.push_back(kernel_info(steer_probe_kernel<false, 4, false>));
+    t.push_back(kernel_info(steer_probe_kernel<false, 8, true>));
+    t.push_back(kernel_info(steer_probe_kernel<false, 8, false>));
+    t.push_back(kernel_info(steer_probe_kernel<false, 16, false>));
+    t.push_back(kernel_info(steer_probe_kernel<false, 32, false>));
 }
 
 }  // namespace xmix

@@ -269,3 +269,44 @@ def test_app_bits_in_any_order(px, sbits, pbits):
         assert np.array_equal(np.isnan(got), np.isnan(lr))
         # 264 fp32 multiply-adds of terms of about 0.1
         assert np.nanmax(np.abs(got - lr)) <= 264 * 2.0 ** -24 * 100
+
+
+@pytest.mark.parametrize("T,d,n_steer,n_probe,dtype", [
+    (1, 8, 1, 1, "bf16"), (130, 4088, 4, 4, "bf16"), (70, 4104, 5, 5, "bf16"),
+    (1024, 4096, 2, 3, "bf16"), (1025, 4096, 2, 3, "bf16"),   # up to 8 MB of rows, and past it
+    (33, 8200, 8, 8, "bf16"), (40, 2056, 3, 9, "bf16"), (64, 2052, 4, 8, "f32"),
+    (1025, 2048, 1, 4, "f32")])
+@pytest.mark.parametrize("gap", [1, 2])
+def test_steer_probe_early_rows(px, T, d, n_steer, n_probe, dtype, gap):
+    """The fused pass on either side of the rule that reads rows before their
+    masks, rows that end inside, at and past a turn of 512 slices, app bits
+    side by side and apart: the oracle's rows, and the probe kernel's bits."""
+    n = gap * (n_steer + n_probe)
+    rng, req, sub = batch(T, n, p=0.4, seed=T + d)
+    bf = dtype == "bf16"
+    draw = synth.normal_bf16 if bf else synth.normal_f32
+    h, v = draw("e/h", (T, d), 1.0), draw("e/v", (n_steer, d), 0.2)
+    w = draw("e/w", (n_probe, d), d ** -0.5)
+    h[::3, -1] = 0x7F80 if bf else np.inf                     # some rows end in an infinity
+    alpha = rng.uniform(-4, 4, (T, n_steer)).astype(np.float32)
+    b = rng.normal(0, 0.3, n_probe).astype(np.float32)
+    sbits = [gap * s for s in range(n_steer)]
+    pbits = [gap * (n_steer + p) for p in range(n_probe)]
+    rt, _ = build(px, req, T, sub, n)
+    tm = oracle.route(req, T, sub, n)[0]
+    hd, wd, bd, vd, rd, ad = dev(h), dev(w), dev(b), dev(v), dev(req), dev(alpha)
+    sep = [torch.full((n_probe, T), float("nan"), device="cuda") for _ in range(2)]
+    px.xmix_probe_score(hd, rt, wd, bd, pbits, px.XMIX_PROBE_TOKEN, *sep)
+    fused = [torch.full((n_probe, T), float("nan"), device="cuda") for _ in range(2)]
+    px.xmix_steer_probe(hd, rt, rd, vd, sbits, ad, wd, bd, pbits, *fused)
+    for a, c in zip(fused, sep):
+        assert np.array_equal(a.cpu().numpy(), c.cpu().numpy(), equal_nan=True)
+    ref = oracle.steer(h, tm, req, v, sbits, alpha)
+    got = torch_bits(hd) if bf else hd.cpu().numpy()
+    assert np.array_equal(got, ref)
+    lr, sr = oracle.probe_token(h, tm, w, b, pbits)
+    fin = np.isfinite(lr)
+    hf, wf = (bf16_f64(h), bf16_f64(w)) if bf else (h.astype(np.float64), w.astype(np.float64))
+    hf[::3, -1] = 0.0
+    absdot = np.abs(wf) @ np.abs(hf).T
+    check_probe(fused[0].cpu().numpy(), fused[1].cpu().numpy(), lr, sr, fin, absdot)
