@@ -872,14 +872,18 @@ __device__ __forceinline__ void narrow_slices(uint4* lds_main, const uint16_t* _
 // (or, with few slices, leaves the reuse to chance), and from about 200 the
 // matrix cores bound it, not HBM.  Here a workgroup multiplies 256 latents by
 // 256 tokens, each of its eight waves 64 x 128 (128 accumulator registers).
-// The token rows of a K stage of 32 are shared through LDS (double buffered,
-// one barrier a stage, staged in registers); the dictionary goes straight into
-// the registers of the two waves that share a latent quarter: both operands
-// through LDS are 128 KB of traffic a stage, as long as the stage's MFMAs.
-// Measured at 391 tokens, m = 32768, d = 4096, per launch: 258 us as four
-// 128-token tiles in turn, 156 with both operands through LDS, 143 so.
+// The token rows of two K stages of 32 are shared through LDS (double buffered,
+// one barrier a pair, staged in registers, a row's whole 128-byte line at a time);
+// the dictionary goes straight into the registers of the two waves that share a
+// latent quarter: both operands through LDS are 128 KB of traffic a stage, as long
+// as the stage's MFMAs.  The second half of a stage is multiplied after the next
+// one's first reads are issued, so that a barrier does not empty the matrix cores.
+// Measured per layer with the merge, 391 tokens, m = 32768, d = 4096: 137 us with a
+// barrier a stage and nothing carried, 131 so; 256 tokens, m = 65536, d = 8192: 300
+// and 279; 900 tokens, m = 16384, d = 2304: 87 and 83.  Before that, per launch: 258
+// us as four 128-token tiles in turn, 156 with both operands through LDS.
 constexpr int kBigTok = 256;
-constexpr int kBigPieces = 1024;  // 16-byte pieces of a stage's token rows
+constexpr int kBigPieces = 1024;  // 16-byte pieces of a stage's token rows; four stages
 
 // Stage swizzle: the 16-byte piece c of token n sits at n*4 + (c ^ gsw(n));
 // with it the MFMA-layout reads of 16 tokens x 4 pieces hit distinct banks.
@@ -924,36 +928,41 @@ __device__ __forceinline__ void big_tile(uint4* lds_main, const uint16_t* __rest
     const char* Wb = reinterpret_cast<const char*>(W) + static_cast<int64_t>(mt) * 32768;
     const int64_t chunk = static_cast<int64_t>(n_mt) * 32768;
     const uint32_t woff = static_cast<uint32_t>(2 * wm * 256 + lane) * 16u;
-    uint32_t xoff[2];
-    int xdst[2];
+    // the token rows of a pair of stages, 128 bytes of each: this thread takes piece
+    // xc of rows xn, xn + 64, xn + 128, xn + 192 (their swizzles are the same).  The
+    // second stage of a pair keeps row n at n ^ 2, so that the eight lanes of a row
+    // write to eight bank groups.
+    uint32_t xoff[4];
+    const int xn = tid >> 3, xc = tid & 7;
+    const int xdst = (xc >> 2) * kBigPieces + (xn ^ ((xc >> 2) << 1)) * 4 + ((xc & 3) ^ gsw(xn));
 #pragma unroll
-    for (int p = 0; p < 2; ++p) {
-        const int P = tid + kEncThreads * p;
-        const int n = P >> 2, c = P & 3;
+    for (int p = 0; p < 4; ++p) {
+        const int n = xn + 64 * p;
         xoff[p] = n < ntok ? static_cast<uint32_t>(tl[n0 + n]) * static_cast<uint32_t>(d) * 2u +
-                                 c * 16u
+                                 xc * 16u
                            : kOutOfRange;
-        xdst[p] = n * 4 + (c ^ gsw(n));
     }
-    auto load_w = [&](uint4 (&w)[4], int j) __attribute__((always_inline)) {
+    // half of a stage's dictionary operands: those of step s
+    auto load_w = [&](uint4 (&w)[4], int j, int s) __attribute__((always_inline)) {
         const int jc = min(j, nS - 1);
         const __amdgpu_buffer_rsrc_t wr = __builtin_amdgcn_make_buffer_rsrc(
             const_cast<char*>(Wb + (jc >> 1) * chunk + (jc & 1) * 2048), 0,
             j < nS ? 32768 - 2048 : 0, kBufferDword3);
 #pragma unroll
-        for (int q = 0; q < 4; ++q)  // q = 2 s + a
-            w[q] = buffer_load16<0>(wr, woff + (q & 1) * 4096u + (q >> 1) * 1024u, 0);
+        for (int a = 0; a < 2; ++a)
+            w[2 * s + a] = buffer_load16<0>(wr, woff + a * 4096u + s * 1024u, 0);
     };
-    auto load_x = [&](uint4 (&x)[2], int j) __attribute__((always_inline)) {
+    auto load_x = [&](uint4 (&x)[4], int k) __attribute__((always_inline)) {
+        const bool in = 2 * k < nS;
         const __amdgpu_buffer_rsrc_t xr = __builtin_amdgcn_make_buffer_rsrc(
-            const_cast<uint16_t*>(h), 0, j < nS ? static_cast<int>(h_bytes) : 0, kBufferDword3);
+            const_cast<uint16_t*>(h), 0, in ? static_cast<int>(h_bytes) : 0, kBufferDword3);
 #pragma unroll
-        for (int p = 0; p < 2; ++p)
-            x[p] = buffer_load16<0>(xr, xoff[p], j < nS ? static_cast<uint32_t>(j) * 64u : 0u);
+        for (int p = 0; p < 4; ++p)
+            x[p] = buffer_load16<0>(xr, xoff[p], in ? static_cast<uint32_t>(k) * 128u : 0u);
     };
-    auto store_x = [&](const uint4 (&x)[2], int j) __attribute__((always_inline)) {
+    auto store_x = [&](const uint4 (&x)[4], int k) __attribute__((always_inline)) {
 #pragma unroll
-        for (int p = 0; p < 2; ++p) xsb[(j & 1) * kBigPieces + xdst[p]] = x[p];
+        for (int p = 0; p < 4; ++p) xsb[(k & 1) * 2 * kBigPieces + xdst + 256 * p] = x[p];
     };
     f32x16_t acc[2][4];
     {
@@ -972,54 +981,66 @@ __device__ __forceinline__ void big_tile(uint4* lds_main, const uint16_t* __rest
                 }
             }
     }
-    auto compute = [&](const uint4 (&w)[4], int j) __attribute__((always_inline)) {
-        const uint4* xb = xsb + (j & 1) * kBigPieces;
+    auto read_b = [&](uint4 (&B)[4], int j, int s) __attribute__((always_inline)) {
+        const uint4* xb = xsb + (j & 3) * kBigPieces;
 #pragma unroll
-        for (int s = 0; s < 2; ++s) {
-            uint4 B[4];
-#pragma unroll
-            for (int nb = 0; nb < 4; ++nb) {
-                const int n = 128 * wn + 32 * nb + j32;
-                B[nb] = xb[n * 4 + ((2 * s + g) ^ gsw(n))];
-            }
-#pragma unroll
-            for (int a = 0; a < 2; ++a)
-#pragma unroll
-                for (int nb = 0; nb < 4; ++nb)
-                    acc[a][nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                        as_bf16x8(w[2 * s + a]), as_bf16x8(B[nb]), acc[a][nb], 0, 0, 0);
+        for (int nb = 0; nb < 4; ++nb) {
+            const int n = 128 * wn + 32 * nb + j32;
+            B[nb] = xb[(n ^ ((j & 1) << 1)) * 4 + ((2 * s + g) ^ gsw(n))];
         }
     };
-    // stage j is multiplied, stage j + 1's token rows move to the other buffer
-    // (which every wave left before this step's barrier), and later stages are
-    // fetched: the rows two ahead, the dictionary three ahead into the
-    // registers just used
-    auto step = [&](int j, uint4 (&w)[4], uint4 (&xload)[2], const uint4 (&xnext)[2])
+    auto multiply = [&](const uint4 (&w)[4], int s, const uint4 (&B)[4])
         __attribute__((always_inline)) {
-        load_x(xload, j + 2);
-        __syncthreads();
-        compute(w, j);
-        store_x(xnext, j + 1);
-        load_w(w, j + 3);
+#pragma unroll
+        for (int a = 0; a < 2; ++a)
+#pragma unroll
+            for (int nb = 0; nb < 4; ++nb)
+                acc[a][nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                    as_bf16x8(w[2 * s + a]), as_bf16x8(B[nb]), acc[a][nb], 0, 0, 0);
     };
-    uint4 w0[4], w1[4], w2[4], x0[2], x1[2];
-    load_x(x0, 0);
-    load_w(w0, 0);
-    load_x(x1, 1);
-    load_w(w1, 1);
-    load_w(w2, 2);
-    store_x(x0, 0);
-    for (int j = 0;; j += 6) {  // an even number of stages
-        step(j, w0, x0, x1);
-        step(j + 1, w1, x1, x0);
-        if (j + 2 == nS) break;
-        step(j + 2, w2, x0, x1);
-        step(j + 3, w0, x1, x0);
-        if (j + 4 == nS) break;
-        step(j + 4, w1, x0, x1);
-        step(j + 5, w2, x1, x0);
-        if (j + 6 == nS) break;
+    // Stage j, two of them per barrier: its step 0 is read while the step carried
+    // over from stage j - 1 is multiplied, its step 1 is read while step 0 is, and
+    // carried on, so that the matrix unit has work while the waves meet.  Between a
+    // pair's stages the token rows of the next pair move into buffers that every
+    // wave left before this pair's barrier, and those of the pair after it are
+    // fetched; the dictionary is fetched two stages ahead into the registers just
+    // used (wp: stage j - 1's).
+    uint4 F[4], P[4], x[4];
+    auto stage = [&](int j, uint4 (&w)[4], uint4 (&wp)[4], bool first)
+        __attribute__((always_inline)) {
+        if ((j & 1) == 0) __syncthreads();
+        read_b(F, j, 0);
+        if (!first) multiply(wp, 1, P);
+        __builtin_amdgcn_sched_barrier(0);
+        load_w(wp, j + 1, 1);
+        read_b(P, j, 1);
+        multiply(w, 0, F);
+        __builtin_amdgcn_sched_barrier(0);
+        load_w(w, j + 2, 0);
+        if ((j & 1) == 0) {
+            store_x(x, j / 2 + 1);
+            load_x(x, j / 2 + 2);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    uint4 w0[4], w1[4];
+    load_x(x, 0);
+    load_w(w0, 0, 0);
+    load_w(w0, 0, 1);
+    load_w(w1, 1, 0);
+    store_x(x, 0);
+    load_x(x, 1);
+    stage(0, w0, w1, true);
+    stage(1, w1, w0, false);
+    stage(2, w0, w1, false);
+    stage(3, w1, w0, false);
+    for (int j = 4; j < nS; j += 4) {  // a multiple of eight stages
+        stage(j, w0, w1, false);
+        stage(j + 1, w1, w0, false);
+        stage(j + 2, w0, w1, false);
+        stage(j + 3, w1, w0, false);
     }
+    multiply(w1, 1, P);
 
     // acc[a][nb][r] holds latent 64*wm + 32*a + 8*(r/4) + 4*g + r%4 of token
     // 128*wn + 32*nb + j32; the tile's tokens are selected 128 at a time
@@ -1070,7 +1091,7 @@ __device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirs
 // slice, its partial-sum planes)
 constexpr int kLdsMain = Narrow<4>::kPart * 4 / 4;  // 16-byte pieces
 static_assert(kLdsMain >= kBN * kSelStride / 4 && kLdsMain >= Narrow<2>::kPart * 2 / 4 &&
-                  kLdsMain >= 2 * Narrow<4>::kPieces && kLdsMain >= 2 * kBigPieces,
+                  kLdsMain >= 2 * Narrow<4>::kPieces && kLdsMain >= 4 * kBigPieces,
               "every path's LDS fits");
 
 // Candidates of one app.  WK: the cut of its slices (1: whole ones of 256

@@ -9,7 +9,7 @@
 // call followed by a steering call.  One workgroup of 512 threads per
 // token slot (a 4096-wide bf16 row is one slice per thread, so every load
 // of the pass goes out at once); a row with neither kind of bit returns
-// after reading its mask word.
+// after reading its mask word (EARLY: and asking for its first slices).
 //
 // With r_tvalid given, the kernel also builds the step's routing (in place
 // of a route-build launch): n_apps more workgroups, dispatched first, each
