@@ -1424,7 +1424,7 @@ constexpr int kStagePieces = 1024;  // 16-byte pieces per operand per stage
 constexpr int kPrefillMinT = 1025;  // token slots from which the prefill GEMM runs
 constexpr int kGBlkTok = 8;         // XCD block: token tiles
 constexpr int kGBlkLat = 4;         // XCD block: latent tiles
-constexpr int kSmallTiles = 768;    // most 128-token tiles of a launch
+constexpr int kSmallTiles = 512;    // most 128-token tiles of a launch
 
 // s_waitcnt: at most n vector-memory operations of this wave outstanding
 // and no LDS operation.
@@ -1453,11 +1453,11 @@ sae_xstage_kernel(const uint16_t* __restrict__ h, int32_t d, const int32_t* __re
 // The live count decides the tile: 64 * NB tokens.  256-token tiles feed the
 // matrix cores best, but few of them leave CUs idle; a 128-token tile has half the
 // MFMAs and the same dictionary copies, so it is taken where its rounds of 256 CUs,
-// priced at 0.58 of a round of the large ones, are the cheaper ones (up to 768 of
+// priced at 0.68 of a round of the large ones, are the cheaper ones (up to 512 of
 // them, which the launch has the workgroups for).  A prefill encode of 1318 tokens,
 // 4608 latents: 46.9 -> 37.8 us at d = 768, 103 -> 82 at d = 4096; 250 tokens, 16384
-// latents, d = 2048: 65 -> 48; at three small rounds for two large ones (1030
-// tokens, 16384 latents, d = 4096) the two sides meet, 240 and 237 us.
+// latents, d = 2048: 65 -> 48; three small rounds for two large ones are
+// the slower (921 tokens, 18944 latents, d = 1792: 121 and 110 us).
 __global__ void __launch_bounds__(kGemmThreads, 1)
 sae_gemm_kernel(const uint16_t* __restrict__ xs_g, int32_t d, int32_t n_pad,
                 const int32_t* __restrict__ app_count, const uint16_t* __restrict__ W,
@@ -1819,7 +1819,7 @@ sae_gemm_kernel(const uint16_t* __restrict__ xs_g, int32_t d, int32_t n_pad,
     const int cnt = *app_count;
     const int L = blockIdx.x;
     const int t256 = n_mt * ((cnt + 255) / 256), t128 = n_mt * ((cnt + 127) / 128);
-    if (t128 <= kSmallTiles && (t128 + 255) / 256 * 58 < (t256 + 255) / 256 * 100) {  // uniform
+    if (t128 <= kSmallTiles && (t128 + 255) / 256 * 68 < (t256 + 255) / 256 * 100) {  // uniform
         if (L >= t128) return;
         const int mt = L % n_mt, n0 = L / n_mt * 128;
         gemm_tile(std::integral_constant<int, 2>{}, mt, n0, min(128, cnt - n0));
