@@ -137,6 +137,9 @@ probe_token_kernel(const void* __restrict__ h, int32_t d, int32_t T_max,
     constexpr int EW = BF16 && MAXP == 4 ? 1 : 4;
     auto slice = [&](const int32_t i0, const uint4* fetched) __attribute__((always_inline)) {
         const int32_t count = min(nvec - i0, kProbeThreads);  // slices of this turn
+        // a wave past the row has nothing to add
+        const int32_t i = i0 + static_cast<int32_t>(threadIdx.x);
+        if (static_cast<int32_t>(__builtin_amdgcn_readfirstlane(i)) >= nvec) return;
         // the rows and the weights of the group's probes, all loaded before the
         // first use, so that the slice waits for one memory round trip
         uint4 hv[TT], wv[AP];

@@ -99,6 +99,9 @@ steer_probe_kernel(void* __restrict__ h, int32_t d, int32_t T_max,
     auto slice = [&](const int32_t i0, const uint4* fetched) __attribute__((always_inline)) {
         const int32_t count = min(nvec - i0, kFuseThreads);  // slices of this turn
         const int32_t i = i0 + static_cast<int32_t>(threadIdx.x);
+        // a wave past the row has nothing to add (340 rows of width 512: 6.6 us
+        // with it, 4.9 without)
+        if (static_cast<int32_t>(__builtin_amdgcn_readfirstlane(i)) >= nvec) return;
         // Every load of the slice before its first use, and none behind a
         // branch: the row, the weights of the token's probes and its first
         // four steering vectors, so that the slice waits for one memory round
