@@ -67,9 +67,11 @@ PyObject* fail(const Function* f, const Arg& a, const char* what) {
     return PyErr_Format(PyExc_AssertionError, "%s: %s: %s", f->name->c_str(), a.name.c_str(), what);
 }
 
+// A dim is bound by its first use (-1: not yet) and compared after it; a
+// negative int is no size.
 bool bind(int64_t* dims, int i, int64_t v) {
     if (dims[i] < 0) dims[i] = v;
-    return dims[i] == v;
+    return v >= 0 && dims[i] == v;
 }
 bool dim_ok(int64_t* dims, int64_t want, int64_t v) {
     if (want >= 0) return want == v;

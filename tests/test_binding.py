@@ -25,6 +25,9 @@ def test_ints_dims_and_bits(px):
     assert g(2, (8, 9)) == 2
     with pytest.raises(AssertionError):
         g(3, (8, 9))
+    for n in (-1, -7):  # no size: it must not pass as whatever comes after it
+        with pytest.raises(AssertionError):
+            g(n, (8, 9))
     with pytest.raises(TypeError):
         f("a", [1])
     with pytest.raises(TypeError):
