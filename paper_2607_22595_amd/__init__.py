@@ -143,50 +143,57 @@ EXPORTED = tuple(_sigs)
 def _native(name: str, args: str, c_args: str):
     """The C entry point `name` behind native checks and marshalling: its Python
     arguments and the C arguments made of them, as csrc/call.cpp describes."""
-    return _call.Function(name, ctypes.cast(getattr(_lib, name), _vp).value, args, c_args)
+    return _call.Function(name, ctypes.cast(getattr(_lib, name), _vp).value, args, c_args,
+                          {"Route": XmixRoute, "Ring": XmixRing, "Dict": XmixSaeDict})
 
 
 _STEER = "vecs:A[...,d] sbits:bits(n) alpha:f32[R,n]"
 _PROBE = "w:A[p,d] b:f32 pbits:bits(p) logit:*[p,T] score:*[p,T]"
-_ENCODE = ("h:bf16[T,d] route:struct bit:int W:struct b_enc?:* b_dec?:* fold?:* k:dim "
-           "idx:i32[T,k] val:bf16[T,k] ws:*")
+_SCORE = "w:A[n,d] b:f32 bits:bits(n) mode:int cu?:*"
+_ENCODE = ("h:bf16[T,d] route:struct(Route) bit:int W:struct(Dict) b_enc?:* b_dec?:* fold?:* "
+           "k:dim idx:i32[T,k] val:bf16[T,k] ws:*")
 _ENCODE_C = "h d route bit W b_enc b_dec fold k idx val ws %ws"
+_SCORE_C = "h @A d route w b bits n mode cu R logit score ws %ws stream"
 
 _route_build = _native(
-    "xmix_route_build", "req:i32{T} T_valid:i32 sub:i32 route:rt err:* stream:stream",
+    "xmix_route_build",
+    "req:i32{T} T_valid:i32 sub:i32 route:rt(Route) err:* stream:stream",
     "req T_valid sub #sub route err stream")
 _route_gate = _native(
-    "xmix_route_gate", "route:struct bit:int signal:f32 threshold:f32 signal_bit:int req?:* "
-    "stream:stream", "route bit signal req #signal signal_bit threshold stream")
+    "xmix_route_gate",
+    "route:struct(Route) bit:int signal:f32 threshold:f32 signal_bit:int req?:* stream:stream",
+    "route bit signal req #signal signal_bit threshold stream")
 _route_trigger = _native(
-    "xmix_route_trigger", "route:struct bit:int ids:i32 vocab:* size:int stream:stream",
+    "xmix_route_trigger",
+    "route:struct(Route) bit:int ids:i32 vocab:* size:int stream:stream",
     "route bit ids vocab size stream")
 _steer_apply = _native(
-    "xmix_steer_apply", f"h:A[T,d] route:rt req:* {_STEER} stream:stream",
+    "xmix_steer_apply", f"h:A[T,d] route:rt(Route) req:* {_STEER} stream:stream",
     "h @A d route req vecs sbits alpha n R stream")
 _steer_probe = _native(
-    "xmix_steer_probe", f"h:A[T,d] route:rt req:* {_STEER} {_PROBE} stream:stream",
+    "xmix_steer_probe", f"h:A[T,d] route:rt(Route) req:* {_STEER} {_PROBE} stream:stream",
     "h @A d route req vecs sbits alpha n R w b pbits p logit score stream")
 _route_steer_probe = _native(
-    "xmix_route_steer_probe", f"req:i32{{T}} T_valid:* sub:* route:rt err:* h:A[T,d] {_STEER} "
-    f"{_PROBE} stream:stream",
+    "xmix_route_steer_probe",
+    f"req:i32{{T}} T_valid:* sub:* route:rt(Route) err:* h:A[T,d] {_STEER} {_PROBE} stream:stream",
     "req T_valid sub #sub route err h @A d vecs sbits alpha n w b pbits p logit score stream")
 _router_write = _native(
-    "xmix_router_write", "logits:A[T,E] route:rt bits:bits(n) offsets:f32[n,E] stream:stream",
+    "xmix_router_write",
+    "logits:A[T,E] route:rt(Route) bits:bits(n) offsets:f32[n,E] stream:stream",
     "logits @A E route bits offsets n stream")
 _probe_score_token = _native(
-    "xmix_probe_score", "h:A[T,d] route:struct w:A[n,d] b:f32 bits:bits(n) mode:int cu?:* R:int "
-    "logit:*[n,T] score:* ws?:* stream:stream",
-    "h @A d route w b bits n mode cu R logit score ws %ws stream")
+    "xmix_probe_score",
+    f"h:A[T,d] route:struct(Route) {_SCORE} R:int logit:*[n,T] score:* ws?:* stream:stream",
+    _SCORE_C)
 _probe_score_span = _native(
-    "xmix_probe_score", "h:A[_,d] route:struct w:A[n,d] b:f32 bits:bits(n) mode:int cu?:* R:dim "
-    "logit:*[n,R] score:* ws?:* stream:stream",
-    "h @A d route w b bits n mode cu R logit score ws %ws stream")
+    "xmix_probe_score",
+    f"h:A[_,d] route:struct(Route) {_SCORE} R:dim logit:*[n,R] score:* ws?:* stream:stream",
+    _SCORE_C)
 _encode_topk = _native("xmix_sae_encode_topk", f"{_ENCODE} stream:stream",
                        f"{_ENCODE_C} stream")
 _encode_topk_ring = _native(
     "xmix_sae_encode_topk_ring",
-    f"{_ENCODE} req:i32{{T}} layer:int app:int ring:struct stream:stream",
+    f"{_ENCODE} req:i32{{T}} layer:int app:int ring:struct(Ring) stream:stream",
     f"{_ENCODE_C} req layer app ring stream")
 _graph_launch = _native("xmix_graph_launch", "graph:int stream:stream", "graph stream")
 
@@ -248,10 +255,6 @@ class Route:
         self.struct = XmixRoute(self.tok_mask.data_ptr(), self.app_count.data_ptr(),
                                 self.app_tokens.data_ptr(), self.T_max, self.n_apps)
 
-    @property
-    def _addr(self) -> int:
-        return ctypes.addressof(self.struct)
-
 
 class Ring:
     """Device readback ring: slots [capacity, row_bytes] and head [2] (uint64)."""
@@ -262,10 +265,6 @@ class Ring:
         self.head = torch.zeros(2, dtype=torch.int64, device=device)
         self.struct = XmixRing(self.slots.data_ptr(), self.head.data_ptr(), self.capacity,
                                self.row_bytes)
-
-    @property
-    def _addr(self) -> int:
-        return ctypes.addressof(self.struct)
 
 
 # ------------------------------------------------------------------ entries
@@ -427,10 +426,6 @@ class SaeDict:
 
     def ref(self):
         return ctypes.byref(self.struct)
-
-    @property
-    def _addr(self) -> int:
-        return ctypes.addressof(self.struct)
 
 
 def _dict(W) -> SaeDict:

@@ -12,8 +12,9 @@
 //                     where they stand first, equal elsewhere) or _ (any), after
 //                     "..." the last ones only; {dim}: the element count instead
 //   name?:...         the same, or None (a null pointer)
-//   name:rt           a Route: its T_max is bound to T, its struct is passed
-//   name:struct       an object whose C struct is passed
+//   name:struct(S)    an object whose `struct` is of the ctypes class given for S;
+//                     that struct is passed
+//   name:rt(S)        the same, its T_max bound to T
 //   name:bits(n)      a sequence of ints (at most 32 pass); n is bound to its length
 //   name:int          an int
 //   name:dim          an int that the dim of this name is bound to
@@ -22,6 +23,7 @@
 // #name (the element count of a tensor), %name (its bytes, 0 for None).
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
+#include <structmember.h>
 #include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
 
@@ -33,7 +35,7 @@ namespace {
 
 constexpr int kMaxArgs = 24, kMaxDims = 12, kMaxBits = 32, kMaxBitArgs = 2;
 
-enum Kind { TENSOR, ROUTE, STRUCT, BITS, INT, STREAM };
+enum Kind { TENSOR, STRUCT, BITS, INT, STREAM };
 enum { ANY_TYPE = -1, LETTER = -2 };
 
 struct Arg {
@@ -44,7 +46,8 @@ struct Arg {
     int letter = 0;
     bool tail = false, count = false, shaped = false;
     std::vector<int64_t> dims;  // >= 0: a number; -1: any; <= -2: name -2 - v
-    int bind = -1;              // ROUTE, BITS, INT: the dim that is bound
+    int bind = -1;              // STRUCT, BITS, INT: the dim that is bound (-1: none)
+    PyTypeObject* type = nullptr;  // STRUCT: the class of the struct (a reference)
 };
 struct Out {
     enum What { ARG, DIM, TYPE, COUNT, BYTES } what;
@@ -58,10 +61,20 @@ struct Function {
     std::string* name;
     std::vector<Arg>* args;
     std::vector<Out>* outs;
+    PyObject* spec;  // the texts and classes it was made of
     int n_dims;
 };
 
-PyObject *s_T_max, *s_addr, *s_cuda_stream, *raw_stream, *get_device;
+PyObject *s_T_max, *s_struct, *s_cuda_stream, *raw_stream, *get_device;
+
+// References held for the length of a call.
+struct Held {
+    PyObject* o[kMaxArgs];
+    int n = 0;
+    ~Held() {
+        for (int i = 0; i < n; ++i) Py_DECREF(o[i]);
+    }
+};
 
 PyObject* fail(const Function* f, const Arg& a, const char* what) {
     return PyErr_Format(PyExc_AssertionError, "%s: %s: %s", f->name->c_str(), a.name.c_str(), what);
@@ -99,6 +112,7 @@ PyObject* call(PyObject* self, PyObject* const* argv, size_t nargsf, PyObject* k
     int letters[26];
     int32_t bits[kMaxBitArgs][kMaxBits];
     int n_bits = 0;
+    Held held;
     for (int i = 0; i < f->n_dims; ++i) dims[i] = -1;
     for (int& l : letters) l = -1;
     for (size_t i = 0; i < n; ++i) {
@@ -148,16 +162,23 @@ PyObject* call(PyObject* self, PyObject* const* argv, size_t nargsf, PyObject* k
                 value[i] = reinterpret_cast<uint64_t>(t.mutable_data_ptr());
                 break;
             }
-            case ROUTE: {
+            case STRUCT: {
+                PyObject* st = PyObject_GetAttr(o, s_struct);
+                if (!st) return nullptr;
+                held.o[held.n++] = st;
+                if (!PyObject_TypeCheck(st, a.type))
+                    return PyErr_Format(PyExc_TypeError, "%s: %s: a struct of class %s is needed",
+                                        f->name->c_str(), a.name.c_str(), a.type->tp_name);
+                Py_buffer view;  // a ctypes struct exports its memory, which lives as long as it
+                if (PyObject_GetBuffer(st, &view, PyBUF_SIMPLE) < 0) return nullptr;
+                value[i] = reinterpret_cast<uint64_t>(view.buf);
+                PyBuffer_Release(&view);
                 uint64_t T = 0;
-                if (!attr_u64(o, s_T_max, &T) || !attr_u64(o, s_addr, &value[i])) return nullptr;
-                if (!bind(dims, a.bind, static_cast<int64_t>(T)))
+                if (a.bind >= 0 && !attr_u64(o, s_T_max, &T)) return nullptr;
+                if (a.bind >= 0 && !bind(dims, a.bind, static_cast<int64_t>(T)))
                     return fail(f, a, "made for another number of token slots");
                 break;
             }
-            case STRUCT:
-                if (!attr_u64(o, s_addr, &value[i])) return nullptr;
-                break;
             case BITS: {
                 PyObject* seq = PySequence_Fast(o, "app bits must be a sequence");
                 if (!seq) return nullptr;
@@ -249,6 +270,7 @@ std::vector<std::string> words(const std::string& s, char sep) {
 }
 
 struct Parser {
+    PyObject* structs;  // name -> ctypes class
     std::map<std::string, int> dim_of;
     int dim(const std::string& n) {
         return dim_of.emplace(n, static_cast<int>(dim_of.size())).first->second;
@@ -267,11 +289,14 @@ struct Parser {
             a->name.pop_back();
         }
         std::string t = w.substr(colon + 1);
-        if (t == "rt") {
-            a->kind = ROUTE;
-            a->bind = dim("T");
-        } else if (t == "struct") {
+        const bool rt = t.rfind("rt(", 0) == 0;
+        if ((rt || t.rfind("struct(", 0) == 0) && t.back() == ')') {
+            const size_t open = t.find('(') + 1;
+            PyObject* type = PyDict_GetItemString(structs, t.substr(open, t.size() - open - 1).c_str());
+            if (!type || !PyType_Check(type)) return false;
             a->kind = STRUCT;
+            a->type = reinterpret_cast<PyTypeObject*>(type);
+            if (rt) a->bind = dim("T");
         } else if (t == "int" || t == "dim") {
             a->kind = INT;
             if (t == "dim") a->bind = dim(a->name);
@@ -313,12 +338,15 @@ int init(PyObject* self, PyObject* args, PyObject*) {
     Function* f = reinterpret_cast<Function*>(self);
     const char *name, *in, *out;
     unsigned long long addr;
-    if (!PyArg_ParseTuple(args, "sKss", &name, &addr, &in, &out)) return -1;
+    PyObject* structs;
+    if (!PyArg_ParseTuple(args, "sKssO!", &name, &addr, &in, &out, &PyDict_Type, &structs)) return -1;
+    f->spec = PyTuple_GetSlice(args, 2, 5);
+    if (!f->spec) return -1;
     f->addr = reinterpret_cast<void*>(addr);
     f->name = new std::string(name);
     f->args = new std::vector<Arg>;
     f->outs = new std::vector<Out>;
-    Parser p;
+    Parser p{structs};
     int bit_args = 0;
     for (const std::string& w : words(in, ' ')) {
         Arg a;
@@ -327,6 +355,7 @@ int init(PyObject* self, PyObject* args, PyObject*) {
             return -1;
         }
         bit_args += a.kind == BITS;
+        Py_XINCREF(a.type);
         f->args->push_back(a);
     }
     auto arg_of = [&](const std::string& n) {
@@ -358,12 +387,18 @@ int init(PyObject* self, PyObject* args, PyObject*) {
 
 void dealloc(PyObject* self) {
     Function* f = reinterpret_cast<Function*>(self);
+    if (f->args)
+        for (const Arg& a : *f->args) Py_XDECREF(a.type);
+    Py_XDECREF(f->spec);
     delete f->name;
     delete f->args;
     delete f->outs;
     Py_TYPE(self)->tp_free(self);
 }
 
+PyMemberDef members[] = {
+    {"spec", T_OBJECT_EX, offsetof(Function, spec), READONLY, "(arguments, C arguments, structs)"},
+    {nullptr, 0, 0, 0, nullptr}};
 PyTypeObject function_type = {PyVarObject_HEAD_INIT(nullptr, 0)};
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_call", nullptr, -1, nullptr};
 
@@ -374,6 +409,7 @@ PyMODINIT_FUNC PyInit__call(void) {
     function_type.tp_basicsize = sizeof(Function);
     function_type.tp_flags = Py_TPFLAGS_DEFAULT | Py_TPFLAGS_HAVE_VECTORCALL;
     function_type.tp_vectorcall_offset = offsetof(Function, vectorcall);
+    function_type.tp_members = members;
     function_type.tp_call = PyVectorcall_Call;
     function_type.tp_new = PyType_GenericNew;
     function_type.tp_init = init;
@@ -386,7 +422,7 @@ PyMODINIT_FUNC PyInit__call(void) {
     Py_DECREF(c);
     if (!raw_stream || !get_device) return nullptr;
     s_T_max = PyUnicode_InternFromString("T_max");
-    s_addr = PyUnicode_InternFromString("_addr");
+    s_struct = PyUnicode_InternFromString("struct");
     s_cuda_stream = PyUnicode_InternFromString("cuda_stream");
     PyObject* m = PyModule_Create(&module);
     if (!m) return nullptr;

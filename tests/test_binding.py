@@ -1,5 +1,6 @@
 """The binding's argument marshalling: what it binds, passes and refuses."""
 import ctypes
+import types
 
 import numpy as np
 import pytest
@@ -14,7 +15,7 @@ def px():
 
 def function(px, args, c_args):
     abs_ = ctypes.cast(ctypes.CDLL(None).abs, ctypes.c_void_p).value
-    return px._call.Function("abs", abs_, args, c_args)
+    return px._call.Function("abs", abs_, args, c_args, {"Route": px.XmixRoute})
 
 
 def test_ints_dims_and_bits(px):
@@ -36,7 +37,8 @@ def test_ints_dims_and_bits(px):
         f(1)
 
 
-@pytest.mark.parametrize("args,c_args", [("x:zz", "x"), ("x", "x"), ("x:int", "y"), ("x:i32[", "x")])
+@pytest.mark.parametrize("args,c_args", [("x:zz", "x"), ("x", "x"), ("x:int", "y"), ("x:i32[", "x"),
+                                         ("x:struct(None)", "x"), ("x:rt", "x")])
 def test_bad_specifications_are_refused(px, args, c_args):
     with pytest.raises(ValueError):
         function(px, args, c_args)
@@ -49,6 +51,31 @@ def test_tensors_without_gpu_storage_are_refused(px):
         f(torch.zeros(3))
     with pytest.raises(AssertionError):
         f(np.zeros(3))
+
+
+def test_structs_are_of_their_class(px):
+    """A ring, a dictionary or anything else in a route's place is refused before
+    its memory is taken for a route, and the other way round."""
+    rt, ring = px.Route(8, 2, "cpu"), px.Ring(4, 32, "cpu")
+    t = torch.zeros(8)  # (not on the GPU: what gets past the structs ends there)
+    dic = types.SimpleNamespace(struct=px.XmixSaeDict())
+    for wrong in (ring, dic, types.SimpleNamespace(struct=ctypes.c_int64())):
+        for call in (lambda r: px.xmix_route_gate(r, 0, t, t),
+                     lambda r: px.xmix_route_trigger(r, 0, t, torch.zeros(8), 8),
+                     lambda r: px._call.Function("f", 1, "r:struct(R)", "r", {"R": px.XmixRoute})(r)):
+            with pytest.raises(TypeError):
+                call(wrong)
+    f = function(px, "r:struct(Route) x:int", "x")
+    assert f(rt, 3) == 3 and f(types.SimpleNamespace(struct=rt.struct), 4) == 4
+    with pytest.raises(AttributeError):
+        f(object(), 3)
+    # the address is the struct's own
+    seen = []
+    take = ctypes.CFUNCTYPE(ctypes.c_int, ctypes.POINTER(px.XmixRoute))(
+        lambda p: seen.append((ctypes.addressof(p.contents), p.contents.T_max)) or 0)
+    g = px._call.Function("take", ctypes.cast(take, ctypes.c_void_p).value, "r:rt(Route)", "r",
+                          {"Route": px.XmixRoute})
+    assert g(rt) == 0 and seen == [(ctypes.addressof(rt.struct), 8)]
 
 
 @pytest.mark.gpu
