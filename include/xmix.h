@@ -36,6 +36,8 @@
  *   token is routed to no app.
  * - Rows of unsubscribed tokens or requests are never written in any
  *   output ("don't use, don't pay").
+ * - A kernel may read any row of an input as documented ([T_max, d], [T_max],
+ *   ...), also of a slot that carries no bit: every input has its full extent.
  * - No C++ exception crosses this interface.
  *
  * Calls, in the order of one layer's step: routing (xmix_route_build) and

@@ -168,7 +168,7 @@ _route_trigger = _native(
     "route:struct(Route) bit:int ids:i32 vocab:* size:int stream:stream",
     "route bit ids vocab size stream")
 _steer_apply = _native(
-    "xmix_steer_apply", f"h:A[T,d] route:rt(Route) req:* {_STEER} stream:stream",
+    "xmix_steer_apply", f"h:A[T,d] route:rt(Route) req:*{{_^}} {_STEER} stream:stream",
     "h @A d route req vecs sbits alpha n R stream")
 _steer_probe = _native(
     "xmix_steer_probe", f"h:A[T,d] route:rt(Route) req:* {_STEER} {_PROBE} stream:stream",
@@ -183,11 +183,11 @@ _router_write = _native(
     "logits @A E route bits offsets n stream")
 _probe_score_token = _native(
     "xmix_probe_score",
-    f"h:A[T,d] route:struct(Route) {_SCORE} R:int logit:*[n,T] score:* ws?:* stream:stream",
+    f"h:A[T^,d] route:struct(Route) {_SCORE} R:int logit:*[n,T] score:* ws?:* stream:stream",
     _SCORE_C)
 _probe_score_span = _native(
     "xmix_probe_score",
-    f"h:A[_,d] route:struct(Route) {_SCORE} R:dim logit:*[n,R] score:* ws?:* stream:stream",
+    f"h:A[_^,d] route:struct(Route) {_SCORE} R:dim logit:*[n,R] score:* ws?:* stream:stream",
     _SCORE_C)
 _encode_topk = _native("xmix_sae_encode_topk", f"{_ENCODE} stream:stream",
                        f"{_ENCODE_C} stream")

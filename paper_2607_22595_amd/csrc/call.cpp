@@ -10,7 +10,10 @@
 //                     case letter (any activation type, the same wherever the
 //                     letter stands) or * (any); dims: numbers, names (bound
 //                     where they stand first, equal elsewhere) or _ (any), after
-//                     "..." the last ones only; {dim}: the element count instead
+//                     "..." the last ones only; {dim}: the element count instead;
+//                     dim^: a Route is passed on with at most so many slots, so
+//                     that a kernel which reads all rows of its slots stays inside
+//                     a tensor of fewer rows
 //   name?:...         the same, or None (a null pointer)
 //   name:struct(S)    an object whose `struct` is of the ctypes class given for S;
 //                     that struct is passed
@@ -27,9 +30,13 @@
 #include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
 
+#include <algorithm>
+#include <cstdint>
 #include <map>
 #include <string>
 #include <vector>
+
+#include "../../include/xmix.h"
 
 namespace {
 
@@ -45,6 +52,7 @@ struct Arg {
     int dtype = ANY_TYPE;  // at::ScalarType, ANY_TYPE or LETTER
     int letter = 0;
     bool tail = false, count = false, shaped = false;
+    int cut = -1;               // the dim with a ^
     std::vector<int64_t> dims;  // >= 0: a number; -1: any; <= -2: name -2 - v
     int bind = -1;              // STRUCT, BITS, INT: the dim that is bound (-1: none)
     PyTypeObject* type = nullptr;  // STRUCT: the class of the struct (a reference)
@@ -63,6 +71,7 @@ struct Function {
     std::vector<Out>* outs;
     PyObject* spec;  // the texts and classes it was made of
     int n_dims;
+    int route;  // the Route argument where a tensor may cut it, else -1
 };
 
 PyObject *s_T_max, *s_struct, *s_cuda_stream, *raw_stream, *get_device;
@@ -113,6 +122,8 @@ PyObject* call(PyObject* self, PyObject* const* argv, size_t nargsf, PyObject* k
     int32_t bits[kMaxBitArgs][kMaxBits];
     int n_bits = 0;
     Held held;
+    int64_t slots = INT64_MAX;  // most slots of a Route that is passed on
+    xmix_route route;
     for (int i = 0; i < f->n_dims; ++i) dims[i] = -1;
     for (int& l : letters) l = -1;
     for (size_t i = 0; i < n; ++i) {
@@ -152,12 +163,14 @@ PyObject* call(PyObject* self, PyObject* const* argv, size_t nargsf, PyObject* k
                 bytes[i] = count[i] * static_cast<int64_t>(t.element_size());
                 if (a.count) {
                     if (!dim_ok(dims, a.dims[0], count[i])) return fail(f, a, "wrong size");
+                    if (a.cut == 0) slots = std::min(slots, count[i]);
                 } else if (a.shaped) {
                     const int64_t nd = t.dim(), want = static_cast<int64_t>(a.dims.size());
                     if (a.tail ? nd < want : nd != want) return fail(f, a, "wrong shape");
                     for (int64_t k = 0; k < want; ++k)
                         if (!dim_ok(dims, a.dims[k], t.size(nd - want + k)))
                             return fail(f, a, "wrong shape");
+                    if (a.cut >= 0) slots = std::min(slots, t.size(nd - want + a.cut));
                 }
                 value[i] = reinterpret_cast<uint64_t>(t.mutable_data_ptr());
                 break;
@@ -226,6 +239,13 @@ PyObject* call(PyObject* self, PyObject* const* argv, size_t nargsf, PyObject* k
                 if (PyErr_Occurred()) return nullptr;
                 break;
             }
+        }
+    }
+    if (f->route >= 0) {
+        route = *reinterpret_cast<const xmix_route*>(value[f->route]);
+        if (route.T_max > slots) {
+            route.T_max = static_cast<int32_t>(slots);
+            value[f->route] = reinterpret_cast<uint64_t>(&route);
         }
     }
     uint64_t c[kMaxArgs] = {};
@@ -326,7 +346,14 @@ struct Parser {
                     a->tail = true;
                     in = in.substr(4);
                 }
-                for (const std::string& d : words(in, ',')) a->dims.push_back(dim_word(d));
+                for (std::string d : words(in, ',')) {
+                    if (d.back() == '^') {
+                        a->cut = static_cast<int>(a->dims.size());
+                        d.pop_back();
+                    }
+                    if (d.empty()) return false;
+                    a->dims.push_back(dim_word(d));
+                }
                 if (a->dims.empty()) return false;
             }
         }
@@ -348,6 +375,7 @@ int init(PyObject* self, PyObject* args, PyObject*) {
     f->outs = new std::vector<Out>;
     Parser p{structs};
     int bit_args = 0;
+    bool cut = false;
     for (const std::string& w : words(in, ' ')) {
         Arg a;
         if (!p.arg(w, &a)) {
@@ -356,6 +384,7 @@ int init(PyObject* self, PyObject* args, PyObject*) {
         }
         bit_args += a.kind == BITS;
         Py_XINCREF(a.type);
+        cut = cut || a.cut >= 0;
         f->args->push_back(a);
     }
     auto arg_of = [&](const std::string& n) {
@@ -376,6 +405,11 @@ int init(PyObject* self, PyObject* args, PyObject*) {
         f->outs->push_back(o);
     }
     f->n_dims = static_cast<int>(p.dim_of.size());
+    f->route = cut ? arg_of("route") : -1;
+    if (cut && (f->route < 0 || (*f->args)[f->route].kind != STRUCT)) {
+        PyErr_Format(PyExc_ValueError, "%s: no route to cut", name);
+        return -1;
+    }
     if (f->args->size() > kMaxArgs || f->outs->size() > kMaxArgs || f->n_dims > kMaxDims ||
         bit_args > kMaxBitArgs) {
         PyErr_Format(PyExc_ValueError, "%s: too many arguments", name);

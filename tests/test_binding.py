@@ -78,6 +78,65 @@ def test_structs_are_of_their_class(px):
     assert g(rt) == 0 and seen == [(ctypes.addressof(rt.struct), 8)]
 
 
+def recorded(px, f):
+    """The Function f with its C entry point replaced by one that keeps the route
+    it is given, and the list that it keeps it in."""
+    args, c_args, structs = f.spec
+    at, seen = c_args.split().index("route"), []
+    take = ctypes.CFUNCTYPE(ctypes.c_int, *[ctypes.c_uint64] * 24)(
+        lambda *c: seen.append(px.XmixRoute.from_buffer_copy(
+            ctypes.string_at(c[at], ctypes.sizeof(px.XmixRoute)))) or 0)
+    g = px._call.Function("recorded", ctypes.cast(take, ctypes.c_void_p).value, args, c_args, structs)
+    g_keep.append(take)
+    return g, seen
+
+
+g_keep = []  # the callbacks, which their Functions do not hold
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("rows,slots", [(5, 5), (8, 8), (11, 8)])
+def test_route_is_cut_to_the_rows_there_are(px, rows, slots):
+    """A kernel may read every row and request id of its route's slots, whether or
+    not the token carries a bit: of a tensor with fewer, so many are passed on."""
+    rt, z = px.Route(8, 2), lambda *s: torch.zeros(s, device="cuda")
+    h, w, b = z(rows, 64), z(2, 64), z(2)
+    token, seen = recorded(px, px._probe_score_token)
+    token(h, rt, w, b, [0, 1], px.XMIX_PROBE_TOKEN, None, 0, z(2, rows), z(2, rows), None, None)
+    span, seen_s = recorded(px, px._probe_score_span)
+    span(h, rt, w, b, [0, 1], px.XMIX_PROBE_MEAN, z(4), 3, z(2, 3), z(2, 3), z(64), None)
+    steer, seen_q = recorded(px, px._steer_apply)
+    steer(z(8, 64), rt, z(rows), w, [0, 1], z(4, 2), None)
+    for r in (seen, seen_s, seen_q):
+        assert len(r) == 1 and r[0].T_max == slots and r[0].n_apps == 2
+        assert r[0].tok_mask == rt.tok_mask.data_ptr() and r[0].app_tokens == rt.app_tokens.data_ptr()
+    assert rt.struct.T_max == 8
+
+
+@pytest.mark.gpu
+def test_probes_of_a_tensor_with_the_valid_rows_only(px):
+    """The scores of a batch whose activations end at its last valid token."""
+    T, n, d = 64, 37, 256
+    g = torch.Generator().manual_seed(3)
+    h, w = torch.randn((T, d), generator=g).cuda(), torch.randn((3, d), generator=g).cuda()
+    b, sub = torch.randn(3, generator=g).cuda(), torch.full((4,), 7, dtype=torch.int32, device="cuda")
+    req = torch.repeat_interleave(torch.arange(4, dtype=torch.int32), T // 4).cuda()
+    cu = torch.tensor([0, 16, 30, 37, 37], dtype=torch.int32, device="cuda")
+    rt = px.Route(T, 3)
+    px.xmix_route_build(req, torch.tensor([n], dtype=torch.int32, device="cuda"), sub, rt,
+                        torch.zeros(1, dtype=torch.int32, device="cuda"))
+    for mode, out in ((px.XMIX_PROBE_TOKEN, T), (px.XMIX_PROBE_MEAN, 4), (px.XMIX_PROBE_LAST, 4)):
+        got = []
+        for x in (h, h[:n].clone()):
+            cols = x.shape[0] if mode == px.XMIX_PROBE_TOKEN else out
+            o = [torch.full((3, cols), 9.0, device="cuda") for _ in range(2)]
+            ws = torch.zeros(max(px.probe_workspace(T, 3, mode), 1), dtype=torch.uint8, device="cuda")
+            px.xmix_probe_score(x, rt, w, b, [0, 1, 2], mode, *o, cu_seqlens=cu, ws=ws)
+            got.append([v[:, :min(n, cols)] for v in o])
+        assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
+        assert not torch.any(got[0][0][:, :3] == 9.0)
+
+
 @pytest.mark.gpu
 def test_gpu_tensors_are_checked(px):
     rt = px.Route(8, 2)
