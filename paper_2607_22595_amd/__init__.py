@@ -157,7 +157,7 @@ _SCORE_C = "h @A d route w b bits n mode cu R logit score ws %ws stream"
 
 _route_build = _native(
     "xmix_route_build",
-    "req:i32{T} T_valid:i32 sub:i32 route:rt(Route) err:* stream:stream",
+    "req:i32{T} T_valid:i32 sub:i32 route:rt(Route) err?:* stream:stream",
     "req T_valid sub #sub route err stream")
 _route_gate = _native(
     "xmix_route_gate",
@@ -168,14 +168,14 @@ _route_trigger = _native(
     "route:struct(Route) bit:int ids:i32 vocab:* size:int stream:stream",
     "route bit ids vocab size stream")
 _steer_apply = _native(
-    "xmix_steer_apply", f"h:A[T,d] route:rt(Route) req:*{{_^}} {_STEER} stream:stream",
+    "xmix_steer_apply", f"h:A[T,d] route:rt(Route) req?:*{{_^}} {_STEER} stream:stream",
     "h @A d route req vecs sbits alpha n R stream")
 _steer_probe = _native(
-    "xmix_steer_probe", f"h:A[T,d] route:rt(Route) req:* {_STEER} {_PROBE} stream:stream",
+    "xmix_steer_probe", f"h:A[T,d] route:rt(Route) req?:* {_STEER} {_PROBE} stream:stream",
     "h @A d route req vecs sbits alpha n R w b pbits p logit score stream")
 _route_steer_probe = _native(
     "xmix_route_steer_probe",
-    f"req:i32{{T}} T_valid:* sub:* route:rt(Route) err:* h:A[T,d] {_STEER} {_PROBE} stream:stream",
+    f"req:i32{{T}} T_valid?:* sub:* route:rt(Route) err?:* h:A[T,d] {_STEER} {_PROBE} stream:stream",
     "req T_valid sub #sub route err h @A d vecs sbits alpha n w b pbits p logit score stream")
 _router_write = _native(
     "xmix_router_write",
@@ -183,11 +183,11 @@ _router_write = _native(
     "logits @A E route bits offsets n stream")
 _probe_score_token = _native(
     "xmix_probe_score",
-    f"h:A[T^,d] route:struct(Route) {_SCORE} R:int logit:*[n,T] score:* ws?:* stream:stream",
+    f"h:A[T^,d] route:struct(Route) {_SCORE} R:int logit:*[n,T] score?:* ws?:* stream:stream",
     _SCORE_C)
 _probe_score_span = _native(
     "xmix_probe_score",
-    f"h:A[_^,d] route:struct(Route) {_SCORE} R:dim logit:*[n,R] score:* ws?:* stream:stream",
+    f"h:A[_^,d] route:struct(Route) {_SCORE} R:dim logit:*[n,R] score?:* ws?:* stream:stream",
     _SCORE_C)
 _encode_topk = _native("xmix_sae_encode_topk", f"{_ENCODE} stream:stream",
                        f"{_ENCODE_C} stream")

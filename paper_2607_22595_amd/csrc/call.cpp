@@ -22,6 +22,7 @@
 //   name:int          an int
 //   name:dim          an int that the dim of this name is bound to
 //   name:stream       None (the current stream), a torch stream or a handle
+//                     (anything that int() takes)
 // C arguments: an argument's name, a bound dim, @L (the type code of letter L),
 // #name (the element count of a tensor), %name (its bytes, 0 for None).
 #define PY_SSIZE_T_CLEAN
@@ -232,6 +233,10 @@ PyObject* call(PyObject* self, PyObject* const* argv, size_t nargsf, PyObject* k
                     Py_INCREF(s);
                 } else {
                     s = PyObject_GetAttr(o, s_cuda_stream);
+                    if (!s && PyErr_ExceptionMatches(PyExc_AttributeError)) {
+                        PyErr_Clear();
+                        s = PyNumber_Long(o);
+                    }
                 }
                 if (!s) return nullptr;
                 value[i] = PyLong_AsUnsignedLongLongMask(s);

@@ -53,6 +53,14 @@ def test_tensors_without_gpu_storage_are_refused(px):
         f(np.zeros(3))
 
 
+def test_streams(px):
+    f = function(px, "s:stream", "s")
+    for handle in (7, np.int64(7), np.uint64(7), types.SimpleNamespace(cuda_stream=7)):
+        assert f(handle) == 7
+    with pytest.raises(TypeError):
+        f(object())
+
+
 def test_structs_are_of_their_class(px):
     """A ring, a dictionary or anything else in a route's place is refused before
     its memory is taken for a route, and the other way round."""
