@@ -166,3 +166,93 @@ def test_gpu_tensors_are_checked(px):
         with pytest.raises(err):
             px.xmix_steer_apply(*bad)
     torch.cuda.synchronize()
+
+
+def calls(px):
+    """Every call that is marshalled natively: its arguments, the wrong ones of
+    each (a check fails), and those whose absence the C entry point reports."""
+    T, d, n, p, R, E, k, m, z = 8, 256, 2, 3, 4, 16, 4, 256, dict(device="cuda")
+    bf, i32 = torch.bfloat16, torch.int32
+
+    def t(*shape, dtype=torch.float32):
+        return torch.zeros(shape, dtype=dtype, **z)
+
+    rt, req, sub, tv, err = px.Route(T, 8), t(T, dtype=i32), t(R, dtype=i32), t(1, dtype=i32), t(1, dtype=i32)
+    h, v, w, b, alpha = t(T, d, dtype=bf), t(n, d, dtype=bf), t(p, d, dtype=bf), t(p), t(R, n)
+    lg, W = t(p, T), px.xmix_sae_pack_encoder(t(m, d, dtype=bf))
+    ids, ring = t(T, dtype=i32), px.Ring(16, 16 + 6 * k)
+    ws = torch.zeros(px.sae_encode_workspace(T, d, m, k), dtype=torch.uint8, device="cuda")
+    bad_h = [t(T - 1, d, dtype=bf), t(T, 2 * d, dtype=bf), t(T, d), t(T, 1, d, dtype=bf)]
+    bad_v = [t(n, d), t(n, d // 2, dtype=bf)]
+    bad_alpha = [t(R, n + 1), t(R * n), t(R, n, dtype=bf)]
+    bad_w = [t(p, d), t(p + 1, d, dtype=bf), t(p, d // 2, dtype=bf)]
+    bad_lg = [t(p, T + 1), t(p + 1, T), t(p * T)]
+    steer = dict(vecs=v, app_bits=[0, 1], alpha=alpha)
+    bad_steer = dict(vecs=bad_v, app_bits=[[0], [0, 1, 2]], alpha=bad_alpha)
+    both = dict(vecs=v, steer_bits=[0, 1], alpha=alpha, w=w, b=b, probe_bits=[2, 3, 4], logit_out=lg,
+                score_out=t(p, T))
+    bad_both = dict(vecs=bad_v, steer_bits=[[0]], alpha=bad_alpha, w=bad_w, b=[b.to(bf)],
+                    probe_bits=[[2]], logit_out=bad_lg, score_out=bad_lg)
+    probe = dict(h=h, route=rt, w=w, b=b, app_bits=[2, 3, 4], mode=px.XMIX_PROBE_TOKEN, logit_out=lg,
+                 score_out=t(p, T))
+    bad_probe = dict(h=bad_h[:3], w=bad_w, b=[b.to(bf)], app_bits=[[2]], logit_out=bad_lg)
+    span = dict(probe, mode=px.XMIX_PROBE_LAST, logit_out=t(p, R), score_out=t(p, R),
+                cu_seqlens=t(R + 1, dtype=i32))
+    bad_span = dict(bad_probe, h=[t(T, 2 * d, dtype=bf), t(T, d)], logit_out=[t(p, R + 1), t(p, T)],
+                    cu_seqlens=[t(0, dtype=i32), t(R, dtype=i32)])
+    enc = dict(h=h, route=rt, app_bit=0, W=W, b_enc=t(m, dtype=bf), b_dec=t(d, dtype=bf), c_fold=None,
+               k=k, idx_out=t(T, k, dtype=i32), val_out=t(T, k, dtype=bf), ws=ws)
+    bad_enc = dict(h=bad_h[:1] + bad_h[2:], k=[k + 1, -1], idx_out=[t(T, k), t(T, k + 1, dtype=i32)],
+                   val_out=[t(T, k), t(T + 1, k, dtype=bf)])
+    ring_args = dict(req_of_token=req, layer_id=0, app_id=0, ring=ring)
+    bad_req = [t(T + 1, dtype=i32), t(T)]
+    return {
+        px.xmix_route_build: (dict(req_of_token=req, T_valid=tv, sub_mask=sub, route=rt, err_word=err),
+                              dict(req_of_token=bad_req, T_valid=[t(1)], sub_mask=[t(R)]),
+                              ["err_word"]),
+        px.xmix_route_gate: (dict(route=rt, app_bit=0, signal=t(T), threshold=t(1)),
+                             dict(signal=[t(T, dtype=bf)], threshold=[t(1, dtype=i32)]), []),
+        px.xmix_route_trigger: (dict(route=rt, app_bit=0, token_ids=ids, vocab_bits=t(4, dtype=i32),
+                                     vocab_size=100),
+                                dict(token_ids=[t(T)], vocab_bits=[t(3, dtype=i32)]), []),
+        px.xmix_steer_apply: (dict(h=h, route=rt, req_of_token=req, **steer),
+                              dict(h=bad_h, **bad_steer), ["req_of_token"]),
+        px.xmix_steer_probe: (dict(h=h, route=rt, req_of_token=req, **both),
+                              dict(h=bad_h, **bad_both), ["req_of_token"]),
+        px.xmix_route_steer_probe: (dict(req_of_token=req, T_valid=tv, sub_mask=sub, route=rt,
+                                         err_word=err, h=h, **both),
+                                    dict(req_of_token=bad_req, h=bad_h, **bad_both),
+                                    ["T_valid", "err_word"]),
+        px.xmix_router_write: (dict(logits=t(T, E), route=rt, app_bits=[0, 1], offsets=t(n, E)),
+                               dict(logits=[t(T - 1, E), t(T, E + 1)], app_bits=[[0]],
+                                    offsets=[t(n, E + 1), t(n + 1, E), t(n, E, dtype=bf)]), []),
+        px.xmix_probe_score: (probe, bad_probe, ["score_out"]),
+        (lambda **a: px.xmix_probe_score(**a)): (span, bad_span, ["score_out"]),
+        px.xmix_sae_encode_topk: (enc, bad_enc, []),
+        px.xmix_sae_encode_topk_ring: (dict(enc, **ring_args), dict(bad_enc, req_of_token=bad_req), []),
+    }
+
+
+@pytest.mark.gpu
+def test_every_call_checks_its_arguments(px):
+    for fn, (args, wrong, absent) in calls(px).items():
+        fn(**args)
+        for name, values in wrong.items():
+            for v in values:
+                with pytest.raises((AssertionError, TypeError)):
+                    fn(**dict(args, **{name: v}))
+        for name in absent:
+            with pytest.raises(px.XmixError):
+                fn(**dict(args, **{name: None}))
+        for name, v in args.items():
+            if isinstance(v, torch.Tensor):
+                with pytest.raises(ValueError):
+                    fn(**dict(args, **{name: v.cpu()}))
+                if v.dim() == 2 and v.shape[0] > 1:
+                    with pytest.raises(ValueError):
+                        fn(**dict(args, **{name: v.t().contiguous().t()}))
+            elif isinstance(v, (px.Route, px.Ring, px.SaeDict)):
+                other = px.Ring(4, 32) if not isinstance(v, px.Ring) else px.Route(8, 8)
+                with pytest.raises(TypeError):
+                    fn(**dict(args, **{name: other}))
+    torch.cuda.synchronize()
