@@ -57,6 +57,7 @@
 #include <type_traits>
 
 #include "common.hpp"
+#include "emit_plan.hpp"
 #include "kernels.hpp"
 #include "launch.hpp"
 #include "route_list.hpp"
@@ -72,7 +73,6 @@ constexpr int kBK = 64;   // K chunk
 constexpr int kEncWaves = 8;
 constexpr int kEncThreads = kEncWaves * kWave;
 constexpr int kRefineIters = 24;
-constexpr int kMaxCap = 64;  // most candidate pairs one slice may emit
 // Values beyond mean +- kTrimZ * stdev of a tile's 256 pre-activations are
 // left out of the statistics behind the decode kernel's first threshold
 // guess (one strong latent, or one of a large norm on either side, would
@@ -2718,73 +2718,6 @@ static bool big_possible(int32_t T_max, int32_t d) {
 static int32_t enc_units(int32_t T_max, int32_t d, int32_t n_mt, int32_t n_sl) {
     const int32_t big = big_possible(T_max, d) && n_sl <= 2 * n_mt ? n_mt * ((T_max + kBigTok - 1) / kBigTok) : 0;
     return n_sl > big ? n_sl : big;
-}
-
-// Candidate emission parameters for a dictionary of m latents in tiles of
-// `width`, and top-k: the per-tile capacity, the lower count bound, and the standard normal
-// quantile of the first threshold guess.
-struct EmitPlan {
-    int cap, lo;
-    float z;
-};
-
-// Pairs one tile may emit: four times a target of twice the tile's share of
-// the k winners, plus one.
-static int emit_cap(int32_t m, int32_t k, int32_t width) {
-    const int t = (2 * k * width + m - 1) / m + 1;
-    const int cap = 4 * (t < 2 ? 2 : t);
-    return cap < kMaxCap ? cap : kMaxCap;
-}
-
-// 0.5 * erfc(z / sqrt 2): the share of a standard normal above z
-static double upper_tail(double z) { return 0.5 * erfc(z / sqrt(2.0)); }
-
-// z with f(z) = want for an f that falls with z, by bisection
-template <typename F>
-static double falling_root(F f, double want) {
-    double a = -8.0, b = 8.0;
-    for (int i = 0; i < 40; ++i) {
-        const double mid = 0.5 * (a + b);
-        if (f(mid) > want) a = mid;
-        else b = mid;
-    }
-    return 0.5 * (a + b);
-}
-
-// The guess mean + z * stdev comes from the tile's own values, so of 256 of
-// them it is off by about sqrt(1/256 + z^2/512) stdev.  A tile whose guess ends up
-// above the token's k-th value hides a winner and sends the token to the
-// repair (50 us of one workgroup), so the guess is aimed five such errors
-// below the k-th value's quantile, and at two values a tile or more.  A
-// lower bound on the count is set only where the tiles together might not
-// supply k values (their total within six Poisson deviations of k): every
-// tile would search for it.  Measured: 391 tokens, m = 32768, k = 64
-// (repairs in most launches with the former aim of 2 a tile) merge 62 -> 9
-// us; 1777 tokens of width 2304, m = 16384, k = 64 (where the former rule
-// asked every tile for exactly 12 values) prefill GEMM 240 -> 146 us.
-static EmitPlan emit_plan(int32_t m, int32_t k, int32_t width) {
-    const int n = m / width;
-    EmitPlan e;
-    e.cap = emit_cap(m, k, width);
-    const double share = static_cast<double>(k) / n;  // of the winners, per tile
-    double target = 2.0;
-    if (share < 0.45 * width) {
-        const double zk = falling_root(upper_tail, share / width);
-        const double z = falling_root(
-            [width](double q) { return -(q + 5.0 * sqrt((1.0 + 0.5 * q * q) / width)); }, -zk);
-        target = width * upper_tail(z);
-        // room for the counts' own spread below the capacity
-        const double most = e.cap < kMaxCap ? e.cap - 1.8 * sqrt(e.cap) : 45.0;
-        target = target < most ? target : most;
-        target = target < 2.0 ? 2.0 : target;
-    } else {
-        target = 45.0;
-    }
-    const double total = n * target;
-    e.lo = total - k >= 6.0 * sqrt(total) ? 0 : (k < e.cap ? k : e.cap);
-    const double want = e.lo ? 0.5 * (e.lo + e.cap) : target;
-    e.z = static_cast<float>(falling_root(upper_tail, want / width));
-    return e;
 }
 
 struct CandArea {
