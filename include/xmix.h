@@ -309,6 +309,9 @@ xmix_status xmix_probe_score(const void *h, xmix_dtype dt, int32_t d, const xmix
  *   the k largest pre_j (equal values: lower j first), ordered by pre
  *   descending;  idx_out[t][q] = j,  val_out[t][q] = bf16(max(pre_j, 0)).
  * Rows t of idx_out/val_out ([T_max, k]) are written only for subscribed t.
+ * A row's bits depend on the token's row of h, the dictionary, the biases and k
+ * alone: every kernel behind these calls sums pre_j in one order, whatever the
+ * batch, T_max or the other apps of a call are.
  * h [T_max, d] bf16; b_enc [m], b_dec [d] bf16.
  * dict: the encoder dictionary (m latents of width d) as packed once per app
  * by xmix_sae_pack_encoder; dict->d must equal d.

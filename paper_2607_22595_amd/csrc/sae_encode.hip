@@ -1,8 +1,9 @@
 // SAE encode with TopK: pre = W_enc . h + c_fold for the tokens subscribed
 // to one app, then the k largest pre-activations per token.
 //
-// Stage 1 (sae_stream_kernel) is an MFMA bf16 GEMM with fp32 accumulation.
-// A workgroup (8 waves, two per SIMD so one wave's waits overlap the other's
+// Stage 1 (sae_stream_kernel) is an MFMA bf16 GEMM with fp32 accumulation, in
+// three kinds of tiles by the live tokens and the size of the dictionary
+// (tile_kind).  In the basic one a workgroup (8 waves, two per SIMD so one wave's waits overlap the other's
 // MFMAs) owns 256 latents x 128 subscribed tokens and walks K = d in chunks
 // of 64:
 //   - the dictionary (operand A) streams from HBM straight into registers
@@ -36,8 +37,11 @@
 // because a latent that was not emitted lies below its tile's bound.  When
 // that certificate fails (only for inputs whose best latents crowd into a
 // few tiles or tie across whole tiles), the workgroup recomputes tiles'
-// 256 pre-activations with plain fp32 dot products, in descending order of
-// their bounds, until no tile left can hold a winner.  The
+// 256 pre-activations, in descending order of
+// their bounds, until no tile left can hold a winner.  Every path, the recompute
+// among them, sums a pre-activation with the same instruction in the same order, so
+// a token's result depends on its row and the dictionary alone: not on the batch
+// it is in, the tiles that are chosen or the other apps of the launch.  The
 // decode kernel's first threshold guess leaves a tile's outlying values
 // out of the statistics (beyond mean +- 5 stdev), so that a few strong
 // latents, such as features clamped high by a steering app, or rows of a
@@ -46,9 +50,9 @@
 // prefill kernel keeps the plain statistics (a GEMM epilogue
 // pays for every extra pass, and the repair covers the rare failure).
 //
-// The workgroup-to-tile map is XCD-aware: launch slots are dealt round-robin
-// to the 8 XCDs, so consecutive tiles of one XCD share a dictionary slice in
-// that XCD's L2.
+// The workgroup-to-tile maps are XCD-aware (unit_tile, sae_gemm_kernel): launch
+// slots are dealt round-robin to the 8 XCDs, so consecutive tiles of one XCD share
+// a dictionary slice in that XCD's L2.
 #include <math.h>
 #include <stddef.h>
 #include <string.h>
@@ -78,18 +82,6 @@ constexpr int kRefineIters = 24;
 // guess (one strong latent, or one of a large norm on either side, would
 // otherwise raise the guess for its whole tile).
 constexpr float kTrimZ = 5.0f;
-
-// v[r] for a lane-varying r in [0, 16), by a select tree on the bits of r
-// (registers cannot be indexed per lane)
-__device__ __forceinline__ float pick16(const f32x16_t& v, int r) {
-    const bool b0 = r & 1, b1 = r & 2, b2 = r & 4, b3 = r & 8;
-    const float a0 = b0 ? v[1] : v[0], a1 = b0 ? v[3] : v[2], a2 = b0 ? v[5] : v[4],
-                a3 = b0 ? v[7] : v[6], a4 = b0 ? v[9] : v[8], a5 = b0 ? v[11] : v[10],
-                a6 = b0 ? v[13] : v[12], a7 = b0 ? v[15] : v[14];
-    const float c0 = b1 ? a1 : a0, c1 = b1 ? a3 : a2, c2 = b1 ? a5 : a4, c3 = b1 ? a7 : a6;
-    const float d0 = b2 ? c1 : c0, d1 = b2 ? c3 : c2;
-    return b3 ? d1 : d0;
-}
 
 // mean + z * stdev of n values with sum s1 and sum of squares s2
 __device__ __forceinline__ float trimmed_guess(float s1, float s2, int n, float z) {
@@ -218,28 +210,19 @@ __device__ __forceinline__ int excl_scan_g(int v, int q) {
     return incl - v;
 }
 
-// The value at v of a tile kept as NP partial sums `pstride` floats apart (the
-// K shares of a narrow slice's waves), added in a fixed order.
-template <int NP>
-__device__ __forceinline__ float tile_value(const float* v, int pstride) {
-    if constexpr (NP == 1) return v[0];
-    else if constexpr (NP == 2) return v[0] + v[pstride];
-    else return (v[0] + v[pstride]) + (v[2 * pstride] + v[3 * pstride]);
-}
-
 // The selection of NT tokens over one slice each: per token a threshold tau
 // with lo_cnt <= count(pre >= tau) <= cap (first guess mean + z * stdev of
 // the slice's values, then bisection on the value), and every latent with
 // pre >= tau written to dst[t][0 .. count) as (fp32 bits, latent), with the
 // count and the slice's bound beside it.  vrow[t]: this lane's VPL values of
-// token t in LDS (NP partial sums each); q: the lane's place in its group;
+// token t in LDS; q: the lane's place in its group;
 // lat0: its first latent.  Every lane of the wave calls it (the cross-lane
 // steps are wave-wide); the lanes of a token with valid[t] == false take part
 // in them and write nothing.  With TRIM, the values beyond mean +- 5 stdev
 // are left out of the statistics behind the first guess (a few outlying
 // latents would otherwise lift it for the whole slice).
-template <bool TRIM, int NT, int VPL, int LPS, int NP>
-__device__ __forceinline__ void select_slices(const float* const (&vrow)[NT], int pstride, int q,
+template <bool TRIM, int NT, int VPL, int LPS>
+__device__ __forceinline__ void select_slices(const float* const (&vrow)[NT], int q,
                                               const bool (&valid)[NT], float z, int lo_cnt,
                                               int cap, int32_t lat0, uint2* const (&dst)[NT],
                                               int32_t* const (&cnt_out)[NT],
@@ -250,19 +233,11 @@ __device__ __forceinline__ void select_slices(const float* const (&vrow)[NT], in
     for (int t = 0; t < NT; ++t) {
 #pragma unroll
         for (int i = 0; i < VPL / 4; ++i) {
-            float4 v[NP];
-#pragma unroll
-            for (int p = 0; p < NP; ++p)
-                v[p] = reinterpret_cast<const float4*>(vrow[t] + p * pstride)[i];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                auto part = [&](int p) __attribute__((always_inline)) {
-                    return e == 0 ? v[p].x : e == 1 ? v[p].y : e == 2 ? v[p].z : v[p].w;
-                };
-                if constexpr (NP == 1) x[t][4 * i + e] = part(0);
-                else if constexpr (NP == 2) x[t][4 * i + e] = part(0) + part(1);
-                else x[t][4 * i + e] = (part(0) + part(1)) + (part(2) + part(3));
-            }
+            const float4 v = reinterpret_cast<const float4*>(vrow[t])[i];
+            x[t][4 * i] = v.x;
+            x[t][4 * i + 1] = v.y;
+            x[t][4 * i + 2] = v.z;
+            x[t][4 * i + 3] = v.w;
         }
     }
     // ax[t]: the largest magnitude among the token's values
@@ -375,7 +350,7 @@ __device__ __forceinline__ void select_slices(const float* const (&vrow)[NT], in
     // out of rounds: the final thresholds were set after the last masks
     if (!settled) masks();
     // emission: this lane's selected latents go to the slots after those of
-    // the lanes before it in the token's group of 8; nk[t]: the largest of
+    // the lanes before it in the token's group; nk[t]: the largest of
     // the token's values that are not kept (NaN never counts: it compares
     // below everything)
     int base[NT], total[NT];
@@ -399,7 +374,7 @@ __device__ __forceinline__ void select_slices(const float* const (&vrow)[NT], in
             const int i = __builtin_ctz(b);
             b &= b - 1;
             if (slot < cap)
-                dst[t][slot] = make_uint2(__float_as_uint(tile_value<NP>(vrow[t] + i, pstride)),
+                dst[t][slot] = make_uint2(__float_as_uint(vrow[t][i]),
                                           static_cast<uint32_t>(lat0 + i));
             ++slot;
         }
@@ -428,7 +403,7 @@ __device__ __forceinline__ SliceSrc slice_src(const uint16_t* W, int32_t n_mt, i
 // operand A of one K chunk at p: this wave's 32 latents of the packed
 // slice.  The dictionary is read once per launch: nontemporal loads stream
 // it past the caches (about 4 % faster than cached loads at 65536 x 4096).
-__device__ __forceinline__ void load_chunk(uint4 (&a)[4], const uint4* p) {
+__device__ __forceinline__ void load_chunk(uint4* a, const uint4* p) {
     const uint32_t off = threadIdx.x & 511;  // wave * 256 + lane: pieces 4 x 64 apart
     const u32x4_t* q = reinterpret_cast<const u32x4_t*>(p) + ((off >> 6) * 256 + (off & 63));
 #pragma unroll
@@ -471,28 +446,40 @@ __device__ __forceinline__ uint4 buffer_load16(__amdgpu_buffer_rsrc_t r, uint32_
 }
 constexpr int kNontemporal = 2;  // cache policy bit of the buffer loads
 
-// The GEMM and candidate emission of latent slice mt over the token tiles of
-// the app's list tl[0, cnt) in turn, cnt > 0.  On entry wa0..wa2 hold
-// the slice's K chunks 0-2 and cfv its folded bias when `issued`.  The K
+// A workgroup's LDS: K loop: token chunks, windows or stages; epilogue: the
+// selection rows.  16-byte pieces.
+constexpr int kLdsMain = kBN * kSelStride / 4;
+
+// The registers of a workgroup's dictionary stream: what is in flight of one tile
+// and, past its last chunk, of the next.
+constexpr int kRing = 16;
+
+// What slice_tile finds loaded of its slice.
+__device__ __forceinline__ void slice_first(uint4 (&ring)[kRing], float (&cfv)[16],
+                                            const SliceSrc src, const float* c_fold, int mt) {
+#pragma unroll
+    for (int c = 0; c < 3; ++c) load_chunk(ring + 4 * c, src.base + c * src.stride);
+    load_bias(cfv, c_fold, mt);
+}
+
+// The GEMM and candidate emission of latent slice mt over one tile of tokens:
+// tl[n0, n0 + ntok) of the app's list, ntok <= kBN.  On entry the ring holds
+// the slice's K chunks 0-2 and cfv its folded bias (slice_first).  The K
 // loop fetches three chunks ahead; past the slice's last chunk it fetches
-// the first chunks of what runs next: the same slice again for the next
-// token tile, else slice `nxt` when has_nxt (then also its bias from
-// nxt_bias_of(), after this tile's selection), else nothing new (the last chunk
-// again, unused).  Returns has_nxt: whether wa0..wa2 and cfv now hold nxt's
-// first chunks and bias.  lds_main is the workgroup's token-chunk and
+// the first chunks of what runs next, slice `nxt` when has_nxt (then also its bias
+// from nxt_bias_of(), after this tile's selection), else nothing new (the last
+// chunk again, unused; no load where has_nxt is false at compile time).  lds_main is the workgroup's token-chunk and
 // selection space; sink_of() is asked for after the K loop, whose scalar
-// registers are few.  ONE: cnt <= kBN, a single tile (its bias then need not
-// outlive the accumulators' start, which leaves the K loop its registers).
-template <bool ONE, typename SinkOf, typename BiasOf>
-__device__ __forceinline__ bool slice_tiles(
-    uint4* lds_main, const uint16_t* __restrict__ h, int32_t d, const int32_t* tl, int cnt,
-    int mt, const SliceSrc cur, SinkOf sink_of, bool issued,
-    const SliceSrc nxt, bool has_nxt, int nxt_mt, BiasOf nxt_bias_of,
-    const float* __restrict__ c_fold, uint4 (&wa0)[4], uint4 (&wa1)[4], uint4 (&wa2)[4],
-    uint4 (&wa3)[4], float (&cfv)[16]) {
+// registers are few.  The candidates are emitted in WK slices of 256 / WK latents.
+template <int WK, typename SinkOf, typename BiasOf>
+__device__ __forceinline__ void slice_tile(
+    uint4* lds_main, const uint16_t* __restrict__ h, int32_t d, const int32_t* tl, int n0,
+    int ntok, int mt, const SliceSrc cur, SinkOf sink_of, const SliceSrc nxt, bool has_nxt,
+    int nxt_mt, BiasOf nxt_bias_of, uint4 (&ring)[kRing], float (&cfv)[16]) {
+    uint4 *wa0 = ring, *wa1 = ring + 4, *wa2 = ring + 8, *wa3 = ring + 12;
     uint4 (*xs)[kBN * 8] = reinterpret_cast<uint4 (*)[kBN * 8]>(lds_main);
     int tid = threadIdx.x;  // opaque (see big_tile)
-    if (ONE) asm volatile("" : "+v"(tid));
+    asm volatile("" : "+v"(tid));
     const int lane = tid & 63, wave = tid >> 6;
     const int g = lane >> 5, j32 = lane & 31;
     const int nK = d / kBK;  // a multiple of 4 (d % 256 == 0)
@@ -518,7 +505,7 @@ __device__ __forceinline__ bool slice_tiles(
             xs[buf][n * 8 + (xc ^ ((n >> 1) & 7))] = v;
         }
     };
-    auto compute = [&](const uint4 (&a)[4], int buf) {
+    auto compute = [&](const uint4* a, int buf) __attribute__((always_inline)) {
 #pragma unroll
         for (int s = 0; s < 4; ++s) {
             const bf16x8_t A = as_bf16x8(a[s]);
@@ -540,8 +527,8 @@ __device__ __forceinline__ bool slice_tiles(
     // the next token chunk to the other LDS buffer.  Loads are issued
     // oldest-needed first, so the in-order vmcnt wait for the next token
     // chunk never waits on a W prefetch.
-    auto step = [&](int kc, const uint4 (&cur_w)[4], uint4 (&wnext)[4], const uint4* wp,
-                    uint4 (&xload)[2], const uint4 (&xstore)[2]) {
+    auto step = [&](int kc, const uint4* cur_w, uint4* wnext, const uint4* wp, uint4 (&xload)[2],
+                    const uint4 (&xstore)[2]) __attribute__((always_inline)) {
         load_x(xload, kc + 2);
         __builtin_amdgcn_sched_barrier(0);  // keep the token loads ahead of the W loads
         load_chunk(wnext, wp);
@@ -551,260 +538,283 @@ __device__ __forceinline__ bool slice_tiles(
         __builtin_amdgcn_sched_barrier(0);
     };
 
-    if (!issued) load_bias(cfv, c_fold, mt);  // the slice's bias serves every token tile
-    for (int n0 = 0;; n0 += kBN) {
-        const int ntok = min(kBN, cnt - n0);
-        const bool last = ONE || n0 + kBN >= cnt;
-        // the stream past this slice's last chunk: the next token tile's
-        // first chunks, nxt's, or the last chunk again (unused)
-        const uint4* after = !last ? cur.base : has_nxt ? nxt.base : cur.base + (nK - 1) * cur.stride;
-        const int64_t after_stride = !last ? cur.stride : has_nxt ? nxt.stride : 0;
+    const uint4* after = has_nxt ? nxt.base : cur.base + (nK - 1) * cur.stride;
+    const int64_t after_stride = has_nxt ? nxt.stride : 0;
 #pragma unroll
-        for (int p = 0; p < 2; ++p) {
-            const int n = xr + 64 * p;
-            const bool ok = n < ntok;
-            xmask[p] = ok ? 0xFFFFFFFFu : 0u;
-            xrow[p] = h + static_cast<int64_t>(tl[n0 + (ok ? n : 0)]) * d + 8 * xc;
-        }
-        // the accumulators start from the folded bias
-#pragma unroll
-        for (int b = 0; b < 4; ++b)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[b][r] = cfv[r];
-
-        load_x(xv0, 0);
-        load_x(xv1, 1);
-        if (!issued) {
-            load_chunk(wa0, cur.base);
-            load_chunk(wa1, cur.base + cur.stride);
-            load_chunk(wa2, cur.base + 2 * cur.stride);
-        }
-        store_x(xv0, 0);
-        // four chunks per round (the W registers rotate); the last round
-        // fetches what follows the slice
-        auto round4 = [&](int kc, const uint4* p0, const uint4* p1, const uint4* p2,
-                          const uint4* p3) {
-            step(kc + 0, wa0, wa3, p0, xv0, xv1);
-            step(kc + 1, wa1, wa0, p1, xv1, xv0);
-            step(kc + 2, wa2, wa1, p2, xv0, xv1);
-            step(kc + 3, wa3, wa2, p3, xv1, xv0);
-        };
-        const uint4* wp = cur.base + 3 * cur.stride;
-        const int64_t ws = cur.stride;
-        if (nK > 4) {
-            // The first round runs apart from the loop: its loads follow the
-            // prologue's (whose W chunks may have been issued long before),
-            // while every round of the loop follows a round.  So the loop's
-            // waits count only a round's loads, and a step waits for its
-            // token chunk without waiting for the W chunk issued a step ago.
-            round4(0, wp, wp + ws, wp + 2 * ws, wp + 3 * ws);
-            wp += 4 * ws;
-            for (int kc = 4; kc < nK - 4; kc += 4) {
-                round4(kc, wp, wp + ws, wp + 2 * ws, wp + 3 * ws);
-                wp += 4 * ws;
-            }
-        }
-        round4(nK - 4, wp, after, after + after_stride, after + 2 * after_stride);
-        // wa0..wa2 now hold the first three chunks of what runs next
-        issued = !last || has_nxt;
-
-        // ------------------------------------------------------ epilogue
-        // acc[nb][r] holds latent 32*wave + 8*(r/4) + 4*g + r%4 of token
-        // 32*nb + j32 (the 32x32 MFMA output layout).  Every lane writes its
-        // values to the tile's 128 token rows in LDS; then wave w selects for
-        // rows 16w .. 16w + 15, eight lanes per row, two rows per lane.
-        __syncthreads();  // every wave is done with the token chunks
-        float* V = reinterpret_cast<float*>(lds_main);
-#pragma unroll
-        for (int nb = 0; nb < 4; ++nb) {
-            float* rowp = V + (32 * nb + j32) * kSelStride + 32 * wave + 4 * g;
-#pragma unroll
-            for (int j = 0; j < 4; ++j)
-                *reinterpret_cast<float4*>(rowp + 8 * j) =
-                    make_float4(acc[nb][4 * j], acc[nb][4 * j + 1], acc[nb][4 * j + 2],
-                                acc[nb][4 * j + 3]);
-        }
-        __syncthreads();
-        const SliceSink sink = sink_of();
-        const int q = lane & 7;
-        const int r0 = 16 * wave + (lane >> 3), r1 = r0 + 8;
-        const int64_t row0 = static_cast<int64_t>(n0 + r0) * sink.n_sl + mt;
-        const int64_t row1 = static_cast<int64_t>(n0 + r1) * sink.n_sl + mt;
-        const float* const vr[2] = {V + r0 * kSelStride + 32 * q, V + r1 * kSelStride + 32 * q};
-        const bool ok[2] = {r0 < ntok, r1 < ntok};
-        uint2* const dst[2] = {sink.cand + row0 * sink.cap, sink.cand + row1 * sink.cap};
-        int32_t* const co[2] = {sink.tile_cnt + row0, sink.tile_cnt + row1};
-        float* const to[2] = {sink.tile_tau + row0, sink.tile_tau + row1};
-        select_slices<true, 2, 32, 8, 1>(vr, 0, q, ok, sink.z, sink.lo_cnt, sink.cap,
-                                         mt * kBM + 32 * q, dst, co, to);
-        if (last) {
-            if (has_nxt) load_bias(cfv, nxt_bias_of(), nxt_mt);
-            return has_nxt;
-        }
-        __syncthreads();  // the tile rows are read before the next tile's token chunks land
+    for (int p = 0; p < 2; ++p) {
+        const int n = xr + 64 * p;
+        const bool ok = n < ntok;
+        xmask[p] = ok ? 0xFFFFFFFFu : 0u;
+        xrow[p] = h + static_cast<int64_t>(tl[n0 + (ok ? n : 0)]) * d + 8 * xc;
     }
+    // the accumulators start from the folded bias
+#pragma unroll
+    for (int b = 0; b < 4; ++b)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[b][r] = cfv[r];
+
+    load_x(xv0, 0);
+    load_x(xv1, 1);
+    store_x(xv0, 0);
+    // four chunks per round (the W registers rotate); the last round
+    // fetches what follows the slice
+    auto round4 = [&](int kc, const uint4* p0, const uint4* p1, const uint4* p2,
+                      const uint4* p3) {
+        step(kc + 0, wa0, wa3, p0, xv0, xv1);
+        step(kc + 1, wa1, wa0, p1, xv1, xv0);
+        step(kc + 2, wa2, wa1, p2, xv0, xv1);
+        step(kc + 3, wa3, wa2, p3, xv1, xv0);
+    };
+    const uint4* wp = cur.base + 3 * cur.stride;
+    const int64_t ws = cur.stride;
+    if (nK > 4) {
+        // The first round runs apart from the loop: its loads follow the
+        // prologue's (whose W chunks may have been issued long before),
+        // while every round of the loop follows a round.  So the loop's
+        // waits count only a round's loads, and a step waits for its
+        // token chunk without waiting for the W chunk issued a step ago.
+        round4(0, wp, wp + ws, wp + 2 * ws, wp + 3 * ws);
+        wp += 4 * ws;
+        for (int kc = 4; kc < nK - 4; kc += 4) {
+            round4(kc, wp, wp + ws, wp + 2 * ws, wp + 3 * ws);
+            wp += 4 * ws;
+        }
+    }
+    round4(nK - 4, wp, after, after + after_stride, after + 2 * after_stride);
+    // wa0..wa2 now hold the first three chunks of what runs next
+
+    // ------------------------------------------------------ epilogue
+    // acc[nb][r] holds latent 32*wave + 8*(r/4) + 4*g + r%4 of token
+    // 32*nb + j32 (the 32x32 MFMA output layout).  Every lane writes its
+    // values to the tile's 128 token rows in LDS; then wave w selects for
+    // rows 16w .. 16w + 15, eight lanes per row, two rows per lane.
+    __syncthreads();  // every wave is done with the token chunks
+    float* V = reinterpret_cast<float*>(lds_main);
+#pragma unroll
+    for (int nb = 0; nb < 4; ++nb) {
+        float* rowp = V + (32 * nb + j32) * kSelStride + 32 * wave + 4 * g;
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            *reinterpret_cast<float4*>(rowp + 8 * j) =
+                make_float4(acc[nb][4 * j], acc[nb][4 * j + 1], acc[nb][4 * j + 2],
+                            acc[nb][4 * j + 3]);
+    }
+    __syncthreads();
+    const SliceSink sink = sink_of();
+    constexpr int LPS = 8 / WK;  // lanes per slice
+    const int q = lane & 7;
+    const int sl = mt * WK + q / LPS;
+    const int r0 = 16 * wave + (lane >> 3), r1 = r0 + 8;
+    const int64_t row0 = static_cast<int64_t>(n0 + r0) * sink.n_sl + sl;
+    const int64_t row1 = static_cast<int64_t>(n0 + r1) * sink.n_sl + sl;
+    const float* const vr[2] = {V + r0 * kSelStride + 32 * q, V + r1 * kSelStride + 32 * q};
+    const bool ok[2] = {r0 < ntok, r1 < ntok};
+    uint2* const dst[2] = {sink.cand + row0 * sink.cap, sink.cand + row1 * sink.cap};
+    int32_t* const co[2] = {sink.tile_cnt + row0, sink.tile_cnt + row1};
+    float* const to[2] = {sink.tile_tau + row0, sink.tile_tau + row1};
+    select_slices<true, 2, 32, LPS>(vr, q % LPS, ok, sink.z, sink.lo_cnt, sink.cap,
+                                    mt * kBM + 32 * q, dst, co, to);
+    if (has_nxt) load_bias(cfv, nxt_bias_of(), nxt_mt);
+    __syncthreads();  // the rows are read before what runs next
 }
 
 // ------------------------------------------------------------ narrow slices
 // A dictionary of few 256-latent slices leaves CUs idle when every slice is
-// one workgroup, so it is cut finer: a workgroup owns 256 / WK latents and
-// its waves share the K loop WK ways (wave = WL * share + latent group, WL =
-// 8 / WK), every wave still streaming whole 4 KB dictionary chunks straight
-// into registers, three in flight.  A window of WK K chunks of the token rows
-// is shared through LDS (double buffered, staged in registers two windows
-// ahead, so that the in-order wait for a window leaves the dictionary chunks
-// issued after it in flight).  The tile's token rows are 32 * NB: 32, 64 or 128
-// by the tokens left, since a batch of a few requests is the usual one here.
-// The WK partial sums of a value are added when the selection reads them.
-// Measured against one workgroup per 256 latents: 9 tokens of width 2304, m =
-// 16384 (64 workgroups then, 256 now) 33.8 -> 16.7 us.
+// one workgroup, so it is cut finer: a workgroup owns 256 / WK latents.  A K chunk
+// of the slice (8 KB for 64 latents, contiguous in the packed layout) and of the
+// token rows is shared through LDS, and the chunks after it are in flight in
+// registers: the loads of a chunk go out together, so that the in-order wait for
+// one leaves the others behind it.  Three LDS buffers: a wave reads the operands of
+// the next chunk, step by step, as it multiplies this one's, so that a step is a
+// barrier and its chain of MFMAs.  The tile's token rows are 32 * NB: 32, 64 or 128
+// by the tokens left, since a batch of a few requests is the usual one here; a wave
+// multiplies 32 latents by one or two groups of 32 tokens over the whole of K, and
+// waves without such a block only copy.  Every value is summed in the order of K, as
+// in the whole and the big tiles, so that a token's candidates do not depend on the
+// path.
+// Measured against one workgroup per 256 latents, per launch: 9 tokens of width
+// 2304, m = 16384 (64 workgroups then, 256 now) 33.8 -> 15.4 us, with the merge 43.4
+// -> 26.7, and 100 tokens 47.8 -> 35.4.  With the waves sharing K instead, each
+// streaming dictionary chunks of its own, the 9 tokens took 15.4 as well and 100
+// tokens 43.1 with the merge; with the operands read after the barrier 19.6 against
+// 16.4 us (9 tokens of width 4096, m = 4096), and steps of four chunks were no faster.
 template <int WK>
 struct Narrow {
-    static constexpr int kSW = kBM / WK;           // latents of a slice
-    static constexpr int kWL = kEncWaves / WK;     // latent groups of 32
-    static constexpr int kStride = kSW + 4;        // floats per selection row
-    static constexpr int kPart = kBN * kStride;    // floats per partial-sum plane (128 rows)
-    static constexpr int kPieces = WK * kBN * 8;   // 16-byte pieces of a token window (128 rows)
+    static constexpr int kSW = kBM / WK;       // latents of a slice
+    static constexpr int kWL = kSW / 32;       // latent groups of 32
+    static constexpr int kStride = kSW + 4;    // floats per selection row
+    static constexpr int kCP = kWL * 256;      // 16-byte pieces of a K chunk of the slice
+    static constexpr int kCR = kCP / kEncThreads;  // ... per thread
+    static constexpr int R = WK == 4 ? 12 : 6;     // K chunks in the ring
+    static_assert(R * kCR <= kRing, "the ring holds them");
 };
 
-// Window w (a K chunk per share) of slice sl's dictionary stream.
-template <int WK>
-__device__ __forceinline__ void narrow_load(uint4 (&a)[4], const uint16_t* W, int n_mt, int sl,
-                                            int w, int nW) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int wl = wave % Narrow<WK>::kWL, wk = wave / Narrow<WK>::kWL;
+// K chunks c .. c + C - 1 of slice sl into their places of the ring: thread tid takes
+// pieces tid + 512 p of a chunk (none past the last one; c is a multiple of C).
+template <int WK, int C>
+__device__ __forceinline__ void narrow_load(uint4* a, const uint16_t* W, int n_mt, int sl, int c,
+                                            int nK) {
+    using N = Narrow<WK>;
     const int64_t chunk = static_cast<int64_t>(n_mt) * 32768;  // bytes of one K chunk
     const char* base = reinterpret_cast<const char*>(W) + static_cast<int64_t>(sl / WK) * 32768 +
-                       chunk * WK * min(w, nW - 1);
+                       (sl % WK) * (N::kCP * 16) + chunk * min(c, nK - C);
     const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<char*>(base), 0, w < nW ? static_cast<int>(chunk * (WK - 1) + 32768) : 0,
-        kBufferDword3);
-    const uint32_t off = static_cast<uint32_t>(wk) * static_cast<uint32_t>(chunk) +
-                         (((sl % WK) * Narrow<WK>::kWL + wl) * 256 + lane) * 16u;
+        const_cast<char*>(base), 0,
+        c < nK ? static_cast<int>((C - 1) * chunk + N::kCP * 16) : 0, kBufferDword3);
 #pragma unroll
-    for (int s = 0; s < 4; ++s) a[s] = buffer_load16<kNontemporal>(r, off + s * 1024u, 0);
+    for (int p = 0; p < C * N::kCR; ++p)
+        a[p] = buffer_load16<kNontemporal>(
+            r, threadIdx.x * 16u,
+            c < nK ? static_cast<uint32_t>(p / N::kCR) * static_cast<uint32_t>(chunk) +
+                         (p % N::kCR) * (kEncThreads * 16u)
+                   : 0u);
+}
+// The first chunks of slice sl.
+template <int WK>
+__device__ __forceinline__ void narrow_first(uint4 (&ring)[kRing], const uint16_t* W, int n_mt,
+                                             int sl, int d) {
+    using N = Narrow<WK>;
+    constexpr int C = WK == 4 ? 4 : 2;  // (d / 64 is a multiple of 4)
+#pragma unroll
+    for (int c = 0; c < N::R; c += C)
+        narrow_load<WK, C>(ring + c * N::kCR, W, n_mt, sl, c, d / kBK);
 }
 
 // One tile: slice sl over tokens [n0, n0 + 32 * NB) of the app's list.  On
-// entry wa0..wa2 hold the slice's first three windows when `issued`; on exit
-// those of slice `nxt` when nxt >= 0.
+// entry the ring holds the slice's first chunks (narrow_first); on exit
+// those of slice `nxt` of dictionary Wn when nxt >= 0.
 template <int WK, int NB>
 __device__ __forceinline__ void narrow_tile(uint4* lds_main, const uint16_t* __restrict__ h,
                                             uint32_t h_bytes, int32_t d, const int32_t* tl,
                                             int cnt, int n0, int sl,
                                             const uint16_t* __restrict__ W, int n_mt,
                                             const SliceSink sink,
-                                            const float* __restrict__ c_fold, bool issued,
-                                            int nxt, uint4 (&wa0)[4], uint4 (&wa1)[4],
-                                            uint4 (&wa2)[4], uint4 (&wa3)[4]) {
+                                            const float* __restrict__ c_fold, int nxt,
+                                            const uint16_t* Wn, int n_mtn,
+                                            uint4 (&ring)[kRing]) {
     using N = Narrow<WK>;
+    constexpr int kWL = N::kWL;
+    constexpr int C = NB == 1 || (WK == 4 && NB == 2) ? 2 : 1;  // K chunks of a step
+    constexpr int R = N::R / C;                        // steps of the slice in flight
+    constexpr int D = WK == 4 && NB == 4 ? R / 2 : R;  // and of the token rows
     constexpr int kRows = 32 * NB;
-    constexpr int kPlane = kRows * 8;       // pieces of one share's token chunk
-    constexpr int kXP = WK * kPlane / kEncThreads;  // pieces per thread and window
-    static_assert(kXP >= 1, "a window has a piece for every thread");
+    constexpr int kPlane = kRows * 8;  // pieces of one chunk of the token rows
+    constexpr int kX = (C * kPlane + kEncThreads - 1) / kEncThreads;  // per thread and step
+    constexpr int kW = C * N::kCR;
+    constexpr int kTB = kWL * NB > kEncWaves ? kWL * NB / kEncWaves : 1;  // token groups per wave
+    constexpr int kBuf = C * (N::kCP + kPlane);  // pieces of an LDS buffer
+    static_assert(3 * kBuf <= kLdsMain && C * kPlane == kX * kEncThreads,
+                  "three buffers fit the LDS, every thread has its pieces");
     int tid = threadIdx.x;  // opaque (see big_tile)
     asm volatile("" : "+v"(tid));
     const int lane = tid & 63, wave = tid >> 6;
-    const int wl = wave % N::kWL, wk = wave / N::kWL;
+    const int wl = wave % kWL, tg = wave / kWL * kTB;  // its latent group and first token group
     const int g = lane >> 5, j32 = lane & 31;
-    const int nW = d / (kBK * WK);
+    const int nW = d / (C * kBK);
     const int ntok = min(kRows, cnt - n0);
-    // piece q of a window: share q / kPlane, row (q % kPlane) / 8, 16-byte chunk
-    // q % 8; thread tid holds q = tid + 512 p
-    uint32_t xoff[kXP];
+    // piece q of a step's rows: chunk q / kPlane, row (q % kPlane) / 8, 16-byte piece
+    // q % 8 of it; thread tid holds q = tid + 512 p
+    uint32_t xoff[kX];
 #pragma unroll
-    for (int p = 0; p < kXP; ++p) {
-        const int q = tid + kEncThreads * p;
-        const int n = (q % kPlane) / 8;
+    for (int p = 0; p < kX; ++p) {
+        const int q = tid + kEncThreads * p, n = (q % kPlane) / 8;
         xoff[p] = n < ntok ? static_cast<uint32_t>(tl[n0 + n]) * static_cast<uint32_t>(d) * 2u +
                                  static_cast<uint32_t>(q / kPlane) * 128u + (q & 7) * 16u
                            : kOutOfRange;
     }
-    f32x16_t acc[NB];
+    f32x16_t acc[kTB];
     {
         const float* cf = c_fold + sl * N::kSW + 32 * wl + 4 * g;
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-            const float c = wk == 0 ? cf[8 * (r / 4) + (r % 4)] : 0.0f;
+            const float c = cf[8 * (r / 4) + (r % 4)];
 #pragma unroll
-            for (int nb = 0; nb < NB; ++nb) acc[nb][r] = c;
+            for (int b = 0; b < kTB; ++b) acc[b][r] = c;
         }
     }
-    uint4 xv0[kXP], xv1[kXP];
-    auto load_x = [&](uint4 (&xv)[kXP], int w) __attribute__((always_inline)) {
+    uint4 xv[D][kX];
+    auto load_x = [&](uint4 (&x)[kX], int w) __attribute__((always_inline)) {
         const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(
             const_cast<uint16_t*>(h), 0, w < nW ? static_cast<int>(h_bytes) : 0, kBufferDword3);
-        const uint32_t soff = w < nW ? static_cast<uint32_t>(w * WK) * 128u : 0u;
 #pragma unroll
-        for (int p = 0; p < kXP; ++p) xv[p] = buffer_load16<0>(r, xoff[p], soff);
+        for (int p = 0; p < kX; ++p)
+            x[p] = buffer_load16<0>(r, xoff[p], w < nW ? static_cast<uint32_t>(w) * (C * 128u) : 0u);
     };
-    // row n's chunk c sits at n*8 + (c ^ ((n >> 1) & 7)) of its share's plane;
-    // 512 pieces on are whole rows on, a multiple of 16 of them
-    static_assert(kEncThreads / 8 % 16 == 0, "the swizzle repeats every 16 rows");
-    const int xdst = (tid & ~7) + ((tid & 7) ^ ((tid >> 4) & 7));
-    auto store_x = [&](const uint4 (&xv)[kXP], int buf) __attribute__((always_inline)) {
+    // row n's piece c sits at n*8 + (c ^ ((n >> 1) & 7)) of its chunk's plane; 512 pieces
+    // on are 64 rows on, or whole planes
+    const int xdst = C * N::kCP + (tid & ~7) + ((tid & 7) ^ ((tid >> 4) & 7));
+    auto store = [&](int slot, int slot_x, uint4* buf) __attribute__((always_inline)) {
 #pragma unroll
-        for (int p = 0; p < kXP; ++p)
-            lds_main[buf * (WK * kPlane) + xdst + kEncThreads * p] = xv[p];
+        for (int p = 0; p < kX; ++p) buf[xdst + kEncThreads * p] = xv[slot_x][p];
+#pragma unroll
+        for (int p = 0; p < kW; ++p) buf[tid + kEncThreads * p] = ring[slot * kW + p];
     };
-    const int xsrc = wk * kPlane + j32 * 8, sw = (j32 >> 1) & 7;
-    auto compute = [&](const uint4 (&a)[4], int buf) __attribute__((always_inline)) {
-        const uint4* xs = lds_main + buf * (WK * kPlane) + xsrc;
+    const int xsrc = C * N::kCP + (32 * tg + j32) * 8, sw = (j32 >> 1) & 7;
+    const int wsrc = wl * 256 + lane;
+    const bool busy = wave * kTB < kWL * NB;  // (uniform over the wave) it has a block
+    uint4 A[4 * C], B[4 * C][kTB];  // a step's operands
+    auto read = [&](int s, const uint4* buf) __attribute__((always_inline)) {
+        A[s] = buf[(s / 4) * N::kCP + wsrc + (s % 4) * 64];
 #pragma unroll
-        for (int s = 0; s < 4; ++s) {
-            uint4 bop[NB];
-#pragma unroll
-            for (int nb = 0; nb < NB; ++nb) bop[nb] = xs[((2 * s + g) ^ sw) + 256 * nb];
-#pragma unroll
-            for (int nb = 0; nb < NB; ++nb)
-                acc[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(a[s]),
-                                                                  as_bf16x8(bop[nb]), acc[nb], 0,
-                                                                  0, 0);
-        }
+        for (int b = 0; b < kTB; ++b)
+            B[s][b] = buf[(s / 4) * kPlane + xsrc + 256 * b + ((2 * (s % 4) + g) ^ sw)];
     };
-    auto step = [&](int w, const uint4 (&cur)[4], uint4 (&wnext)[4], uint4 (&xload)[kXP],
-                    const uint4 (&xstore)[kXP]) __attribute__((always_inline)) {
-        load_x(xload, w + 2);
-        __builtin_amdgcn_sched_barrier(0);  // keep the token loads ahead of the W loads
-        narrow_load<WK>(wnext, W, n_mt, sl, w + 3, nW);
-        __syncthreads();
-        compute(cur, w & 1);
-        store_x(xstore, (w + 1) & 1);
+    // Step w, in slot w % R of the ring: its place there was stored two steps ago and
+    // takes step w + R.  Its operands are in registers; the next step's, stored a step
+    // ago, are read as they are multiplied, and the one after it is stored to the
+    // buffer that every wave has read a step ago.
+    uint4 *b0 = lds_main, *b1 = lds_main + kBuf, *b2 = lds_main + 2 * kBuf;  // of w, w + 1, w + 2
+    auto step = [&](int w, int slot) __attribute__((always_inline)) {
+        load_x(xv[slot % D], w + D);
+        narrow_load<WK, C>(ring + slot * kW, W, n_mt, sl, (w + R) * C, nW * C);
         __builtin_amdgcn_sched_barrier(0);
+        __syncthreads();
+        if (busy) {
+#pragma unroll
+            for (int s = 0; s < 4 * C; ++s) {
+#pragma unroll
+                for (int b = 0; b < kTB; ++b)
+                    acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                        as_bf16x8(A[s]), as_bf16x8(B[s][b]), acc[b], 0, 0, 0);
+                read(s, b1);
+            }
+        }
+        store((slot + 2) % R, (slot + 2) % D, b2);
+        __builtin_amdgcn_sched_barrier(0);
+        uint4* t = b0;
+        b0 = b1;
+        b1 = b2;
+        b2 = t;
     };
-    load_x(xv0, 0);
-    load_x(xv1, 1);
-    if (!issued) {
-        narrow_load<WK>(wa0, W, n_mt, sl, 0, nW);
-        narrow_load<WK>(wa1, W, n_mt, sl, 1, nW);
-        narrow_load<WK>(wa2, W, n_mt, sl, 2, nW);
+#pragma unroll
+    for (int w = 0; w < D; ++w) load_x(xv[w], w);
+    __builtin_amdgcn_sched_barrier(0);
+    store(0, 0, b0);
+    store(1, 1, b1);
+    __syncthreads();
+    if (busy)
+#pragma unroll
+        for (int s = 0; s < 4 * C; ++s) read(s, b0);
+    static_assert(R % D == 0 && D > 2, "the slots of the rings");
+    for (int w = 0; w < nW;) {  // any number of steps
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            step(w, r);
+            if (++w == nW) break;
+        }
     }
-    store_x(xv0, 0);
-    for (int w = 0;;) {  // the W registers rotate; any number of windows
-        step(w, wa0, wa3, xv0, xv1);
-        if (++w == nW) break;
-        step(w, wa1, wa0, xv1, xv0);
-        if (++w == nW) break;
-        step(w, wa2, wa1, xv0, xv1);
-        if (++w == nW) break;
-        step(w, wa3, wa2, xv1, xv0);
-        if (++w == nW) break;
-    }
-    if (nxt >= 0) {  // uniform: the next slice's stream starts under the selection
-        narrow_load<WK>(wa0, W, n_mt, nxt, 0, nW);
-        narrow_load<WK>(wa1, W, n_mt, nxt, 1, nW);
-        narrow_load<WK>(wa2, W, n_mt, nxt, 2, nW);
-    }
-    __syncthreads();  // every wave is done with the token windows
-    constexpr int kPlaneF = kRows * N::kStride;  // floats of a partial-sum plane
+    if (nxt >= 0) narrow_first<WK>(ring, Wn, n_mtn, nxt, d);  // under the selection
+    __syncthreads();  // every wave is done with the windows
     float* V = reinterpret_cast<float*>(lds_main);
+    if (busy) {
 #pragma unroll
-    for (int nb = 0; nb < NB; ++nb) {
-        float* rowp = V + wk * kPlaneF + (32 * nb + j32) * N::kStride + 32 * wl + 4 * g;
+        for (int b = 0; b < kTB; ++b) {
+            float* rowp = V + (32 * (tg + b) + j32) * N::kStride + 32 * wl + 4 * g;
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
-            *reinterpret_cast<float4*>(rowp + 8 * j) = make_float4(
-                acc[nb][4 * j], acc[nb][4 * j + 1], acc[nb][4 * j + 2], acc[nb][4 * j + 3]);
+            for (int j = 0; j < 4; ++j)
+                *reinterpret_cast<float4*>(rowp + 8 * j) = make_float4(
+                    acc[b][4 * j], acc[b][4 * j + 1], acc[b][4 * j + 2], acc[b][4 * j + 3]);
+        }
     }
     __syncthreads();
     // NT rows per lane group: 16 rows a wave in the widest tile, 8 below (every
@@ -828,43 +838,30 @@ __device__ __forceinline__ void narrow_tile(uint4* lds_main, const uint16_t* __r
             co[t] = sink.tile_cnt + row;
             to[t] = sink.tile_tau + row;
         }
-        select_slices<true, NT, VPL, 8, WK>(vr, kPlaneF, q, ok, sink.z, sink.lo_cnt, sink.cap,
-                                            sl * N::kSW + VPL * q, dst, co, to);
+        select_slices<true, NT, VPL, 8>(vr, q, ok, sink.z, sink.lo_cnt, sink.cap,
+                                        sl * N::kSW + VPL * q, dst, co, to);
     }
     __syncthreads();  // the rows are read before the next tile's tokens land
 }
 
-// Candidates of narrow slices sl, sl + step, ... (< n_end), each over the live
-// token tiles in turn.  On entry wa0..wa2 hold the first one's first three
-// windows when `issued`.
+// The tile by the tokens left of the list from n0 on.
 template <int WK>
-__device__ __forceinline__ void narrow_slices(uint4* lds_main, const uint16_t* __restrict__ h,
-                                              uint32_t h_bytes, int32_t d, const int32_t* tl,
-                                              int cnt, int sl, int step, int n_end,
-                                              const uint16_t* __restrict__ W, int n_mt,
-                                              const SliceSink sink,
-                                              const float* __restrict__ c_fold, bool issued,
-                                              uint4 (&wa0)[4], uint4 (&wa1)[4], uint4 (&wa2)[4],
-                                              uint4 (&wa3)[4]) {
-    for (;;) {
-        for (int n0 = 0; n0 < cnt; n0 += kBN) {
-            const int left = cnt - n0;
-            // what streams next: the slice again for its next tile, or the next slice
-            const int nxt = left > kBN ? sl : sl + step < n_end ? sl + step : -1;
-            if (left <= 32)
-                narrow_tile<WK, 1>(lds_main, h, h_bytes, d, tl, cnt, n0, sl, W, n_mt, sink, c_fold,
-                                   issued, nxt, wa0, wa1, wa2, wa3);
-            else if (left <= 64)
-                narrow_tile<WK, 2>(lds_main, h, h_bytes, d, tl, cnt, n0, sl, W, n_mt, sink, c_fold,
-                                   issued, nxt, wa0, wa1, wa2, wa3);
-            else
-                narrow_tile<WK, 4>(lds_main, h, h_bytes, d, tl, cnt, n0, sl, W, n_mt, sink, c_fold,
-                                   issued, nxt, wa0, wa1, wa2, wa3);
-            issued = nxt >= 0;
-        }
-        sl += step;
-        if (sl >= n_end) return;
-    }
+__device__ __forceinline__ void narrow_any(uint4* lds_main, const uint16_t* __restrict__ h,
+                                           uint32_t h_bytes, int32_t d, const int32_t* tl,
+                                           int cnt, int n0, int sl,
+                                           const uint16_t* __restrict__ W, int n_mt,
+                                           const SliceSink sink, const float* __restrict__ c_fold,
+                                           int nxt, const uint16_t* Wn, int n_mtn, uint4 (&ring)[kRing]) {
+    const int left = cnt - n0;
+    if (left <= 32)
+        narrow_tile<WK, 1>(lds_main, h, h_bytes, d, tl, cnt, n0, sl, W, n_mt, sink, c_fold, nxt,
+                           Wn, n_mtn, ring);
+    else if (left <= 64)
+        narrow_tile<WK, 2>(lds_main, h, h_bytes, d, tl, cnt, n0, sl, W, n_mt, sink, c_fold, nxt,
+                           Wn, n_mtn, ring);
+    else
+        narrow_tile<WK, 4>(lds_main, h, h_bytes, d, tl, cnt, n0, sl, W, n_mt, sink, c_fold, nxt,
+                           Wn, n_mtn, ring);
 }
 
 // ------------------------------------------------------------- big token tiles
@@ -884,26 +881,59 @@ __device__ __forceinline__ void narrow_slices(uint4* lds_main, const uint16_t* _
 // us as four 128-token tiles in turn, 156 with both operands through LDS.
 constexpr int kBigTok = 256;
 constexpr int kBigPieces = 1024;  // 16-byte pieces of a stage's token rows; four stages
+static_assert(4 * kBigPieces <= kLdsMain, "the stages fit the LDS");
 
 // Stage swizzle: the 16-byte piece c of token n sits at n*4 + (c ^ gsw(n));
 // with it the MFMA-layout reads of 16 tokens x 4 pieces hit distinct banks.
 __device__ __forceinline__ int gsw(int n) { return ((n >> 3) ^ (n >> 4)) & 3; }
 
-// Whether an app with cnt live tokens takes big tiles: always from 129 tokens
-// on whole slices, where the alternative streams the dictionary once per 128
-// tokens; on slices cut in two where they are the cheaper way to deal the work
-// to 256 CUs (a 128-token tile of half a slice costs about 12 units, a big
-// tile 20); never on slices cut in four, whose dictionaries have too few whole
-// ones to fill the CUs.  The rule holds the routing's count against sizes
-// alone, so that every call that can encode an app decides alike.
-__device__ __forceinline__ bool big_tiles(int cnt, int n_mt, int n_sl) {
-    if (cnt <= kBN) return false;
-    if (n_sl == n_mt) return true;
-    const int cut = n_sl / n_mt;
-    if (cut > 2) return false;
-    const int small = ((n_sl + 255) / 256) * ((cnt + kBN - 1) / kBN) * (4 + 16 / cut);
-    const int big = ((n_mt * ((cnt + kBigTok - 1) / kBigTok) + 255) / 256) * 20;
-    return big < small;
+// A value that is the same in every lane, in a scalar register.
+__device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
+
+// The tiles that an app's live tokens are encoded in.  All of them add in the order
+// of K, so the choice shows in no result.  It is made by the rounds of units
+// (slice, tokens) over 256 CUs, as counted over the apps of the launch:
+//  - narrow tiles while they are one round.  One of a slice cut in four takes 0.66 of
+//    a whole tile (200 tokens, width 4096, m = 8192: 53 us an encode against 70), but
+//    a second round more than one of whole tiles (m = 16384: 90 and 77);
+//  - big tiles for more than 128 tokens where whole ones take 5/3 of their rounds or
+//    more.  Two rounds of whole tiles are about one of big ones, or up to a quarter
+//    more (width 4096: 512 tokens, m = 32768: 153 and 140; m = 65536: 288 and 267; 140
+//    tokens: 182 and 147), three rounds less than two (384 tokens, m = 65536: 233 and
+//    250), and one round 0.7 of one (500 tokens, m = 8192: 74 and 104);
+//  - whole tiles else.
+constexpr int kRoundCUs = 256;
+enum TileKind { kNarrowTiles, kWholeTiles, kBigTiles };
+struct TileUnits {
+    int narrow = 0, whole = 0, big = 0;  // of the launch, were all of its tiles such
+    __device__ __forceinline__ void add(int cnt, int n_mt, int n_sl) {
+        const int t128 = (cnt + kBN - 1) / kBN;
+        narrow += n_sl * t128;
+        whole += n_mt * t128;
+        big += n_mt * ((cnt + kBigTok - 1) / kBigTok);
+    }
+};
+__device__ __forceinline__ int rounds(int units) { return (units + kRoundCUs - 1) / kRoundCUs; }
+template <int WK>
+__device__ __forceinline__ TileKind tile_kind(int cnt, const TileUnits& u, int d, int T_max) {
+    if (WK > 1 && u.narrow <= kRoundCUs) return kNarrowTiles;
+    // (the big tiles' buffer offsets are 32 bits)
+    if (WK < 4 && cnt > kBN && 3 * rounds(u.whole) >= 5 * rounds(u.big) &&
+        static_cast<int64_t>(T_max) * d * 2 <= 0x7FFFFFFF)
+        return kBigTiles;
+    return kWholeTiles;
+}
+// Its number of units (slice, tokens), of n slices and n_nt token tiles, and the
+// unit u: the token tiles of eight slices together, a slice to each XCD, the
+// slices fastest, so that the workgroups that run the tiles of one slice side by
+// side draw it through the same L2.
+__device__ __forceinline__ void unit_tile(int u, int n, int n_nt, int* slice, int* nt) {
+    *slice = u;
+    *nt = 0;
+    if (n_nt == 1) return;  // uniform
+    const int grp = u / (8 * n_nt), r = u - grp * 8 * n_nt, w = min(8, n - 8 * grp);
+    *nt = r / w;
+    *slice = 8 * grp + r - *nt * w;
 }
 
 template <int WK>
@@ -1076,29 +1106,18 @@ __device__ __forceinline__ void big_tile(uint4* lds_main, const uint16_t* __rest
                 uint2* const dst[1] = {sink.cand + row * sink.cap};
                 int32_t* const co[1] = {sink.tile_cnt + row};
                 float* const to[1] = {sink.tile_tau + row};
-                select_slices<true, 1, 32, LPS, 1>(vr, 0, q8 % LPS, ok, sink.z, sink.lo_cnt,
-                                                   sink.cap, mt * kBM + 32 * q8, dst, co, to);
+                select_slices<true, 1, 32, LPS>(vr, q8 % LPS, ok, sink.z, sink.lo_cnt,
+                                                sink.cap, mt * kBM + 32 * q8, dst, co, to);
             }
         }
     }
     __syncthreads();  // the rows are read before what runs next
 }
 
-// A value that is the same in every lane, in a scalar register.
-__device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
-
-// K loop: token chunks and stages; epilogue: the selection rows (of a narrow
-// slice, its partial-sum planes)
-constexpr int kLdsMain = Narrow<4>::kPart * 4 / 4;  // 16-byte pieces
-static_assert(kLdsMain >= kBN * kSelStride / 4 && kLdsMain >= Narrow<2>::kPart * 2 / 4 &&
-                  kLdsMain >= 2 * Narrow<4>::kPieces && kLdsMain >= 4 * kBigPieces,
-              "every path's LDS fits");
-
 // Candidates of one app.  WK: the cut of its slices (1: whole ones of 256
-// latents); BIG: the batch may hold more than 128 live tokens of the app, so
-// that big tiles are compiled in.  Workgroup u owns slice u and takes its live
-// token tiles in turn; with big tiles the pairs (slice, 256 tokens) are dealt
-// to the workgroups.
+// latents); MANY: the batch has more than 128 token slots, so that an app may have
+// several token tiles, and big ones.  The app's units (slice, tokens) are dealt to
+// the workgroups; the dictionary stream runs on from one unit into the next.
 //
 // With r_req given, the kernel also builds the step's routing (in place
 // of a route-build launch): every workgroup builds its app's token list
@@ -1108,7 +1127,7 @@ static_assert(kLdsMain >= kBN * kSelStride / 4 && kLdsMain >= Narrow<2>::kPart *
 // workgroup with a slice starts its first dictionary chunks as soon as the
 // staged table shows a request subscribed to the app, so that the stream
 // runs while the list is built (without a subscriber it reads nothing).
-template <int WK, bool BIG>
+template <int WK, bool MANY>
 __global__ void __launch_bounds__(kEncThreads, 1)
 sae_stream_kernel(const uint16_t* __restrict__ h, int32_t d,
                   const int32_t* __restrict__ app_count, const int32_t* __restrict__ tok_list,
@@ -1120,34 +1139,19 @@ sae_stream_kernel(const uint16_t* __restrict__ h, int32_t d,
                   int32_t r_Rmax, int32_t r_napps, int32_t r_bit,
                   uint32_t* __restrict__ r_mask, int32_t* __restrict__ r_count,
                   int32_t* __restrict__ r_lists, uint32_t* __restrict__ r_err) {
-    __shared__ uint4 lds_main[WK == 1 ? kBN * kSelStride / 4 : kLdsMain];
+    __shared__ uint4 lds_main[kLdsMain];
     __shared__ int32_t list_s[kRouteMaxT];    // the app's token list (in-kernel route build)
     __shared__ int32_t rtot_s[kEncWaves];
     __shared__ int32_t seen_s[kEncWaves];
-    const int own = blockIdx.x;
+    const int own = blockIdx.x, G = gridDim.x;
     const int n_sl = n_mt * WK;
-    const bool live = own < n_sl;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int nW = d / (kBK * WK);
-    const SliceSrc src = slice_src(W, n_mt, min(own, n_mt - 1));
-    uint4 wa0[4], wa1[4], wa2[4], wa3[4];   // W ring: 4 chunks, 3 in flight
+    uint4 ring[kRing];
     float cfv[16];
-    auto first_chunks = [&]() __attribute__((always_inline)) {
-        if constexpr (WK == 1) {
-            load_chunk(wa0, src.base);
-            load_chunk(wa1, src.base + src.stride);
-            load_chunk(wa2, src.base + 2 * src.stride);
-            load_bias(cfv, c_fold, own);
-        } else {
-            narrow_load<WK>(wa0, W, n_mt, own, 0, nW);
-            narrow_load<WK>(wa1, W, n_mt, own, 1, nW);
-            narrow_load<WK>(wa2, W, n_mt, own, 2, nW);
-        }
-    };
 
     const int32_t* tl = tok_list;
     int cnt = 0;
-    bool w_issued = false;
+    int started = -1;  // the slice whose first chunks are in flight
     if (r_req) {  // uniform
         static_assert(sizeof(lds_main) >= (kRouteMaxT + kStageSubMax) * 4, "staging fits");
         int32_t* req_s = reinterpret_cast<int32_t*>(lds_main);
@@ -1167,11 +1171,14 @@ sae_stream_kernel(const uint16_t* __restrict__ h, int32_t d,
         // no request subscribes to the app: no token is listed, and a
         // workgroup with nothing to publish is done
         if (!any && own >= r_napps) return;  // uniform
-        // (of a narrow slice that may yet be part of a big tile they would
-        // only hold registers)
-        if (live && any && (WK == 1 || !BIG)) {  // uniform
-            first_chunks();
-            w_issued = true;
+        // Slice `own`, the first unit of a single token tile.  With more tiles
+        // another slice may come first, or a big tile, and the chunks are read for
+        // nothing: not where they are a good part of a row (K chunks 0-2 of d / 64),
+        // nor of a cut slice.
+        if (own < n_sl && any && (!MANY || (WK == 1 && d >= 1024))) {  // uniform
+            if constexpr (WK == 1) slice_first(ring, cfv, slice_src(W, n_mt, own), c_fold, own);
+            else narrow_first<WK>(ring, W, n_mt, own, d);
+            started = own;
         }
         if (own < r_napps && own != r_bit) {
             const int32_t n = build_token_list<kEncThreads>(req_s, tv, sub_s, r_sub, r_Rmax, keep,
@@ -1194,35 +1201,67 @@ sae_stream_kernel(const uint16_t* __restrict__ h, int32_t d,
     } else {
         cnt = *app_count;
     }
+    if (cnt <= 0) return;
     const SliceSink sink{cand, tile_cnt, tile_tau, n_sl, lo_cnt, cap, z_guess};
-    if constexpr (BIG) {
-        if (big_tiles(cnt, n_mt, n_sl)) {  // uniform
-            const int units = n_mt * ((cnt + kBigTok - 1) / kBigTok);
-            const uint32_t h_bytes = static_cast<uint32_t>(T_max) * static_cast<uint32_t>(d) * 2u;
-            for (int u = own; u < units; u += static_cast<int>(gridDim.x))
-                big_tile<WK>(lds_main, h, h_bytes, d, tl, cnt, u / n_mt, u % n_mt, W, n_mt, sink,
-                             c_fold);
+    const uint32_t h_bytes = static_cast<uint32_t>(T_max) * static_cast<uint32_t>(d) * 2u;
+    TileUnits tu;
+    tu.add(cnt, n_mt, n_sl);
+    const TileKind kind = MANY ? tile_kind<WK>(cnt, tu, d, T_max)
+                               : WK == 1 ? kWholeTiles : kNarrowTiles;
+    const int tok = kind == kBigTiles ? kBigTok : kBN, n_nt = (cnt + tok - 1) / tok;
+    const int n = kind == kNarrowTiles ? n_sl : n_mt, units = n * n_nt;
+    int u = own, sl, nt;
+    if (u >= units) return;
+    unit_tile(u, n, n_nt, &sl, &nt);
+    if constexpr (MANY && WK < 4) {
+        if (kind == kBigTiles) {  // uniform
+            for (; u < units; u += G) {
+                unit_tile(u, n, n_nt, &sl, &nt);
+                big_tile<WK>(lds_main, h, h_bytes, d, tl, cnt, nt, sl, W, n_mt, sink, c_fold);
+            }
             return;
         }
     }
-    if (!live || cnt <= 0) return;
-    if constexpr (WK == 1)
-        slice_tiles<BIG>(lds_main, h, d, tl, cnt, own, src, [&]() { return sink; }, w_issued, src,
-                         false, 0, [&]() { return c_fold; }, c_fold, wa0, wa1, wa2, wa3, cfv);
-    else
-        narrow_slices<WK>(lds_main, h,
-                          static_cast<uint32_t>(T_max) * static_cast<uint32_t>(d) * 2u, d, tl, cnt,
-                          own, n_sl, n_sl, W, n_mt, sink, c_fold, w_issued, wa0, wa1, wa2, wa3);
+    if constexpr (WK > 1) {
+        if (!MANY || kind == kNarrowTiles) {  // uniform
+            if (started != sl) narrow_first<WK>(ring, W, n_mt, sl, d);
+            for (;;) {
+                int sn = -1, ntn = 0;
+                if ((u += G) < units) unit_tile(u, n, n_nt, &sn, &ntn);
+                narrow_any<WK>(lds_main, h, h_bytes, d, tl, cnt, nt * kBN, sl, W, n_mt, sink, c_fold,
+                               sn, W, n_mt, ring);
+                if (sn < 0) return;
+                sl = sn;
+                nt = ntn;
+            }
+        }
+    }
+    if constexpr (WK == 1 || MANY) {
+        SliceSrc src = slice_src(W, n_mt, sl);
+        if (WK > 1 || started != sl) slice_first(ring, cfv, src, c_fold, sl);
+        const auto sink_of = [&]() __attribute__((always_inline)) { return sink; };
+        const auto bias_of = [&]() __attribute__((always_inline)) { return c_fold; };
+        for (u += G; u < units; u += G) {
+            int sn, ntn;
+            unit_tile(u, n, n_nt, &sn, &ntn);
+            const SliceSrc nsrc = slice_src(W, n_mt, sn);
+            slice_tile<WK>(lds_main, h, d, tl, nt * kBN, min(kBN, cnt - nt * kBN), sl, src, sink_of,
+                           nsrc, true, sn, bias_of, ring, cfv);
+            src = nsrc;
+            sl = sn;
+            nt = ntn;
+        }
+        slice_tile<WK>(lds_main, h, d, tl, nt * kBN, min(kBN, cnt - nt * kBN), sl, src, sink_of, src,
+                       false, sl, bias_of, ring, cfv);
+    }
 }
 
-// Several SAE apps of one hook in one launch, on a persistent grid: an app's
-// units are its slices, each over the live token tiles in turn, or its (slice,
-// 256 tokens) pairs with big tiles; an app without a token has none.
-// Workgroup w runs units w, w + G, w + 2G, ... of the apps' units laid end to
-// end (G the grid, at most one workgroup per CU).  The routing inputs are
-// staged once per workgroup, in LDS of their own; the dictionary stream runs on
-// from one whole slice into the next, so the next slice's first chunks load
-// while this one's candidates are selected.
+// Several SAE apps of one hook in one launch, on a persistent grid: the apps'
+// units (slice, tokens) are laid end to end, none of an app without a token, and
+// workgroup w runs units w, w + G, w + 2G, ... (G the grid, at most one workgroup
+// per CU).  The routing inputs are staged once per workgroup, in LDS of their own;
+// the dictionary stream runs on from one unit into the next, so the next slice's
+// first chunks load while this one's candidates are selected.
 struct EncApp {
     const int32_t* app_count;
     const int32_t* tok_list;
@@ -1231,7 +1270,7 @@ struct EncApp {
     uint2* cand;
     int32_t* tile_cnt;
     float* tile_tau;
-    int32_t n_mt, n_sl, lo_cnt, cap, bit;
+    int32_t n_mt, lo_cnt, cap, bit;
     float z;
 };
 struct EncApps {
@@ -1239,8 +1278,8 @@ struct EncApps {
     int32_t n;
 };
 
-// NARROW: every app's slices are cut, else none's; BIG: as in sae_stream_kernel.
-template <bool NARROW, bool BIG>
+// WK, MANY: as in sae_stream_kernel, the same for every app.
+template <int WK, bool MANY>
 __global__ void __launch_bounds__(kEncThreads, 1)
 sae_stream_apps_kernel(const uint16_t* __restrict__ h, int32_t d, EncApps apps,
                        const int32_t* __restrict__ r_req, const int32_t* __restrict__ r_tvalid,
@@ -1248,11 +1287,12 @@ sae_stream_apps_kernel(const uint16_t* __restrict__ h, int32_t d, EncApps apps,
                        int32_t r_napps, uint32_t* __restrict__ r_mask,
                        int32_t* __restrict__ r_count, int32_t* __restrict__ r_lists,
                        uint32_t* __restrict__ r_err) {
-    __shared__ uint4 lds_main[NARROW ? kLdsMain : kBN * kSelStride / 4];
+    __shared__ uint4 lds_main[kLdsMain];
     __shared__ int32_t list_s[kRouteMaxT];
     __shared__ int32_t rtot_s[kEncWaves];
     __shared__ int32_t stage_s[kRouteMaxT + kStageSubMax];
     __shared__ int32_t cnt_s[kMultiMax];
+    __shared__ int32_t kind_s[kMultiMax], n_s[kMultiMax], nt_s[kMultiMax];
     const int tid = threadIdx.x, lane = tid & 63;
     const int own = blockIdx.x, G = gridDim.x;
 
@@ -1290,115 +1330,126 @@ sae_stream_apps_kernel(const uint16_t* __restrict__ h, int32_t d, EncApps apps,
         cnt_s[tid] = *apps.a[tid].app_count;
     }
     __syncthreads();  // the counts; list_s free
-
-    // the app's units: 0 without a token
-    auto units_of = [&](int i) {
-        const EncApp& a = apps.a[i];
-        const int c = uniform(cnt_s[i]);
-        if (c <= 0) return 0;
-        if (BIG && big_tiles(c, a.n_mt, a.n_sl)) return a.n_mt * ((c + kBigTok - 1) / kBigTok);
-        return a.n_sl;
-    };
-    // moves (i, base), an app and its first unit, to the app of unit u; false
-    // past the last unit
-    auto seek = [&](int u, int& i, int& base) {
+    // each app's kind of tiles, its slices and token tiles (0 without a token)
+    if (tid < apps.n) {
+        const int c = cnt_s[tid], n_mt = apps.a[tid].n_mt;
+        TileUnits tu;
+        for (int i = 0; MANY && i < apps.n; ++i)
+            tu.add(max(cnt_s[i], 0), apps.a[i].n_mt, apps.a[i].n_mt * WK);
+        const TileKind kind = MANY ? tile_kind<WK>(c, tu, d, T_max)
+                                   : WK == 1 ? kWholeTiles : kNarrowTiles;
+        const int tok = kind == kBigTiles ? kBigTok : kBN;
+        kind_s[tid] = kind;
+        n_s[tid] = n_mt * (kind == kNarrowTiles ? WK : 1);
+        nt_s[tid] = c > 0 ? (c + tok - 1) / tok : 0;
+    }
+    __syncthreads();
+    // The units, laid end to end: narrow tiles of every app, whole ones, big ones,
+    // each kind in a loop of its own (together they would not fit the registers).
+    // seek moves (i, base), an app and its first unit, to the app of kind `kind`
+    // with unit u; false past the last one, with base past them.
+    auto seek = [&](int kind, int u, int& i, int& base) {
         for (; i < apps.n; ++i) {
-            const int n = units_of(i);
+            if (uniform(kind_s[i]) != kind) continue;
+            const int n = uniform(n_s[i]) * uniform(nt_s[i]);
             if (u < base + n) return true;
             base += n;
         }
         return false;
     };
-    // whether a unit of app i is a whole slice whose stream can start early
-    auto whole = [&](int i) {
-        const EncApp& a = apps.a[i];
-        return !NARROW && !(BIG && big_tiles(uniform(cnt_s[i]), a.n_mt, a.n_sl));
+    auto place = [&](int u, int i, int base, int* sl, int* nt) {
+        *sl = u - base;
+        *nt = 0;
+        if (MANY) unit_tile(u - base, uniform(n_s[i]), uniform(nt_s[i]), sl, nt);
     };
-    const uint32_t h_bytes = static_cast<uint32_t>(T_max) * static_cast<uint32_t>(d) * 2u;
-    int u = own, i = 0, base = 0;
-    if (!seek(u, i, base)) return;  // uniform
-    uint4 wa0[4], wa1[4], wa2[4], wa3[4];
-    float cfv[16];
-    SliceSrc src = slice_src(apps.a[i].W, apps.a[i].n_mt, 0);
-    bool issued = false;
-    if (whole(i)) {
-        src = slice_src(apps.a[i].W, apps.a[i].n_mt, u - base);
-        load_chunk(wa0, src.base);
-        load_chunk(wa1, src.base + src.stride);
-        load_chunk(wa2, src.base + 2 * src.stride);
-        load_bias(cfv, apps.a[i].c_fold, u - base);
-        issued = true;
-    }
     int list_app = -1, cnt = 0;
     const int32_t* tl = nullptr;
-    for (;;) {
-        const EncApp& a = apps.a[i];
-        if (i != list_app) {  // uniform
-            if (r_req) {
-                uint32_t e = 0;
-                cnt = build_token_list<kEncThreads>(req_s, tv, sub_s, r_sub, r_Rmax, keep, a.bit,
-                                                    T_max, list_s, rtot_s, nullptr, e);
-                tl = list_s;
-            } else {
-                cnt = uniform(cnt_s[i]);
-                tl = a.tok_list;
-            }
-            list_app = i;
-        }
-        const int unit = u - base;
-        const SliceSink sink{a.cand, a.tile_cnt, a.tile_tau, a.n_sl, a.lo_cnt, a.cap, a.z};
-        const bool bt = BIG && big_tiles(cnt, a.n_mt, a.n_sl);
-        int un = u + G;  // what runs next, if anything
-        // every narrow slice of this app that is this workgroup's, in one go
-        if (NARROW && !bt) un = u + (a.n_sl - unit + G - 1) / G * G;
-        int in = i, bn = base;
-        const bool more = seek(un, in, bn);
-        if (NARROW || bt) {
-            const int nt = unit / a.n_mt, mt = unit % a.n_mt;
-            if (bt)
-                big_tile<NARROW ? 2 : 1>(lds_main, h, h_bytes, d, tl, cnt, nt, mt, a.W, a.n_mt,
-                                         sink, a.c_fold);
-            else if (a.n_sl == 4 * a.n_mt)
-                narrow_slices<4>(lds_main, h, h_bytes, d, tl, cnt, unit, G, a.n_sl, a.W, a.n_mt,
-                                 sink, a.c_fold, false, wa0, wa1, wa2, wa3);
-            else
-                narrow_slices<2>(lds_main, h, h_bytes, d, tl, cnt, unit, G, a.n_sl, a.W, a.n_mt,
-                                 sink, a.c_fold, false, wa0, wa1, wa2, wa3);
-            // nothing is in flight (and the registers need not outlive the tile)
-            issued = false;
-#pragma unroll
-            for (int r = 0; r < 4; ++r)
-                wa0[r] = wa1[r] = wa2[r] = wa3[r] = make_uint4(0u, 0u, 0u, 0u);
-#pragma unroll
-            for (int r = 0; r < 16; ++r) cfv[r] = 0.0f;
+    auto list_of = [&](int i) {
+        if (i == list_app) return;  // uniform
+        if (r_req) {
+            uint32_t e = 0;
+            cnt = build_token_list<kEncThreads>(req_s, tv, sub_s, r_sub, r_Rmax, keep,
+                                                apps.a[i].bit, T_max, list_s, rtot_s, nullptr, e);
+            tl = list_s;
         } else {
-            if (!issued) src = slice_src(a.W, a.n_mt, unit);
-            const bool run_on = more && whole(in);
-            const int mtn = run_on ? un - bn : unit;
-            const SliceSrc nsrc = run_on ? slice_src(apps.a[in].W, apps.a[in].n_mt, mtn) : src;
-            // the descriptors are read again where they are used (an opaque index
-            // keeps their fields out of registers until then)
-            auto sink_of = [&]() __attribute__((always_inline)) {
-                int k = i;
-                asm volatile("" : "+s"(k));
-                const EncApp& b = apps.a[k];
-                return SliceSink{b.cand, b.tile_cnt, b.tile_tau, b.n_sl, b.lo_cnt, b.cap, b.z};
-            };
+            cnt = uniform(cnt_s[i]);
+            tl = apps.a[i].tok_list;
+        }
+        list_app = i;
+    };
+    // the descriptors are read again where they are used (an opaque index
+    // keeps their fields out of registers until then)
+    auto sink_of = [&](int i) __attribute__((always_inline)) {
+        asm volatile("" : "+s"(i));
+        const EncApp& b = apps.a[i];
+        return SliceSink{b.cand, b.tile_cnt, b.tile_tau, b.n_mt * WK, b.lo_cnt, b.cap, b.z};
+    };
+    const uint32_t h_bytes = static_cast<uint32_t>(T_max) * static_cast<uint32_t>(d) * 2u;
+    int u = own, base = 0;
+    if constexpr (WK > 1) {
+        int i = 0, sl = 0, nt = 0;
+        bool more = seek(kNarrowTiles, u, i, base);
+        uint4 ring[kRing];
+        if (more) {
+            place(u, i, base, &sl, &nt);
+            narrow_first<WK>(ring, apps.a[i].W, apps.a[i].n_mt, sl, d);
+        }
+        while (more) {
+            list_of(i);
+            const EncApp& a = apps.a[i];
+            int in = i, sn = -1, ntn = 0;
+            u += G;
+            more = seek(kNarrowTiles, u, in, base);
+            if (more) place(u, in, base, &sn, &ntn);
+            const EncApp& b = apps.a[more ? in : i];
+            narrow_any<WK>(lds_main, h, h_bytes, d, tl, cnt, nt * kBN, sl, a.W, a.n_mt, sink_of(i),
+                           a.c_fold, sn, b.W, b.n_mt, ring);
+            i = in;
+            sl = sn;
+            nt = ntn;
+        }
+    }
+    if constexpr (WK == 1 || MANY) {
+        int i = 0, sl = 0, nt = 0;
+        bool more = seek(kWholeTiles, u, i, base);
+        uint4 ring[kRing];
+        float cfv[16];
+        SliceSrc src{};
+        if (more) {
+            place(u, i, base, &sl, &nt);
+            // in flight while the list is built
+            src = slice_src(apps.a[i].W, apps.a[i].n_mt, sl);
+            slice_first(ring, cfv, src, apps.a[i].c_fold, sl);
+        }
+        while (more) {
+            list_of(i);
+            int in = i, sn = sl, ntn = 0;
+            u += G;
+            more = seek(kWholeTiles, u, in, base);
             auto bias_of = [&]() __attribute__((always_inline)) {
                 int k = in;
                 asm volatile("" : "+s"(k));
                 return apps.a[k].c_fold;
             };
-            slice_tiles<BIG>(lds_main, h, d, tl, cnt, unit, src, sink_of, issued, nsrc, run_on,
-                             mtn, bias_of, a.c_fold, wa0, wa1, wa2, wa3, cfv);
+            auto sink_i = [&]() __attribute__((always_inline)) { return sink_of(i); };
+            if (more) place(u, in, base, &sn, &ntn);
+            const SliceSrc nsrc = more ? slice_src(apps.a[in].W, apps.a[in].n_mt, sn) : src;
+            slice_tile<WK>(lds_main, h, d, tl, nt * kBN, min(kBN, cnt - nt * kBN), sl, src, sink_i,
+                           nsrc, more, sn, bias_of, ring, cfv);
             src = nsrc;
-            issued = run_on;
+            i = in;
+            sl = sn;
+            nt = ntn;
         }
-        if (!more) return;  // uniform
-        __syncthreads();  // the tile rows and list_s are read before they are rewritten
-        u = un;
-        i = in;
-        base = bn;
+    }
+    if constexpr (MANY && WK < 4) {
+        for (int i = 0; seek(kBigTiles, u, i, base); u += G) {
+            int sl, nt;
+            place(u, i, base, &sl, &nt);
+            list_of(i);
+            const EncApp& a = apps.a[i];
+            big_tile<WK>(lds_main, h, h_bytes, d, tl, cnt, nt, sl, a.W, a.n_mt, sink_of(i), a.c_fold);
+        }
     }
 }
 
@@ -2028,55 +2079,55 @@ __device__ __forceinline__ uint64_t wave_minmax_u64(uint64_t v) {
               op(readlane_u64(v, 32), readlane_u64(v, 48)));
 }
 
-// The pre-activation without bias of latent 256*mt + threadIdx.x for one
-// token: a plain fp32 dot product of the packed dictionary row with the
-// token row, the whole workgroup computing the 256 latents of slice mt
-// together.  The slice's K chunks of 64 (32 KB contiguous each in the
-// packed layout) are read with coalesced 16-byte loads: thread tid reads
-// pieces tid + 256 w (w = 0..7), elements 16 s + 8 g .. + 7 (s = tid >> 6,
-// g = (tid >> 5) & 1) of latent 32 w + (tid & 31), and keeps one partial
-// sum per latent; the 8 partials of a latent are added in a fixed order,
-// in pairs across lanes and then through LDS (part: 4 * 256 floats).
-__device__ __forceinline__ float slice_dot(const uint16_t* __restrict__ Wp,
-                                           const uint16_t* __restrict__ hrow, int32_t mt,
+// The pre-activation of latent 256*mt + threadIdx.x for one token, the workgroup
+// computing the 256 latents of slice mt together with the encode's own matrix
+// instruction in its order (bias first, then K ascending), so that a recomputed
+// value has the bits that the encode kernels gave it.  A wave takes 64 latents; the
+// token's row is every column of operand B, so a lane's accumulators hold the same
+// values in each of the 32 columns.  part: 256 floats of LDS.
+__device__ __forceinline__ float slice_pre(const uint16_t* __restrict__ Wp,
+                                           const uint16_t* __restrict__ hrow,
+                                           const float* __restrict__ c_fold, int32_t mt,
                                            int32_t n_mt, int32_t d, float* part) {
-    const int tid = threadIdx.x;
-    const int sg = tid >> 5;  // 2 s + g
-    const uint4* P = reinterpret_cast<const uint4*>(Wp) + static_cast<int64_t>(mt) * 2048 + tid;
+    const int tid = threadIdx.x, lane = lane_id(), wave = tid / kWave;
+    const int g = lane >> 5, j32 = lane & 31;
+    const uint4* P = reinterpret_cast<const uint4*>(Wp) + static_cast<int64_t>(mt) * 2048 +
+                     2 * wave * 256 + lane;
     const int64_t stride = static_cast<int64_t>(n_mt) * 2048;  // pieces per K chunk
-    const uint4* hr = reinterpret_cast<const uint4*>(hrow) + sg;
-    float acc[8];
+    const uint4* hr = reinterpret_cast<const uint4*>(hrow) + g;
+    // acc[a][r]: latent 64*wave + 32*a + 8*(r/4) + 4*g + r%4
+    const float* cf = c_fold + mt * kBM + 64 * wave + 4 * g;
+    f32x16_t acc[2];
 #pragma unroll
-    for (int w = 0; w < 8; ++w) acc[w] = 0.0f;
-    const int nK = d / 64;
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[a][r] = cf[32 * a + 8 * (r / 4) + r % 4];
+    const int nK = d / kBK;
 #pragma unroll 1
     for (int kc = 0; kc < nK; ++kc) {
-        const uint4 hv = hr[kc * 8];
-        uint4 wv[8];
+        uint4 hv[4], wv[2][4];
 #pragma unroll
-        for (int w = 0; w < 8; ++w) wv[w] = P[kc * stride + w * 256];
-        const uint32_t hw[4] = {hv.x, hv.y, hv.z, hv.w};
+        for (int s = 0; s < 4; ++s) {
+            hv[s] = hr[kc * 8 + 2 * s];
 #pragma unroll
-        for (int w = 0; w < 8; ++w) {
-            const uint32_t ww[4] = {wv[w].x, wv[w].y, wv[w].z, wv[w].w};
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                acc[w] = fmaf(lo_bf16(ww[e]), lo_bf16(hw[e]), acc[w]);
-                acc[w] = fmaf(hi_bf16(ww[e]), hi_bf16(hw[e]), acc[w]);
-            }
+            for (int a = 0; a < 2; ++a) wv[a][s] = P[kc * stride + a * 256 + s * 64];
         }
-    }
-    // lanes r and r + 32 hold the two halves g of one latent's elements
-    const int s = tid >> 6;
 #pragma unroll
-    for (int w = 0; w < 8; ++w) {
-        const float both = acc[w] + __shfl_xor(acc[w], 32, kWave);
-        if ((tid & 32) == 0) part[s * kBM + 32 * w + (tid & 31)] = both;
+        for (int s = 0; s < 4; ++s)
+#pragma unroll
+            for (int a = 0; a < 2; ++a)
+                acc[a] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(wv[a][s]),
+                                                                 as_bf16x8(hv[s]), acc[a], 0, 0, 0);
     }
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+            if (j32 == r) part[64 * wave + 32 * a + 8 * (r / 4) + 4 * g + r % 4] = acc[a][r];
     __syncthreads();
-    const float dot = (part[tid] + part[kBM + tid]) + (part[2 * kBM + tid] + part[3 * kBM + tid]);
+    const float pre = part[tid];
     __syncthreads();  // part is free for the next slice
-    return dot;
+    return pre;
 }
 
 // One workgroup per subscribed token.  Every thread gathers the candidates
@@ -2087,8 +2138,8 @@ __device__ __forceinline__ float slice_dot(const uint16_t* __restrict__ Wp,
 // check is repaired by the whole workgroup; wave 0 then writes each winner
 // at its rank.  When the candidates exceed the pool, the k-th best of the
 // first kPoolMax of them is a lower bound of the k-th best of all: the pool
-// is filled again with the candidates at or above it (a little below, so
-// that a repair finds what it needs; when exact ties leave that value floor
+// is filled again with the candidates at or above it (a little below; when
+// exact ties leave that value floor
 // where it was, the k-th composite (value, latent) itself), up to
 // kFloorRounds times.  n: the workgroup's slot of the app's token list.
 __device__ __forceinline__ void merge_token(
@@ -2103,7 +2154,7 @@ __device__ __forceinline__ void merge_token(
     __shared__ __align__(16) uint32_t K2[kWave];  // the selected k entries (k <= 64)
     __shared__ __align__(16) int32_t I2[kWave];
     __shared__ __align__(16) int hist_s[3][256];  // radix digit counts, 3 rounds in flight
-    __shared__ float part_s[4 * kBM];  // partial sums of a slice recompute
+    __shared__ float part_s[kBM];  // a recomputed slice
     __shared__ uint64_t cmin_s[kMergeWaves], cmax_s[kMergeWaves];
     __shared__ int sel_n_s;
     __shared__ int scan_s[2][kMergeWaves];  // gather rounds alternate between the two
@@ -2349,8 +2400,7 @@ __device__ __forceinline__ void merge_token(
         const uint64_t prefix = radix_kth(refill ? kPoolMax : total, &shift);
         if (refill) {
             // the k-th key is >= the prefix's key bits (the bits below its
-            // last digit are zero); step a little below it, as the repair's
-            // floor does
+            // last digit are zero); step a little below it
             const float fv = key_f32(static_cast<uint32_t>(prefix >> 32));
             uint64_t fl = static_cast<uint64_t>(f32_key(fv - fabsf(fv) * 0x1p-11f)) << 32;
             if (fl <= floor_c) {
@@ -2390,8 +2440,8 @@ __device__ __forceinline__ void merge_token(
     const uint32_t sel_tau = wave_minmax_u32<false>(lane < k ? wk : 0xFFFFFFFFu);
     const int fix = !fits ? 2 : (tau_tiles <= sel_tau ? 0 : 1);
     if (fix != 0) {  // uniform
-        // Repair: whole slices are recomputed exactly (fp32 dot products,
-        // the workgroup streaming each slice once).  A slice hides only
+        // Repair: whole slices are recomputed (the workgroup streaming each
+        // slice once).  A slice hides only
         // values below its threshold, none of them at a latent below its
         // first: that composite bound says whether it can hide a winner.
         // The pool is cut down to what can still reach the top k; then the
@@ -2433,14 +2483,8 @@ __device__ __forceinline__ void merge_token(
         };
         bool all = total > kPoolMax;  // uniform: the pool misses candidates
         if (!all && wave == 0) {
-            // with a selection, a little below its k-th value, so that a
-            // value whose recomputed rounding differs from the GEMM's still
-            // enters; without one, the whole pool
-            uint32_t fl = 0u;
-            if (fix == 1) {
-                const float tv = key_f32(sel_tau);
-                fl = f32_key(tv - fabsf(tv) * 0x1p-12f);
-            }
+            // with a selection, its k-th value; without one, the whole pool
+            const uint32_t fl = fix == 1 ? sel_tau : 0u;
             const int out = cut_pool(total, fl, -1);
             if (lane == 0) {
                 pool_n_s = out;
@@ -2478,8 +2522,7 @@ __device__ __forceinline__ void merge_token(
                 }
                 __syncthreads();
                 const int32_t j = q * kBM + tid;
-                const float dot = slice_dot(Wp, hrow, q, n_mt, d, part_s);
-                const uint32_t key = f32_key(dot + c_fold[j]);
+                const uint32_t key = f32_key(slice_pre(Wp, hrow, c_fold, q, n_mt, d, part_s));
                 if (key >= floor_s) {
                     const int pos = atomicAdd(&pool_n_s, 1);
                     K[pos] = key;
@@ -2528,7 +2571,7 @@ __device__ __forceinline__ void merge_token(
                     I[lane] = b;
                 }
             }
-            all = pn < k;  // (rounding) redo every slice
+            all = pn < k;  // (fewer than k candidates) redo every slice
         }
         if (all) {  // uniform
             __syncthreads();  // every thread has read the pool size
@@ -2539,8 +2582,7 @@ __device__ __forceinline__ void merge_token(
             __syncthreads();
             for (int q = 0; q < n_mt; ++q) {
                 const int32_t j = q * kBM + tid;
-                const float dot = slice_dot(Wp, hrow, q, n_mt, d, part_s);
-                const uint32_t key = f32_key(dot + c_fold[j]);
+                const uint32_t key = f32_key(slice_pre(Wp, hrow, c_fold, q, n_mt, d, part_s));
                 if (key >= floor_s) {
                     const int pos = atomicAdd(&pool_n_s, 1);
                     K[pos] = key;
@@ -2698,26 +2740,28 @@ static int32_t cu_count() {
     return n;
 }
 
-// Slices that one 256-latent tile is cut into (see narrow_tile): as many as
-// keep the workgroups at 256 or fewer.  A CU alone draws about 45 GB/s, so 160
-// whole slices saturate HBM and more than 128 are left whole; batches of more
-// than 512 slots keep whole slices too, which keeps the candidate area of
-// every call that fitted the static workspace within it.
-static int32_t slice_cut(int32_t T_max, int32_t d, int32_t m) {
-    const int32_t n_mt = m / kBM;
+// Slices that one 256-latent tile is cut into (see narrow_tile), for a launch of
+// n_mt tiles: as many as keep the workgroups at 256 or fewer.  A CU alone draws
+// about 45 GB/s, so 160 whole slices saturate HBM and more than 128 are left whole;
+// the apps of a batched call count together (eight dictionaries of 16384 latents,
+// 102 tokens of width 2048 each: 275 us cut by each one's own slices, 148 whole).
+// Batches of more than 512 slots keep whole slices too, which keeps the candidate
+// area of every call that fitted the static workspace within it.
+static int32_t slice_cut(int32_t T_max, int32_t d, int64_t n_mt) {
     if (T_max > 512 || static_cast<int64_t>(T_max) * d * 2 > 0x7FFFFFFF) return 1;
     return n_mt <= 64 ? 4 : n_mt <= 128 ? 2 : 1;
 }
 
-// Whether big token tiles are compiled in (their buffer offsets are 32 bits).
-static bool big_possible(int32_t T_max, int32_t d) {
-    return T_max > kBN && static_cast<int64_t>(T_max) * d * 2 <= 0x7FFFFFFF;
-}
+// Whether an app may have several token tiles, big ones among them (whose buffer
+// offsets are 32 bits).
+static bool many_tiles(int32_t T_max) { return T_max > kBN; }
 
-// Most workgroups an app's candidates can use.
-static int32_t enc_units(int32_t T_max, int32_t d, int32_t n_mt, int32_t n_sl) {
-    const int32_t big = big_possible(T_max, d) && n_sl <= 2 * n_mt ? n_mt * ((T_max + kBigTok - 1) / kBigTok) : 0;
-    return n_sl > big ? n_sl : big;
+// Workgroups for an app's candidates: one per unit, at most one per CU where the
+// token tiles are several.
+static int32_t enc_grid(int32_t T_max, int64_t n_sl) {
+    if (!many_tiles(T_max) || n_sl >= cu_count()) return static_cast<int32_t>(n_sl);
+    const int64_t units = n_sl * ((T_max + kBN - 1) / kBN);
+    return static_cast<int32_t>(units < cu_count() ? units : cu_count());
 }
 
 struct CandArea {
@@ -2740,7 +2784,7 @@ static int32_t stage_tokens(int32_t T_max) {
 }
 
 static size_t candidate_bytes(int32_t T_max, int32_t d, int32_t m, int32_t k) {
-    const int32_t cut = slice_cut(T_max, d, m);
+    const int32_t cut = slice_cut(T_max, d, m / kBM);
     const size_t slots = static_cast<size_t>(T_max) * (m / kBM * cut);
     return slots * (static_cast<size_t>(emit_cap(m, k, kBM / cut)) * 8u + 8u);
 }
@@ -2772,11 +2816,10 @@ hipError_t launch_sae_candidates(const uint16_t* h, int32_t d, int32_t T_max,
                                  const uint16_t* W_enc, const float* c_fold, int32_t m,
                                  int32_t k, void* cand, hipStream_t stream,
                                  const RouteIn* route) {
-    const int32_t n_mt = m / kBM, cut = slice_cut(T_max, d, m), n_sl = n_mt * cut;
+    const int32_t n_mt = m / kBM, cut = slice_cut(T_max, d, n_mt), n_sl = n_mt * cut;
     const EmitPlan e = emit_plan(m, k, kBM / cut);
     const CandArea a = cand_area(cand, T_max, n_sl, e.cap);
-    int32_t grid = enc_units(T_max, d, n_mt, n_sl);
-    if (grid > n_sl) grid = n_sl > cu_count() ? n_sl : grid < cu_count() ? grid : cu_count();
+    const int32_t grid = enc_grid(T_max, n_sl);
     // the decode kernel routes when the batch fits its LDS list and its grid
     // has a workgroup for every app to publish
     if (route && (T_max > kRouteMaxT || grid < route->n_apps)) {
@@ -2810,10 +2853,10 @@ hipError_t launch_sae_candidates(const uint16_t* h, int32_t d, int32_t T_max,
     }
     const RouteIn none{};
     const RouteIn& ri = route ? *route : none;
-    const bool big = big_possible(T_max, d);
-    const auto kernel = cut == 4   ? sae_stream_kernel<4, false>
-                        : cut == 2 ? (big ? sae_stream_kernel<2, true> : sae_stream_kernel<2, false>)
-                                   : (big ? sae_stream_kernel<1, true> : sae_stream_kernel<1, false>);
+    const bool many = many_tiles(T_max);
+    const auto kernel = cut == 4   ? (many ? sae_stream_kernel<4, true> : sae_stream_kernel<4, false>)
+                        : cut == 2 ? (many ? sae_stream_kernel<2, true> : sae_stream_kernel<2, false>)
+                                   : (many ? sae_stream_kernel<1, true> : sae_stream_kernel<1, false>);
     hipLaunchKernelGGL(kernel, dim3(grid), dim3(kEncThreads), 0, stream, h, d, app_count, tok_list,
                        W_enc, c_fold, n_mt, T_max, e.z, e.lo, e.cap, a.cand, a.cnt, a.tau, ri.req,
                        ri.T_valid, ri.sub, ri.R_max, ri.n_apps, ri.app_bit, ri.tok_mask,
@@ -2826,7 +2869,7 @@ hipError_t launch_sae_merge(const uint16_t* h, int32_t d, int32_t T_max,
                             const uint16_t* W_enc, const float* c_fold, int32_t m, int32_t k,
                             int32_t* idx_out, uint16_t* val_out, void* cand,
                             const MergeRing* ring, hipStream_t stream) {
-    const int32_t n_mt = m / kBM, cut = slice_cut(T_max, d, m), n_sl = n_mt * cut;
+    const int32_t n_mt = m / kBM, cut = slice_cut(T_max, d, n_mt), n_sl = n_mt * cut;
     const int cap = emit_cap(m, k, kBM / cut);
     const CandArea a = cand_area(cand, T_max, n_sl, cap);
     RingOut r{};
@@ -2850,27 +2893,26 @@ bool sae_multi_supported(int32_t T_max) { return T_max < kPrefillMinT; }
 hipError_t launch_sae_encode_multi(const uint16_t* h, int32_t d, int32_t T_max, int32_t n,
                                    const SaeAppIn* apps, hipStream_t stream,
                                    const RouteIn* route) {
-    const bool big = big_possible(T_max, d);
+    const bool many = many_tiles(T_max);
     for (int32_t c0 = 0; c0 < n; c0 += kMultiMax) {
         const int32_t nc = n - c0 < kMultiMax ? n - c0 : kMultiMax;
-        // whole slices and cut ones in a launch each (most batches are of one
-        // kind): together they would not fit the registers
-        EncApps ea[2];
+        // one cut for all: by the slices of the batch together, so no app's is
+        // finer than a call of its own has, whose workspace it fits
+        int64_t n_all = 0;
+        for (int32_t i = 0; i < nc; ++i) n_all += apps[c0 + i].m / kBM;
+        const int32_t cut = slice_cut(T_max, d, n_all);
+        EncApps ea;
         MergeApps ma;
-        memset(ea, 0, sizeof(ea));
+        memset(&ea, 0, sizeof(ea));
         memset(&ma, 0, sizeof(ma));
-        int32_t units[2] = {0, 0};
+        ea.n = nc;
         for (int32_t i = 0; i < nc; ++i) {
             const SaeAppIn& in = apps[c0 + i];
-            const int32_t n_mt = in.m / kBM, cut = slice_cut(T_max, d, in.m);
-            const int32_t n_sl = n_mt * cut;
+            const int32_t n_mt = in.m / kBM, n_sl = n_mt * cut;
             const EmitPlan e = emit_plan(in.m, in.k, kBM / cut);
             const CandArea a = cand_area(in.cand, T_max, n_sl, e.cap);
-            const int kind = cut > 1 ? 1 : 0;
-            ea[kind].a[ea[kind].n++] =
-                EncApp{in.app_count, in.tok_list, in.W, in.c_fold, a.cand, a.cnt, a.tau,
-                       n_mt, n_sl, e.lo, e.cap, in.bit, e.z};
-            units[kind] += enc_units(T_max, d, n_mt, n_sl);
+            ea.a[i] = EncApp{in.app_count, in.tok_list, in.W, in.c_fold, a.cand, a.cnt, a.tau,
+                             n_mt, e.lo, e.cap, in.bit, e.z};
             RingOut r{};
             if (in.ring) {
                 r.slots = in.ring->slots;
@@ -2885,9 +2927,8 @@ hipError_t launch_sae_encode_multi(const uint16_t* h, int32_t d, int32_t T_max, 
                                in.idx_out, in.val_out, r, n_sl, n_mt, e.cap, in.k};
         }
         // the first launch builds the routing when the batch fits its LDS list
-        // and its grid has a workgroup for every app to publish
         const RouteIn* ri = c0 == 0 ? route : nullptr;
-        if (ri && (T_max > kRouteMaxT || units[0] + units[1] < ri->n_apps)) {
+        if (ri && T_max > kRouteMaxT) {
             const hipError_t r = launch_route_build(ri->req, ri->T_valid, ri->sub, ri->R_max,
                                                     T_max, ri->n_apps, ri->tok_mask,
                                                     ri->app_count, ri->app_tokens,
@@ -2895,25 +2936,21 @@ hipError_t launch_sae_encode_multi(const uint16_t* h, int32_t d, int32_t T_max, 
             if (r != hipSuccess) return r;
             ri = nullptr;
         }
-        hipError_t e = hipSuccess;
-        for (int kind = 0; kind < 2; ++kind) {
-            if (ea[kind].n == 0) continue;
-            const RouteIn none{};
-            const RouteIn& rr = ri ? *ri : none;
-            // persistent: one workgroup per CU (and one per app to publish)
-            int32_t g = units[kind] < cu_count() ? units[kind] : cu_count();
-            if (ri && g < ri->n_apps) g = ri->n_apps;
-            const auto kernel =
-                kind ? (big ? sae_stream_apps_kernel<true, true> : sae_stream_apps_kernel<true, false>)
-                     : (big ? sae_stream_apps_kernel<false, true>
-                            : sae_stream_apps_kernel<false, false>);
-            hipLaunchKernelGGL(kernel, dim3(g), dim3(kEncThreads), 0, stream, h, d, ea[kind],
-                               rr.req, rr.T_valid, rr.sub, rr.R_max, T_max, rr.n_apps,
-                               rr.tok_mask, rr.app_count, rr.app_tokens, rr.err_word);
-            e = hipGetLastError();
-            if (e != hipSuccess) return e;
-            ri = nullptr;  // the routing is built
-        }
+        const RouteIn none{};
+        const RouteIn& rr = ri ? *ri : none;
+        // persistent: one workgroup per CU (and one per app to publish)
+        const int64_t units = n_all * cut * (many ? (T_max + kBN - 1) / kBN : 1);
+        int32_t g = units < cu_count() ? static_cast<int32_t>(units) : cu_count();
+        if (ri && g < ri->n_apps) g = ri->n_apps;
+        const auto kernel =
+            cut == 4   ? (many ? sae_stream_apps_kernel<4, true> : sae_stream_apps_kernel<4, false>)
+            : cut == 2 ? (many ? sae_stream_apps_kernel<2, true> : sae_stream_apps_kernel<2, false>)
+                       : (many ? sae_stream_apps_kernel<1, true> : sae_stream_apps_kernel<1, false>);
+        hipLaunchKernelGGL(kernel, dim3(g), dim3(kEncThreads), 0, stream, h, d, ea, rr.req,
+                           rr.T_valid, rr.sub, rr.R_max, T_max, rr.n_apps, rr.tok_mask,
+                           rr.app_count, rr.app_tokens, rr.err_word);
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
         // persistent merges: up to four workgroups per CU
         const int32_t mg = nc * T_max < 4 * cu_count() ? nc * T_max : 4 * cu_count();
         hipLaunchKernelGGL(sae_merge_apps_kernel, dim3(mg), dim3(kMergeThreads), 0, stream, h, d,
@@ -2972,14 +3009,17 @@ void add_sae_kernels(std::vector<KernelInfo>& t) {
     t.push_back(kernel_info(sae_stream_kernel<2, false>));
     t.push_back(kernel_info(sae_stream_kernel<2, true>));
     t.push_back(kernel_info(sae_stream_kernel<4, false>));
+    t.push_back(kernel_info(sae_stream_kernel<4, true>));
     t.push_back(kernel_info(sae_xstage_kernel));
     t.push_back(kernel_info(sae_gemm_kernel));
     t.push_back(kernel_info(sae_merge_kernel));
     t.push_back(kernel_info(sae_merge_apps_kernel));
-    t.push_back(kernel_info(sae_stream_apps_kernel<false, false>));
-    t.push_back(kernel_info(sae_stream_apps_kernel<false, true>));
-    t.push_back(kernel_info(sae_stream_apps_kernel<true, false>));
-    t.push_back(kernel_info(sae_stream_apps_kernel<true, true>));
+    t.push_back(kernel_info(sae_stream_apps_kernel<1, false>));
+    t.push_back(kernel_info(sae_stream_apps_kernel<1, true>));
+    t.push_back(kernel_info(sae_stream_apps_kernel<2, false>));
+    t.push_back(kernel_info(sae_stream_apps_kernel<2, true>));
+    t.push_back(kernel_info(sae_stream_apps_kernel<4, false>));
+    t.push_back(kernel_info(sae_stream_apps_kernel<4, true>));
 }
 
 }  // namespace xmix
