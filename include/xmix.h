@@ -323,7 +323,11 @@ xmix_status xmix_probe_score(const void *h, xmix_dtype dt, int32_t d, const xmix
  * exact.
  * Requires d % 256 == 0, m % 256 == 0, 1 <= k <= min(64, m),
  * (m / 256) * k <= 16384.
- * ws: at least xmix_sae_encode_workspace(T_max, d, m, k) bytes.
+ * ws: at least xmix_sae_encode_workspace(T_max, d, m, k) bytes, which also serve
+ * every call of no more token slots, width and k on the same dictionary size.  (The
+ * size allows for the finest cut of the work; a workspace that holds a coarser one
+ * is taken too, and only one that holds none is refused.  The two stages of an
+ * encode are given the same ws_bytes.)
  * Errors: XMIX_E_INVAL (null pointer, bad size, a dictionary struct not made
  * by xmix_sae_pack_encoder or of another width), XMIX_E_UNSUPPORTED (too
  * many candidates per token), XMIX_E_WORKSPACE. */

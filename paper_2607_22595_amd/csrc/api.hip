@@ -43,6 +43,11 @@ bool dict_ok(const xmix_sae_dict* w, int32_t d) {
            (d < 0 || w->d == d);
 }
 
+// The folded bias (used when the caller passes none) at the start of a workspace.
+size_t fold_bytes(int32_t m) {
+    return (static_cast<size_t>(m) * sizeof(float) + 255u) / 256u * 256u;
+}
+
 const int32_t* app_list(const xmix_route* rt, int32_t a) {
     return rt->app_tokens + static_cast<int64_t>(a) * rt->T_max;
 }
@@ -206,10 +211,13 @@ xmix_status xmix_probe_score(const void* h, xmix_dtype dt, int32_t d, const xmix
 
 size_t xmix_sae_encode_workspace(int32_t T_max, int32_t d, int32_t m, int32_t k) {
     if (T_max < 1 || d < 1 || m < 256 || k < 1) return 0;
-    // folded bias (used when the caller passes none), then the candidates
-    // (and, for many token slots, the staged token rows)
-    const size_t fold = (static_cast<size_t>(m) * sizeof(float) + 255u) / 256u * 256u;
-    return fold + sae_candidate_bytes(T_max, d, m, k);
+    size_t bytes = sae_candidate_bytes(T_max, d, m, k);
+    // with room for the cut slices of a smaller batch, which may need more
+    if (T_max > kMaxCutSlots) {
+        const size_t cut = sae_candidate_bytes(kMaxCutSlots, 256, m, k);
+        bytes = cut > bytes ? cut : bytes;
+    }
+    return fold_bytes(m) + bytes;
 }
 
 xmix_status xmix_sae_pack_encoder(const uint16_t* W_enc, int32_t m, int32_t d,
@@ -242,10 +250,11 @@ xmix_status xmix_sae_fold_bias(const xmix_sae_dict* dict, const uint16_t* b_enc,
 namespace {
 
 // Checks shared by the encode entry points; returns the folded-bias area
-// and the candidate area of the workspace.
+// and the candidate area of the workspace.  A workspace too small for the cut of
+// slices that xmix_sae_encode_workspace counts on is taken if it holds whole ones.
 xmix_status encode_args(const uint16_t* h, int32_t d, const xmix_route* rt, int32_t app_bit,
                         const xmix_sae_dict* dict, int32_t k, void* ws, size_t ws_bytes,
-                        float** fold, void** cand) {
+                        float** fold, void** cand, size_t* cand_bytes) {
     if (!route_ok(rt) || app_bit < 0 || app_bit >= rt->n_apps) return XMIX_E_INVAL;
     if (!h || !aligned16(h) || d < 256 || d % 256 != 0) return XMIX_E_INVAL;
     if (!dict_ok(dict, d)) return XMIX_E_INVAL;
@@ -253,11 +262,11 @@ xmix_status encode_args(const uint16_t* h, int32_t d, const xmix_route* rt, int3
     if (k < 1 || k > XMIX_MAX_TOPK || k > m) return XMIX_E_INVAL;
     // the merge keeps (m / 256) * k candidates per token in registers
     if (static_cast<int64_t>(m / 256) * k > 64 * 256) return XMIX_E_UNSUPPORTED;
-    const size_t need = xmix_sae_encode_workspace(rt->T_max, d, m, k);
+    const size_t need = fold_bytes(m) + sae_whole_bytes(rt->T_max, d, m, k);
     if (!ws || ws_bytes < need || !aligned16(ws)) return XMIX_E_WORKSPACE;
-    const size_t fold_bytes = (static_cast<size_t>(m) * sizeof(float) + 255u) / 256u * 256u;
     *fold = static_cast<float*>(ws);
-    *cand = static_cast<char*>(ws) + fold_bytes;
+    *cand = static_cast<char*>(ws) + fold_bytes(m);
+    *cand_bytes = ws_bytes - fold_bytes(m);
     return XMIX_OK;
 }
 
@@ -273,7 +282,9 @@ xmix_status xmix_sae_encode_candidates(const uint16_t* h, int32_t d, const xmix_
     if (!c_fold && (!b_enc || !b_dec || !aligned16(b_dec))) return XMIX_E_INVAL;
     float* fold;
     void* cand;
-    const xmix_status st = encode_args(h, d, rt, app_bit, dict, k, ws, ws_bytes, &fold, &cand);
+    size_t cand_bytes;
+    const xmix_status st =
+        encode_args(h, d, rt, app_bit, dict, k, ws, ws_bytes, &fold, &cand, &cand_bytes);
     if (st != XMIX_OK) return st;
     hipStream_t s = as_stream(stream);
     const int32_t m = dict->m;
@@ -284,7 +295,7 @@ xmix_status xmix_sae_encode_candidates(const uint16_t* h, int32_t d, const xmix_
     }
     return launched(launch_sae_candidates(h, d, rt->T_max, rt->app_count + app_bit,
                                           app_list(rt, app_bit), dict->pieces, c_fold, m, k,
-                                          cand, s));
+                                          cand, cand_bytes, s));
 }
 
 xmix_status xmix_route_sae_encode_candidates(const int32_t* req_of_token, const int32_t* T_valid,
@@ -299,7 +310,9 @@ xmix_status xmix_route_sae_encode_candidates(const int32_t* req_of_token, const 
     if (!c_fold && (!b_enc || !b_dec || !aligned16(b_dec))) return XMIX_E_INVAL;
     float* fold;
     void* cand;
-    const xmix_status st = encode_args(h, d, rt, app_bit, dict, k, ws, ws_bytes, &fold, &cand);
+    size_t cand_bytes;
+    const xmix_status st =
+        encode_args(h, d, rt, app_bit, dict, k, ws, ws_bytes, &fold, &cand, &cand_bytes);
     if (st != XMIX_OK) return st;
     hipStream_t s = as_stream(stream);
     const int32_t m = dict->m;
@@ -321,7 +334,7 @@ xmix_status xmix_route_sae_encode_candidates(const int32_t* req_of_token, const 
     r.err_word = err_word;
     return launched(launch_sae_candidates(h, d, rt->T_max, rt->app_count + app_bit,
                                           app_list(rt, app_bit), dict->pieces, c_fold, m, k,
-                                          cand, s, &r));
+                                          cand, cand_bytes, s, &r));
 }
 
 xmix_status xmix_sae_merge_topk(const uint16_t* h, int32_t d, const xmix_route* rt,
@@ -331,12 +344,14 @@ xmix_status xmix_sae_merge_topk(const uint16_t* h, int32_t d, const xmix_route* 
     if (!idx_out || !val_out) return XMIX_E_INVAL;
     float* fold;
     void* cand;
-    const xmix_status st = encode_args(h, d, rt, app_bit, dict, k, ws, ws_bytes, &fold, &cand);
+    size_t cand_bytes;
+    const xmix_status st =
+        encode_args(h, d, rt, app_bit, dict, k, ws, ws_bytes, &fold, &cand, &cand_bytes);
     if (st != XMIX_OK) return st;
     return launched(launch_sae_merge(h, d, rt->T_max, rt->app_count + app_bit,
                                      app_list(rt, app_bit), dict->pieces,
                                      c_fold ? c_fold : fold, dict->m, k, idx_out, val_out, cand,
-                                     nullptr, as_stream(stream)));
+                                     cand_bytes, nullptr, as_stream(stream)));
 }
 
 xmix_status xmix_sae_merge_topk_ring(const uint16_t* h, int32_t d, const xmix_route* rt,
@@ -352,7 +367,9 @@ xmix_status xmix_sae_merge_topk_ring(const uint16_t* h, int32_t d, const xmix_ro
         return XMIX_E_INVAL;
     float* fold;
     void* cand;
-    const xmix_status st = encode_args(h, d, rt, app_bit, dict, k, ws, ws_bytes, &fold, &cand);
+    size_t cand_bytes;
+    const xmix_status st =
+        encode_args(h, d, rt, app_bit, dict, k, ws, ws_bytes, &fold, &cand, &cand_bytes);
     if (st != XMIX_OK) return st;
     MergeRing r;
     r.slots = ring->slots;
@@ -365,7 +382,7 @@ xmix_status xmix_sae_merge_topk_ring(const uint16_t* h, int32_t d, const xmix_ro
     return launched(launch_sae_merge(h, d, rt->T_max, rt->app_count + app_bit,
                                      app_list(rt, app_bit), dict->pieces,
                                      c_fold ? c_fold : fold, dict->m, k, idx_out, val_out, cand,
-                                     &r, as_stream(stream)));
+                                     cand_bytes, &r, as_stream(stream)));
 }
 
 xmix_status xmix_sae_encode_topk_ring(const uint16_t* h, int32_t d, const xmix_route* rt,
@@ -422,8 +439,9 @@ xmix_status encode_multi(const uint16_t* h, int32_t d, const xmix_route* rt, int
         if (!a.c_fold && (!a.b_enc || !a.b_dec || !aligned16(a.b_dec))) return XMIX_E_INVAL;
         if (a.ring && (!req_of_token || !ring_ok(a.ring, a.k))) return XMIX_E_INVAL;
         void* cand;
-        const xmix_status st =
-            encode_args(h, d, rt, a.app_bit, a.dict, a.k, a.ws, a.ws_bytes, &fold[i], &cand);
+        size_t cand_bytes;
+        const xmix_status st = encode_args(h, d, rt, a.app_bit, a.dict, a.k, a.ws, a.ws_bytes,
+                                           &fold[i], &cand, &cand_bytes);
         if (st != XMIX_OK) return st;
         if (a.ring) {
             rings[i] = MergeRing{a.ring->slots, a.ring->head, a.ring->capacity,
@@ -431,7 +449,7 @@ xmix_status encode_multi(const uint16_t* h, int32_t d, const xmix_route* rt, int
         }
         in[i] = SaeAppIn{rt->app_count + a.app_bit, app_list(rt, a.app_bit), a.dict->pieces,
                          a.c_fold ? a.c_fold : fold[i], a.dict->m, a.k, a.app_bit, cand,
-                         a.idx_out, a.val_out, a.ring ? &rings[i] : nullptr};
+                         cand_bytes, a.idx_out, a.val_out, a.ring ? &rings[i] : nullptr};
     }
     for (int32_t i = 0; i < n; ++i) {
         const xmix_sae_app& a = apps[i];
@@ -444,9 +462,10 @@ xmix_status encode_multi(const uint16_t* h, int32_t d, const xmix_route* rt, int
     for (int32_t i = 0; i < n; ++i) {  // many token slots: one app after the other
         const SaeAppIn& a = in[i];
         if (launch_sae_candidates(h, d, rt->T_max, a.app_count, a.tok_list, a.W, a.c_fold, a.m,
-                                  a.k, a.cand, s, i == 0 ? route : nullptr) != hipSuccess ||
+                                  a.k, a.cand, a.cand_bytes, s, i == 0 ? route : nullptr) !=
+                hipSuccess ||
             launch_sae_merge(h, d, rt->T_max, a.app_count, a.tok_list, a.W, a.c_fold, a.m, a.k,
-                             a.idx_out, a.val_out, a.cand, a.ring, s) != hipSuccess)
+                             a.idx_out, a.val_out, a.cand, a.cand_bytes, a.ring, s) != hipSuccess)
             return XMIX_E_LAUNCH;
     }
     return XMIX_OK;

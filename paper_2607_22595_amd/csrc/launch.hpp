@@ -55,6 +55,12 @@ hipError_t launch_probe(const void* h, bool bf16, int32_t d, int32_t T_max,
                         const int32_t* cu_seqlens, int32_t R_max, float* logit, float* score,
                         float* ws, hipStream_t stream);
 
+// Bytes that an encode of these sizes uses for its candidates and, for many token
+// slots, the staged token rows: of whole slices, and of slices cut where that is the
+// faster (up to kMaxCutSlots token slots and kMaxCutLatents latents).  An encode with
+// at least the former in its candidate area (cand_bytes) runs, on the cut that fits.
+constexpr int32_t kMaxCutSlots = 512, kMaxCutLatents = 32768;
+size_t sae_whole_bytes(int32_t T_max, int32_t d, int32_t m, int32_t k);
 size_t sae_candidate_bytes(int32_t T_max, int32_t d, int32_t m, int32_t k);
 hipError_t launch_sae_pack(const uint16_t* W_enc, int32_t m, int32_t d, uint16_t* W_packed,
                            hipStream_t stream);
@@ -85,7 +91,7 @@ hipError_t launch_steer_probe(void* h, bool bf16, int32_t d, int32_t T_max,
 hipError_t launch_sae_candidates(const uint16_t* h, int32_t d, int32_t T_max,
                                  const int32_t* app_count, const int32_t* tok_list,
                                  const uint16_t* W_enc, const float* c_fold, int32_t m,
-                                 int32_t k, void* cand, hipStream_t stream,
+                                 int32_t k, void* cand, size_t cand_bytes, hipStream_t stream,
                                  const RouteIn* route = nullptr);
 struct MergeRing {  // readback of the merged rows into a ring
     uint8_t* slots;
@@ -97,7 +103,7 @@ struct MergeRing {  // readback of the merged rows into a ring
 hipError_t launch_sae_merge(const uint16_t* h, int32_t d, int32_t T_max,
                             const int32_t* app_count, const int32_t* tok_list,
                             const uint16_t* W_enc, const float* c_fold, int32_t m, int32_t k,
-                            int32_t* idx_out, uint16_t* val_out, void* cand,
+                            int32_t* idx_out, uint16_t* val_out, void* cand, size_t cand_bytes,
                             const MergeRing* ring, hipStream_t stream);
 // One SAE app of a batched encode: its list, dictionary, folded bias,
 // candidate area, outputs and optional ring.
@@ -108,6 +114,7 @@ struct SaeAppIn {
     const float* c_fold;
     int32_t m, k, bit;
     void* cand;
+    size_t cand_bytes;
     int32_t* idx_out;
     uint16_t* val_out;
     const MergeRing* ring;

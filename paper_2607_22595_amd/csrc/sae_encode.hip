@@ -2748,7 +2748,8 @@ static int32_t cu_count() {
 // Batches of more than 512 slots keep whole slices too, which keeps the candidate
 // area of every call that fitted the static workspace within it.
 static int32_t slice_cut(int32_t T_max, int32_t d, int64_t n_mt) {
-    if (T_max > 512 || static_cast<int64_t>(T_max) * d * 2 > 0x7FFFFFFF) return 1;
+    static_assert(kMaxCutLatents == 128 * kBM, "the last dictionary that is cut");
+    if (T_max > kMaxCutSlots || static_cast<int64_t>(T_max) * d * 2 > 0x7FFFFFFF) return 1;
     return n_mt <= 64 ? 4 : n_mt <= 128 ? 2 : 1;
 }
 
@@ -2783,17 +2784,31 @@ static int32_t stage_tokens(int32_t T_max) {
     return (T_max + kGemmTok - 1) / kGemmTok * kGemmTok;
 }
 
-static size_t candidate_bytes(int32_t T_max, int32_t d, int32_t m, int32_t k) {
-    const int32_t cut = slice_cut(T_max, d, m / kBM);
+static size_t area_bytes(int32_t T_max, int32_t m, int32_t k, int32_t cut) {
     const size_t slots = static_cast<size_t>(T_max) * (m / kBM * cut);
     return slots * (static_cast<size_t>(emit_cap(m, k, kBM / cut)) * 8u + 8u);
 }
 
-size_t sae_candidate_bytes(int32_t T_max, int32_t d, int32_t m, int32_t k) {
-    size_t bytes = (candidate_bytes(T_max, d, m, k) + 255u) / 256u * 256u;
+// The cut that an area of `bytes` holds, at most `cut` (a finer one needs more, and
+// every accepted area holds whole slices).
+static int32_t fit_cut(int32_t T_max, int32_t m, int32_t k, int32_t cut, size_t bytes) {
+    while (cut > 1 && area_bytes(T_max, m, k, cut) > bytes) cut /= 2;
+    return cut;
+}
+
+static size_t sae_bytes(int32_t T_max, int32_t d, int32_t m, int32_t k, int32_t cut) {
+    size_t bytes = (area_bytes(T_max, m, k, cut) + 255u) / 256u * 256u;
     if (T_max >= kPrefillMinT)  // staged token rows of the prefill GEMM
         bytes += static_cast<size_t>(stage_tokens(T_max)) * d * sizeof(uint16_t);
     return bytes;
+}
+
+size_t sae_whole_bytes(int32_t T_max, int32_t d, int32_t m, int32_t k) {
+    return sae_bytes(T_max, d, m, k, 1);
+}
+
+size_t sae_candidate_bytes(int32_t T_max, int32_t d, int32_t m, int32_t k) {
+    return sae_bytes(T_max, d, m, k, slice_cut(T_max, d, m / kBM));
 }
 
 hipError_t launch_sae_pack(const uint16_t* W_enc, int32_t m, int32_t d, uint16_t* W_packed,
@@ -2814,9 +2829,11 @@ hipError_t launch_sae_fold(const uint16_t* W_enc, const uint16_t* b_enc, const u
 hipError_t launch_sae_candidates(const uint16_t* h, int32_t d, int32_t T_max,
                                  const int32_t* app_count, const int32_t* tok_list,
                                  const uint16_t* W_enc, const float* c_fold, int32_t m,
-                                 int32_t k, void* cand, hipStream_t stream,
+                                 int32_t k, void* cand, size_t cand_bytes, hipStream_t stream,
                                  const RouteIn* route) {
-    const int32_t n_mt = m / kBM, cut = slice_cut(T_max, d, n_mt), n_sl = n_mt * cut;
+    const int32_t n_mt = m / kBM;
+    const int32_t cut = fit_cut(T_max, m, k, slice_cut(T_max, d, n_mt), cand_bytes);
+    const int32_t n_sl = n_mt * cut;
     const EmitPlan e = emit_plan(m, k, kBM / cut);
     const CandArea a = cand_area(cand, T_max, n_sl, e.cap);
     const int32_t grid = enc_grid(T_max, n_sl);
@@ -2833,7 +2850,7 @@ hipError_t launch_sae_candidates(const uint16_t* h, int32_t d, int32_t T_max,
     if (T_max >= kPrefillMinT) {
         const int32_t n_pad = stage_tokens(T_max);
         uint16_t* xs = reinterpret_cast<uint16_t*>(
-            static_cast<char*>(cand) + (candidate_bytes(T_max, d, m, k) + 255u) / 256u * 256u);
+            static_cast<char*>(cand) + (area_bytes(T_max, m, k, cut) + 255u) / 256u * 256u);
         const int64_t pieces = static_cast<int64_t>(n_pad) * (d / 8);
         hipLaunchKernelGGL(sae_xstage_kernel, dim3(static_cast<uint32_t>((pieces + 255) / 256)),
                            dim3(256), 0, stream, h, d, app_count, tok_list, n_pad, xs);
@@ -2867,9 +2884,11 @@ hipError_t launch_sae_candidates(const uint16_t* h, int32_t d, int32_t T_max,
 hipError_t launch_sae_merge(const uint16_t* h, int32_t d, int32_t T_max,
                             const int32_t* app_count, const int32_t* tok_list,
                             const uint16_t* W_enc, const float* c_fold, int32_t m, int32_t k,
-                            int32_t* idx_out, uint16_t* val_out, void* cand,
+                            int32_t* idx_out, uint16_t* val_out, void* cand, size_t cand_bytes,
                             const MergeRing* ring, hipStream_t stream) {
-    const int32_t n_mt = m / kBM, cut = slice_cut(T_max, d, n_mt), n_sl = n_mt * cut;
+    const int32_t n_mt = m / kBM;
+    const int32_t cut = fit_cut(T_max, m, k, slice_cut(T_max, d, n_mt), cand_bytes);
+    const int32_t n_sl = n_mt * cut;
     const int cap = emit_cap(m, k, kBM / cut);
     const CandArea a = cand_area(cand, T_max, n_sl, cap);
     RingOut r{};
@@ -2896,11 +2915,12 @@ hipError_t launch_sae_encode_multi(const uint16_t* h, int32_t d, int32_t T_max, 
     const bool many = many_tiles(T_max);
     for (int32_t c0 = 0; c0 < n; c0 += kMultiMax) {
         const int32_t nc = n - c0 < kMultiMax ? n - c0 : kMultiMax;
-        // one cut for all: by the slices of the batch together, so no app's is
-        // finer than a call of its own has, whose workspace it fits
+        // one cut for all, by the slices of the batch together
         int64_t n_all = 0;
         for (int32_t i = 0; i < nc; ++i) n_all += apps[c0 + i].m / kBM;
-        const int32_t cut = slice_cut(T_max, d, n_all);
+        int32_t cut = slice_cut(T_max, d, n_all);
+        for (int32_t i = 0; i < nc; ++i)
+            cut = fit_cut(T_max, apps[c0 + i].m, apps[c0 + i].k, cut, apps[c0 + i].cand_bytes);
         EncApps ea;
         MergeApps ma;
         memset(&ea, 0, sizeof(ea));

@@ -89,6 +89,40 @@ def test_workspace_queries(lib):
     assert lib.xmix_probe_workspace(8192, 4, 0) == 0
 
 
+def test_a_workspace_serves_smaller_calls(lib):
+    """A workspace made for the largest call is taken by every smaller one: fewer
+    slots, a smaller dictionary, a smaller k.  The second app of each call is
+    invalid, so that one whose workspace is taken is refused for that (1, not 3)."""
+    import paper_2607_22595_amd as px
+    f = lib.xmix_sae_encode_topk_multi
+    f.restype, f.argtypes = ctypes.c_int, None
+    A = 0x100000
+
+    def taken(T, m, k, ws_bytes):
+        rt = px.XmixRoute(0x10000, 0x20000, 0x30000, T, 1)
+        w = px.XmixSaeDict(A, m, 1024, px.XMIX_SAE_DICT_TILED)
+        apps = (px.XmixSaeApp * 2)(*[px.XmixSaeApp(b, ctypes.pointer(w), A, A, A, k, A, A, A,
+                                                   ws_bytes, None, b) for b in (0, 5)])
+        st = f(ctypes.c_void_p(A), 1024, ctypes.byref(rt), 2, apps, ctypes.c_void_p(A), 0, None)
+        assert st in (1, 3)
+        return st == 1
+    def whole(T, m, k):   # what whole slices need: pairs, a count and a bound per slice
+        cap = min(64, 4 * max(2, -(-2 * k * 256 // m) + 1))
+        return m * 4 + -(-T * (m // 256) * (8 + 8 * cap) // 256) * 256
+
+    for m in (256, 4096, 8192, 16384, 16640, 24576, 32768, 33024, 65536):
+        for T2 in (1, 128, 300, 512, 513, 1000, 1024, 1025, 2000):
+            for k2 in (8, 32, 64):
+                ws = px.sae_encode_workspace(T2, 1024, m, k2)
+                assert ws >= whole(T2, m, k2)
+                for T1 in {t for t in (1, 100, 128, 511, 512, 513, 1024) if t <= T2} | {T2}:
+                    assert px.sae_encode_workspace(T1, 1024, m, k2) <= ws
+                    assert taken(T1, m, k2, ws) and taken(T1, m, 8, ws), (T2, m, k2, T1)
+                if T2 <= 1024:   # and what was made for whole slices
+                    assert taken(T2, m, k2, whole(T2, m, k2))
+                    assert not taken(T2, m, k2, whole(T2, m, k2) - 1)
+
+
 def test_encode_rejects_unsupported_shapes_on_the_host(lib):
     """Fake (never dereferenced) device addresses: every case below is
     refused by the host-side checks before anything is launched."""

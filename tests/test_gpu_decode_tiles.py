@@ -160,6 +160,33 @@ def test_repair_of_cut_slices(px, m, T, n_tied):
         assert len(set(val[t].tolist())) == 1
 
 
+@pytest.mark.parametrize("m,T,n", [(4096, 70, 64), (16384, 300, 200), (24576, 512, 300)])
+def test_a_workspace_for_whole_slices(px, m, T, n):
+    """A workspace that only holds whole slices is taken, by the single, the staged
+    and the batched call, with the same results."""
+    d, k = 512, 32
+    wl = synth.make("c3", d=d, m=m, k=k, T=T, n_sub=n, seed=m)
+    s, h, rt = wl.layers[0].saes[0], dev(wl.layers[0].h), route(px, T, wl.sub, 1)
+    e = Enc(px, s, T, d)
+    e.single(h, rt, 0)
+    ref = e.result()
+    cap = min(64, 4 * max(2, -(-2 * k * 256 // m) + 1))
+    whole = m * 4 + -(-T * (m // 256) * (8 + 8 * cap) // 256) * 256
+    assert whole < e.ws.numel()
+    area = e.ws
+    e.ws = area[:whole]
+    guard = area[whole:].fill_(0x5A)
+    for call in (lambda: e.single(h, rt, 0),
+                 lambda: px.xmix_sae_encode_topk_multi(h, rt, [e.app(0)]),
+                 lambda: (px.xmix_sae_encode_candidates(h, rt, 0, e.W, e.be, e.bd, e.c, k, e.ws),
+                          px.xmix_sae_merge_topk(h, rt, 0, e.W, e.c, k, e.idx, e.val, e.ws))):
+        e.reset()
+        call()
+        got = e.result()
+        assert np.array_equal(got[0], ref[0]) and np.array_equal(got[1], ref[1])
+    assert bool((guard == 0x5A).all())
+
+
 def test_workspace_of_every_cut_stays_in_the_static_array(px):
     """What xmix_sae_encode_topk_noalloc took with whole slices, it still takes."""
     for m in (256, 4096, 16384, 16640, 32768, 33024, 65536):
