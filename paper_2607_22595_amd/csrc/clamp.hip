@@ -3,14 +3,15 @@
 // rounding per app.  Only the n_clamp decoder rows are read; the dense m x d
 // decode is never formed.
 //
-// One workgroup takes kClampTok tokens: the coefficients c - z of every
-// (app, clamp, token) are worked out in LDS first, then a thread owns a
-// 16-byte column slice of the group's rows, so that each decoder slice is
-// fetched and widened once for the group and the rows are in flight together.
-// HBM bounds a chunk of many tokens (each selected row read and written once);
-// with one token per workgroup the chain mask -> clamp table -> encoded values
-// -> decoder rows bounded it (8192 tokens of width 4096, two apps of four
-// clamps, half of the tokens each: 48 us).
+// A workgroup takes one token, or four of a large launch: the coefficients
+// c - z of every (app, clamp, token) are worked out in LDS first, then a thread
+// owns a 16-byte column slice of the group's rows.  A launch of few tokens is the
+// chain mask -> clamp table and encoded values -> decoder rows, and one token per
+// workgroup keeps it short: 140 tokens of width 512, three apps of six clamps,
+// 30 % of the tokens each, take 5.6 us, and 9.3 in groups of four.  With many
+// subscribed tokens the decoder slices, read again for each token, bound it, and
+// a group fetches and widens each once for its four: 8192 tokens of width 4096,
+// four apps of twelve clamps, every token, take 90 us, and 142 one by one.
 #include <stddef.h>
 #include <string.h>
 
@@ -22,8 +23,6 @@ namespace xmix {
 
 constexpr int kClampThreads = 256;
 constexpr int kClampMax = 16;
-constexpr int kClampTok = 4;  // tokens per workgroup
-
 struct ClampApps {
     ClampAppIn a[kMultiMax];
     int32_t n;
@@ -31,85 +30,118 @@ struct ClampApps {
 
 // LIST: the tokens are slots of one app's token list (apps.n == 1), slots past
 // its count left alone; otherwise token slots whose masks select the apps.
-template <bool LIST>
+template <bool LIST, int TOK>
 __global__ void __launch_bounds__(kClampThreads)
 clamp_kernel(uint16_t* __restrict__ h, int32_t d, int32_t T_max,
              const uint32_t* __restrict__ tok_mask, const int32_t* __restrict__ app_count,
-             const int32_t* __restrict__ tok_list, ClampApps apps) {
-    __shared__ __align__(16) float coef[kMultiMax][kClampMax][kClampTok];
+             const int32_t* __restrict__ tok_list, int32_t fours, ClampApps apps) {
+    __shared__ __align__(16) float coef[kMultiMax][kClampMax][TOK];
     __shared__ int32_t cid[kMultiMax][kClampMax];  // the row read for each clamp (0 if invalid)
-    __shared__ int32_t rid[kMultiMax][kClampMax];  // the id a selected latent must match (-1: none)
-    __shared__ float cval[kMultiMax][kClampMax];
-    const int32_t n0 = static_cast<int32_t>(blockIdx.x) * kClampTok;
-    const int tid = threadIdx.x, threads = blockDim.x;
-    int32_t tok[kClampTok];
-    uint32_t sel[kClampTok], any = 0;  // apps that clamp the token
+    int32_t n0 = static_cast<int32_t>(blockIdx.x) * TOK;
+    if (TOK == 1 && fours > 0) {  // token 4 x + j where workgroup x of fours per column runs
+        const int32_t x = n0 / 32 * 8 + ((n0 - static_cast<int32_t>(blockIdx.y) * fours) & 7);
+        n0 = 4 * x + (n0 / 8 & 3);
+    }
+    const int tid = threadIdx.x;
+    int32_t tok[TOK];
+    uint32_t sel[TOK], any = 0;  // apps that clamp the token
     const int32_t cnt = LIST ? min(max(*app_count, 0), T_max) : T_max;
 #pragma unroll
-    for (int j = 0; j < kClampTok; ++j) {
+    for (int j = 0; j < TOK; ++j) {
+        const int32_t n = min(n0 + j, T_max - 1);
         const bool in = n0 + j < cnt;
-        tok[j] = LIST ? (in ? tok_list[n0 + j] : 0) : n0 + j;
-        uint32_t m = 0;
-        if (in) {
-            if constexpr (LIST) {
-                m = 1u;
-            } else {
-                const uint32_t mask = tok_mask[n0 + j];
-                for (int a = 0; a < apps.n; ++a) m |= ((mask >> apps.a[a].bit) & 1u) << a;
-            }
+        if constexpr (LIST) {
+            const int32_t t = tok_list[n];
+            tok[j] = in ? t : 0;
+            sel[j] = in ? 1u : 0u;
+        } else {
+            const uint32_t mask = tok_mask[n];
+            uint32_t m = 0;
+#pragma unroll
+            for (int a = 0; a < kMultiMax; ++a)
+                if (a < apps.n) m |= ((mask >> apps.a[a].bit) & 1u) << a;
+            tok[j] = n;
+            sel[j] = in ? m : 0u;
         }
-        sel[j] = m;
-        any |= m;
+        any |= sel[j];
     }
     if (any == 0) return;  // uniform
 
+    // z of a clamped feature = its encoded value if selected: one wave per
+    // (app, token), a lane per clamp and per encoded latent (k <= 64).  The
+    // clamp table and the encoded values of kTurn pairs, and behind them the
+    // first slices of the rows, are asked for together and behind no branch.
+    constexpr int kWaves = kClampThreads / kWave;
+    constexpr int kTurn = LIST ? 1 : TOK == 1 ? kMultiMax / kWaves : 4;
+    const int lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const int pairs = (LIST ? 1 : apps.n) * TOK;
+    int32_t id[kTurn], li[kTurn];
+    float cv[kTurn], lv[kTurn];
+    bool on[kTurn];
+    auto ask = [&](const int w0) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < kTurn; ++u) {
+            const int w = min(w0 + u * kWaves, pairs - 1), a = w / TOK, j = w % TOK;
+            const ClampAppIn& p = apps.a[a];
+            int32_t t = tok[0];
+            uint32_t sj = sel[0];
+#pragma unroll
+            for (int v = 1; v < TOK; ++v) {
+                t = j == v ? tok[v] : t;
+                sj = j == v ? sel[v] : sj;
+            }
+            on[u] = w0 + u * kWaves < pairs && ((sj >> a) & 1u);
+            const int64_t o = static_cast<int64_t>(t) * p.k;
+            const int32_t nc = on[u] ? p.n_clamp : 0, nk = on[u] ? p.k : 0;
+            id[u] = lane_load(p.clamp_ids, nc, lane);
+            cv[u] = __int_as_float(lane_load(p.clamp_vals, nc, lane));
+            li[u] = lane_load(p.idx + o, nk, lane);
+            lv[u] = bf16_to_f32(lane_load(p.val + o, nk, lane));
+        }
+    };
+    ask(wave);
+    __builtin_amdgcn_sched_barrier(0);
     const int32_t nvec = d / 8;
-    const int32_t step = static_cast<int32_t>(gridDim.y) * threads;
-    int32_t i = static_cast<int32_t>(blockIdx.y) * threads + tid;
-    uint4 hv[kClampTok];
+    const int32_t step = static_cast<int32_t>(gridDim.y) * kClampThreads;
+    int32_t i = static_cast<int32_t>(blockIdx.y) * kClampThreads + tid;
+    uint4 hv[TOK];
     auto load_rows = [&]() __attribute__((always_inline)) {
 #pragma unroll
-        for (int j = 0; j < kClampTok; ++j)
+        for (int j = 0; j < TOK; ++j)
             hv[j] = sel[j] && i < nvec
                         ? reinterpret_cast<const uint4*>(h)[static_cast<int64_t>(tok[j]) * nvec + i]
                         : make_uint4(0u, 0u, 0u, 0u);
     };
-    load_rows();  // the first slices are on their way while the tables are made
-    for (int e = tid; e < apps.n * kClampMax; e += threads) {
-        const int a = e / kClampMax, q = e % kClampMax;
-        const ClampAppIn& p = apps.a[a];
-        if (((any >> a) & 1u) && q < p.n_clamp) {
-            const int32_t id = p.clamp_ids[q];
-            const bool ok = id >= 0 && id < p.m;  // an id outside [0, m) clamps nothing
-            const float c = p.clamp_vals[q];
-            cid[a][q] = ok ? id : 0;
-            rid[a][q] = ok ? id : -1;
-            cval[a][q] = c;
+    load_rows();
+    __builtin_amdgcn_sched_barrier(0);
+    for (int w0 = wave; w0 < pairs;) {
 #pragma unroll
-            for (int j = 0; j < kClampTok; ++j) coef[a][q][j] = ok ? c : 0.0f;
-        }
-    }
-    __syncthreads();
-    // z of a clamped feature = its encoded value if selected: one wave per
-    // (token, app), one lane per encoded latent (k <= 64)
-    const int lane = lane_id(), waves = threads / kWave;
-    for (int w = tid / kWave; w < apps.n * kClampTok; w += waves) {
-        const int a = w / kClampTok, j = w % kClampTok;
-        const ClampAppIn& p = apps.a[a];
-        int32_t t = tok[0];
-        uint32_t sj = sel[0];
+        for (int u = 0; u < kTurn; ++u) {
+            if (!on[u]) continue;  // uniform
+            const int w = w0 + u * kWaves, a = w / TOK, j = w % TOK;
+            const ClampAppIn& p = apps.a[a];
+            const bool ok = id[u] >= 0 && id[u] < p.m;  // an id outside [0, m) clamps nothing
+            const int32_t have = lane < p.k ? li[u] : -1;
+            float c = cv[u];
+            for (int q0 = 0; q0 < p.n_clamp; q0 += 4) {  // kClampMax is a multiple of 4
+                uint64_t hit[4];
 #pragma unroll
-        for (int u = 1; u < kClampTok; ++u) {
-            t = j == u ? tok[u] : t;
-            sj = j == u ? sel[u] : sj;
+                for (int e = 0; e < 4; ++e)
+                    hit[e] = wave_ballot(have == __builtin_amdgcn_readlane(id[u], q0 + e));
+                if ((hit[0] | hit[1] | hit[2] | hit[3]) == 0) continue;  // uniform
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (hit[e] != 0 && lane == q0 + e)
+                        c = cv[u] - readlane_f(lv[u], 63 - __builtin_clzll(hit[e]));
+            }
+            if (lane < p.n_clamp) {
+                cid[a][lane] = ok ? id[u] : 0;
+                coef[a][lane][j] = ok ? c : 0.0f;
+            }
         }
-        if (((sj >> a) & 1u) && lane < p.k) {
-            const int64_t o = static_cast<int64_t>(t) * p.k + lane;
-            const int32_t id = p.idx[o];
-            const float z = bf16_to_f32(p.val[o]);
-            for (int q = 0; q < p.n_clamp; ++q)
-                if (id >= 0 && id == rid[a][q]) coef[a][q][j] = cval[a][q] - z;
-        }
+        w0 += kTurn * kWaves;
+        if (w0 >= pairs) break;
+        ask(w0);
     }
     __syncthreads();
 
@@ -119,20 +151,26 @@ clamp_kernel(uint16_t* __restrict__ h, int32_t d, int32_t T_max,
             for (int a = 0; a < apps.n; ++a) {
                 if (!((any >> a) & 1u)) continue;  // uniform
                 const ClampAppIn& p = apps.a[a];
-                float delta[kClampTok][8];
+                float delta[TOK][8];
 #pragma unroll
-                for (int j = 0; j < kClampTok; ++j)
+                for (int j = 0; j < TOK; ++j)
 #pragma unroll
                     for (int e = 0; e < 8; ++e) delta[j][e] = 0.0f;
                 const uint4* W = reinterpret_cast<const uint4*>(p.W_dec) + i;
 #pragma unroll 4
                 for (int q = 0; q < p.n_clamp; ++q) {
                     const uint4 wv = W[static_cast<int64_t>(cid[a][q]) * nvec];
-                    const float4 c4 = *reinterpret_cast<const float4*>(coef[a][q]);
-                    const float c[kClampTok] = {c4.x, c4.y, c4.z, c4.w};
+                    float c[TOK];
+                    if constexpr (TOK == 4) {
+                        const float4 c4 = *reinterpret_cast<const float4*>(coef[a][q]);
+                        c[0] = c4.x, c[1] = c4.y, c[2] = c4.z, c[3] = c4.w;
+                    } else {
+#pragma unroll
+                        for (int j = 0; j < TOK; ++j) c[j] = coef[a][q][j];
+                    }
                     const uint32_t ww[4] = {wv.x, wv.y, wv.z, wv.w};
 #pragma unroll
-                    for (int j = 0; j < kClampTok; ++j)
+                    for (int j = 0; j < TOK; ++j)
 #pragma unroll
                         for (int e = 0; e < 4; ++e) {
                             delta[j][2 * e] = fmaf(c[j], lo_bf16(ww[e]), delta[j][2 * e]);
@@ -140,7 +178,7 @@ clamp_kernel(uint16_t* __restrict__ h, int32_t d, int32_t T_max,
                         }
                 }
 #pragma unroll
-                for (int j = 0; j < kClampTok; ++j) {
+                for (int j = 0; j < TOK; ++j) {
                     if (!((sel[j] >> a) & 1u)) continue;  // uniform
                     uint32_t hw[4] = {hv[j].x, hv[j].y, hv[j].z, hv[j].w};
 #pragma unroll
@@ -157,7 +195,7 @@ clamp_kernel(uint16_t* __restrict__ h, int32_t d, int32_t T_max,
                 }
             }
 #pragma unroll
-            for (int j = 0; j < kClampTok; ++j)
+            for (int j = 0; j < TOK; ++j)
                 if (sel[j])
                     reinterpret_cast<uint4*>(h)[static_cast<int64_t>(tok[j]) * nvec + i] = hv[j];
         }
@@ -168,30 +206,63 @@ clamp_kernel(uint16_t* __restrict__ h, int32_t d, int32_t T_max,
 }
 
 // Workgroups: the token groups, and while these alone do not fill the chip
-// several times the column slices beside them (each repeats the small table
-// work of its group).
-static void clamp_grid(int32_t T_max, int32_t d, dim3* grid, dim3* block) {
-    const int32_t nvec = d / 8, groups = (T_max + kClampTok - 1) / kClampTok;
+// several times the column slices beside them (each repeats the table work of
+// its group).  A list launch holds fewer groups than its slots allow (4096 slots
+// of width 8192, 30 % of them listed, two clamps: 12.5 us with column slices,
+// 16.7 without).
+template <bool LIST, int TOK>
+static hipError_t launch_clamp_t(uint16_t* h, int32_t d, int32_t T_max, const uint32_t* tok_mask,
+                                 const int32_t* app_count, const int32_t* tok_list,
+                                 const ClampApps& ca, hipStream_t stream) {
+    const int32_t nvec = d / 8, slices = (nvec + kClampThreads - 1) / kClampThreads;
     // also for a narrow row: the waves share the table work of (app, token) pairs
     // (340 tokens of width 512, three apps of 16 clamps: 22.7 us with one wave)
-    const int32_t threads = kClampThreads;
-    *block = dim3(threads);
-    *grid = dim3(groups, groups >= 1024 ? 1 : (nvec + threads - 1) / threads);
+    const int32_t cols = T_max >= (LIST ? 8192 : 4096) ? 1 : slices;
+    // Tokens taken one by one where the steering kernel groups its rows: the same
+    // rows on the same XCDs, whose L2 holds what a steering call before this one
+    // wrote (1100 rows of 8192, two steering vectors and two clamps, every token:
+    // 25 us for both in that order, 32 without)
+    int32_t groups = (T_max + TOK - 1) / TOK, fours = 0;
+    if (TOK == 1 && rows_grouped(T_max, slices)) {
+        fours = (T_max + 3) / 4;
+        groups = (fours + 7) / 8 * 32;
+    }
+    hipLaunchKernelGGL((clamp_kernel<LIST, TOK>), dim3(groups, cols), dim3(kClampThreads), 0,
+                       stream, h, d, T_max, tok_mask, app_count, tok_list, fours, ca);
+    return hipGetLastError();
+}
+
+template <bool LIST>
+static hipError_t launch_clamp(uint16_t* h, int32_t d, int32_t T_max, const uint32_t* tok_mask,
+                               const int32_t* app_count, const int32_t* tok_list,
+                               const ClampApps& ca, hipStream_t stream) {
+    int32_t clamps = 0;
+    for (int32_t i = 0; i < ca.n; ++i) clamps += ca.a[i].n_clamp;
+    // Groups of four pay where the decoder slices shared by a group outweigh its
+    // longer chain.  How many tokens subscribe is not known here, so the line is
+    // drawn where a fully subscribed launch gains little (one token against four:
+    // 1024 rows of 4096, four apps of twelve clamps 22.2 and 20.4 us with every
+    // token, three of six 11.1 and 11.9 with 30 %), and further out for few
+    // clamps, which leave little to share (4096 rows of 4096, two apps of three:
+    // 25.5 and 23.2 us with every token, 9.4 and 12.3 with 10 %).  Beyond it a
+    // sparse launch would still do better one by one (4096 rows of 8192, four
+    // apps of two, 10 %: 19 and 30 us), a full one far worse (2048 rows of 8192,
+    // four of twelve: 70 and 52).
+    const int64_t work = static_cast<int64_t>(T_max) * d;
+    const bool one = work <= (4 << 20) || (clamps <= 6 && work <= (16 << 20));
+    return (one ? launch_clamp_t<LIST, 1> : launch_clamp_t<LIST, 4>)(
+        h, d, T_max, tok_mask, app_count, tok_list, ca, stream);
 }
 
 hipError_t launch_clamp_multi(uint16_t* h, int32_t d, int32_t T_max, const uint32_t* tok_mask,
                               int32_t n, const ClampAppIn* apps, hipStream_t stream) {
-    dim3 grid, block;
-    clamp_grid(T_max, d, &grid, &block);
     for (int32_t c0 = 0; c0 < n; c0 += kMultiMax) {
         ClampApps ca;
         memset(&ca, 0, sizeof(ca));
         ca.n = n - c0 < kMultiMax ? n - c0 : kMultiMax;
         for (int32_t i = 0; i < ca.n; ++i) ca.a[i] = apps[c0 + i];
-        hipLaunchKernelGGL(clamp_kernel<false>, grid, block, 0, stream, h, d, T_max, tok_mask,
-                           static_cast<const int32_t*>(nullptr),
-                           static_cast<const int32_t*>(nullptr), ca);
-        const hipError_t e = hipGetLastError();
+        const hipError_t e =
+            launch_clamp<false>(h, d, T_max, tok_mask, nullptr, nullptr, ca, stream);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
@@ -202,8 +273,6 @@ hipError_t launch_clamp_decode(uint16_t* h, int32_t d, const int32_t* app_count,
                                const uint16_t* val, int32_t k, const uint16_t* W_dec, int32_t m,
                                const int32_t* clamp_ids, const float* clamp_vals,
                                int32_t n_clamp, float* delta_out, hipStream_t stream) {
-    dim3 grid, block;
-    clamp_grid(T_max, d, &grid, &block);
     ClampApps ca;
     memset(&ca, 0, sizeof(ca));
     ca.n = 1;
@@ -216,9 +285,7 @@ hipError_t launch_clamp_decode(uint16_t* h, int32_t d, const int32_t* app_count,
     ca.a[0].k = k;
     ca.a[0].m = m;
     ca.a[0].n_clamp = n_clamp;
-    hipLaunchKernelGGL(clamp_kernel<true>, grid, block, 0, stream, h, d, T_max,
-                       static_cast<const uint32_t*>(nullptr), app_count, tok_list, ca);
-    return hipGetLastError();
+    return launch_clamp<true>(h, d, T_max, nullptr, app_count, tok_list, ca, stream);
 }
 
 // Where the batched descriptor holds device pointers (for the graph
@@ -239,8 +306,10 @@ struct ArgPointers<ClampApps> {
 };
 
 void add_clamp_kernels(std::vector<KernelInfo>& t) {
-    t.push_back(kernel_info(clamp_kernel<true>));
-    t.push_back(kernel_info(clamp_kernel<false>));
+    t.push_back(kernel_info(clamp_kernel<true, 1>));
+    t.push_back(kernel_info(clamp_kernel<true, 4>));
+    t.push_back(kernel_info(clamp_kernel<false, 1>));
+    t.push_back(kernel_info(clamp_kernel<false, 4>));
 }
 
 }  // namespace xmix

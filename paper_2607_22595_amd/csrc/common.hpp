@@ -42,6 +42,18 @@ __device__ __forceinline__ uint4 slice_load(const uint4* p, int32_t n, uint32_t 
     return make_uint4(v.x, v.y, v.z, v.w);
 }
 
+// This lane's element of the n at p (uniform), in the same way: zero past them.
+__device__ __forceinline__ int32_t lane_load(const void* p, int32_t n, int lane) {
+    const __amdgpu_buffer_rsrc_t r =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, n * 4, kBufferDword3);
+    return __builtin_amdgcn_raw_buffer_load_b32(r, lane * 4, 0, 0);
+}
+__device__ __forceinline__ uint16_t lane_load(const uint16_t* p, int32_t n, int lane) {
+    const __amdgpu_buffer_rsrc_t r =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(p), 0, n * 2, kBufferDword3);
+    return __builtin_amdgcn_raw_buffer_load_b16(r, lane * 2, 0, 0);
+}
+
 // ---------------------------------------------------------------- bf16 bits
 __device__ __forceinline__ float bf16_to_f32(uint16_t b) {
     return __uint_as_float(static_cast<uint32_t>(b) << 16);

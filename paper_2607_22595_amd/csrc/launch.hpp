@@ -40,6 +40,12 @@ hipError_t launch_route_trigger(int32_t T_max, int32_t app_bit, uint32_t* tok_ma
                                 const int32_t* token_ids, const uint32_t* vocab_bits,
                                 int32_t vocab_size, hipStream_t stream);
 
+// Whether the steering kernel takes its rows in groups of four: a group of rows
+// per workgroup once that still fills the chip with several workgroups a CU;
+// below, one row each for the shortest chain.
+inline bool rows_grouped(int32_t T_max, int32_t cols) {
+    return static_cast<int64_t>(T_max) * cols >= 4096;
+}
 hipError_t launch_steer(void* h, bool bf16, int32_t d, int32_t T_max, const uint32_t* tok_mask,
                         const int32_t* req, const void* vecs, const BitList& bits,
                         const float* alpha, int32_t n_steer, hipStream_t stream);
@@ -141,8 +147,8 @@ struct ClampAppIn {
     float* delta_out;
     int32_t k, m, n_clamp, bit;
 };
-// Up to kMultiMax clamp apps in one launch, one workgroup per token slot,
-// the apps applied to each row in the given order.
+// Up to kMultiMax clamp apps in one launch over token slots, the apps applied
+// to each row in the given order.
 hipError_t launch_clamp_multi(uint16_t* h, int32_t d, int32_t T_max, const uint32_t* tok_mask,
                               int32_t n, const ClampAppIn* apps, hipStream_t stream);
 

@@ -146,9 +146,7 @@ static hipError_t launch_steer_t(void* h, int32_t d, int32_t T_max, const uint32
     const int32_t nvec = d / (BF16 ? 8 : 4);
     const int32_t threads = nvec < kSteerThreads ? (nvec + kWave - 1) / kWave * kWave : kSteerThreads;
     const int32_t cols = (nvec + threads - 1) / threads;
-    // a group of rows per workgroup once that still fills the chip with
-    // several workgroups a CU; below, one row each for the shortest chain
-    if (static_cast<int64_t>(T_max) * cols >= 4096)
+    if (rows_grouped(T_max, cols))
         hipLaunchKernelGGL((steer_kernel<BF16, kSteerGroup>),
                            dim3((T_max + kSteerGroup - 1) / kSteerGroup, cols), dim3(threads), 0,
                            stream, h, d, T_max, tok_mask, req, vecs, alpha, n_steer, bits);

@@ -200,6 +200,59 @@ def test_clamp_token_groups(px, T, d, k, n_clamp, n_apps):
         assert torch.equal(a[6], b[6])
 
 
+@pytest.mark.parametrize("T,d,n_clamp", [(1024, 4096, 7), (1025, 4096, 7), (1030, 4096, 2),
+                                         (4096, 4096, 2), (4097, 4096, 2), (8203, 520, 16),
+                                         (2046, 2056, 3), (513, 8200, 5)])
+def test_clamp_launches_of_every_size_agree(px, T, d, n_clamp):
+    """A launch of many rows (four tokens per workgroup where the rule says so,
+    groups with no, some and all of their tokens subscribed) leaves the bits that
+    launches of a few hundred rows leave (one token per workgroup), for one app
+    and for three; some of its rows against the oracle."""
+    m, k, n_apps = 300, 24, 3
+    rng, req, sub = batch(T, n_apps, p=0.4, seed=T + d)
+    sub[:64] = np.where(np.arange(64) < 32, 0, 7)   # whole groups of none and of all
+    req[:64] = np.arange(64)
+    tm = oracle.route(req, T, sub, n_apps)[0]
+    h = synth.normal_bf16("c/h", (T, d), 1.0)
+    apps = []
+    for a in range(n_apps):
+        idx = np.argsort(rng.random((T, m)), axis=1)[:, :k].astype(np.int32)
+        val = synth.normal_bf16(f"c/val{a}", (T, k), 2.0) & np.uint16(0x7FFF)
+        apps.append((idx, val, synth.normal_bf16(f"c/W{a}", (m, d), d ** -0.5),
+                     rng.choice(m, n_clamp, replace=False).astype(np.int32),
+                     rng.normal(5, 2, n_clamp).astype(np.float32)))
+
+    def run(t0, n):
+        one, many = dev(h[t0:t0 + n]), dev(h[t0:t0 + n])
+        rt, _ = build(px, req[t0:t0 + n], n, sub, n_apps)
+        args = []
+        for a, (idx, val, W, ids, vals) in enumerate(apps):
+            x = [dev(v) for v in (idx[t0:t0 + n], val[t0:t0 + n], W, ids, vals)]
+            args.append((a, *x, torch.zeros((n, d), dtype=torch.float32, device="cuda")))
+        for x in args:
+            px.xmix_sae_clamp_decode(one, rt, *x)
+        deltas = [x[6].clone() for x in args]
+        px.xmix_sae_clamp_decode_multi(many, rt, args)
+        assert torch.equal(many.view(torch.int16), one.view(torch.int16))
+        assert all(torch.equal(x[6], y) for x, y in zip(args, deltas))
+        return torch_bits(one), [x.cpu().numpy() for x in deltas]
+
+    got, deltas = run(0, T)
+    for t0 in range(0, T, 512):
+        n = min(512, T - t0)
+        part, dp = run(t0, n)
+        assert np.array_equal(part, got[t0:t0 + n])
+        assert all(np.array_equal(x, y[t0:t0 + n]) for x, y in zip(dp, deltas))
+    assert np.array_equal(got[(tm & 7) == 0], h[(tm & 7) == 0])
+    idx, val, W, ids, vals = apps[0]
+    rows = np.nonzero(tm & 1)[0][::97]
+    _, ref = oracle.clamp_decode(h[rows], np.ones(len(rows), np.uint32), 0, idx[rows], val[rows],
+                                 W, ids, vals, want_delta=True)
+    # n_clamp fp32 multiply-adds: each within 2^-24 of the sum of magnitudes
+    worst = np.abs(vals).sum() + 64 * n_clamp
+    assert np.all(np.abs(deltas[0][rows] - ref) <= n_clamp * 2.0 ** -23 * worst)
+
+
 @pytest.mark.parametrize("widths", [(4,), (12, 16), (1024, 4), (1036, 20), (4096, 1028), (2, 6),
                                     (2048, 10)])
 @pytest.mark.parametrize("off", [0, 4])
