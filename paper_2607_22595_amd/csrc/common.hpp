@@ -20,6 +20,9 @@ constexpr int kWave = 64;
 // fused probe and steering pass with this, its arguments read together and no
 // load behind a branch: 32 layers of 256 rows of 8 KB 150 -> 128 us, 16 layers of
 // 512 rows of 16 KB 177 -> 143 us (a third of the bits set) and 130 -> 102 (5 %).
+// Reading every row is what costs where few carry a bit: 16 layers of 512 fp32
+// rows of 8 KB take 52.3 us with it and 50.1 without at 5 % of the bits, 61.7 and
+// 64.5 at 40 %; of 1024 such rows, at the line, 62.1 and 59.5, and 78.6 and 82.2.
 // The steering kernel keeps to the rows it needs: few rows of a gated step carry
 // a bit, and eight such layers took 62 us with this and 56 without.
 __host__ __device__ inline bool early_rows(int32_t rows, int32_t nvec) {

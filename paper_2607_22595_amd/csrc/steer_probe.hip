@@ -27,7 +27,8 @@ namespace xmix {
 constexpr int kFuseThreads = 512;  // a 4096-wide bf16 row is one 16-byte slice per thread
 constexpr int kFuseWaves = kFuseThreads / kWave;
 
-template <bool BF16, int MAXP, bool EARLY>
+// MAXP: at most this many probes; NS: steering vectors fetched together.
+template <bool BF16, int MAXP, int NS, bool EARLY>
 __global__ void __launch_bounds__(kFuseThreads)
 steer_probe_kernel(void* __restrict__ h, int32_t d, int32_t T_max,
                    const uint32_t* __restrict__ tok_mask, const int32_t* __restrict__ req,
@@ -89,7 +90,7 @@ steer_probe_kernel(void* __restrict__ h, int32_t d, int32_t T_max,
     float part[MAXP];
 #pragma unroll
     for (int p = 0; p < MAXP; ++p) part[p] = 0.0f;
-    SteerGroup g0;  // the token's first four steering vectors
+    SteerGroup<NS> g0;  // the token's first NS steering vectors
     uint32_t rest0 = ss;
     steer_pick(g0, rest0, a_row, n_steer);
 
@@ -103,9 +104,9 @@ steer_probe_kernel(void* __restrict__ h, int32_t d, int32_t T_max,
         // with it, 4.9 without)
         if (static_cast<int32_t>(__builtin_amdgcn_readfirstlane(i)) >= nvec) return;
         // Every load of the slice before its first use, and none behind a
-        // branch: the row, the weights of the token's probes and its first
-        // four steering vectors, so that the slice waits for one memory round
-        // trip, not one per operand.
+        // branch: the row, the weights of the token's probes and its first NS
+        // steering vectors, so that the slice waits for one memory round trip,
+        // not one per operand.
         const uint4 hv = fetched ? *fetched : slice_load(row + i0, count, off);
         uint4 wv[AP];
 #pragma unroll
@@ -144,15 +145,15 @@ steer_probe_kernel(void* __restrict__ h, int32_t d, int32_t T_max,
             }
             part[p] = acc;
         }
-        // steering, written back: the first four vectors as fetched, then
-        // the rest (more than four steering apps) four at a time
+        // steering, written back: the first NS vectors as fetched, then the
+        // rest NS at a time
         if (ss) {
             double acc[EPV];
 #pragma unroll
             for (int e = 0; e < EPV; ++e) acc[e] = x[e];
             steer_add_group<BF16>(acc, g0);
             for (uint32_t rest = rest0; rest != 0;) {
-                SteerGroup g;
+                SteerGroup<NS> g;
                 steer_pick(g, rest, a_row, n_steer);
                 steer_fetch(g, V + i0, nvec, count, off);
                 steer_add_group<BF16>(acc, g);
@@ -196,6 +197,14 @@ steer_probe_kernel(void* __restrict__ h, int32_t d, int32_t T_max,
     }
 }
 
+template <bool BF16, int MAXP>
+static auto pick_kernel(bool two, bool early) {
+    return two ? (early ? steer_probe_kernel<BF16, MAXP, 2, true>
+                        : steer_probe_kernel<BF16, MAXP, 2, false>)
+               : (early ? steer_probe_kernel<BF16, MAXP, 4, true>
+                        : steer_probe_kernel<BF16, MAXP, 4, false>);
+}
+
 template <bool BF16>
 static hipError_t launch_steer_probe_t(void* h, int32_t d, int32_t T_max,
                                        const uint32_t* tok_mask, const int32_t* req,
@@ -204,14 +213,20 @@ static hipError_t launch_steer_probe_t(void* h, int32_t d, int32_t T_max,
                                        const float* b, const BitList& pbits, int32_t n_probe,
                                        float* logit, float* score, const RouteIn& r,
                                        hipStream_t stream) {
+    // A load that finds nothing to fetch still has to be issued: with two probes
+    // and two steering vectors at most no more are asked for (16 layers of 512 fp32
+    // rows of 16 KB, two of each, 5 % of the bits set: 79.5 us with room for four
+    // of each, 67.0 without).
+    const bool two = n_steer <= 2;
     // more than eight probes leave a pass bound by its weights, not by the chain
     const bool early = early_rows(T_max, d / (BF16 ? 8 : 4));
-    const auto kernel = n_probe <= 4    ? (early ? steer_probe_kernel<BF16, 4, true>
-                                                 : steer_probe_kernel<BF16, 4, false>)
-                        : n_probe <= 8  ? (early ? steer_probe_kernel<BF16, 8, true>
-                                                 : steer_probe_kernel<BF16, 8, false>)
-                        : n_probe <= 16 ? steer_probe_kernel<BF16, 16, false>
-                                        : steer_probe_kernel<BF16, 32, false>;
+    const auto kernel =
+        n_probe <= 2    ? pick_kernel<BF16, 2>(two, early)
+        : n_probe <= 4  ? pick_kernel<BF16, 4>(two, early)
+        : n_probe <= 8  ? (early ? steer_probe_kernel<BF16, 8, 4, true>
+                                 : steer_probe_kernel<BF16, 8, 4, false>)
+        : n_probe <= 16 ? steer_probe_kernel<BF16, 16, 4, false>
+                        : steer_probe_kernel<BF16, 32, 4, false>;
     hipLaunchKernelGGL(kernel, dim3(T_max + (r.T_valid ? r.n_apps : 0)), dim3(kFuseThreads), 0,
                        stream, h, d, T_max, tok_mask, req, r.T_valid, r.sub, r.R_max, r.n_apps,
                        vecs, alpha, n_steer, w, b, n_probe, logit, score, r.tok_mask, r.app_count,
@@ -246,19 +261,22 @@ hipError_t launch_steer_probe(void* h, bool bf16, int32_t d, int32_t T_max,
                                               stream);
 }
 
+template <bool BF16>
+static void add_steer_probe_t(std::vector<KernelInfo>& t) {
+    for (const bool two : {false, true})
+        for (const bool early : {false, true}) {
+            t.push_back(kernel_info(pick_kernel<BF16, 2>(two, early)));
+            t.push_back(kernel_info(pick_kernel<BF16, 4>(two, early)));
+        }
+    t.push_back(kernel_info(steer_probe_kernel<BF16, 8, 4, true>));
+    t.push_back(kernel_info(steer_probe_kernel<BF16, 8, 4, false>));
+    t.push_back(kernel_info(steer_probe_kernel<BF16, 16, 4, false>));
+    t.push_back(kernel_info(steer_probe_kernel<BF16, 32, 4, false>));
+}
+
 void add_steer_probe_kernels(std::vector<KernelInfo>& t) {
-    t.push_back(kernel_info(steer_probe_kernel<true, 4, true>));
-    t.push_back(kernel_info(steer_probe_kernel<true, 4, false>));
-    t.push_back(kernel_info(steer_probe_kernel<true, 8, true>));
-    t.push_back(kernel_info(steer_probe_kernel<true, 8, false>));
-    t.push_back(kernel_info(steer_probe_kernel<true, 16, false>));
-    t.push_back(kernel_info(steer_probe_kernel<true, 32, false>));
-    t.push_back(kernel_info(steer_probe_kernel<false, 4, true>));
-    t.push_back(kernel_info(steer_probe_kernel<false, 4, false>));
-    t.push_back(kernel_info(steer_probe_kernel<false, 8, true>));
-    t.push_back(kernel_info(steer_probe_kernel<false, 8, false>));
-    t.push_back(kernel_info(steer_probe_kernel<false, 16, false>));
-    t.push_back(kernel_info(steer_probe_kernel<false, 32, false>));
+    add_steer_probe_t<true>(t);
+    add_steer_probe_t<false>(t);
 }
 
 }  // namespace xmix

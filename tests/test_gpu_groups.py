@@ -363,3 +363,12 @@ def test_steer_probe_early_rows(px, T, d, n_steer, n_probe, dtype, gap):
     hf[::3, -1] = 0.0
     absdot = np.abs(wf) @ np.abs(hf).T
     check_probe(fused[0].cpu().numpy(), fused[1].cpu().numpy(), lr, sr, fin, absdot)
+
+
+@pytest.mark.parametrize("n_steer,n_probe", [(1, 2), (2, 2), (2, 3), (2, 4), (2, 5), (3, 2),
+                                             (3, 4), (9, 2)])
+@pytest.mark.parametrize("T,d,dtype", [(65, 4100, "f32"), (513, 4096, "f32"), (40, 4104, "bf16")])
+def test_steer_probe_few_apps(px, T, d, n_steer, n_probe, dtype):
+    """The numbers of probes and of steering vectors where the fused pass changes
+    how many it asks for together, rows of more than one turn of 512 slices."""
+    test_steer_probe_early_rows(px, T, d, n_steer, n_probe, dtype, 1)
