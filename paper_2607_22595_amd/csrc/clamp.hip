@@ -217,7 +217,7 @@ static hipError_t launch_clamp_t(uint16_t* h, int32_t d, int32_t T_max, const ui
     const int32_t nvec = d / 8, slices = (nvec + kClampThreads - 1) / kClampThreads;
     // also for a narrow row: the waves share the table work of (app, token) pairs
     // (340 tokens of width 512, three apps of 16 clamps: 22.7 us with one wave)
-    const int32_t cols = T_max >= (LIST ? 8192 : 4096) ? 1 : slices;
+    const int32_t cols = T_max >= (LIST ? 8192 : 4096) ? 1 : min(slices, kGridCols);
     // Tokens taken one by one where the steering kernel groups its rows: the same
     // rows on the same XCDs, whose L2 holds what a steering call before this one
     // wrote (1100 rows of 8192, two steering vectors and two clamps, every token:

@@ -40,6 +40,9 @@ hipError_t launch_route_trigger(int32_t T_max, int32_t app_bit, uint32_t* tok_ma
                                 const int32_t* token_ids, const uint32_t* vocab_bits,
                                 int32_t vocab_size, hipStream_t stream);
 
+// Column slices that a grid holds in y (a launch takes fewer than 65536 there).
+constexpr int32_t kGridCols = 32768;
+
 // Whether the steering kernel takes its rows in groups of four: a group of rows
 // per workgroup once that still fills the chip with several workgroups a CU;
 // below, one row each for the shortest chain.

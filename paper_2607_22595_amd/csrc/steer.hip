@@ -33,7 +33,8 @@ steer_kernel(void* __restrict__ h, int32_t d, int32_t T_max,
     constexpr int EPV = BF16 ? 8 : 4;  // elements per 16-byte vector
     const int32_t t0 = static_cast<int32_t>(blockIdx.x) * TT;
     const int32_t nvec = d / EPV;
-    const int32_t i = static_cast<int32_t>(blockIdx.y * kSteerThreads + threadIdx.x);
+    const int32_t i = static_cast<int32_t>(
+        (blockIdx.z * gridDim.y + blockIdx.y) * kSteerThreads + threadIdx.x);
     // masks and requests of the group in one round trip
     uint32_t sel[TT], any = 0;
     int32_t rq[TT];
@@ -146,12 +147,13 @@ static hipError_t launch_steer_t(void* h, int32_t d, int32_t T_max, const uint32
     const int32_t nvec = d / (BF16 ? 8 : 4);
     const int32_t threads = nvec < kSteerThreads ? (nvec + kWave - 1) / kWave * kWave : kSteerThreads;
     const int32_t cols = (nvec + threads - 1) / threads;
+    const int32_t z = (cols - 1) / kGridCols + 1, y = z > 1 ? kGridCols : cols;
     if (rows_grouped(T_max, cols))
         hipLaunchKernelGGL((steer_kernel<BF16, kSteerGroup>),
-                           dim3((T_max + kSteerGroup - 1) / kSteerGroup, cols), dim3(threads), 0,
+                           dim3((T_max + kSteerGroup - 1) / kSteerGroup, y, z), dim3(threads), 0,
                            stream, h, d, T_max, tok_mask, req, vecs, alpha, n_steer, bits);
     else
-        hipLaunchKernelGGL((steer_kernel<BF16, 1>), dim3(T_max, cols), dim3(threads), 0, stream, h,
+        hipLaunchKernelGGL((steer_kernel<BF16, 1>), dim3(T_max, y, z), dim3(threads), 0, stream, h,
                            d, T_max, tok_mask, req, vecs, alpha, n_steer, bits);
     return hipGetLastError();
 }

@@ -372,3 +372,28 @@ def test_steer_probe_few_apps(px, T, d, n_steer, n_probe, dtype):
     """The numbers of probes and of steering vectors where the fused pass changes
     how many it asks for together, rows of more than one turn of 512 slices."""
     test_steer_probe_early_rows(px, T, d, n_steer, n_probe, dtype, 1)
+
+
+def test_rows_of_more_column_slices_than_a_grid_holds(px):
+    """A row of 65537 workgroups' columns: steering and a clamp, against torch on
+    the columns where a grid's y would end and on the last ones."""
+    d = (1 << 27) + 2056
+    at = torch.tensor([0, 1, 32768 * 2048 - 1, 32768 * 2048, 65535 * 2048 + 5, 65536 * 2048 - 1,
+                       65536 * 2048, d - 9, d - 8, d - 1], device="cuda")
+    rt, _ = build(px, np.zeros(1, np.int32), 1, np.array([3], np.uint32), 2)
+    W = torch.empty((1, d), dtype=torch.bfloat16, device="cuda")
+    for c in range(0, d, 1 << 24):                     # small whole numbers, exact in bf16
+        n = min(1 << 24, d - c)
+        W[0, c:c + n] = ((torch.arange(n, device="cuda") + c // 512) % 61).to(torch.bfloat16)
+    h = torch.zeros((1, d), dtype=torch.bfloat16, device="cuda")
+    px.xmix_steer_apply(h, rt, dev(np.zeros(1, np.int32)), W, [0],
+                        torch.full((1, 1), 2.0, device="cuda"))
+    assert torch.equal(h[0, at], 2 * W[0, at])
+    assert torch.equal(h, 2 * W)
+    idx = torch.full((1, 1), -1, dtype=torch.int32, device="cuda")
+    args = (1, idx, torch.zeros((1, 1), dtype=torch.bfloat16, device="cuda"), W,
+            torch.zeros(1, dtype=torch.int32, device="cuda"), torch.ones(1, device="cuda"))
+    px.xmix_sae_clamp_decode(h, rt, *args)
+    assert torch.equal(h, 3 * W)
+    px.xmix_sae_clamp_decode_multi(h, rt, [args])
+    assert torch.equal(h, 4 * W)
