@@ -151,6 +151,52 @@ def test_probe_token_groups(px, T, d, n_probe, R, dtype):
     check_probe(lg, sg, lr, sr, ~np.isnan(lr), floor)
 
 
+@pytest.mark.parametrize("R", [2047, 2048, 2050])
+@pytest.mark.parametrize("d,n_probe,dtype", [(264, 4, "bf16"), (4104, 5, "bf16"), (1028, 9, "f32")])
+def test_probe_last_request_groups(px, R, d, n_probe, dtype):
+    """Last-token probes on either side of the group rule: empty spans at each
+    place of a group and a whole group of them, spans that end past the slots,
+    and the bits of launches of fewer requests."""
+    rng = np.random.default_rng(R + d)
+    size = rng.integers(1, 4, R)
+    for j in range(4):
+        size[40 + 4 * j + j] = 0                               # at place j of a group
+    size[80:84] = 0
+    cu = np.concatenate([[0], np.cumsum(size)]).astype(np.int32)
+    T = int(cu[-1])
+    req = np.repeat(np.arange(R), size).astype(np.int32)
+    cu[R - 1:] += 2                                            # these two end past the slots
+    sub = (rng.random((R, n_probe)) < 0.5) @ (1 << np.arange(n_probe, dtype=np.uint64))
+    sub = sub.astype(np.uint32)
+    bf = dtype == "bf16"
+    draw = synth.normal_bf16 if bf else synth.normal_f32
+    h, w = draw("l/h", (T, d), 1.0), draw("l/w", (n_probe, d), d ** -0.5)
+    b = rng.normal(0, 0.3, n_probe).astype(np.float32)
+    bits = list(range(n_probe))
+    rt, _ = build(px, req, T, sub, n_probe)
+    tm = oracle.route(req, T, sub, n_probe)[0]
+    hd, wd, bd = dev(h), dev(w), dev(b)
+
+    def call(cu_d):
+        out = [torch.full((n_probe, len(cu_d) - 1), float("nan"), device="cuda")
+               for _ in range(2)]
+        px.xmix_probe_score(hd, rt, wd, bd, bits, px.XMIX_PROBE_LAST, *out,
+                            cu_seqlens=dev(cu_d))
+        return [o.cpu().numpy() for o in out]
+
+    lg, sg = call(cu)
+    lr, sr = oracle.probe_last(h, tm, w, b, bits, np.minimum(cu, T))
+    lr[:, cu[1:] > T] = np.nan                                 # not the oracle's to read
+    assert np.array_equal(np.isnan(lg), np.isnan(lr))
+    assert np.isnan(lr[:, 40]).all() and np.isnan(lr[:, 80:84]).all() and np.isnan(lr[:, -1]).all()
+    hf, wf = (bf16_f64(h), bf16_f64(w)) if bf else (h.astype(np.float64), w.astype(np.float64))
+    absdot = (np.abs(wf) @ np.abs(hf).T)[:, np.clip(cu[1:] - 1, 0, T - 1)]
+    check_probe(lg, sg, lr, sr, ~np.isnan(lr), absdot)
+    for r0 in (0, 1001):
+        lp, _ = call(cu[r0:r0 + 1001])
+        assert np.array_equal(lp, lg[:, r0:r0 + 1000], equal_nan=True)
+
+
 @pytest.mark.parametrize("T,d,k,n_clamp,n_apps", [(1, 8, 1, 1, 1), (5, 264, 64, 16, 3),
                                                   (4097, 264, 32, 5, 9), (130, 4104, 8, 4, 2)])
 def test_clamp_token_groups(px, T, d, k, n_clamp, n_apps):
