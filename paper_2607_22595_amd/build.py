@@ -6,8 +6,9 @@ ceiling/ (a benchmark aid, no part of the hook step) become
 libxmix_ceiling.so.  Packed-fp32 instruction selection is switched off for
 device code; a kernel's first arguments arrive in scalar registers (the chain
 of a short kernel is one round trip shorter: 32 fused probe and steering passes
-134 -> 128 us, eight gated layers 65 -> 62).  The binding's argument marshalling (call.cpp, host code against
-Python's and torch's headers) becomes the extension module _call.so."""
+134 -> 128 us, eight gated layers 65 -> 62).  The binding's argument
+marshalling (call.cpp, host code against Python's and torch's headers) becomes
+the extension module _call.so."""
 import concurrent.futures as cf
 import glob
 import os

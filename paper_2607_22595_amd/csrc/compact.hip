@@ -1,6 +1,7 @@
-// Readback compaction into a fixed-capacity device ring.  One wave per row of
-// the app's token list (the list is already ascending and compact, built by
-// the routing kernel's ballot/prefix pass); slot = (head + i) mod capacity.
+// Readback compaction into a fixed-capacity device ring: row i of the app's
+// token list (already ascending and compact, built by the routing kernel's
+// ballot/prefix pass) goes to slot (head + i) mod capacity.  A wave takes a row,
+// or one of the two or four parts of a long one.
 // Every workgroup that holds a row reads head[0] before it takes a ticket
 // from head[1]; the one drawing the last ticket has therefore seen every
 // other read, and it alone advances head[0] and returns the ticket counter
@@ -27,7 +28,7 @@ typedef uint32_t words4_t __attribute__((ext_vector_type(4), aligned(4)));
 // outstanding per lane and turn, did not keep it busy (2500 rows of 8 KB: 21.6
 // us), so with U = uint32_t a wave moves 16 bytes per lane, four of them in
 // flight, and single words only at a segment's end; a row of more than 4 KB is
-// shared by `parts` waves (2 or 4), so that it too is one turn of loads (15.9 us
+// shared by `parts` waves (2 or 4): up to 16 KB it too is one turn of loads (15.9 us
 // with whole rows, 12.2 with this).  At most 256 workgroups of 16 waves take the
 // rows in turn: every workgroup draws a ticket, the tickets are atomics on one
 // address, and a workgroup for every 4 rows drew 625 of them here.

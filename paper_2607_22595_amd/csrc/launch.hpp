@@ -128,8 +128,8 @@ struct SaeAppIn {
     uint16_t* val_out;
     const MergeRing* ring;
 };
-// The candidates of up to kMultiMax apps in one launch, then their merges in
-// one launch (decode shapes: T_max < the prefill threshold).
+// Per kMultiMax apps the candidates of all in one launch, then their merges in
+// one (decode shapes: T_max < the prefill threshold).
 hipError_t launch_sae_encode_multi(const uint16_t* h, int32_t d, int32_t T_max, int32_t n,
                                    const SaeAppIn* apps, hipStream_t stream,
                                    const RouteIn* route = nullptr);
