@@ -34,7 +34,7 @@ steer_kernel(void* __restrict__ h, int32_t d, int32_t T_max,
     const int32_t t0 = static_cast<int32_t>(blockIdx.x) * TT;
     const int32_t nvec = d / EPV;
     const int32_t i = static_cast<int32_t>(
-        (blockIdx.z * gridDim.y + blockIdx.y) * kSteerThreads + threadIdx.x);
+        (blockIdx.z * kGridCols + blockIdx.y) * kSteerThreads + threadIdx.x);
     // masks and requests of the group in one round trip
     uint32_t sel[TT], any = 0;
     int32_t rq[TT];
